@@ -171,6 +171,7 @@ struct dgs_ctx {
     uint32_t *grpcnt = nullptr, *segstart = nullptr;
     uint32_t ngroups = 0, gparts = 1;  // join groups; parts per group
     uint32_t bgroup = 8;               // parts per re-collecting workgroup (about 2048 tiles)
+    uint32_t slabs = 1;                // slabs of the longest part (dense requests)
     uint32_t *segcnt = nullptr, *segG1 = nullptr;
     uint2 *segOut = nullptr;
     SegState *segstate = nullptr;
@@ -228,8 +229,8 @@ struct ProfSlot {
 // k_j = ceil(density * n_j) in IEEE double; k2 = rank that sets the next predicted threshold.
 // Which tensors take the chain kernels behind the selection: those of at least SEG_MIN_N
 // elements whose hinted candidate list is longer than one workgroup selects from
-// (SEL_LIST_MAX), and, for a dense request, all of that size (one workgroup would crawl
-// through the tensor itself).
+// (SEL_LIST_MAX).  For a dense request `seg` means the kernels that read the tensors themselves
+// (launch_dense): all of them, unless the option forbids it.
 void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out, uint64_t *K_out,
                uint32_t *nseg_active, uint64_t *wire_words_out)
 {
@@ -251,11 +252,9 @@ void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out,
             if (k2p > nj) k2p = nj;
             out[j].k2_pull = (uint32_t)k2p;
             bool seg = false;
-            if (nj >= SEG_MIN_N && c->seg_mode != SEG_MODE_NEVER) {
-                if (density > DENSE_DENSITY)
-                    seg = true;   // dense request: the chain reads the tensor itself, one workgroup would crawl
-                else
-                    seg = c->seg_mode == SEG_MODE_ALWAYS || (k2 > k2p ? k2 : k2p) > list_limit;
+            if (c->seg_mode != SEG_MODE_NEVER) {
+                if (density > DENSE_DENSITY) seg = true;
+                else if (nj >= SEG_MIN_N) seg = c->seg_mode == SEG_MODE_ALWAYS || (k2 > k2p ? k2 : k2p) > list_limit;
             }
             out[j].seg = seg ? 1u : 0u;
             // wire form: local indices of b bits each, the tensor's block padded to whole words
@@ -393,14 +392,13 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
     const bool have_seg = c->plan_slot[slot].nseg_active != 0;
     uint32_t *tprev = c->tprev + (size_t)hint_set * c->J;
     if (dense_req && have_seg) {
-        // dense request with large tensors: the accumulate pass also histograms the keys, and
-        // k_pick turns that into a lower bound of each k-th key; the chain then reads the
-        // tensors themselves
+        // dense request: the accumulate pass also histograms the keys, which
+        // gives the leading bits of each k-th key; the rest is found by reading the tensors again
         ProfSlot ps(c, prof_stream);
         const uint32_t blocks = stream_blocks(c, MODE_HIST, &sa.quads_per_block);
         launch_stream(op_stream, MODE_HIST, vec, sa, blocks, c->stream, ps.ev0, ps.ev1);
         ps.launched();
-        launch_pick(c->tdesc, plan, c->ghist, tau, tprev, c->stats, c->J, false, c->stream);
+        launch_pick_dense(c->tdesc, plan, c->ghist, c->segstate, c->stats, c->J, c->stream);
     } else if (dense_req) {
         if (op_stream == OP_FMA) {
             ProfSlot ps(c, prof_stream);
@@ -495,18 +493,20 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
     se.exact_mode = exact ? 1u : 0u;
     se.repair = (c->repair_round && !dense_req) ? 1u : 0u;   // a dense request has no lists to collect again
     se.spin_limit = c->spin_limit;
-    {
+    se.slabs = c->slabs;
+    if (!(dense_req && have_seg)) {
         ProfSlot ps(c, prof_select);
         launch_select(op_select, se, c->stream, ps.ev0, ps.ev1);
         ps.launched();
     }
     if (have_seg) {
         ProfSlot ps(c, prof_seg);
-        launch_chain(op_select, se, c->stream, ps.ev0, ps.ev1);
+        if (dense_req) launch_dense(op_select, se, c->stream, ps.ev0, ps.ev1);
+        else launch_chain(op_select, se, c->stream, ps.ev0, ps.ev1);
         ps.launched();
     }
     if (!dense_req) c->hint_density[hint_set] = density;
-    else if (have_seg) c->hint_density[hint_set] = 0.0;   // k_pick has overwritten this stream's hints
+    else if (have_seg) c->hint_density[hint_set] = 0.0;   // a dense message leaves no threshold near the hinted one
     if (hipGetLastError() != hipSuccess) return DGS_EHIP;
     return DGS_OK;
 }
@@ -567,6 +567,7 @@ void fill_tables(dgs_ctx *c, TensorDesc *td, uint32_t *tau0, uint32_t *toff, Seg
             d.ntiles = (thi + 1 - d.tile0 < per) ? (thi + 1 - d.tile0) : per;
             d.sidx = sidx;
             segs[nsegs++] = d;
+            c->slabs = std::max(c->slabs, (d.ntiles + SLAB_TILES - 1) / SLAB_TILES);
         }
         for (uint32_t w = 0; w <= W; ++w) tau0[(size_t)w * J + j] = td[j].big ? 1u : TAU_NEVER;
     }

@@ -62,12 +62,16 @@ constexpr uint32_t SEG_LOWBITS = 12;               // key bits resolved by the s
 constexpr uint32_t SEG_WBINS = 2048;               // window of key >> SEG_LOWBITS above the threshold
 constexpr uint32_t SEG_LBINS = 1u << SEG_LOWBITS;
 constexpr uint32_t PFX_CAP = 8192;                 // candidates sharing the k-th key's prefix, per tensor
+// Dense requests: tiles of one workgroup (4 wavefronts) of the passes over the tensors themselves.
+constexpr uint32_t SLAB_TILES = 16;
+constexpr uint32_t SLAB_THREADS = 256;
+static_assert(SLAB_TILES * TILE >= SMALL_N + TILE && SLAB_TILES <= SEG_TILES, "a small tensor is one slab");
 constexpr uint32_t SEG_MAX_PER_TENSOR = 512;       // parts per tensor whose list positions fit the selection's LDS
 // Status of a tensor inside one selection call.
 //   SEG_IDLE      nothing decided yet
 //   SEG_DONE      selected and emitted
 //   SEG_ACTIVE    the chain kernels finish it (prefix of the k-th key known)
-//   SEG_ALL       k_j = n_j: the chain's emission sends every element
+//   SEG_ALL       dense request with k_j = n_j: the emission sends every element
 //   SEG_PENDING   the prediction failed: the parts collect again with a fresh threshold
 //   SEG_FALLBACK  left to the dense single-workgroup selection
 enum SegStatus { SEG_IDLE = 0, SEG_DONE = 1, SEG_FALLBACK = 2, SEG_PENDING = 4, SEG_ALL = 6, SEG_ACTIVE = 8 };
@@ -104,7 +108,7 @@ struct SegDesc {
 
 struct SegState {        // per tensor, rewritten by every selection
     uint32_t status;     // SegStatus
-    uint32_t pfx;        // key >> SEG_LOWBITS of the k-th entry
+    uint32_t pfx;        // key >> SEG_LOWBITS of the k-th entry (dense request: its leading bits so far)
     uint32_t r2;         // its rank among the entries sharing that prefix
     uint32_t T;          // the k-th key
     uint32_t pfxcount;   // entries appended to the prefix list
@@ -188,6 +192,7 @@ struct SelectArgs {
     uint32_t repair;              // the launch carries the re-collecting workgroups
     uint32_t spin_limit;          // polls before a waiting workgroup gives up
     uint32_t bgroup;              // parts looked after by one re-collecting workgroup
+    uint32_t slabs;               // dense request: slabs (runs of SLAB_TILES tiles) of the longest part
 };
 
 // Host-callable launchers (defined next to the kernels).
@@ -196,11 +201,16 @@ void launch_stream(int op, int mode, bool vec, const StreamArgs &a, uint32_t blo
                    void *ev0, void *ev1);
 void launch_pick(const TensorDesc *tdesc, const PlanEntry *plan, uint32_t *ghist, uint32_t *tau,
                  uint32_t *tprev, DevStats *stats, uint32_t J, bool sample, void *stream);
+// Dense request: the accumulate pass's histogram -> the leading 12 bits of each k-th key, into segstate.
+void launch_pick_dense(const TensorDesc *tdesc, const PlanEntry *plan, uint32_t *ghist, SegState *segstate,
+                       DevStats *stats, uint32_t J, void *stream);
 // The selection: one launch for every tensor (join, exact k-th key, ordered emission, state
 // fix-up, next hint; failed predictions are collected again inside the same launch).
 void launch_select(int op, const SelectArgs &a, void *stream, void *ev0, void *ev1);
-// What remains for tensors left SEG_ACTIVE / SEG_ALL (very long candidate lists, dense requests).
+// What remains for tensors left SEG_ACTIVE (very long candidate lists).
 void launch_chain(int op, const SelectArgs &a, void *stream, void *ev0, void *ev1);
+// Dense request: exact k-th keys and emission, reading the tensors themselves.
+void launch_dense(int op, const SelectArgs &a, void *stream, void *ev0, void *ev1);
 void launch_push(float *model, float *diff, uint32_t W, uint32_t n, const uint32_t *idx,
                  const float *val, uint32_t nnz, void *stream, void *ev0, void *ev1);
 void launch_validate_idx(const uint32_t *idx, uint32_t nnz, uint32_t n, uint32_t *flag, void *stream);

@@ -74,6 +74,39 @@ struct SrcSplit {          // a list whose first SEL_LDS_LIST entries are in LDS
     __device__ __forceinline__ uint32_t index(uint32_t p) const { return get(p).x; }
 };
 
+// The four consecutive elements e0 .. e0 + 3 (e0 a multiple of 4) of the ranked row as bit
+// patterns, and which of them belong to the tensor [lo, hi): one 16-byte load per buffer where
+// the quad lies inside the tensor and the buffers are 16-byte aligned (`vec`), element by
+// element at a tensor border or off alignment.
+template <int OP>
+__device__ __forceinline__ uint32_t quad_bits(const SelectArgs &A, uint32_t e0, uint32_t lo, uint32_t hi, bool vec,
+                                              uint32_t (&bits)[4])
+{
+    if (vec && e0 >= lo && e0 + 3u < hi) {
+        f32x4 v = *(const f32x4 *)(A.state + e0);
+        if (OP == SEL_PULL_V) v = *(const f32x4 *)(A.model + e0) - v;      // one fp32 subtraction per element
+        bits[0] = __float_as_uint(v.x);
+        bits[1] = __float_as_uint(v.y);
+        bits[2] = __float_as_uint(v.z);
+        bits[3] = __float_as_uint(v.w);
+        return 0xFu;
+    }
+    uint32_t in = 0;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+        const uint32_t e = e0 + x;
+        const bool ok = e >= lo && e < hi;
+        bits[x] = ok ? __float_as_uint(row_value<OP>(A.state, A.model, e)) : 0u;
+        in |= ok ? (1u << x) : 0u;
+    }
+    return in;
+}
+
+__device__ __forceinline__ bool rows_aligned(const SelectArgs &A)
+{
+    return (((uintptr_t)A.state | (uintptr_t)A.model) & 15u) == 0;   // (a null model counts as aligned)
+}
+
 struct SelShared {
     uint32_t h[2048];
     uint32_t wsum[SEL_WAVES];

@@ -105,6 +105,46 @@ void launch_pick(const TensorDesc *tdesc, const PlanEntry *plan, uint32_t *ghist
                        stats, sample ? 1u : 0u);
 }
 
+// Dense request: the histogram covers every nonzero element of the tensor, so the bucket that
+// holds the k-th key is certain (the zeros, not counted by the pass, complete bucket 0).
+__global__ __launch_bounds__(1024) void k_pick_dense(const TensorDesc *tdesc, const PlanEntry *plan, uint32_t *ghist,
+                                                     SegState *segstate, DevStats *stats)
+{
+    const uint32_t j = blockIdx.x;
+    const TensorDesc td = tdesc[j];
+    if (!td.big) return;
+    __shared__ uint32_t h[HBINS];
+    __shared__ uint32_t rowsum[64];
+    __shared__ int res[6];
+    __shared__ uint32_t wsum[SEL_WAVES];
+    uint32_t *g = ghist + (size_t)j * HBINS;
+    uint32_t mine = 0;
+    for (uint32_t b = threadIdx.x; b < HBINS; b += SEL_THREADS) {
+        const uint32_t v = g[b];
+        h[b] = v;
+        mine += v;
+        g[b] = 0;   // leave the histogram clean for the next use
+    }
+    const uint32_t nonzero = block_sum(mine, wsum, SEL_WAVES);
+    if (threadIdx.x == 0) h[0] += td.n - nonzero;
+    const uint32_t k = plan[j].k;
+    find_ranks<HBINS, SEL_WAVES>(h, k, 0u, 0u, rowsum, res);
+    if (threadIdx.x == 0) {
+        SegState *st = &segstate[j];
+        st->status = (k == td.n) ? SEG_ALL : SEG_ACTIVE;
+        st->pfx = (uint32_t)res[0];
+        st->r2 = (uint32_t)res[1];
+        atomicAdd(&stats->segmented_tensors, 1ull);
+    }
+}
+
+void launch_pick_dense(const TensorDesc *tdesc, const PlanEntry *plan, uint32_t *ghist, SegState *segstate,
+                       DevStats *stats, uint32_t J, void *stream)
+{
+    hipLaunchKernelGGL(k_pick_dense, dim3(J), dim3(SEL_THREADS), 0, (hipStream_t)stream, tdesc, plan, ghist, segstate,
+                       stats);
+}
+
 // ---------------------------------------------------------------------------
 // the selection kernel
 // ---------------------------------------------------------------------------
@@ -305,39 +345,6 @@ __device__ __forceinline__ DenseRun dense_run(const TensorDesc &td, const SegDes
     return r;
 }
 
-// The four consecutive elements e0 .. e0 + 3 (e0 a multiple of 4) of the ranked row as bit
-// patterns, and which of them belong to the tensor [lo, hi): one 16-byte load per buffer where
-// the quad lies inside the tensor and the buffers are 16-byte aligned (`vec`), element by
-// element at a tensor border or off alignment.
-template <int OP>
-__device__ __forceinline__ uint32_t quad_bits(const SelectArgs &A, uint32_t e0, uint32_t lo, uint32_t hi, bool vec,
-                                              uint32_t (&bits)[4])
-{
-    if (vec && e0 >= lo && e0 + 3u < hi) {
-        f32x4 v = *(const f32x4 *)(A.state + e0);
-        if (OP == SEL_PULL_V) v = *(const f32x4 *)(A.model + e0) - v;      // one fp32 subtraction per element
-        bits[0] = __float_as_uint(v.x);
-        bits[1] = __float_as_uint(v.y);
-        bits[2] = __float_as_uint(v.z);
-        bits[3] = __float_as_uint(v.w);
-        return 0xFu;
-    }
-    uint32_t in = 0;
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-        const uint32_t e = e0 + x;
-        const bool ok = e >= lo && e < hi;
-        bits[x] = ok ? __float_as_uint(row_value<OP>(A.state, A.model, e)) : 0u;
-        in |= ok ? (1u << x) : 0u;
-    }
-    return in;
-}
-
-__device__ __forceinline__ bool rows_aligned(const SelectArgs &A)
-{
-    return (((uintptr_t)A.state | (uintptr_t)A.model) & 15u) == 0;   // (a null model counts as aligned)
-}
-
 // RE-HISTOGRAM of one part: key bits [30:19] of the tensor's nonzero elements in the part,
 // into lh (HBINS counters in LDS, zeroed here).  Ends with a barrier.
 template <int OP>
@@ -446,27 +453,6 @@ __device__ __forceinline__ uint32_t dense_compact(const SelectArgs &A, const Ten
     return total;
 }
 
-// Dense request on a tensor that takes the chain: how many of the part's elements reach the
-// threshold, counted into the tensor's window histogram (LDS h, SEG_WBINS bins).
-template <int OP>
-__device__ __forceinline__ uint32_t dense_window_count(const SelectArgs &A, const TensorDesc &td, const SegDesc &sd,
-                                                       uint32_t tau, uint32_t win_base, uint32_t *h, uint32_t *wsum)
-{
-    const uint64_t lo = max((uint64_t)td.off, (uint64_t)sd.tile0 * TILE);
-    const uint64_t hi = min((uint64_t)td.off + td.n, ((uint64_t)sd.tile0 + sd.ntiles) * TILE);
-    uint32_t mine = 0;
-    for (uint64_t e = lo + threadIdx.x; e < hi; e += SEL_THREADS) {
-        const uint32_t key = __float_as_uint(row_value<OP>(A.state, A.model, (uint32_t)e)) & 0x7FFFFFFFu;
-        if (key >= tau) {
-            const uint32_t hi12 = key >> SEG_LOWBITS;
-            const uint32_t w = (hi12 > win_base) ? (hi12 - win_base) : 0u;
-            atomicAdd(&h[min(w, SEG_WBINS - 1u)], 1u);
-            ++mine;
-        }
-    }
-    return block_sum(mine, wsum, SEL_WAVES);
-}
-
 // First bin (key >> SEG_LOWBITS) of the window histogram of a tensor that takes the chain.
 // Candidates start at the collection threshold; when that lies far below the k-th key of the
 // previous selection on this stream (a relaxed hint), the window is centred on that key
@@ -482,7 +468,7 @@ __device__ __forceinline__ uint32_t seg_window_base(uint32_t tau_cur, uint32_t t
 
 // The last part of a tensor that takes the chain: the tensor's window histogram (global, c
 // candidates in all) -> the 19-bit prefix of the k-th key, its rank among the entries sharing
-// it, and the next hint.  Returns the tensor's status (SEG_ACTIVE, SEG_ALL, or 0 = failed);
+// it, and the next hint.  Returns the tensor's status (SEG_ACTIVE, or 0 = failed);
 // thread 0 writes segstate / hints.  h: SEG_WBINS words of LDS.
 template <int OP>
 __device__ __forceinline__ uint32_t window_step(const SelectArgs &A, const TensorDesc &td, const PlanEntry &pe,
@@ -512,12 +498,11 @@ __device__ __forceinline__ uint32_t window_step(const SelectArgs &A, const Tenso
     find_ranks<SEG_WBINS, SEL_WAVES>(h, pe.k, measurable ? R : pe.k, third, P.S.rowsum, P.S.res);
     const int bk = P.S.res[0], bR = P.S.res[2];
     const uint32_t lowest = P.S.kmin;
-    const bool all = (pe.k == td.n);   // everything is sent: no threshold to find
-    const bool ok = all || (!ovf && (c >= pe.k) && bk >= bin_min && bk < (int)SEG_WBINS - 1);
+    const bool ok = !ovf && (c >= pe.k) && bk >= bin_min && bk < (int)SEG_WBINS - 1;
     if (tid == 0 && ok) {
         SegState *st = &A.segstate[j];
         st->pfxcount = 0;
-        st->pfx = win_base + (uint32_t)max(bk, 0);
+        st->pfx = win_base + (uint32_t)bk;
         st->r2 = (uint32_t)P.S.res[1];
         st->T = 0;
         atomicAdd(&A.stats->candidates, (unsigned long long)c);
@@ -550,7 +535,7 @@ __device__ __forceinline__ uint32_t window_step(const SelectArgs &A, const Tenso
         }
     }
     __syncthreads();
-    return all ? (uint32_t)SEG_ALL : (ok ? (uint32_t)SEG_ACTIVE : 0u);
+    return ok ? (uint32_t)SEG_ACTIVE : 0u;
 }
 
 // Selection of a whole tensor straight from the buffers by this one workgroup: small tensors,
@@ -731,7 +716,7 @@ __device__ __forceinline__ uint32_t trim_list(const SelectArgs &A, const Src &sr
 
 // What the workgroup that completes a tensor's candidate lists does with them (`round` 0: the
 // streaming pass's candidates, 1: re-collected with a fresh threshold).  Returns the tensor's
-// status: SEG_DONE, SEG_ACTIVE / SEG_ALL (the chain kernels go on), or SEG_PENDING (round 0
+// status: SEG_DONE, SEG_ACTIVE (the chain kernels go on), or SEG_PENDING (round 0
 // only: collect again).
 //   multi: the lists are global lists of several units -- the tensor's parts (by_parts: counts
 //   in segcnt) or its join groups (counts in grpcnt) -- and are gathered here; otherwise the
@@ -789,8 +774,8 @@ __device__ __forceinline__ uint32_t tensor_select(const SelectArgs &A, const Ten
     }
     uint32_t status = 0;
     bool early = false;      // the verdict went out before the work
-    // every nonzero is in the lists (a dense request has no lists: it falls back instead)
-    const bool zerofill = !A.dense && !ovf && c < pe.k && tau_cur <= 1u && (!multi || have_pbase);
+    // every nonzero is in the lists
+    const bool zerofill = !ovf && c < pe.k && tau_cur <= 1u && (!multi || have_pbase);
     if (pe.seg) status = window_step<OP>(A, td, pe, j, c, ovf, tau_cur, tprev_cur, exact_mode, P);
     if (status == 0 && zerofill) {
         // the message is completed with the tensor's lowest-index zeros
@@ -1025,11 +1010,10 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const SelectArgs A)
     SegState *st = &A.segstate[j];
     uint2 *plist = A.ord + (size_t)(sd.tile0 + j) * CAPT;       // this group's list
     const uint32_t part_cap = sd.ntiles * CAPT;
-    const bool chain_dense = A.dense && pe.seg;                  // the chain reads the tensor itself
 
     {
         // ------------------------------------------------------------------ JOIN
-        if (!td.big || (A.dense && !pe.seg)) {
+        if (!td.big || A.dense) {
             if (sd.sidx != 0) return;
             if (tid == 0) st->status = SEG_DONE;
             dense_select<OP>(A, td, pe, j, td.big ? A.tau[j] : TAU_NEVER, P, llist);
@@ -1051,49 +1035,32 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const SelectArgs A)
             const uint32_t p0 = td.seg_first + sd.sidx * A.gparts;
             const uint32_t p1 = min(p0 + A.gparts, td.seg_first + td.nseg);
             uint32_t *gh = A.ghist + (size_t)j * HBINS;
-            if (chain_dense) {
-                for (uint32_t p = p0; p < p1; ++p) {       // no lists: the parts' elements are counted
-                    const SegDesc ps = A.segtab[p];
-                    for (uint32_t b = tid; b < 2048; b += SEL_THREADS) P.S.h[b] = 0;
-                    __syncthreads();
-                    const uint32_t cp = dense_window_count<OP>(A, td, ps, tau_cur, win_seg, P.S.h, P.S.wsum);
-                    __syncthreads();
-                    for (uint32_t b = tid; b < SEG_WBINS; b += SEL_THREADS) {
-                        const uint32_t v = P.S.h[b];
-                        if (v) atomicAdd(&gh[b], v);
-                    }
-                    if (tid == 0) st_dev(&A.segcnt[p], cp);
-                    cs += cp;
-                    __syncthreads();
-                }
-            } else {
-                for (uint32_t b = tid; b < 2048; b += SEL_THREADS) P.S.h[b] = 0;
-                __syncthreads();
-                const uint32_t ptiles = A.segtab[p0].ntiles;         // tiles per part (the tensor's last part may have fewer)
-                const uint32_t gbase = (sd.tile0 + j) * CAPT;        // below 2^32: n < 2^32
-                cs = join_part(
-                    A, td, sd, P, ovf,
-                    [&](uint32_t pos, uint2 e) {
-                        st_dev(&plist[pos], e);          // read by the chain kernels, and by a zero fill
-                        const uint32_t hi12 = (e.y & 0x7FFFFFFFu) >> SEG_LOWBITS;
-                        const uint32_t w = (hi12 > win_seg) ? (hi12 - win_seg) : 0u;
-                        atomicAdd(&P.S.h[min(w, SEG_WBINS - 1u)], 1u);
-                    },
-                    [&](uint32_t tl, uint32_t pos) {
-                        if (tl % ptiles == 0) P.pbase[tl / ptiles] = pos;
-                    });
-                for (uint32_t b = tid; b < SEG_WBINS; b += SEL_THREADS) {
-                    const uint32_t v = P.S.h[b];
-                    if (v) atomicAdd(&gh[b], v);
-                }
-                const uint32_t np = p1 - p0;
-                if (tid < np) {
-                    const uint32_t start = P.pbase[tid], end = (tid + 1 < np) ? P.pbase[tid + 1] : cs;
-                    st_dev(&A.segstart[p0 + tid], gbase + start);
-                    st_dev(&A.segcnt[p0 + tid], (end - start) | (ovf ? 0x80000000u : 0u));
-                }
-                __syncthreads();
+            for (uint32_t b = tid; b < 2048; b += SEL_THREADS) P.S.h[b] = 0;
+            __syncthreads();
+            const uint32_t ptiles = A.segtab[p0].ntiles;         // tiles per part (the tensor's last part may have fewer)
+            const uint32_t gbase = (sd.tile0 + j) * CAPT;        // below 2^32: n < 2^32
+            cs = join_part(
+                A, td, sd, P, ovf,
+                [&](uint32_t pos, uint2 e) {
+                    st_dev(&plist[pos], e);          // read by the chain kernels, and by a zero fill
+                    const uint32_t hi12 = (e.y & 0x7FFFFFFFu) >> SEG_LOWBITS;
+                    const uint32_t w = (hi12 > win_seg) ? (hi12 - win_seg) : 0u;
+                    atomicAdd(&P.S.h[min(w, SEG_WBINS - 1u)], 1u);
+                },
+                [&](uint32_t tl, uint32_t pos) {
+                    if (tl % ptiles == 0) P.pbase[tl / ptiles] = pos;
+                });
+            for (uint32_t b = tid; b < SEG_WBINS; b += SEL_THREADS) {
+                const uint32_t v = P.S.h[b];
+                if (v) atomicAdd(&gh[b], v);
             }
+            const uint32_t np = p1 - p0;
+            if (tid < np) {
+                const uint32_t start = P.pbase[tid], end = (tid + 1 < np) ? P.pbase[tid + 1] : cs;
+                st_dev(&A.segstart[p0 + tid], gbase + start);
+                st_dev(&A.segcnt[p0 + tid], (end - start) | (ovf ? 0x80000000u : 0u));
+            }
+            __syncthreads();
             if (multi) {
                 if (!arrive_last(&st->arrive[0], td.ngrp, &P.bc)) return;
             } else {
