@@ -225,10 +225,12 @@ void launch_apply(float *dst, uint32_t n, const uint32_t *idx, const float *val,
 void launch_fill_u32(uint32_t *p, uint32_t v, size_t count, void *stream);
 // Host words -> device through kernel arguments (for the entry point that must not copy).
 void launch_put_words(uint32_t *dst, const uint32_t *src_host, size_t words, void *stream);
-void launch_pull_all_count(const float *row, const float *model, uint32_t n, uint32_t ntiles,
-                           uint32_t *tile_cnt, void *stream);
-void launch_pull_all_scan(uint32_t *tile_cnt, uint32_t ntiles, uint32_t *total, void *stream);
-void launch_pull_all_emit(float *row, const float *model, uint32_t n, uint32_t ntiles,
-                          const uint32_t *tile_pos, uint32_t *out_idx, float *out_val, void *stream);
+// Pull without secondary compression.  scratch: ntiles + 2 ceil(ntiles / PULL_CHUNK) words; arrive: a
+// counter, zero between calls; counted: hipEvent_t that completes once *host_total is in place.  The
+// row and the outputs are left alone if there are more nonzeros than `capacity`.
+constexpr uint32_t PULL_CHUNK = 4096;      // tiles of one workgroup of the position scan
+void launch_pull_all(float *row, const float *model, uint32_t n, uint32_t ntiles, uint32_t *tile_cnt, uint2 *slots,
+                     uint32_t *scratch, uint32_t *arrive, uint32_t *total, uint32_t *host_total, uint64_t capacity,
+                     uint32_t *out_idx, float *out_val, void *stream, void *counted);
 
 }  // namespace dgs

@@ -240,67 +240,50 @@ void launch_put_words(uint32_t *dst, const uint32_t *src_host, size_t words, voi
 // pull without secondary compression: every nonzero of one difference row, or of
 // model - sent_k when a model is given (the server state as Algorithm 2 prints it)
 // ---------------------------------------------------------------------------
+//
+// count  one wavefront per tile reads the row once (bound by that read), counts the nonzeros and
+//        leaves them, in order, in the tile's slots as long as they fit (a quarter of the tile)
+// scan   one workgroup per PULL_CHUNK tiles: list positions inside the chunk; the last one to
+//        finish adds the chunks up and hands the total to the host
+// emit   copies the lists to their place and settles the row; only a tile that outgrew its slots
+//        is read again.  Does nothing if the total exceeds the caller's capacity.
+// 108M parameters, 2 % nonzero: see the figures at launch_pull_all.
 
-__device__ __forceinline__ void load_tile_guarded(const float *row, const float *model, uint32_t base,
-                                                  uint32_t n, float (&a)[4][4])
+__device__ __forceinline__ void load_tile(const float *row, const float *model, uint32_t base, uint32_t n,
+                                          float (&a)[4][4])
 {
     const uint32_t lane = lane_id();
+    if (base + TILE <= n && base + TILE > base) {
+        // rows of a server with an odd number of parameters start at odd addresses: 16-byte loads all
+        // the same (the hardware asks for 4-byte alignment only)
+        f32x4 v[4], m[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = __builtin_nontemporal_load((const f32x4_any *)(row + base + r * 256 + lane * 4));
+        if (model) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) m[r] = *(const f32x4_any *)(model + base + r * 256 + lane * 4);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) a[r][j] = model ? m[r][j] - v[r][j] : v[r][j];
+        return;
+    }
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const uint32_t e = base + r * 256 + lane * 4 + j;
+            const uint64_t e = (uint64_t)base + r * 256 + lane * 4 + j;
             a[r][j] = (e < n) ? (model ? model[e] - row[e] : row[e]) : 0.0f;
         }
 }
 
-__global__ __launch_bounds__(STREAM_THREADS) void k_pull_all_count(const float *row, const float *model,
-                                                                   uint32_t n, uint32_t ntiles,
-                                                                   uint32_t *tile_cnt)
+// The tile's nonzeros in index order through put(position in the tile, element, value); returns how many.
+template <class Put>
+__device__ __forceinline__ uint32_t each_nonzero(const float (&a)[4][4], uint32_t base, Put put)
 {
-    const uint32_t t = blockIdx.x * WAVES_PER_BLOCK + (threadIdx.x >> 6);
-    if (t >= ntiles) return;
-    float a[4][4];
-    load_tile_guarded(row, model, t * TILE, n, a);
-    uint32_t cnt = 0;
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            cnt += (uint32_t)__popcll(ballot64((__float_as_uint(a[r][j]) & 0x7FFFFFFFu) != 0));
-    if (lane_id() == 0) tile_cnt[t] = cnt;
-}
-
-// single workgroup: in-place exclusive scan of tile_cnt, total to *total
-__global__ __launch_bounds__(1024) void k_pull_all_scan(uint32_t *tile_cnt, uint32_t ntiles, uint32_t *total)
-{
-    __shared__ uint32_t wsum[16];
-    const uint32_t per = (ntiles + 1023) / 1024;
-    const uint32_t lo = min(threadIdx.x * per, ntiles), hi = min(lo + per, ntiles);
-    uint32_t sum = 0;
-    for (uint32_t t = lo; t < hi; ++t) sum += tile_cnt[t];
-    uint32_t tot;
-    uint32_t pos = block_excl_scan<16>(sum, wsum, tot);
-    for (uint32_t t = lo; t < hi; ++t) {
-        const uint32_t c = tile_cnt[t];
-        tile_cnt[t] = pos;
-        pos += c;
-    }
-    if (threadIdx.x == 0) *total = tot;
-}
-
-// What is sent leaves the row as +0 (D_k -= G), or is added to it (sent_k += G, Eq. 6).
-__global__ __launch_bounds__(STREAM_THREADS) void k_pull_all_emit(float *row, const float *model, uint32_t n,
-                                                                  uint32_t ntiles, const uint32_t *tile_pos,
-                                                                  uint32_t *out_idx, float *out_val)
-{
-    const uint32_t t = blockIdx.x * WAVES_PER_BLOCK + (threadIdx.x >> 6);
-    if (t >= ntiles) return;
     const uint32_t lane = lane_id();
-    const uint32_t base = t * TILE;
-    float a[4][4];
-    load_tile_guarded(row, model, base, n, a);
-    uint32_t run = tile_pos[t];
+    uint32_t run = 0;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         bool f[4];
@@ -310,41 +293,141 @@ __global__ __launch_bounds__(STREAM_THREADS) void k_pull_all_emit(float *row, co
             f[j] = (__float_as_uint(a[r][j]) & 0x7FFFFFFFu) != 0;
             mk[j] = ballot64(f[j]);
         }
-        if ((mk[0] | mk[1] | mk[2] | mk[3]) != 0) {
-            uint32_t p = run + mbcnt64(mk[0]) + mbcnt64(mk[1]) + mbcnt64(mk[2]) + mbcnt64(mk[3]);
+        if ((mk[0] | mk[1] | mk[2] | mk[3]) == 0) continue;
+        uint32_t p = run + mbcnt64(mk[0]) + mbcnt64(mk[1]) + mbcnt64(mk[2]) + mbcnt64(mk[3]);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (f[j]) {
-                    const uint32_t e = base + r * 256 + lane * 4 + j;
-                    out_idx[p] = e;
-                    out_val[p] = a[r][j];
-                    store_scattered(&row[e], model ? row[e] + a[r][j] : 0.0f);
-                    ++p;
-                }
-            }
-            run += (uint32_t)(__popcll(mk[0]) + __popcll(mk[1]) + __popcll(mk[2]) + __popcll(mk[3]));
+        for (int j = 0; j < 4; ++j)
+            if (f[j]) put(p++, base + r * 256 + lane * 4 + j, a[r][j]);
+        run += (uint32_t)(__popcll(mk[0]) + __popcll(mk[1]) + __popcll(mk[2]) + __popcll(mk[3]));
+    }
+    return run;
+}
+
+__global__ __launch_bounds__(STREAM_THREADS) void k_pull_all_count(const float *row, const float *model, uint32_t n,
+                                                                   uint32_t ntiles, uint32_t *tile_cnt, uint2 *slots)
+{
+    __shared__ uint2 stage_all[WAVES_PER_BLOCK][CAPT];
+    const uint32_t wave = uniform(threadIdx.x >> 6), lane = lane_id();
+    const uint32_t t = blockIdx.x * WAVES_PER_BLOCK + wave;
+    if (t >= ntiles) return;
+    float a[4][4];
+    load_tile(row, model, t * TILE, n, a);
+    uint2 *stage = stage_all[wave];
+    const uint32_t cnt = each_nonzero(a, t * TILE, [&](uint32_t p, uint32_t e, float v) {
+        if (p < CAPT) stage[p] = make_uint2(e, __float_as_uint(v));
+    });
+    __builtin_amdgcn_wave_barrier();
+    if (cnt <= CAPT) {
+        // whole 64-byte lines, as in the streaming pass
+        const uint32_t end = (cnt + HEAD - 1u) / HEAD * HEAD;
+        for (uint32_t i = lane; i < end; i += 64)
+            slots[(size_t)t * CAPT + i] = (i < cnt) ? stage[i] : make_uint2(0u, 0u);
+    }
+    if (lane == 0) tile_cnt[t] = cnt;
+}
+
+// chunk: [0, nc) the chunks' totals, [nc, 2 nc) their first positions.  The total also goes to
+// host memory, where the caller reads it once this launch has ended.
+__global__ __launch_bounds__(1024) void k_pull_all_scan(const uint32_t *tile_cnt, uint32_t ntiles, uint32_t *tile_pos,
+                                                        uint32_t *chunk, uint32_t nc, uint32_t *arrive, uint32_t *total,
+                                                        uint32_t *host_total)
+{
+    __shared__ uint32_t wsum[16];
+    __shared__ uint32_t bc;
+    constexpr uint32_t PER = PULL_CHUNK / 1024u;
+    const uint32_t t0 = blockIdx.x * PULL_CHUNK + threadIdx.x * PER;
+    uint32_t c[PER], sum = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < PER; ++i) {
+        c[i] = (t0 + i < ntiles) ? tile_cnt[t0 + i] : 0u;
+        sum += c[i];
+    }
+    uint32_t tot;
+    uint32_t pos = block_excl_scan<16>(sum, wsum, tot);
+#pragma unroll
+    for (uint32_t i = 0; i < PER; ++i) {
+        if (t0 + i < ntiles) tile_pos[t0 + i] = pos;
+        pos += c[i];
+    }
+    if (threadIdx.x == 0) st_dev(&chunk[blockIdx.x], tot);
+    if (!arrive_last(arrive, nc, &bc)) return;
+    uint32_t run = 0;
+    for (uint32_t b0 = 0; b0 < nc; b0 += 1024u) {
+        const uint32_t b = b0 + threadIdx.x;
+        const uint32_t v = (b < nc) ? ld_dev(&chunk[b]) : 0u;
+        const uint32_t ex = run + block_excl_scan<16>(v, wsum, tot);
+        if (b < nc) chunk[nc + b] = ex;
+        run += tot;
+    }
+    if (threadIdx.x == 0) {
+        *total = run;
+        __hip_atomic_store(host_total, run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
+// What is sent leaves the row as +0 (D_k -= G), or is added to it (sent_k += G, Eq. 6).
+constexpr uint32_t PULL_TPW = 4;      // tiles of one wavefront: their first 64 entries are in flight together
+
+__global__ __launch_bounds__(STREAM_THREADS) void k_pull_all_emit(float *row, const float *model, uint32_t n,
+                                                                  uint32_t ntiles, const uint32_t *tile_cnt,
+                                                                  const uint32_t *tile_pos, const uint32_t *chunk_base,
+                                                                  const uint2 *slots, const uint32_t *total,
+                                                                  uint64_t capacity, uint32_t *out_idx, float *out_val)
+{
+    const uint32_t lane = lane_id();
+    const uint32_t t0 = (blockIdx.x * WAVES_PER_BLOCK + uniform(threadIdx.x >> 6)) * PULL_TPW;
+    if (*total > capacity) return;
+    uint32_t cnt[PULL_TPW], pos[PULL_TPW];
+    uint2 first[PULL_TPW];
+    float old[PULL_TPW];
+#pragma unroll
+    for (uint32_t i = 0; i < PULL_TPW; ++i) {
+        const uint32_t t = t0 + i;
+        cnt[i] = (t < ntiles) ? tile_cnt[t] : 0u;
+        pos[i] = (t < ntiles) ? tile_pos[t] + chunk_base[t / PULL_CHUNK] : 0u;
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < PULL_TPW; ++i)
+        first[i] = (cnt[i] <= CAPT && lane < cnt[i]) ? slots[(size_t)(t0 + i) * CAPT + lane] : make_uint2(0u, 0u);
+    auto put = [&](uint32_t p, uint32_t e, float v, float was) {
+        out_idx[p] = e;
+        out_val[p] = v;
+        store_scattered(&row[e], model ? was + v : 0.0f);
+    };
+#pragma unroll
+    for (uint32_t i = 0; i < PULL_TPW; ++i)
+        old[i] = (model && cnt[i] <= CAPT && lane < cnt[i]) ? row[first[i].x] : 0.0f;
+#pragma unroll
+    for (uint32_t i = 0; i < PULL_TPW; ++i) {
+        if (cnt[i] > CAPT) {       // wave-uniform
+            float a[4][4];
+            load_tile(row, model, (t0 + i) * TILE, n, a);
+            each_nonzero(a, (t0 + i) * TILE, [&](uint32_t p, uint32_t e, float v) { put(pos[i] + p, e, v, model ? row[e] : 0.0f); });
+            continue;
+        }
+        if (lane < cnt[i]) put(pos[i] + lane, first[i].x, __uint_as_float(first[i].y), old[i]);
+        for (uint32_t q = 64 + lane; q < cnt[i]; q += 64) {
+            const uint2 e = slots[(size_t)(t0 + i) * CAPT + q];
+            put(pos[i] + q, e.x, __uint_as_float(e.y), model ? row[e.x] : 0.0f);
         }
     }
 }
 
-void launch_pull_all_count(const float *row, const float *model, uint32_t n, uint32_t ntiles,
-                           uint32_t *tile_cnt, void *stream)
+void launch_pull_all(float *row, const float *model, uint32_t n, uint32_t ntiles, uint32_t *tile_cnt, uint2 *slots,
+                     uint32_t *scratch, uint32_t *arrive, uint32_t *total, uint32_t *host_total, uint64_t capacity,
+                     uint32_t *out_idx, float *out_val, void *stream, void *counted)
 {
-    hipLaunchKernelGGL(k_pull_all_count, dim3((ntiles + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK),
-                       dim3(STREAM_THREADS), 0, (hipStream_t)stream, row, model, n, ntiles, tile_cnt);
-}
-
-void launch_pull_all_scan(uint32_t *tile_cnt, uint32_t ntiles, uint32_t *total, void *stream)
-{
-    hipLaunchKernelGGL(k_pull_all_scan, dim3(1), dim3(1024), 0, (hipStream_t)stream, tile_cnt, ntiles, total);
-}
-
-void launch_pull_all_emit(float *row, const float *model, uint32_t n, uint32_t ntiles,
-                          const uint32_t *tile_pos, uint32_t *out_idx, float *out_val, void *stream)
-{
-    hipLaunchKernelGGL(k_pull_all_emit, dim3((ntiles + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK),
-                       dim3(STREAM_THREADS), 0, (hipStream_t)stream, row, model, n, ntiles, tile_pos, out_idx,
-                       out_val);
+    hipStream_t st = (hipStream_t)stream;
+    const uint32_t nc = (ntiles + PULL_CHUNK - 1) / PULL_CHUNK;
+    uint32_t *tile_pos = scratch, *chunk = scratch + ntiles;
+    hipLaunchKernelGGL(k_pull_all_count, dim3((ntiles + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK), dim3(STREAM_THREADS), 0,
+                       st, row, model, n, ntiles, tile_cnt, slots);
+    launch_k(k_pull_all_scan, dim3(nc), dim3(1024), st, nullptr, counted, tile_cnt, ntiles, tile_pos, chunk, nc, arrive,
+             total, host_total);
+    if (capacity == 0) return;
+    constexpr uint32_t per = WAVES_PER_BLOCK * PULL_TPW;
+    hipLaunchKernelGGL(k_pull_all_emit, dim3((ntiles + per - 1) / per), dim3(STREAM_THREADS), 0, st, row, model, n,
+                       ntiles, tile_cnt, tile_pos, chunk + nc, slots, total, capacity, out_idx, out_val);
 }
 
 }  // namespace dgs

@@ -9,6 +9,8 @@
 namespace dgs {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+// The same 16 bytes at any 4-byte boundary: still one load or store instruction.
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
 __device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & 63u; }
 
@@ -73,6 +75,10 @@ __device__ __forceinline__ void store_through16(float *base, uint32_t byte_off, 
     __builtin_memcpy(&u, &v, 16);
     __builtin_amdgcn_raw_buffer_store_b128(u, r, (int)byte_off, 0, 16);   // aux 16: sc1 = device scope
 }
+#endif
+
+#ifndef __HIP_MEMORY_SCOPE_SYSTEM      // (a CPU build)
+#define __HIP_MEMORY_SCOPE_SYSTEM 5
 #endif
 
 // All vector memory operations of this wavefront (stores and atomics included) are complete.
