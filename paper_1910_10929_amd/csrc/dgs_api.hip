@@ -335,7 +335,6 @@ int get_plan(dgs_ctx *c, double density, uint32_t *slot_out, uint64_t *K_out)
     return DGS_OK;
 }
 
-bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 bool aligned4(const void *p) { return ((uintptr_t)p & 3u) == 0; }
 
 uint32_t stream_blocks(const dgs_ctx *c, int mode, uint32_t *qpb_out)
@@ -365,7 +364,6 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
     if (rc != DGS_OK) return rc;
     if (nnz_out) *nnz_out = K;
 
-    const bool vec = aligned16(state) && (op_stream == OP_IDENT || aligned16(grad));
     // the read-only pass that sees the same values again (second pass of the non-predicted path,
     // repair round): the worker's are in `state` by then, a model - sent_k pull recomputes them
     const int op_again = (op_stream == OP_SUB) ? OP_SUB : OP_IDENT;
@@ -398,14 +396,14 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
         // gives the leading bits of each k-th key; the rest is found by reading the tensors again
         ProfSlot ps(c, prof_stream);
         const uint32_t blocks = stream_blocks(c, MODE_HIST, &sa.quads_per_block);
-        launch_stream(op_stream, MODE_HIST, vec, sa, blocks, c->stream, ps.ev0, ps.ev1);
+        launch_stream(op_stream, MODE_HIST, sa, blocks, c->stream, ps.ev0, ps.ev1);
         ps.launched();
         launch_pick_dense(c->tdesc, plan, c->ghist, c->segstate, c->stats, c->J, c->stream);
     } else if (dense_req) {
         if (op_stream == OP_FMA) {
             ProfSlot ps(c, prof_stream);
             const uint32_t blocks = stream_blocks(c, MODE_PLAIN, &sa.quads_per_block);
-            launch_stream(OP_FMA, MODE_PLAIN, vec, sa, blocks, c->stream, ps.ev0, ps.ev1);
+            launch_stream(OP_FMA, MODE_PLAIN, sa, blocks, c->stream, ps.ev0, ps.ev1);
             ps.launched();
         }
     } else if (exact && !c->force_exact && c->nqlist != 0) {
@@ -423,20 +421,20 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
         // hundred addresses (at 1e9 parameters: 119 us with two per unit, 90 with four, 101 with eight)
         const uint32_t wgs = (uint32_t)c->cus * DGS_SAMPLE_WGS_PER_CU;
         sb.quads_per_block = std::max<uint32_t>(1u, (sb.nquads + wgs - 1u) / wgs);
-        launch_stream(op_stream, MODE_SAMPLE, vec, sb, (sb.nquads + sb.quads_per_block - 1u) / sb.quads_per_block,
+        launch_stream(op_stream, MODE_SAMPLE, sb, (sb.nquads + sb.quads_per_block - 1u) / sb.quads_per_block,
                       c->stream, ps.ev0, ps.ev1);
         ps.launched();
         launch_pick(c->tdesc, plan, c->ghist, tau, tprev, c->stats, c->J, true, c->stream);
         ProfSlot pc(c, prof_stream);
         const uint32_t blocks = stream_blocks(c, MODE_COLLECT, &sa.quads_per_block);
-        launch_stream(op_stream, MODE_COLLECT, vec, sa, blocks, c->stream, pc.ev0, pc.ev1);
+        launch_stream(op_stream, MODE_COLLECT, sa, blocks, c->stream, pc.ev0, pc.ev1);
         pc.launched();
     } else if (exact) {
         ++c->exact_calls;
         {
             ProfSlot ps(c, prof_stream);
             const uint32_t blocks = stream_blocks(c, MODE_HIST, &sa.quads_per_block);
-            launch_stream(op_stream, MODE_HIST, vec, sa, blocks, c->stream, ps.ev0, ps.ev1);
+            launch_stream(op_stream, MODE_HIST, sa, blocks, c->stream, ps.ev0, ps.ev1);
             ps.launched();
         }
         {
@@ -445,14 +443,14 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
             StreamArgs sb = sa;
             if (op_again == OP_IDENT) sb.grad = nullptr;
             const uint32_t blocks = stream_blocks(c, MODE_COLLECT, &sb.quads_per_block);
-            launch_stream(op_again, MODE_COLLECT, op_again == OP_IDENT ? aligned16(state) : vec, sb, blocks,
+            launch_stream(op_again, MODE_COLLECT, sb, blocks,
                           c->stream, ps.ev0, ps.ev1);
             ps.launched();
         }
     } else {
         ProfSlot ps(c, prof_stream);
         const uint32_t blocks = stream_blocks(c, MODE_COLLECT, &sa.quads_per_block);
-        launch_stream(op_stream, MODE_COLLECT, vec, sa, blocks, c->stream, ps.ev0, ps.ev1);
+        launch_stream(op_stream, MODE_COLLECT, sa, blocks, c->stream, ps.ev0, ps.ev1);
         ps.launched();
     }
 

@@ -321,7 +321,6 @@ __device__ __forceinline__ void load_slab(const SelectArgs &A, const Slab &s, ui
                                           uint32_t (&in)[TPW])
 {
     const uint32_t lane = lane_id(), wave = uniform(threadIdx.x >> 6);
-    const bool vec = rows_aligned(A);
     const uint32_t lo = s.td.off, hi = s.td.off + s.td.n;
 #pragma unroll
     for (uint32_t i = 0; i < TPW; ++i) {
@@ -336,7 +335,7 @@ __device__ __forceinline__ void load_slab(const SelectArgs &A, const Slab &s, ui
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            in[i] |= quad_bits<OP>(A, (s.tile0 + ti) * TILE + r * 256 + lane * 4, lo, hi, vec, bits[i][r]) << (4 * r);
+            in[i] |= quad_bits<OP>(A, (s.tile0 + ti) * TILE + r * 256 + lane * 4, lo, hi, bits[i][r]) << (4 * r);
     }
 }
 
@@ -487,7 +486,6 @@ __global__ __launch_bounds__(SLAB_THREADS) void k_dense_emit(const SelectArgs A)
     const PlanEntry pe = A.plan[s.part.j];
     const uint32_t lane = lane_id(), wave = uniform(threadIdx.x >> 6);
     const bool all = (status == SEG_ALL);
-    const bool vec = rows_aligned(A);
     const uint32_t *rec = slab_record(A, s.tile0, s.part.j);
     // density 1: everything is a "tie" that is sent, at its own position
     const uint32_t T = all ? 0u : st->T;
@@ -561,11 +559,11 @@ __global__ __launch_bounds__(SLAB_THREADS) void k_dense_emit(const SelectArgs A)
             for (int x = 0; x < 4; ++x)
                 if (f[x]) stage[p++] = make_uint2(e0 + x, bits[i][r][x]);
             run += (uint32_t)(__popcll(mk[0]) + __popcll(mk[1]) + __popcll(mk[2]) + __popcll(mk[3]));
-            const bool quad = vec && ((in[i] >> (4 * r)) & 0xFu) == 0xFu;
+            const bool quad = ((in[i] >> (4 * r)) & 0xFu) == 0xFu;
             if (quad) {
                 if (((any >> (lane & ~3u)) & 0xFull) != 0) {
                     f32x4 o;
-                    if (OP == SEL_PULL_V) o = *(const f32x4 *)(A.state + e0);
+                    if (OP == SEL_PULL_V) o = *(const f32x4_any *)(A.state + e0);
 #pragma unroll
                     for (int x = 0; x < 4; ++x) {
                         const float v = __uint_as_float(bits[i][r][x]);
@@ -575,7 +573,7 @@ __global__ __launch_bounds__(SLAB_THREADS) void k_dense_emit(const SelectArgs A)
                             o[x] = !f[x] ? v : (OP == SEL_WORKER ? A.m * v : 0.0f);
                         }
                     }
-                    __builtin_nontemporal_store(o, (f32x4 *)(A.state + e0));
+                    __builtin_nontemporal_store((f32x4_any)o, (f32x4_any *)(A.state + e0));
                 }
             } else {
 #pragma unroll

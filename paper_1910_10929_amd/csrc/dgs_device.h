@@ -197,8 +197,7 @@ struct SelectArgs {
 
 // Host-callable launchers (defined next to the kernels).
 // ev0 / ev1: optional hipEvent_t recorded at the begin / end of the kernel (both or neither).
-void launch_stream(int op, int mode, bool vec, const StreamArgs &a, uint32_t blocks, void *stream,
-                   void *ev0, void *ev1);
+void launch_stream(int op, int mode, const StreamArgs &a, uint32_t blocks, void *stream, void *ev0, void *ev1);
 void launch_pick(const TensorDesc *tdesc, const PlanEntry *plan, uint32_t *ghist, uint32_t *tau,
                  uint32_t *tprev, DevStats *stats, uint32_t J, bool sample, void *stream);
 // Dense request: the accumulate pass's histogram -> the leading 12 bits of each k-th key, into segstate.

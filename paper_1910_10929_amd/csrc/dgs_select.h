@@ -76,15 +76,14 @@ struct SrcSplit {          // a list whose first SEL_LDS_LIST entries are in LDS
 
 // The four consecutive elements e0 .. e0 + 3 (e0 a multiple of 4) of the ranked row as bit
 // patterns, and which of them belong to the tensor [lo, hi): one 16-byte load per buffer where
-// the quad lies inside the tensor and the buffers are 16-byte aligned (`vec`), element by
-// element at a tensor border or off alignment.
+// the quad lies inside the tensor, element by element at a tensor border.
 template <int OP>
-__device__ __forceinline__ uint32_t quad_bits(const SelectArgs &A, uint32_t e0, uint32_t lo, uint32_t hi, bool vec,
+__device__ __forceinline__ uint32_t quad_bits(const SelectArgs &A, uint32_t e0, uint32_t lo, uint32_t hi,
                                               uint32_t (&bits)[4])
 {
-    if (vec && e0 >= lo && e0 + 3u < hi) {
-        f32x4 v = *(const f32x4 *)(A.state + e0);
-        if (OP == SEL_PULL_V) v = *(const f32x4 *)(A.model + e0) - v;      // one fp32 subtraction per element
+    if (e0 >= lo && e0 + 3u < hi) {
+        f32x4 v = *(const f32x4_any *)(A.state + e0);
+        if (OP == SEL_PULL_V) v = *(const f32x4_any *)(A.model + e0) - v;      // one fp32 subtraction per element
         bits[0] = __float_as_uint(v.x);
         bits[1] = __float_as_uint(v.y);
         bits[2] = __float_as_uint(v.z);
@@ -100,11 +99,6 @@ __device__ __forceinline__ uint32_t quad_bits(const SelectArgs &A, uint32_t e0, 
         in |= ok ? (1u << x) : 0u;
     }
     return in;
-}
-
-__device__ __forceinline__ bool rows_aligned(const SelectArgs &A)
-{
-    return (((uintptr_t)A.state | (uintptr_t)A.model) & 15u) == 0;   // (a null model counts as aligned)
 }
 
 struct SelShared {

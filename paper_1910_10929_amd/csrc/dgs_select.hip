@@ -354,7 +354,6 @@ __device__ __forceinline__ void dense_hist(const SelectArgs &A, const TensorDesc
     __syncthreads();
     const DenseRun r = dense_run(td, sd);
     const uint32_t lane = lane_id();
-    const bool vec = rows_aligned(A);
     // two tiles per turn, all of their loads issued before the first counter is touched (the odd
     // last turn reads its one tile twice and counts it once)
     for (uint32_t t = r.t0; t < r.t1; t += 2) {
@@ -364,7 +363,7 @@ __device__ __forceinline__ void dense_hist(const SelectArgs &A, const TensorDesc
         for (int u = 0; u < 2; ++u)
 #pragma unroll
             for (int row = 0; row < 4; ++row)
-                quad_bits<OP>(A, (u && two ? t + 1 : t) * TILE + row * 256 + lane * 4, r.lo, r.hi, vec, bits[u][row]);
+                quad_bits<OP>(A, (u && two ? t + 1 : t) * TILE + row * 256 + lane * 4, r.lo, r.hi, bits[u][row]);
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -387,7 +386,6 @@ __device__ __forceinline__ uint32_t dense_compact(const SelectArgs &A, const Ten
 {
     const DenseRun r = dense_run(td, sd);
     const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
-    const bool vec = rows_aligned(A);
     uint32_t mine = 0;
     for (uint32_t t = r.t0; t < r.t1; t += 2) {      // two tiles in flight, as in dense_hist
         const bool two = t + 1 < r.t1;
@@ -396,7 +394,7 @@ __device__ __forceinline__ uint32_t dense_compact(const SelectArgs &A, const Ten
         for (int u = 0; u < 2; ++u)
 #pragma unroll
             for (int row = 0; row < 4; ++row)
-                in[u][row] = quad_bits<OP>(A, (u && two ? t + 1 : t) * TILE + row * 256 + lane * 4, r.lo, r.hi, vec,
+                in[u][row] = quad_bits<OP>(A, (u && two ? t + 1 : t) * TILE + row * 256 + lane * 4, r.lo, r.hi,
                                            bits[u][row]);
 #pragma unroll
         for (int u = 0; u < 2; ++u)
@@ -422,7 +420,7 @@ __device__ __forceinline__ uint32_t dense_compact(const SelectArgs &A, const Ten
     for (uint32_t t = r.t0; t < r.t1; ++t) {
         uint32_t tbits[4][4], tin[4];
 #pragma unroll
-        for (int row = 0; row < 4; ++row) tin[row] = quad_bits<OP>(A, t * TILE + row * 256 + lane * 4, r.lo, r.hi, vec, tbits[row]);
+        for (int row = 0; row < 4; ++row) tin[row] = quad_bits<OP>(A, t * TILE + row * 256 + lane * 4, r.lo, r.hi, tbits[row]);
 #pragma unroll
         for (int row = 0; row < 4; ++row) {
             const uint32_t e0 = t * TILE + row * 256 + lane * 4;

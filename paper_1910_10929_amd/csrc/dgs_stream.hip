@@ -4,7 +4,7 @@
 
 namespace dgs {
 
-template <int OP, int MODE, bool VEC>
+template <int OP, int MODE>
 __global__ __launch_bounds__(STREAM_THREADS) void k_stream(const StreamArgs A,
                                                            const uint32_t *__restrict__ toff,
                                                            const uint32_t *__restrict__ tau)
@@ -36,41 +36,34 @@ __global__ __launch_bounds__(STREAM_THREADS) void k_stream(const StreamArgs A,
                 cur = qt;
             }
         }
-        if (t < A.ntiles) process_tile<OP, MODE, VEC>(A, toff, tau, t, lhist, cur, stage);
+        if (t < A.ntiles) process_tile<OP, MODE>(A, toff, tau, t, lhist, cur, stage);
     }
     flush_hist<MODE>(lhist, A.ghist, cur);
 }
 
 template <int OP, int MODE>
-static void launch_stream_t(bool vec, const StreamArgs &a, uint32_t blocks, hipStream_t st, void *ev0,
-                            void *ev1)
+static void launch_stream_t(const StreamArgs &a, uint32_t blocks, hipStream_t st, void *ev0, void *ev1)
 {
-    if (vec)
-        launch_k(k_stream<OP, MODE, true>, dim3(blocks), dim3(STREAM_THREADS), st, ev0, ev1, a,
-                 a.toff, a.tau);
-    else
-        launch_k(k_stream<OP, MODE, false>, dim3(blocks), dim3(STREAM_THREADS), st, ev0, ev1, a,
-                 a.toff, a.tau);
+    launch_k(k_stream<OP, MODE>, dim3(blocks), dim3(STREAM_THREADS), st, ev0, ev1, a, a.toff, a.tau);
 }
 
-void launch_stream(int op, int mode, bool vec, const StreamArgs &a, uint32_t blocks, void *stream,
-                   void *ev0, void *ev1)
+void launch_stream(int op, int mode, const StreamArgs &a, uint32_t blocks, void *stream, void *ev0, void *ev1)
 {
     hipStream_t st = (hipStream_t)stream;
     if (blocks == 0) return;
     if (op == OP_FMA) {
-        if (mode == MODE_PLAIN) launch_stream_t<OP_FMA, MODE_PLAIN>(vec, a, blocks, st, ev0, ev1);
-        else if (mode == MODE_COLLECT) launch_stream_t<OP_FMA, MODE_COLLECT>(vec, a, blocks, st, ev0, ev1);
-        else if (mode == MODE_SAMPLE) launch_stream_t<OP_FMA, MODE_SAMPLE>(vec, a, blocks, st, ev0, ev1);
-        else launch_stream_t<OP_FMA, MODE_HIST>(vec, a, blocks, st, ev0, ev1);
+        if (mode == MODE_PLAIN) launch_stream_t<OP_FMA, MODE_PLAIN>(a, blocks, st, ev0, ev1);
+        else if (mode == MODE_COLLECT) launch_stream_t<OP_FMA, MODE_COLLECT>(a, blocks, st, ev0, ev1);
+        else if (mode == MODE_SAMPLE) launch_stream_t<OP_FMA, MODE_SAMPLE>(a, blocks, st, ev0, ev1);
+        else launch_stream_t<OP_FMA, MODE_HIST>(a, blocks, st, ev0, ev1);
     } else if (op == OP_SUB) {
-        if (mode == MODE_COLLECT) launch_stream_t<OP_SUB, MODE_COLLECT>(vec, a, blocks, st, ev0, ev1);
-        else if (mode == MODE_HIST) launch_stream_t<OP_SUB, MODE_HIST>(vec, a, blocks, st, ev0, ev1);
-        else if (mode == MODE_SAMPLE) launch_stream_t<OP_SUB, MODE_SAMPLE>(vec, a, blocks, st, ev0, ev1);
+        if (mode == MODE_COLLECT) launch_stream_t<OP_SUB, MODE_COLLECT>(a, blocks, st, ev0, ev1);
+        else if (mode == MODE_HIST) launch_stream_t<OP_SUB, MODE_HIST>(a, blocks, st, ev0, ev1);
+        else if (mode == MODE_SAMPLE) launch_stream_t<OP_SUB, MODE_SAMPLE>(a, blocks, st, ev0, ev1);
     } else {
-        if (mode == MODE_COLLECT) launch_stream_t<OP_IDENT, MODE_COLLECT>(vec, a, blocks, st, ev0, ev1);
-        else if (mode == MODE_HIST) launch_stream_t<OP_IDENT, MODE_HIST>(vec, a, blocks, st, ev0, ev1);
-        else if (mode == MODE_SAMPLE) launch_stream_t<OP_IDENT, MODE_SAMPLE>(vec, a, blocks, st, ev0, ev1);
+        if (mode == MODE_COLLECT) launch_stream_t<OP_IDENT, MODE_COLLECT>(a, blocks, st, ev0, ev1);
+        else if (mode == MODE_HIST) launch_stream_t<OP_IDENT, MODE_HIST>(a, blocks, st, ev0, ev1);
+        else if (mode == MODE_SAMPLE) launch_stream_t<OP_IDENT, MODE_SAMPLE>(a, blocks, st, ev0, ev1);
     }
 }
 

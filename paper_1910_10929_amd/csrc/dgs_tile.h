@@ -193,7 +193,7 @@ __device__ __forceinline__ void tile_tail(const StreamArgs &A, const uint32_t *_
     }
 }
 
-template <int OP, int MODE, bool VEC>
+template <int OP, int MODE>
 __device__ __forceinline__ void process_tile(const StreamArgs &A, const uint32_t *__restrict__ toff,
                                              const uint32_t *__restrict__ tau, uint32_t t,
                                              uint32_t *lhist, int cur, uint2 *stage, int only = -1)
@@ -204,18 +204,20 @@ __device__ __forceinline__ void process_tile(const StreamArgs &A, const uint32_t
     float a[4][4];
     uint4 d = make_uint4(0, 0, 0xFFFFFFFFu, 0xFFFFFFFFu);
 
-    if (VEC && full) {
+    if (full) {
         // Issue the tile's vector loads first; the scalar search for the tensors touched by
-        // the tile then runs while they are in flight.
+        // the tile then runs while they are in flight.  The buffers need no alignment beyond that
+        // of a float: on rows at odd addresses (a server with an odd number of parameters) a wave's
+        // kilobyte takes one more line.
         f32x4 g[4], s[4];
         if (OP == OP_FMA) {
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                g[r] = __builtin_nontemporal_load((const f32x4 *)(A.grad + base + r * 256 + lane * 4));
+                g[r] = __builtin_nontemporal_load((const f32x4_any *)(A.grad + base + r * 256 + lane * 4));
         }
         if (OP == OP_SUB) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) g[r] = *(const f32x4 *)(A.grad + base + r * 256 + lane * 4);
+            for (int r = 0; r < 4; ++r) g[r] = *(const f32x4_any *)(A.grad + base + r * 256 + lane * 4);
         }
         // Non-temporal like the gradient: a pass that allocates what it streams in the
         // last-level cache pushes out the dirty lines earlier kernels left there and waits for
@@ -224,7 +226,7 @@ __device__ __forceinline__ void process_tile(const StreamArgs &A, const uint32_t
         // 2165 us; buffers small enough to stay cached (102 MB) lose nothing.
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            s[r] = __builtin_nontemporal_load((const f32x4 *)(A.state + base + r * 256 + lane * 4));
+            s[r] = __builtin_nontemporal_load((const f32x4_any *)(A.state + base + r * 256 + lane * 4));
         if (MODE != MODE_PLAIN) d = span_desc(toff, A.J, base, base + TILE - 1u);
 #pragma unroll
         for (int r = 0; r < 4; ++r)
@@ -246,15 +248,15 @@ __device__ __forceinline__ void process_tile(const StreamArgs &A, const uint32_t
 #pragma unroll
                 for (int j = 0; j < 4; ++j) o[j] = a[r][j];
                 float *dst = A.state + base + r * 256 + lane * 4;
-                if (A.store_mode == STORE_NT) __builtin_nontemporal_store(o, (f32x4 *)dst);
+                if (A.store_mode == STORE_NT) __builtin_nontemporal_store((f32x4_any)o, (f32x4_any *)dst);
                 else if (A.store_mode == STORE_WT) store_through16(A.state + uniform(base), (r * 256 + lane * 4) * 4u, o);
-                else *(f32x4 *)dst = o;
+                else *(f32x4_any *)dst = o;
             }
         }
         return;
     }
 
-    // ragged last tile, or buffers that are only 4-byte aligned
+    // ragged last tile
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll

@@ -60,11 +60,11 @@ __device__ __forceinline__ uint2 ld_dev(const uint2 *p)
     return make_uint2((uint32_t)x, (uint32_t)(x >> 32));
 }
 // 16-byte device-scope (write-through) store at base + byte_off; `base` must be wave-uniform
-// and the 16 bytes must lie within 1 MB of it.
+// and the 16 bytes must lie within 1 MB of it (4-byte alignment is enough).
 #ifdef DGS_HOST_EMULATION
 __device__ __forceinline__ void store_through16(float *base, uint32_t byte_off, f32x4 v)
 {
-    *(f32x4 *)((char *)base + byte_off) = v;
+    *(f32x4_any *)((char *)base + byte_off) = v;
 }
 #else
 typedef unsigned u32x4_store __attribute__((__vector_size__(16)));
