@@ -29,7 +29,7 @@ size_t align_up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
 struct Layout {          // byte offsets inside the workspace
     size_t tile_desc, tdesc, plans, tau, hint2, tprev, ghist, tile_cnt, heads, slots, ord, stats, flag;
-    size_t qlist, segtab, grptab, grpcnt, segstart, segcnt, segG1, segOut, segstate, pfxlist, total;
+    size_t qlist, segtab, grptab, grpcnt, segstart, segcnt, segstate, cslabs, slabs_done, total;
 };
 
 bool check_offsets(const uint64_t *offsets, uint32_t J)
@@ -62,6 +62,14 @@ uint32_t tensor_segments(uint64_t off, uint64_t n, uint32_t scale)
     return (uint32_t)((nt + per - 1) / per);
 }
 
+// Chain slabs of a tensor: its parts cut into runs of CSLAB_TILES tiles.
+uint32_t chain_slabs(uint64_t off, uint64_t n, uint32_t scale)
+{
+    const uint64_t nt = (off + n - 1) / TILE - off / TILE + 1;
+    const uint64_t per = part_tiles(off, n, scale), full = nt / per, rest = nt - full * per;
+    return (uint32_t)(full * ((per + CSLAB_TILES - 1) / CSLAB_TILES) + (rest + CSLAB_TILES - 1) / CSLAB_TILES);
+}
+
 uint32_t layout_scale(const uint64_t *offsets, uint32_t J)
 {
     const uint64_t ntiles = (offsets[J] + TILE - 1) / TILE;
@@ -74,12 +82,14 @@ Layout make_layout(const uint64_t *offsets, uint32_t J, uint32_t W)
 {
     const uint64_t n = offsets[J];
     const size_t ntiles = (size_t)((n + TILE - 1) / TILE);
-    size_t nseg_total = 0, ncap = 0;
+    size_t nseg_total = 0, ncs = 0;
     const uint32_t scale = layout_scale(offsets, J);
     for (uint32_t j = 0; j < J; ++j) {
         const uint32_t ns = tensor_segments(offsets[j], offsets[j + 1] - offsets[j], scale);
         nseg_total += ns;
-        ncap += (offsets[j + 1] - offsets[j] >= SEG_MIN_N) ? 1 : 0;
+        const uint64_t nj = offsets[j + 1] - offsets[j];
+        if (nj < SEG_MIN_N) continue;
+        ncs += chain_slabs(offsets[j], nj, scale);
     }
     Layout L;
     size_t o = 0;
@@ -102,10 +112,9 @@ Layout make_layout(const uint64_t *offsets, uint32_t J, uint32_t W)
     L.grpcnt = o;    o = align_up(o + (nseg_total + 1) * sizeof(uint32_t));
     L.segstart = o;  o = align_up(o + (nseg_total + 1) * sizeof(uint32_t));
     L.segcnt = o;    o = align_up(o + (nseg_total + 1) * sizeof(uint32_t));
-    L.segG1 = o;     o = align_up(o + (nseg_total + 1) * sizeof(uint32_t));
-    L.segOut = o;    o = align_up(o + (nseg_total + 1) * sizeof(uint2));
     L.segstate = o;  o = align_up(o + (size_t)J * sizeof(SegState));
-    L.pfxlist = o;   o = align_up(o + (ncap * PFX_CAP + 1) * sizeof(uint4));
+    L.cslabs = o;    o = align_up(o + ncs * sizeof(SegDesc));
+    L.slabs_done = o; o = align_up(o + ncs * sizeof(uint2));
     L.total = o;
     return L;
 }
@@ -172,10 +181,11 @@ struct dgs_ctx {
     uint32_t ngroups = 0, gparts = 1;  // join groups; parts per group
     uint32_t bgroup = 8;               // parts per re-collecting workgroup (about 2048 tiles)
     uint32_t slabs = 1;                // slabs of the longest part (dense requests)
-    uint32_t *segcnt = nullptr, *segG1 = nullptr;
-    uint2 *segOut = nullptr;
+    uint32_t *segcnt = nullptr;
     SegState *segstate = nullptr;
-    uint4 *pfxlist = nullptr;
+    uint2 *slabs_done = nullptr;
+    SegDesc *cslabs = nullptr;
+    uint32_t ncslabs = 0;              // chain slabs
     uint32_t nseg_total = 0;
     HostArr<uint32_t> nseg;            // per tensor: parts (at least one)
     float *diff = nullptr;
@@ -183,8 +193,8 @@ struct dgs_ctx {
     // plan cache
     PlanSlot plan_slot[NPLAN];
     PlanEntry *plan_stage = nullptr;   // pinned host, NPLAN * J
-    uint32_t *host_total = nullptr;    // pinned host: the count of a pull without secondary compression
-    hipEvent_t counted = nullptr;      // ... and the event that says it is in place
+    uint32_t *host_total = nullptr;    // pinned host, behind the staging area: the count of a pull without secondary compression
+    hipEvent_t counted = nullptr;      // ... and the event that says it is in place (from the first such pull on)
     uint64_t tick = 0;
     // which density each hint set was produced for (0 = none yet)
     HostArr<double> hint_density;      // W + 1 entries; entry 0 = worker
@@ -231,13 +241,12 @@ struct ProfSlot {
 // k_j = ceil(density * n_j) in IEEE double; k2 = rank that sets the next predicted threshold.
 // Which tensors take the chain kernels behind the selection: those of at least SEG_MIN_N
 // elements whose hinted candidate list is longer than one workgroup selects from
-// (SEL_LIST_MAX).  For a dense request `seg` means the kernels that read the tensors themselves
+// (SEL_LIST_MAX), and then also those beyond SEL_LIST_CROWDED.  For a dense request `seg` means the kernels that read the tensors themselves
 // (launch_dense): all of them, unless the option forbids it.
 void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out, uint64_t *K_out,
                uint32_t *nseg_active, uint64_t *wire_words_out)
 {
     {
-        const uint64_t list_limit = SEL_LIST_MAX;
         uint64_t K = 0, words = 0;
         uint32_t active = 0;
         for (uint32_t j = 0; j < c->J; ++j) {
@@ -256,7 +265,7 @@ void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out,
             bool seg = false;
             if (c->seg_mode != SEG_MODE_NEVER) {
                 if (density > DENSE_DENSITY) seg = true;
-                else if (nj >= SEG_MIN_N) seg = c->seg_mode == SEG_MODE_ALWAYS || (k2 > k2p ? k2 : k2p) > list_limit;
+                else if (nj >= SEG_MIN_N) seg = c->seg_mode == SEG_MODE_ALWAYS || std::max(k2, k2p) > SEL_LIST_MAX;
             }
             out[j].seg = seg ? 1u : 0u;
             // wire form: local indices of b bits each, the tensor's block padded to whole words
@@ -270,6 +279,13 @@ void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out,
             active += seg ? 1u : 0u;
             K += k;
         }
+        if (active && density <= DENSE_DENSITY)
+            for (uint32_t j = 0; j < c->J; ++j) {
+                const uint64_t nj = c->offsets[j + 1] - c->offsets[j];
+                if (out[j].seg || nj < SEL_CROWDED_TILES * TILE || std::max(out[j].k2, out[j].k2_pull) <= SEL_LIST_CROWDED) continue;
+                out[j].seg = 1u;
+                ++active;
+            }
         *nseg_active = active;
         *K_out = K;
         *wire_words_out = words;
@@ -476,9 +492,9 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
     se.ghist = c->ghist;
     se.segstate = c->segstate;
     se.segcnt = c->segcnt;
-    se.segG1 = c->segG1;
-    se.segOut = c->segOut;
-    se.pfxlist = c->pfxlist;
+    se.cslabs = c->cslabs;
+    se.ncslabs = c->ncslabs;
+    se.slabs_done = c->slabs_done;
     se.out_idx = idx_out;
     se.out_val = val_out;
     se.stats = c->stats;
@@ -496,7 +512,8 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
     se.slabs = c->slabs;
     if (!(dense_req && have_seg)) {
         ProfSlot ps(c, prof_select);
-        launch_select(op_select, se, c->stream, ps.ev0, ps.ev1);
+        if (have_seg) launch_window(se, c->stream, ps.ev0);
+        launch_select(op_select, se, c->stream, have_seg ? nullptr : ps.ev0, ps.ev1);
         ps.launched();
     }
     if (have_seg) {
@@ -535,18 +552,19 @@ void carve_workspace(dgs_ctx *c, void *workspace, const Layout &L)
     c->grpcnt = (uint32_t *)(c->ws + L.grpcnt);
     c->segstart = (uint32_t *)(c->ws + L.segstart);
     c->segcnt = (uint32_t *)(c->ws + L.segcnt);
-    c->segG1 = (uint32_t *)(c->ws + L.segG1);
-    c->segOut = (uint2 *)(c->ws + L.segOut);
     c->segstate = (SegState *)(c->ws + L.segstate);
-    c->pfxlist = (uint4 *)(c->ws + L.pfxlist);
+    c->cslabs = (SegDesc *)(c->ws + L.cslabs);
+    c->slabs_done = (uint2 *)(c->ws + L.slabs_done);
 }
 
 // Tensor, segment and initial-threshold tables of a layout, into host arrays of J,
-// (W + 1) J, J + 1 and (sum of tensor_segments) entries; fills c->nseg and c->nseg_total.
-void fill_tables(dgs_ctx *c, TensorDesc *td, uint32_t *tau0, uint32_t *toff, SegDesc *segs, SegDesc *groups)
+// (W + 1) J, J + 1, (sum of tensor_segments) twice and (sum of chain_slabs) entries; fills c->nseg,
+// c->nseg_total, c->ngroups and c->ncslabs.
+void fill_tables(dgs_ctx *c, TensorDesc *td, uint32_t *tau0, uint32_t *toff, SegDesc *segs, SegDesc *groups,
+                 SegDesc *slabs)
 {
     const uint32_t J = c->J, W = c->W;
-    uint32_t pfx_slots = 0, nsegs = 0;
+    uint32_t nsegs = 0, ncs = 0;
     const uint32_t scale = layout_scale(&c->offsets[0], J);
     for (uint32_t j = 0; j < J; ++j) {
         td[j].off = (uint32_t)c->offsets[j];
@@ -557,7 +575,9 @@ void fill_tables(dgs_ctx *c, TensorDesc *td, uint32_t *tau0, uint32_t *toff, Seg
         const uint32_t per = part_tiles(c->offsets[j], c->offsets[j + 1] - c->offsets[j], scale);
         td[j].seg_first = nsegs;
         td[j].nseg = ns;
-        td[j].pfx_slot = (td[j].n >= SEG_MIN_N) ? pfx_slots++ : 0u;
+        const bool chain = td[j].n >= SEG_MIN_N;
+        td[j].pad = 0;
+        td[j].cs_first = ncs;
         c->nseg[j] = ns;
         const uint32_t tlo = td[j].off / TILE, thi = (td[j].off + td[j].n - 1) / TILE;
         for (uint32_t sidx = 0; sidx < ns; ++sidx) {
@@ -566,13 +586,17 @@ void fill_tables(dgs_ctx *c, TensorDesc *td, uint32_t *tau0, uint32_t *toff, Seg
             d.tile0 = tlo + sidx * per;
             d.ntiles = (thi + 1 - d.tile0 < per) ? (thi + 1 - d.tile0) : per;
             d.sidx = sidx;
+            for (uint32_t t = 0; chain && t < d.ntiles; t += CSLAB_TILES)
+                slabs[ncs++] = SegDesc{j, d.tile0 + t, std::min(CSLAB_TILES, d.ntiles - t), nsegs};
             segs[nsegs++] = d;
             c->slabs = std::max(c->slabs, (d.ntiles + SLAB_TILES - 1) / SLAB_TILES);
         }
+        td[j].ncs = ncs - td[j].cs_first;
         for (uint32_t w = 0; w <= W; ++w) tau0[(size_t)w * J + j] = td[j].big ? 1u : TAU_NEVER;
     }
     for (uint32_t j = 0; j <= J; ++j) toff[j] = (uint32_t)c->offsets[j];
     c->nseg_total = nsegs;
+    c->ncslabs = ncs;
     // re-collecting workgroups: both roles together about as many as the compute units that the
     // tensors' selecting workgroups (at most one per tensor) leave free, each looking after at
     // most 8 consecutive parts
@@ -619,7 +643,7 @@ int upload(dgs_ctx *c, void *dst, const void *src, size_t bytes)
 
 // Tables up, counters cleared: what a context's workspace holds before its first call.
 int upload_tables(dgs_ctx *c, const TensorDesc *td, const uint32_t *tau0, const uint32_t *toff, const SegDesc *segs,
-                  const SegDesc *groups)
+                  const SegDesc *groups, const SegDesc *slabs)
 {
     const uint32_t J = c->J, W = c->W;
     int rc = upload(c, c->toff, toff, ((size_t)J + 1) * sizeof(uint32_t));
@@ -627,6 +651,7 @@ int upload_tables(dgs_ctx *c, const TensorDesc *td, const uint32_t *tau0, const 
     if (rc == DGS_OK) rc = upload(c, c->tau, tau0, (size_t)(W + 1) * J * sizeof(uint32_t));
     if (rc == DGS_OK) rc = upload(c, c->segtab, segs, (size_t)c->nseg_total * sizeof(SegDesc));
     if (rc == DGS_OK) rc = upload(c, c->grptab, groups, (size_t)c->ngroups * sizeof(SegDesc));
+    if (rc == DGS_OK) rc = upload(c, c->cslabs, slabs, (size_t)c->ncslabs * sizeof(SegDesc));
     if (rc != DGS_OK) return rc;
     launch_fill_u32(c->hint2, 0u, (size_t)(W + 1) * J, c->stream);
     launch_fill_u32(c->tprev, 0u, (size_t)(W + 1) * J, c->stream);
@@ -695,16 +720,19 @@ int dgs_create(dgs_ctx **out, const uint64_t *offsets, uint32_t J, uint32_t W, v
     if (env) c->stream_quads = (uint32_t)std::strtoul(env, nullptr, 10);
 
     // host-side plan: tensor and tile descriptors
-    uint32_t nseg_total = 0;
-    for (uint32_t j = 0; j < J; ++j)
-        nseg_total += tensor_segments(offsets[j], offsets[j + 1] - offsets[j], layout_scale(offsets, J));
+    uint32_t nseg_total = 0, ncs = 0;
+    const uint32_t scale = layout_scale(offsets, J);
+    for (uint32_t j = 0; j < J; ++j) {
+        nseg_total += tensor_segments(offsets[j], offsets[j + 1] - offsets[j], scale);
+        if (offsets[j + 1] - offsets[j] >= SEG_MIN_N) ncs += chain_slabs(offsets[j], offsets[j + 1] - offsets[j], scale);
+    }
     std::vector<TensorDesc> td(J);
     std::vector<uint32_t> tau0((size_t)(W + 1) * J);
     std::vector<SegDesc> segs(nseg_total + 1);
     std::vector<uint32_t> toff(J + 1);
-    std::vector<SegDesc> groups(nseg_total + 1);
+    std::vector<SegDesc> groups(nseg_total + 1), slabs(ncs + 1);
     c->nseg.assign(J, 0u);
-    fill_tables(c, td.data(), tau0.data(), toff.data(), segs.data(), groups.data());
+    fill_tables(c, td.data(), tau0.data(), toff.data(), segs.data(), groups.data(), slabs.data());
 
     // What a sampling pass visits: every 16th tile of the buffer, and every tile of the tensors of
     // at most 64 tiles, whose ranks are too small to estimate from a sixteenth.
@@ -724,16 +752,14 @@ int dgs_create(dgs_ctx **out, const uint64_t *offsets, uint32_t J, uint32_t W, v
     c->nqlist = (uint32_t)qlist.size();
     bool ok = true;
     ok = ok && upload(c, c->qlist, qlist.data(), qlist.size() * sizeof(uint32_t)) == DGS_OK;
-    ok = ok && hipHostMalloc((void **)&c->plan_stage, (size_t)NPLAN * J * sizeof(PlanEntry), hipHostMallocDefault) == hipSuccess;
-    ok = ok && hipHostMalloc((void **)&c->host_total, 64, hipHostMallocDefault) == hipSuccess;
-    ok = ok && hipEventCreate(&c->counted) == hipSuccess;
-    ok = ok && upload_tables(c, td.data(), tau0.data(), toff.data(), segs.data(), groups.data()) == DGS_OK;
+    const size_t stage_bytes = align_up((size_t)NPLAN * J * sizeof(PlanEntry));
+    ok = ok && hipHostMalloc((void **)&c->plan_stage, stage_bytes + 64, hipHostMallocDefault) == hipSuccess;
+    if (ok) c->host_total = (uint32_t *)((char *)c->plan_stage + stage_bytes);
+    ok = ok && upload_tables(c, td.data(), tau0.data(), toff.data(), segs.data(), groups.data(), slabs.data()) == DGS_OK;
     ok = ok && hipStreamSynchronize(c->stream) == hipSuccess;
     ok = ok && hipGetLastError() == hipSuccess;
     if (!ok) {
         if (c->plan_stage) (void)hipHostFree(c->plan_stage);
-        if (c->host_total) (void)hipHostFree(c->host_total);
-        if (c->counted) (void)hipEventDestroy(c->counted);
         delete c;
         return DGS_EHIP;
     }
@@ -750,7 +776,6 @@ int dgs_destroy(dgs_ctx *c)
         for (auto e : p.stop) (void)hipEventDestroy(e);
     }
     if (c->plan_stage) (void)hipHostFree(c->plan_stage);
-    if (c->host_total) (void)hipHostFree(c->host_total);
     if (c->counted) (void)hipEventDestroy(c->counted);
     delete c;
     return DGS_OK;
@@ -801,6 +826,7 @@ static __device__ __align__(256) unsigned char scratch[DGS_STATIC_SCRATCH_BYTES]
 
 constexpr int STATIC_MAX_DEVICES = 64;
 constexpr uint32_t STATIC_MAX_SEGS = 1024;
+constexpr uint32_t STATIC_MAX_SLABS = SEG_TILES < 64 ? 2048 : 1024;
 void *g_scratch_ptr[STATIC_MAX_DEVICES];   // device address of `scratch`, per device (0 = not asked yet)
 std::mutex g_scratch_mutex;
 
@@ -847,6 +873,10 @@ int dgs_worker_step_static(const uint64_t *offsets, uint32_t J, const float *gra
     for (uint32_t j = 0; j < J; ++j)
         nseg_total += tensor_segments(offsets[j], offsets[j + 1] - offsets[j], layout_scale(offsets, J));
     if (nseg_total > STATIC_MAX_SEGS) return DGS_ECAPACITY;
+    // (chain slabs: the limit holds T tiles, of which at most T / CSLAB_TILES full slabs, and one
+    // shorter slab per part: at most T / SEG_TILES full parts and one shorter part per tensor)
+    constexpr size_t T = DGS_STATIC_SCRATCH_BYTES / (2 * CAPT * sizeof(uint2)) + DGS_STATIC_MAX_TENSORS;
+    static_assert(T / CSLAB_TILES + T / SEG_TILES + DGS_STATIC_MAX_TENSORS <= STATIC_MAX_SLABS, "slab table of a static call");
     void *ws = nullptr;
     int rc = static_scratch(&ws);
     if (rc != DGS_OK) return rc;
@@ -858,7 +888,7 @@ int dgs_worker_step_static(const uint64_t *offsets, uint32_t J, const float *gra
     TensorDesc td[DGS_STATIC_MAX_TENSORS];
     uint32_t tau0[DGS_STATIC_MAX_TENSORS], toff[DGS_STATIC_MAX_TENSORS + 1];
     SegDesc segs[STATIC_MAX_SEGS + 1];
-    SegDesc groups[STATIC_MAX_SEGS + 1];
+    SegDesc groups[STATIC_MAX_SEGS + 1], slabs[STATIC_MAX_SLABS];
     PlanEntry plan[DGS_STATIC_MAX_TENSORS];
     for (uint32_t j = 0; j <= J; ++j) offs[j] = offsets[j];
     dgs_ctx c;
@@ -874,10 +904,10 @@ int dgs_worker_step_static(const uint64_t *offsets, uint32_t J, const float *gra
     c.hint_density.borrow(hint_density);
     c.plan_stage = plan;               // one density per call: only the first cache slot is used
     carve_workspace(&c, ws, L);
-    fill_tables(&c, td, tau0, toff, segs, groups);
+    fill_tables(&c, td, tau0, toff, segs, groups, slabs);
     // every call starts from a clean workspace (the array keeps the previous call's contents);
     // with no threshold hints the step takes the two-pass path
-    rc = upload_tables(&c, td, tau0, toff, segs, groups);
+    rc = upload_tables(&c, td, tau0, toff, segs, groups, slabs);
     if (rc != DGS_OK) return rc;
     return run_selection(&c, OP_FMA, SEL_WORKER, grad, state, lr, m, density, 0, idx_out, val_out, nnz_out,
                          DGS_PROF_WORKER_STREAM, DGS_PROF_WORKER_SELECT, DGS_PROF_WORKER_SEGMENTED);
@@ -975,6 +1005,7 @@ namespace {
 int pull_all(dgs_ctx *c, float *row, const float *model, uint32_t *idx_out, float *val_out, uint64_t capacity,
              uint64_t *nnz_out)
 {
+    if (!c->counted && hipEventCreate(&c->counted) != hipSuccess) return DGS_EHIP;
     launch_pull_all(row, model, c->n, c->ntiles, c->tile_cnt, c->slots, (uint32_t *)c->heads, c->flag + 8, c->flag + 4,
                     c->host_total, capacity, idx_out, val_out, c->stream, c->counted);
     if (hipGetLastError() != hipSuccess) return DGS_EHIP;

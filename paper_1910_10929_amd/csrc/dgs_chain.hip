@@ -1,256 +1,374 @@
-// The chain: what follows the selection kernel for tensors whose candidate lists are too long
-// for one workgroup.  The selection kernel has left, per tensor, the 19-bit prefix of the k-th key and
-// its rank among the entries sharing that prefix; here
-//   prefix  per part   : counts the entries above the prefix, appends those sharing it to the
-//                        tensor's prefix list and counts their low 12 bits; the part that
-//                        arrives last for a tensor RANKS: exact k-th key, tie budget, and every
-//                        part's output position
-//   emit    per part   : ordered emission ("encode()" of Algorithms 1-3) and the state fix-up
-//                        (Eq. 12 / Eq. 6).
-// Dense requests have no candidate lists; their passes over the tensors themselves are at the end
-// of this file.
+// The chain: tensors whose candidate lists are too long for one workgroup to join and select from.
+// The candidates stay where the streaming pass has left them, tile by tile; one wavefront takes 8 or
+// 16 tiles at a time, all of their first 64 candidates in flight together, and the work is cut into
+// slabs of CSLAB_TILES tiles, so that it fills the chip for any number of tensors.  Joining the
+// candidates into one ordered list first, one workgroup per 4096 tiles, was bound by that
+// workgroup: 92 us of a call on ResNet-50 shapes at 1 % without momentum (now 10 for the window
+// and 23 for the finish), 232 us at 1 % of 1e9 parameters.  At that size each pass reads 240 MB of
+// candidates and the emission is bound by its scattered 4-byte stores (1e7 of them: 420 us).
+//   window  (before the selection kernel) per part: window histogram of the candidates, in a slot
+//           of its own -- no atomics between workgroups; the selection kernel adds a tensor's
+//           parts up and leaves the 19-bit prefix of the k-th key and its rank below it
+//   finish  two workgroups per slab.  RANK counts the low 12 bits of the entries that share the
+//           prefix; the one arriving last for a tensor ranks: the exact k-th key and how many of the
+//           entries equal to it are taken.  EMIT awaits that, counts its winners, adds up what the
+//           slabs before it have published, and writes its stretch of the message ("encode()" of
+//           Algorithms 1-3) and the state fix-up (Eq. 12 / Eq. 6).  Ties need no list and no case
+//           of their own.  Waiting is for blocks with lower indices only, and bounded.
+// A tensor whose prediction failed was collected again into one list per part by the selection
+// kernel (SEG_LISTS); its slabs then take equal shares of those lists in place of their tiles.
+// Dense requests have no candidates; their passes over the tensors themselves are at the end of
+// this file.
 #include "dgs_select.h"
 
 namespace dgs {
 
-// The entries one part contributes: its stretch of the tensor's candidate lists, in index order.
-struct PartSource {
-    const uint2 *list;
-    uint32_t count;
+constexpr uint32_t WINDOW_TPW = 16;       // tiles of one wavefront of k_list_window at a time
+
+// The candidates of up to 64 consecutive tiles: lane i describes tile i.
+struct WaveTiles {
+    uint32_t t0;         // the first of them
+    uint32_t n, start;   // candidates of the tensor, and where they start: in the tile (after those of a
+                         // previous tensor), or in the ordered lists
+    bool lists;
+    int ovf;
 };
 
-__device__ __forceinline__ PartSource part_source(const SelectArgs &A, uint32_t part)
+__device__ __forceinline__ WaveTiles wave_tiles(const SelectArgs &A, const TensorDesc &td, uint32_t t0, uint32_t nt,
+                                                bool lists, uint32_t part)
 {
-    return PartSource{A.ord + A.segstart[part], A.segcnt[part] & 0x7FFFFFFFu};
+    const uint32_t lane = lane_id();
+    WaveTiles w;
+    w.t0 = t0;
+    w.lists = lists;
+    w.n = w.start = 0;
+    w.ovf = 0;
+    if (!lists) {
+        const uint32_t cnt = (lane < nt) ? A.tile_cnt[t0 + lane] : 0u;
+        tile_counts(cnt, t0 + lane, td.off / TILE, (td.off % TILE) != 0, w.n, w.start, w.ovf);
+    } else if (lane < nt) {
+        const SegDesc ps = A.segtab[part];
+        const uint64_t cnt = A.segcnt[part] & 0x7FFFFFFFu, i = t0 + lane - ps.tile0;
+        const uint64_t lo = cnt * i / ps.ntiles, hi = cnt * (i + 1) / ps.ntiles;
+        w.n = (uint32_t)(hi - lo);
+        w.start = A.segstart[part] + (uint32_t)lo;
+    }
+    return w;
 }
 
-constexpr uint32_t PFX_STAGE = 1024;   // entries sharing the prefix that one part can stage in LDS
+__device__ __forceinline__ uint32_t tile_n(const WaveTiles &w, uint32_t i)
+{
+    return (uint32_t)__builtin_amdgcn_readlane((int)w.n, (int)i);
+}
 
-struct ChainShared {
+// Candidate q of tile i (q below its count).
+__device__ __forceinline__ uint2 tile_get(const SelectArgs &A, const WaveTiles &w, uint32_t i, uint32_t start, uint32_t q)
+{
+    const uint32_t p = start + q;
+    if (w.lists) return A.ord[p];
+    return (p < HEAD) ? A.heads[(size_t)(w.t0 + i) * HEAD + p] : A.slots[(size_t)(w.t0 + i) * CAPT + p];
+}
+
+// The first 64 candidates of every tile, candidate `lane` of tile i in e[i].
+template <uint32_t CTPW>
+__device__ __forceinline__ void tile_firsts(const SelectArgs &A, const WaveTiles &w, uint2 (&e)[CTPW])
+{
+    const uint32_t lane = lane_id();
+#pragma unroll
+    for (uint32_t i = 0; i < CTPW; ++i) {
+        const uint32_t start = (uint32_t)__builtin_amdgcn_readlane((int)w.start, (int)i);
+        e[i] = (lane < tile_n(w, i)) ? tile_get(A, w, i, start, lane) : make_uint2(0u, 0u);
+    }
+}
+
+// f(entry) for every candidate, in no particular order (lanes diverge inside f).
+template <uint32_t CTPW, class F>
+__device__ __forceinline__ void each_candidate(const SelectArgs &A, const WaveTiles &w, F f)
+{
+    const uint32_t lane = lane_id();
+    uint2 e[CTPW];
+    tile_firsts(A, w, e);
+#pragma unroll
+    for (uint32_t i = 0; i < CTPW; ++i)
+        if (lane < tile_n(w, i)) f(e[i]);
+#pragma unroll 1
+    for (uint32_t i = 0; i < CTPW; ++i) {
+        const uint32_t n = tile_n(w, i);
+        if (n <= 64) continue;
+        const uint32_t start = (uint32_t)__builtin_amdgcn_readlane((int)w.start, (int)i);
+        for (uint32_t q = 64 + lane; q < n; q += 64) f(tile_get(A, w, i, start, q));
+    }
+}
+
+__global__ __launch_bounds__(SEL_THREADS) void k_list_window(const SelectArgs A)
+{
+    __shared__ uint32_t h[SEG_WBINS];
+    __shared__ uint32_t wsum[SEL_WAVES];
+    const uint32_t part = blockIdx.x;
+    const SegDesc sd = A.segtab[part];
+    if (!A.plan[sd.j].seg) return;
+    const TensorDesc td = A.tdesc[sd.j];
+    const uint32_t tid = threadIdx.x, wave = uniform(tid >> 6);
+    const uint32_t win = seg_window_base(A.tau[sd.j], A.tprev[sd.j]);
+    for (uint32_t b = tid; b < SEG_WBINS; b += SEL_THREADS) h[b] = 0;
+    __syncthreads();
+    uint32_t mine = 0;
+    int ovf = 0;
+    for (uint32_t t = wave * WINDOW_TPW; t < sd.ntiles; t += SEL_WAVES * WINDOW_TPW) {
+        const WaveTiles w = wave_tiles(A, td, sd.tile0 + t, min(WINDOW_TPW, sd.ntiles - t), false, part);
+        mine += w.n;
+        ovf |= w.ovf;
+        each_candidate<WINDOW_TPW>(A, w, [&](uint2 e) {
+            const uint32_t hi12 = (e.y & 0x7FFFFFFFu) >> SEG_LOWBITS;
+            const uint32_t b = (hi12 > win) ? (hi12 - win) : 0u;
+            atomicAdd(&h[min(b, SEG_WBINS - 1u)], 1u);
+        });
+    }
+    const uint32_t c = block_sum(mine, wsum, SEL_WAVES);
+    const bool over = __syncthreads_or(ovf) != 0;
+    uint32_t *out = part_hist(A, td, sd.j, sd.sidx);
+    for (uint32_t b = tid; b < SEG_WBINS; b += SEL_THREADS) out[b] = h[b];
+    if (tid == 0) A.segcnt[part] = c | (over ? 0x80000000u : 0u);
+}
+
+// What a slab publishes for the slabs behind it: its entries above the k-th key and equal to it
+// (SLAB_OWN), or the same for all slabs of the tensor up to and including it (SLAB_SUM).
+constexpr uint64_t SLAB_OWN = 1ull << 62, SLAB_SUM = 2ull << 62;
+__device__ __forceinline__ uint64_t slab_word(uint64_t kind, uint32_t g, uint32_t q)
+{
+    return kind | ((uint64_t)q << 31) | g;       // 31 bits each: fewer than n / 4 candidates
+}
+__device__ __forceinline__ uint32_t slab_g(uint64_t w) { return (uint32_t)w & 0x7FFFFFFFu; }
+__device__ __forceinline__ uint32_t slab_q(uint64_t w) { return (uint32_t)(w >> 31) & 0x7FFFFFFFu; }
+
+__device__ __forceinline__ void slab_publish(const SelectArgs &A, uint32_t slab, uint64_t w)
+{
+    st_dev(&A.slabs_done[slab], make_uint2((uint32_t)w, (uint32_t)(w >> 32)));
+}
+
+// Entries above / equal to the k-th key in the tensor's slabs before this one, by one wavefront
+// looking back over up to 64 slabs at a time until one has published its running sum.  Those are
+// blocks with lower indices; bounded by A.spin_limit polls.
+__device__ __forceinline__ void slab_look_back(const SelectArgs &A, uint32_t slab, uint32_t first, uint32_t &g, uint32_t &q)
+{
+    const uint32_t lane = lane_id();
+    g = q = 0;
+    for (uint32_t hi = slab; hi > first;) {          // slabs [first, hi) are still to be added
+        const bool in = hi - first > lane;
+        uint64_t w = 0;
+        uint64_t have = 0, sums = 0;
+        for (uint32_t spin = 0; spin < A.spin_limit; ++spin) {
+            if (in && w == 0) {
+                const uint2 x = ld_dev(&A.slabs_done[hi - 1u - lane]);
+                w = ((uint64_t)x.y << 32) | x.x;
+            }
+            have = ballot64(!in || w != 0);
+            sums = ballot64(in && (w & SLAB_SUM) != 0);
+            // everything up to the nearest running sum (or all 64) has been published
+            const uint64_t upto = sums ? (((sums & (0ull - sums)) << 1) - 1ull) : ~0ull;
+            if ((have & upto) == upto) break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        const uint64_t upto = sums ? (((sums & (0ull - sums)) << 1) - 1ull) : ~0ull;
+        if ((have & upto) != upto) {                 // gave up waiting
+            if (lane == 0) atomicAdd(&A.stats->internal_errors, 1ull);
+            return;
+        }
+        w &= 0ull - ((upto >> lane) & 1ull);         // (lanes beyond `first` hold 0)
+        g += wave_sum(slab_g(w));
+        q += wave_sum(slab_q(w));
+        if (sums) return;
+        hi = (hi - first > 64u) ? hi - 64u : first;
+    }
+}
+
+struct FinishShared {
     uint32_t h[SEG_LBINS];
-    uint32_t sG[SEG_MAX_PER_TENSOR];
-    uint32_t sQ[SEG_MAX_PER_TENSOR];
     uint32_t rowsum[64];
     int res[6];
-    uint32_t wsum[SEL_WAVES];
-    uint2 stage[PFX_STAGE];
-    uint32_t nstage, base, bc;
+    uint32_t wtot[SEL_WAVES];
+    uint32_t g, q, T, rT, bc;
 };
 
-__global__ __launch_bounds__(SEL_THREADS) void k_chain_prefix(const SelectArgs A)
+// RANK (blocks below A.ncslabs): the low key bits of the slab's entries that share the prefix.
+template <uint32_t THREADS>
+__device__ __forceinline__ void rank_slab(const SelectArgs &A, uint32_t slab, const SegDesc &sd, const TensorDesc &td,
+                                          SegState *st, bool lists, FinishShared &C)
 {
-    __shared__ ChainShared C;
-    const uint32_t part = blockIdx.x;
-    const SegDesc sd = A.segtab[part];
-    const uint32_t j = sd.j;
-    const PlanEntry pe = A.plan[j];
-    if (!pe.seg) return;
-    SegState *st = &A.segstate[j];
-    if (st->status != SEG_ACTIVE) return;
-    const TensorDesc td = A.tdesc[j];
-    const PartSource src = part_source(A, part);
-    const uint32_t cs = src.count;
-    const uint32_t tid = threadIdx.x;
+    constexpr uint32_t CTPW = CSLAB_TILES / (THREADS / 64);      // tiles of one wavefront
+    const uint32_t tid = threadIdx.x, wave = uniform(tid >> 6);
     const uint32_t pfx = st->pfx;
-    uint4 *plist = A.pfxlist + (size_t)td.pfx_slot * PFX_CAP;
-    uint32_t *glow = A.ghist + (size_t)j * HBINS;   // low key bits of the entries sharing the prefix
-    if (tid == 0) C.nstage = 0;
-    __syncthreads();
-    uint32_t g1 = 0;
-    for (uint32_t eb = 0; eb < cs; eb += 4 * SEL_THREADS) {
-        uint2 ent[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint32_t e = eb + u * SEL_THREADS + tid;
-            ent[u] = (e < cs) ? src.list[e] : make_uint2(0, 0);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint32_t e = eb + u * SEL_THREADS + tid;
-            if (e < cs) {
-                const uint32_t hi12 = (ent[u].y & 0x7FFFFFFFu) >> SEG_LOWBITS;
-                if (hi12 > pfx) {
-                    ++g1;
-                } else if (hi12 == pfx) {
-                    atomicAdd(&glow[ent[u].y & (SEG_LBINS - 1u)], 1u);
-                    const uint32_t p = atomicAdd(&C.nstage, 1u);
-                    if (p < PFX_STAGE) C.stage[p] = ent[u];
-                }
-            }
-        }
-    }
-    const uint32_t G1 = block_sum(g1, C.wsum, SEL_WAVES);   // its barriers also complete `stage`
-    const uint32_t ns = C.nstage;
-    if (tid == 0) {
-        st_dev(&A.segG1[part], G1);
-        // one reservation per part in the tensor's prefix list; a part that could not stage all
-        // of its entries pushes the count past the capacity, and the ranking counts instead
-        if (ns) C.base = __hip_atomic_fetch_add(&st->pfxcount, ns > PFX_STAGE ? PFX_CAP + 1u : ns,
-                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __syncthreads();
-    if (ns && ns <= PFX_STAGE) {
-        const uint32_t b0 = C.base;
-        for (uint32_t i = tid; i < ns; i += SEL_THREADS)
-            if (b0 + i < PFX_CAP) {
-                // (index, value bits) and (part, 0) as two 8-byte device-scope stores
-                uint2 *dst = (uint2 *)&plist[b0 + i];
-                st_dev(&dst[0], C.stage[i]);
-                st_dev(&dst[1], make_uint2(sd.sidx, 0u));
-            }
-    }
-    if (!arrive_last(&st->arrive[3], td.nseg, &C.bc)) return;
-
-    // ------------------------------------------------------------------ RANK (last part)
-    const uint32_t m = ld_dev(&st->pfxcount);
-    const uint32_t r2 = st->r2;
-    for (uint32_t s = tid; s < td.nseg; s += SEL_THREADS) { C.sG[s] = 0; C.sQ[s] = 0; }
-    for (uint32_t b = tid; b < SEG_LBINS; b += SEL_THREADS) {
+    uint32_t *glow = A.ghist + (size_t)sd.j * HBINS;
+    const uint32_t first = min(wave * CTPW, sd.ntiles);
+    const WaveTiles w = wave_tiles(A, td, sd.tile0 + first, min(CTPW, sd.ntiles - first), lists, sd.sidx);
+    if (tid == 0) slab_publish(A, slab, 0);          // nothing published yet (complete before the arrival below)
+    each_candidate<CTPW>(A, w, [&](uint2 e) {
+        if (((e.y & 0x7FFFFFFFu) >> SEG_LOWBITS) == pfx) atomicAdd(&glow[e.y & (SEG_LBINS - 1u)], 1u);
+    });
+    if (!arrive_last(&st->arrive[3], td.ncs, &C.bc)) return;
+    // the tensor's last slab: exact k-th key and tie budget
+    for (uint32_t b = tid; b < SEG_LBINS; b += THREADS) {
         const uint32_t v = ld_dev(&glow[b]);
         C.h[b] = v;
-        if (v) st_dev(&glow[b], 0u);   // clean for the next use
+        if (v) st_dev(&glow[b], 0u);                 // clean for the next use
     }
-    find_ranks<SEG_LBINS, SEL_WAVES>(C.h, r2, 0u, 0u, C.rowsum, C.res);
-    const int b3 = C.res[0];
-    if (b3 < 0) {   // the rank exceeds what the parts counted: cannot happen
-        if (tid == 0) {
-            st->status = SEG_FALLBACK;
-            atomicAdd(&A.stats->internal_errors, 1ull);
-        }
-        return;
-    }
-    const uint32_t T = (pfx << SEG_LOWBITS) | (uint32_t)b3;
-    const uint32_t rT = (uint32_t)C.res[1];   // entries equal to T that are taken, lowest index first
-    __syncthreads();
-    if (m <= PFX_CAP) {
-        for (uint32_t p = tid; p < m; p += SEL_THREADS) {
-            const uint2 *srcp = (const uint2 *)&plist[p];
-            const uint2 e = ld_dev(&srcp[0]);
-            const uint32_t seg = ld_dev(&srcp[1]).x;
-            const uint32_t low = e.y & (SEG_LBINS - 1u);
-            if (seg >= td.nseg) continue;      // (a corrupted list entry)
-            if (low > (uint32_t)b3) atomicAdd(&C.sG[seg], 1u);
-            else if (low == (uint32_t)b3) atomicAdd(&C.sQ[seg], 1u);
-        }
-        __syncthreads();
-    } else {
-        // too many entries share the prefix for the list (massive ties): count every part
-        // against T here -- slow, reached by degenerate data only
-        for (uint32_t s = 0; s < td.nseg; ++s) {
-            const PartSource q = part_source(A, td.seg_first + s);
-            uint32_t g = 0, qq = 0;
-            for (uint32_t e = tid; e < q.count; e += SEL_THREADS) {
-                const uint2 ent = ld_dev(&q.list[e]);
-                const uint32_t key = ent.y & 0x7FFFFFFFu;
-                if ((key >> SEG_LOWBITS) == pfx) {
-                    g += (key > T) ? 1u : 0u;
-                    qq += (key == T) ? 1u : 0u;
-                }
-            }
-            const uint32_t Gs = block_sum(g, C.wsum, SEL_WAVES);
-            const uint32_t Qs = block_sum(qq, C.wsum, SEL_WAVES);
-            if (tid == 0) { C.sG[s] = Gs; C.sQ[s] = Qs; }
-        }
-        __syncthreads();
-    }
-    // parts in order: ties are taken lowest index first, i.e. earlier parts first
-    uint32_t carry_q = 0, carry_o = 0;
-    for (uint32_t sb = 0; sb < td.nseg; sb += SEL_THREADS) {
-        const uint32_t s = sb + tid;
-        const bool in = s < td.nseg;
-        const uint32_t G = in ? (ld_dev(&A.segG1[td.seg_first + s]) + C.sG[s]) : 0u;
-        const uint32_t Q = in ? C.sQ[s] : 0u;
-        uint32_t totq, toto;
-        const uint32_t qb = carry_q + block_excl_scan<SEL_WAVES>(Q, C.wsum, totq);
-        const uint32_t take = min(Q, (rT > qb) ? (rT - qb) : 0u);
-        const uint32_t ob = carry_o + block_excl_scan<SEL_WAVES>(G + take, C.wsum, toto);
-        if (in) A.segOut[td.seg_first + s] = make_uint2(ob, take);
-        carry_q += totq;
-        carry_o += toto;
-    }
+    find_ranks<SEG_LBINS, (int)(THREADS / 64)>(C.h, st->r2, 0u, 0u, C.rowsum, C.res);
     if (tid == 0) {
-        st->T = T;
-        st->pfxcount = 0;
-        A.tprev[j] = T;
-        if (carry_o != pe.k) atomicAdd(&A.stats->internal_errors, 1ull);
+        // (a rank beyond what the slabs counted cannot happen: nothing is sent then, and it is reported)
+        if (C.res[0] < 0) atomicAdd(&A.stats->internal_errors, 1ull);
+        const uint32_t T = (C.res[0] < 0) ? 0x7FFFFFFFu : ((pfx << SEG_LOWBITS) | (uint32_t)C.res[0]);
+        st_dev(&st->T, T);
+        st_dev(&st->rT, (C.res[0] < 0) ? 0u : (uint32_t)C.res[1]);
+        st_dev(&A.tprev[sd.j], T);
+        wait_mem();
+        st_dev(&st->ready, 1u);
     }
 }
 
-template <int OP>
-__global__ __launch_bounds__(SEG_THREADS) void k_chain_emit(const SelectArgs A)
+// EMIT (the other blocks): ordered emission of the slab and the state fix-up.
+template <int OP, uint32_t THREADS>
+__device__ __forceinline__ void emit_slab(const SelectArgs &A, uint32_t slab, const SegDesc &sd, const TensorDesc &td,
+                                          const PlanEntry &pe, SegState *st, bool lists, FinishShared &C)
 {
-    __shared__ uint32_t wsum[SEG_THREADS / 64];
-    const uint32_t part = blockIdx.x;
-    const SegDesc sd = A.segtab[part];
+    constexpr uint32_t WAVES = THREADS / 64, CTPW = CSLAB_TILES / WAVES;
+    const uint32_t tid = threadIdx.x, lane = lane_id(), wave = uniform(tid >> 6);
+    const uint32_t first = min(wave * CTPW, sd.ntiles);
+    const WaveTiles w = wave_tiles(A, td, sd.tile0 + first, min(CTPW, sd.ntiles - first), lists, sd.sidx);
+    uint2 e[CTPW];
+    tile_firsts(A, w, e);                            // on their way while the ranking is awaited
+    if (wait_word(&st->ready, A.spin_limit, &C.bc) == 0) {
+        if (tid == 0) atomicAdd(&A.stats->internal_errors, 1ull);
+        return;
+    }
+    const uint32_t T = uniform(ld_dev(&st->T)), rT = uniform(ld_dev(&st->rT));
+    // entries above T (low half) and equal to it (high half) of this wavefront: a few thousand at most
+    uint32_t mine = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < CTPW; ++i) {
+        const uint32_t key = e[i].y & 0x7FFFFFFFu;
+        if (lane < tile_n(w, i)) mine += (key > T ? 1u : 0u) + (key == T ? 0x10000u : 0u);
+    }
+#pragma unroll 1
+    for (uint32_t i = 0; i < CTPW; ++i) {
+        const uint32_t n = tile_n(w, i), start = (uint32_t)__builtin_amdgcn_readlane((int)w.start, (int)i);
+        for (uint32_t q = 64 + lane; q < n; q += 64) {
+            const uint32_t key = tile_get(A, w, i, start, q).y & 0x7FFFFFFFu;
+            mine += (key > T ? 1u : 0u) + (key == T ? 0x10000u : 0u);
+        }
+    }
+    const uint32_t sum = wave_sum(mine);
+    if (lane == 0) C.wtot[wave] = sum;
+    // sent_k += G reads the row: all of these reads are in flight before the first is needed
+    float old[CTPW];
+    if (OP == SEL_PULL_V) {
+#pragma unroll
+        for (uint32_t i = 0; i < CTPW; ++i)
+            old[i] = (lane < tile_n(w, i) && (e[i].y & 0x7FFFFFFFu) >= T && e[i].x < A.n) ? A.state[e[i].x] : 0.0f;
+    }
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+#pragma unroll
+    for (uint32_t x = 0; x < WAVES; ++x) {
+        before += (x < wave) ? C.wtot[x] : 0u;
+        all += C.wtot[x];
+    }
+    if (wave == 0) {
+        const bool head = (slab == td.cs_first);
+        if (lane == 0) slab_publish(A, slab, slab_word(head ? SLAB_SUM : SLAB_OWN, all & 0xFFFFu, all >> 16));
+        uint32_t g, q;
+        slab_look_back(A, slab, td.cs_first, g, q);
+        if (lane == 0) {
+            if (!head) slab_publish(A, slab, slab_word(SLAB_SUM, g + (all & 0xFFFFu), q + (all >> 16)));
+            C.g = g;
+            C.q = q;
+            if (slab + 1 == td.cs_first + td.ncs && g + (all & 0xFFFFu) + rT != pe.k)      // the tensor's last slab
+                atomicAdd(&A.stats->internal_errors, 1ull);
+        }
+    }
+    __syncthreads();
+    uint32_t eq = C.q + (before >> 16);              // the tensor's ties seen so far: lowest index first, rT of them are taken
+    uint32_t pos = C.g + (before & 0xFFFFu) + min(eq, rT);
+    auto send = [&](uint2 x, float was, bool valid) {             // up to 64 consecutive entries; all lanes call
+        const uint32_t key = x.y & 0x7FFFFFFFu;
+        bool f = valid && key > T;
+        const bool tie = valid && key == T;
+        const uint64_t mq = ballot64(tie);
+        if (mq != 0) {
+            if (tie) f = eq + mbcnt64(mq) < rT;
+            eq += (uint32_t)__popcll(mq);
+        }
+        const uint64_t mk = ballot64(f);
+        const uint32_t p = pos + mbcnt64(mk);
+        if (f && p < pe.k) {
+            const float v = __uint_as_float(x.y);
+            A.out_idx[pe.outoff + p] = x.x;
+            A.out_val[pe.outoff + p] = v;
+            if (index_ok(A, x.x)) {
+                if (OP == SEL_WORKER) store_scattered(&A.state[x.x], A.m * v);
+                else if (OP == SEL_PULL) store_scattered(&A.state[x.x], 0.0f);
+                else store_scattered(&A.state[x.x], was + v);
+            }
+        }
+        pos += (uint32_t)__popcll(mk);
+    };
+#pragma unroll
+    for (uint32_t i = 0; i < CTPW; ++i) {
+        const uint32_t n = tile_n(w, i);
+        if (n == 0) continue;                                     // (wave-uniform, like all of this loop)
+        send(e[i], OP == SEL_PULL_V ? old[i] : 0.0f, lane < n);
+        const uint32_t start = (uint32_t)__builtin_amdgcn_readlane((int)w.start, (int)i);
+        for (uint32_t q0 = 64; q0 < n; q0 += 64) {
+            const bool valid = q0 + lane < n;
+            const uint2 x = valid ? tile_get(A, w, i, start, q0 + lane) : make_uint2(0u, 0u);
+            const float was = (OP == SEL_PULL_V && valid && x.x < A.n) ? A.state[x.x] : 0.0f;
+            send(x, was, valid);
+        }
+    }
+}
+
+template <int OP, uint32_t THREADS>
+__global__ __launch_bounds__(THREADS) void k_list_finish(const SelectArgs A)
+{
+    __shared__ FinishShared C;
+    const bool emit = blockIdx.x >= A.ncslabs;
+    const uint32_t slab = emit ? blockIdx.x - A.ncslabs : blockIdx.x;
+    const SegDesc sd = A.cslabs[slab];               // (its sidx is the part it lies in)
     const PlanEntry pe = A.plan[sd.j];
     if (!pe.seg) return;
-    const SegState *st = &A.segstate[sd.j];
-    const uint32_t tid = threadIdx.x;
-    if (st->status != SEG_ACTIVE) return;
-    const uint32_t T = st->T;
-    const uint2 so = A.segOut[part];
-    const PartSource src = part_source(A, part);
-    const uint32_t cs = src.count;
-    constexpr uint32_t ITEMS = 4;
-    uint32_t run_sel = so.x, run_eq = 0;
-    const uint32_t rT = so.y;
-    for (uint32_t cb = 0; cb < cs; cb += SEG_THREADS * ITEMS) {
-        const uint32_t p0 = cb + tid * ITEMS;
-        uint2 v[ITEMS];
-        uint32_t g = 0, q = 0;
-#pragma unroll
-        for (uint32_t i = 0; i < ITEMS; ++i) v[i] = (p0 + i < cs) ? src.list[p0 + i] : make_uint2(0, 0);
-#pragma unroll
-        for (uint32_t i = 0; i < ITEMS; ++i) {
-            const uint32_t key = v[i].y & 0x7FFFFFFFu;
-            if (p0 + i < cs) {
-                g += (key > T);
-                q += (key == T);
-            }
-        }
-        uint32_t total;
-        const uint32_t before = block_excl_scan<SEG_THREADS / 64>(g | (q << 16), wsum, total);
-        const uint32_t g_before = before & 0xFFFFu, q_before = before >> 16;
-        const uint32_t G = total & 0xFFFFu, Q = total >> 16;
-        const uint32_t rem = (rT > run_eq) ? (rT - run_eq) : 0u;
-        uint32_t pos = run_sel + g_before + min(q_before, rem);
-        uint32_t eq_seen = q_before;
-        if (g | q) {
-#pragma unroll
-            for (uint32_t i = 0; i < ITEMS; ++i) {
-                if (p0 + i >= cs) break;
-                const uint32_t key = v[i].y & 0x7FFFFFFFu;
-                bool sel = key > T;
-                if (key == T) {
-                    sel = eq_seen < rem;
-                    ++eq_seen;
-                }
-                if (sel) {
-                    if (pos < pe.k) {
-                        A.out_idx[pe.outoff + pos] = v[i].x;
-                        A.out_val[pe.outoff + pos] = __uint_as_float(v[i].y);
-                        if (index_ok(A, v[i].x)) fix_sent<OP>(A.state, v[i].x, __uint_as_float(v[i].y), A.m);
-                    }
-                    ++pos;
-                }
-            }
-        }
-        run_sel += G + min(Q, rem);
-        run_eq += Q;
-    }
+    SegState *st = &A.segstate[sd.j];
+    const uint32_t status = st->status;
+    if (status != SEG_ACTIVE && status != SEG_LISTS) return;
+    const TensorDesc td = A.tdesc[sd.j];
+    if (emit) emit_slab<OP, THREADS>(A, slab, sd, td, pe, st, status == SEG_LISTS, C);
+    else rank_slab<THREADS>(A, slab, sd, td, st, status == SEG_LISTS, C);
+}
+
+void launch_window(const SelectArgs &a, void *stream, void *ev0)
+{
+    if (a.nparts == 0) return;
+    launch_k(k_list_window, dim3(a.nparts), dim3(SEL_THREADS), (hipStream_t)stream, ev0, nullptr, a);
+}
+
+template <uint32_t THREADS>
+static void launch_finish(int op, const SelectArgs &a, hipStream_t st, void *ev0, void *ev1)
+{
+    const dim3 grid(2 * a.ncslabs), block(THREADS);
+    if (op == SEL_WORKER) launch_k(k_list_finish<SEL_WORKER, THREADS>, grid, block, st, ev0, ev1, a);
+    else if (op == SEL_PULL) launch_k(k_list_finish<SEL_PULL, THREADS>, grid, block, st, ev0, ev1, a);
+    else launch_k(k_list_finish<SEL_PULL_V, THREADS>, grid, block, st, ev0, ev1, a);
 }
 
 void launch_chain(int op, const SelectArgs &a, void *stream, void *ev0, void *ev1)
 {
     hipStream_t st = (hipStream_t)stream;
-    if (a.nparts == 0) return;
-    launch_k(k_chain_prefix, dim3(a.nparts), dim3(SEL_THREADS), st, ev0, nullptr, a);
-    if (op == SEL_WORKER)
-        launch_k(k_chain_emit<SEL_WORKER>, dim3(a.nparts), dim3(SEG_THREADS), st, nullptr, ev1, a);
-    else if (op == SEL_PULL)
-        launch_k(k_chain_emit<SEL_PULL>, dim3(a.nparts), dim3(SEG_THREADS), st, nullptr, ev1, a);
-    else
-        launch_k(k_chain_emit<SEL_PULL_V>, dim3(a.nparts), dim3(SEG_THREADS), st, nullptr, ev1, a);
+    if (a.ncslabs == 0) return;
+    // While all slabs run at once (or nearly so) the depth of a workgroup counts: 8 tiles per wavefront.
+    // Many rounds of workgroups are better served by twice as many workgroups per compute unit with 16
+    // tiles per wavefront.  Rounds with 1024 / 512 threads: ResNet-50 shapes without momentum at 1 %
+    // (about 260 slabs) 110 / 114 us, transformer shapes (about 900) 394 / 408 us, 1e9 parameters
+    // (7.8 K) at 1 % 5596 / 5338 us.
+    if (a.ncslabs < 2048u) launch_finish<1024>(op, a, st, ev0, ev1);
+    else launch_finish<512>(op, a, st, ev0, ev1);
 }
 
 // ---------------------------------------------------------------------------

@@ -35,7 +35,10 @@ constexpr uint32_t HSHIFT = 31 - HBITS;
 constexpr uint32_t SEL_THREADS = 1024;
 constexpr uint32_t SEL_WAVES = SEL_THREADS / 64;
 constexpr uint32_t SEL_LDS_LIST = 16384;           // candidates kept in LDS (128 KB); longer lists continue in global scratch
-constexpr uint32_t SEL_LIST_MAX = 24576;           // longest candidate list one workgroup is planned for
+constexpr uint32_t SEL_LIST_MAX = 20480;           // longest candidate list one workgroup is planned for
+// ... and where the plan holds a tensor beyond that, so that the chain's launches are there anyway,
+// for tensors of at least SEL_CROWDED_TILES tiles (their join is then what the launch waits for).
+constexpr uint32_t SEL_LIST_CROWDED = 8192, SEL_CROWDED_TILES = 512;
 constexpr uint32_t SEL_LIST_HARD = 65536;          // longest it accepts when a tail has grown beyond the plan
 // Above this density candidates stop paying off; such requests select densely.
 constexpr double DENSE_DENSITY = 1.0 / 32.0;
@@ -55,13 +58,14 @@ constexpr uint32_t SEG_TILES = DGS_SEG_TILES;
 #define DGS_GROUP_TILES 4096
 #endif
 constexpr uint32_t GROUP_TILES = DGS_GROUP_TILES;
-constexpr uint32_t SEG_THREADS = 256;
 constexpr uint32_t SEG_MIN_N = 65536;              // smaller tensors never take the chain
 constexpr uint32_t SEG_AUTO_N = 1u << 22;          // (kept for the plan: tensors this large always may)
 constexpr uint32_t SEG_LOWBITS = 12;               // key bits resolved by the second level
 constexpr uint32_t SEG_WBINS = 2048;               // window of key >> SEG_LOWBITS above the threshold
 constexpr uint32_t SEG_LBINS = 1u << SEG_LOWBITS;
-constexpr uint32_t PFX_CAP = 8192;                 // candidates sharing the k-th key's prefix, per tensor
+// The chain: tiles of one workgroup (64 / 128 / 256 of them: 405 / 394 / 398 us a round on transformer
+// shapes, 5398 / 5338 / 5368 us at 1 % of 1e9 parameters).
+constexpr uint32_t CSLAB_TILES = SEG_TILES < 128 ? SEG_TILES : 128;
 // Dense requests: tiles of one workgroup (4 wavefronts) of the passes over the tensors themselves.
 constexpr uint32_t SLAB_TILES = 16;
 constexpr uint32_t SLAB_THREADS = 256;
@@ -70,11 +74,12 @@ constexpr uint32_t SEG_MAX_PER_TENSOR = 512;       // parts per tensor whose lis
 // Status of a tensor inside one selection call.
 //   SEG_IDLE      nothing decided yet
 //   SEG_DONE      selected and emitted
-//   SEG_ACTIVE    the chain kernels finish it (prefix of the k-th key known)
+//   SEG_ACTIVE    the chain kernels finish it (prefix of the k-th key known), reading the tiles' candidates
+//   SEG_LISTS     the same, reading the parts' lists (collected again after a failed prediction)
 //   SEG_ALL       dense request with k_j = n_j: the emission sends every element
 //   SEG_PENDING   the prediction failed: the parts collect again with a fresh threshold
 //   SEG_FALLBACK  left to the dense single-workgroup selection
-enum SegStatus { SEG_IDLE = 0, SEG_DONE = 1, SEG_FALLBACK = 2, SEG_PENDING = 4, SEG_ALL = 6, SEG_ACTIVE = 8 };
+enum SegStatus { SEG_IDLE = 0, SEG_DONE = 1, SEG_FALLBACK = 2, SEG_PENDING = 4, SEG_ALL = 6, SEG_ACTIVE = 8, SEG_LISTS = 10 };
 enum SegMode { SEG_MODE_AUTO = 0, SEG_MODE_ALWAYS = 1, SEG_MODE_NEVER = 2 };
 
 struct TensorDesc {
@@ -83,9 +88,11 @@ struct TensorDesc {
     uint32_t big;        // n > SMALL_N
     uint32_t seg_first;  // first entry of this tensor in the segment table
     uint32_t nseg;       // segments (0: the tensor never goes segmented)
-    uint32_t pfx_slot;   // which PFX_CAP-sized block of the prefix list belongs to it
+    uint32_t pad;
     uint32_t grp_first;  // first entry of this tensor in the group table
     uint32_t ngrp;       // its join groups (>= 1)
+    uint32_t cs_first;   // first entry of this tensor in the table of chain slabs
+    uint32_t ncs;        // its chain slabs (0: never takes the chain)
 };
 
 struct PlanEntry {
@@ -111,8 +118,9 @@ struct SegState {        // per tensor, rewritten by every selection
     uint32_t pfx;        // key >> SEG_LOWBITS of the k-th entry (dense request: its leading bits so far)
     uint32_t r2;         // its rank among the entries sharing that prefix
     uint32_t T;          // the k-th key
-    uint32_t pfxcount;   // entries appended to the prefix list
-    uint32_t pad0, pad1, pad2;
+    uint32_t rT;         // how many of the entries equal to it are taken (lowest index first)
+    uint32_t ready;      // 1: T and rT are in place (chain)
+    uint32_t pad0, pad1;
     // Hand-over between the workgroups of one launch (all zero between launches):
     uint32_t arrive[4];  // parts that have finished: [0] join, [1] re-histogram, [2] re-collection, [3] chain prefix
     uint32_t verdict;    // 0 = not decided; else 0x100 | SegStatus, written by the last joining part
@@ -174,10 +182,10 @@ struct SelectArgs {
     SegState *segstate;
     uint32_t *segcnt;             // per part: candidates (bit 31: a tile of the part overflowed)
     uint32_t *grpcnt;             // per join group: the same, for the lists joined by groups
-    uint32_t *segstart;           // per part of a tensor that takes the chain: where its list starts in ord
-    uint32_t *segG1;              // per part: candidates with a larger key prefix than the k-th
-    uint2 *segOut;                // per part: (output position within the tensor, ties to take)
-    uint4 *pfxlist;               // per tensor PFX_CAP x (index, value bits, part, 0)
+    uint32_t *segstart;           // per part of a tensor that takes the chain and was collected again: where its list starts in ord
+    const SegDesc *cslabs;        // chain slabs (sidx: the part they lie in), tensor after tensor
+    uint2 *slabs_done;            // per chain slab: what it has published (slab_word)
+    uint32_t ncslabs;
     uint32_t *out_idx;
     float *out_val;
     DevStats *stats;
@@ -206,7 +214,9 @@ void launch_pick_dense(const TensorDesc *tdesc, const PlanEntry *plan, uint32_t 
 // The selection: one launch for every tensor (join, exact k-th key, ordered emission, state
 // fix-up, next hint; failed predictions are collected again inside the same launch).
 void launch_select(int op, const SelectArgs &a, void *stream, void *ev0, void *ev1);
-// What remains for tensors left SEG_ACTIVE (very long candidate lists).
+// Long candidate lists: the parts' window histograms, before the selection kernel, and what
+// remains behind it for tensors left SEG_ACTIVE / SEG_LISTS.
+void launch_window(const SelectArgs &a, void *stream, void *ev0);
 void launch_chain(int op, const SelectArgs &a, void *stream, void *ev0, void *ev1);
 // Dense request: exact k-th keys and emission, reading the tensors themselves.
 void launch_dense(int op, const SelectArgs &a, void *stream, void *ev0, void *ev1);

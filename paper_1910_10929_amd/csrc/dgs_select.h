@@ -101,8 +101,54 @@ __device__ __forceinline__ uint32_t quad_bits(const SelectArgs &A, uint32_t e0, 
     return in;
 }
 
+// What a tile's counter word says about tensor td's candidates in tile t: how many, and after
+// how many of the previous tensor's (a first tile shared with it).  An overflowed tile, or a
+// count beyond the slots (a corrupted word), sets ovf and counts as empty.
+__device__ __forceinline__ void tile_counts(uint32_t w, uint32_t t, uint32_t tlo, bool head_shared, uint32_t &n_t,
+                                            uint32_t &start, int &ovf)
+{
+    n_t = 0;
+    start = 0;
+    if (w == CNT_OVERFLOW) {
+        ovf = 1;
+    } else if (head_shared && t == tlo) {
+        start = w & 0xFFFFu;      // the previous tensor's candidates come first in this tile
+        n_t = w >> 16;
+    } else {
+        n_t = w & 0xFFFFu;
+    }
+    if (start + n_t > CAPT) {
+        ovf = 1;
+        n_t = 0;
+        start = 0;
+    }
+}
+
+// First bin (key >> SEG_LOWBITS) of the window histogram of a tensor that takes the chain.
+// Candidates start at the collection threshold; when that lies far below the k-th key of the
+// previous selection on this stream (a relaxed hint), the window is centred on that key
+// instead, so that it reaches half an octave to either side of it.  Keys below the window are
+// counted into bin 0, which then holds no usable rank.
+__device__ __forceinline__ uint32_t seg_window_base(uint32_t tau_cur, uint32_t t_prev)
+{
+    const uint32_t b_tau = tau_cur >> SEG_LOWBITS;
+    const uint32_t b_prev = t_prev >> SEG_LOWBITS;
+    const uint32_t b_mid = (b_prev > SEG_WBINS / 2) ? (b_prev - SEG_WBINS / 2) : 0u;
+    return max(b_tau, b_mid);
+}
+
+// Window histogram of part `sidx` of a tensor that takes the chain: in the ordered-list scratch of
+// the tensor, which holds nothing until a failed prediction is collected again.  A part of at
+// least SEG_TILES tiles (or the only one of at least 64) has room for the SEG_WBINS counters, the
+// shorter last part uses what the others leave.
+__device__ __forceinline__ uint32_t *part_hist(const SelectArgs &A, const TensorDesc &td, uint32_t j, uint32_t sidx)
+{
+    return (uint32_t *)(A.ord + (size_t)(td.off / TILE + j) * CAPT) + (size_t)sidx * SEG_WBINS;
+}
+static_assert(SEG_MIN_N / TILE * 2 * CAPT >= (SEG_MIN_N / TILE / SEG_TILES + 2) * SEG_WBINS, "part histograms fit");
+
 struct SelShared {
-    uint32_t h[2048];
+    alignas(16) uint32_t h[2048];
     uint32_t wsum[SEL_WAVES];
     uint32_t rowsum[64];
     int res[6];

@@ -196,29 +196,6 @@ __device__ __forceinline__ uint2 tile_entry(const uint2 *hd, const uint2 *sl, ui
     return (q < HEAD) ? hd[q] : sl[q];
 }
 
-// What a tile's counter word says about tensor td's candidates in tile t: how many, and after
-// how many of the previous tensor's (a first tile shared with it).  An overflowed tile, or a
-// count beyond the slots (a corrupted word), sets ovf and counts as empty.
-__device__ __forceinline__ void tile_counts(uint32_t w, uint32_t t, uint32_t tlo, bool head_shared, uint32_t &n_t,
-                                            uint32_t &start, int &ovf)
-{
-    n_t = 0;
-    start = 0;
-    if (w == CNT_OVERFLOW) {
-        ovf = 1;
-    } else if (head_shared && t == tlo) {
-        start = w & 0xFFFFu;      // the previous tensor's candidates come first in this tile
-        n_t = w >> 16;
-    } else {
-        n_t = w & 0xFFFFu;
-    }
-    if (start + n_t > CAPT) {
-        ovf = 1;
-        n_t = 0;
-        start = 0;
-    }
-}
-
 // JOIN of a run of tiles: the candidates of tensor j in tiles [sd.tile0, sd.tile0 + sd.ntiles),
 // in index order, through `put(position, entry)`.  Returns the count; `ovf` is set if a tile had
 // overflowed its slots.  Rounds of SEL_THREADS tiles.  Every lane takes one tile's count; a
@@ -227,14 +204,9 @@ __device__ __forceinline__ void tile_counts(uint32_t w, uint32_t t, uint32_t tlo
 // four lines per lane -- and put in place with the positions read back from LDS; crowded tiles
 // and a first tile shared with the previous tensor go to a worklist that the wavefronts then
 // copy entry by entry.
-struct NoTileHook {
-    __device__ __forceinline__ void operator()(uint32_t, uint32_t) const {}
-};
-
-// (`at_tile(tile index within the run, list position)` is called once for every tile.)
-template <class Put, class AtTile = NoTileHook>
+template <class Put>
 __device__ __forceinline__ uint32_t join_part(const SelectArgs &A, const TensorDesc &td, const SegDesc &sd,
-                                              PartShared &P, bool &ovf_out, Put put, AtTile at_tile = AtTile())
+                                              PartShared &P, bool &ovf_out, Put put)
 {
     const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = tid & 63u;
     const uint32_t tlo = td.off / TILE;
@@ -265,7 +237,6 @@ __device__ __forceinline__ uint32_t join_part(const SelectArgs &A, const TensorD
         P.tile_n[tid] = n_t | (crowded ? 0x80000000u : 0u);
         if (crowded) P.crowd_slot[excl >> 19] = tid;
         if (head_shared && t == tlo) P.start0 = start;      // (the tensor's first tile, shared with the one before)
-        if (r0 + tid < sd.ntiles) at_tile(r0 + tid, pos);
         __syncthreads();
 #pragma unroll
         for (uint32_t v = 0; v < 4; ++v) {
@@ -451,38 +422,49 @@ __device__ __forceinline__ uint32_t dense_compact(const SelectArgs &A, const Ten
     return total;
 }
 
-// First bin (key >> SEG_LOWBITS) of the window histogram of a tensor that takes the chain.
-// Candidates start at the collection threshold; when that lies far below the k-th key of the
-// previous selection on this stream (a relaxed hint), the window is centred on that key
-// instead, so that it reaches half an octave to either side of it.  Keys below the window are
-// counted into bin 0, which then holds no usable rank.
-__device__ __forceinline__ uint32_t seg_window_base(uint32_t tau_cur, uint32_t t_prev)
-{
-    const uint32_t b_tau = tau_cur >> SEG_LOWBITS;
-    const uint32_t b_prev = t_prev >> SEG_LOWBITS;
-    const uint32_t b_mid = (b_prev > SEG_WBINS / 2) ? (b_prev - SEG_WBINS / 2) : 0u;
-    return max(b_tau, b_mid);
-}
-
-// The last part of a tensor that takes the chain: the tensor's window histogram (global, c
-// candidates in all) -> the 19-bit prefix of the k-th key, its rank among the entries sharing
-// it, and the next hint.  Returns the tensor's status (SEG_ACTIVE, or 0 = failed);
-// thread 0 writes segstate / hints.  h: SEG_WBINS words of LDS.
+// A tensor that takes the chain: its window histogram (c candidates in all; the sum of its parts'
+// own, or, collected again, the one the parts have added to in ghist) -> the 19-bit prefix of the k-th key, its rank among the entries sharing
+// it, and the next hint.  Returns the tensor's status (SEG_ACTIVE / SEG_LISTS, or 0 = failed);
+// thread 0 writes segstate / hints.
 template <int OP>
 __device__ __forceinline__ uint32_t window_step(const SelectArgs &A, const TensorDesc &td, const PlanEntry &pe,
                                                 uint32_t j, uint32_t c, bool ovf, uint32_t tau_cur, uint32_t tprev_cur,
-                                                bool exact_mode, PartShared &P)
+                                                bool exact_mode, bool lists, PartShared &P)
 {
     const uint32_t tid = threadIdx.x;
     uint32_t *h = P.S.h;
     uint32_t *gh = A.ghist + (size_t)j * HBINS;
     uint32_t mylow = 0xFFFFFFFFu;
     if (tid == 0) P.S.kmin = 0xFFFFFFFFu;
+    if (!lists) {
+        // four counters per load, every other part: a tensor of 90 parts costs a thread 45 loads
+        static_assert(SEG_WBINS == 2 * SEL_THREADS, "two threads per four counters");
+        const uint32_t b4 = tid & (SEL_THREADS / 2 - 1u), half = tid / (SEL_THREADS / 2);
+        const uint4 *ph = (const uint4 *)part_hist(A, td, j, 0) + b4;
+        uint4 sum = make_uint4(0, 0, 0, 0);
+#pragma unroll 8
+        for (uint32_t s = half; s < td.nseg; s += 2) {
+            const uint4 v = ph[(size_t)s * (SEG_WBINS / 4)];
+            sum.x += v.x;
+            sum.y += v.y;
+            sum.z += v.z;
+            sum.w += v.w;
+        }
+        if (half == 0) ((uint4 *)h)[b4] = sum;
+        __syncthreads();
+        if (half != 0) {
+            uint4 t = ((uint4 *)h)[b4];
+            ((uint4 *)h)[b4] = make_uint4(t.x + sum.x, t.y + sum.y, t.z + sum.z, t.w + sum.w);
+        }
+    }
     __syncthreads();
     for (uint32_t b = tid; b < SEG_WBINS; b += SEL_THREADS) {
-        const uint32_t v = ld_dev(&gh[b]);
-        h[b] = v;
-        if (v) st_dev(&gh[b], 0u);   // clean for the next use
+        uint32_t v = h[b];
+        if (lists) {
+            v = ld_dev(&gh[b]);
+            if (v) st_dev(&gh[b], 0u);   // clean for the next use
+            h[b] = v;
+        }
         if (v && mylow == 0xFFFFFFFFu) mylow = b;
     }
     if (mylow != 0xFFFFFFFFu) atomicMin(&P.S.kmin, mylow);
@@ -499,10 +481,10 @@ __device__ __forceinline__ uint32_t window_step(const SelectArgs &A, const Tenso
     const bool ok = !ovf && (c >= pe.k) && bk >= bin_min && bk < (int)SEG_WBINS - 1;
     if (tid == 0 && ok) {
         SegState *st = &A.segstate[j];
-        st->pfxcount = 0;
         st->pfx = win_base + (uint32_t)bk;
         st->r2 = (uint32_t)P.S.res[1];
         st->T = 0;
+        st->ready = 0;
         atomicAdd(&A.stats->candidates, (unsigned long long)c);
         atomicAdd(&A.stats->segmented_tensors, 1ull);
         if (A.write_hint) {
@@ -533,7 +515,7 @@ __device__ __forceinline__ uint32_t window_step(const SelectArgs &A, const Tenso
         }
     }
     __syncthreads();
-    return ok ? (uint32_t)SEG_ACTIVE : 0u;
+    return !ok ? 0u : (lists ? (uint32_t)SEG_LISTS : (uint32_t)SEG_ACTIVE);
 }
 
 // Selection of a whole tensor straight from the buffers by this one workgroup: small tensors,
@@ -714,12 +696,12 @@ __device__ __forceinline__ uint32_t trim_list(const SelectArgs &A, const Src &sr
 
 // What the workgroup that completes a tensor's candidate lists does with them (`round` 0: the
 // streaming pass's candidates, 1: re-collected with a fresh threshold).  Returns the tensor's
-// status: SEG_DONE, SEG_ACTIVE (the chain kernels go on), or SEG_PENDING (round 0
+// status: SEG_DONE, SEG_ACTIVE / SEG_LISTS (the chain kernels go on), or SEG_PENDING (round 0
 // only: collect again).
 //   multi: the lists are global lists of several units -- the tensor's parts (by_parts: counts
 //   in segcnt) or its join groups (counts in grpcnt) -- and are gathered here; otherwise the
-//   one list is in llist / glist (or, for a tensor that takes the chain, in its global list
-//   only) with count c0, overflow ovf0, smallest key (or a lower bound of it) kmin0, and --
+//   one list is in llist / glist (or, for a tensor that takes the chain, still in its tiles, and
+//   in round 1 in its global list only) with count c0, overflow ovf0, smallest key (or a lower bound of it) kmin0, and --
 //   win_counted -- the window histogram counted on the way.
 //   verdict: where the outcome is published for the re-collecting workgroups of the launch
 //   (null: nobody waits); a success is published as soon as it is certain, before the work.
@@ -761,9 +743,7 @@ __device__ __forceinline__ uint32_t tensor_select(const SelectArgs &A, const Ten
             const uint32_t ex = block_excl_scan<SEL_WAVES>(cnt, P.S.wsum, tot);
             if (s < nunits && have_pbase) {
                 P.pbase[s] = c + ex;
-                // (a part of a tensor that takes the chain lies where its group's join put it)
-                P.pofs[s] = (by_parts && pe.seg) ? ld_dev(&A.segstart[td.seg_first + s])
-                                                 : (units[s].tile0 + j) * CAPT;   // below 2^32: n < 2^32
+                P.pofs[s] = (units[s].tile0 + j) * CAPT;   // below 2^32: n < 2^32
             }
             c += tot;
         }
@@ -774,12 +754,22 @@ __device__ __forceinline__ uint32_t tensor_select(const SelectArgs &A, const Ten
     bool early = false;      // the verdict went out before the work
     // every nonzero is in the lists
     const bool zerofill = !ovf && c < pe.k && tau_cur <= 1u && (!multi || have_pbase);
-    if (pe.seg) status = window_step<OP>(A, td, pe, j, c, ovf, tau_cur, tprev_cur, exact_mode, P);
+    if (pe.seg) status = window_step<OP>(A, td, pe, j, c, ovf, tau_cur, tprev_cur, exact_mode, round != 0, P);
     if (status == 0 && zerofill) {
         // the message is completed with the tensor's lowest-index zeros
         early = true;
         if (verdict && tid == 0) st_dev(verdict, 0x100u | (uint32_t)SEG_DONE);
-        if (multi) {
+        if (pe.seg && round == 0) {
+            // a nearly empty row: its few candidates are joined here
+            const uint32_t nt = (td.off + td.n - 1u) / TILE - tlo + 1u;
+            bool again;
+            const uint32_t cj = join_part(A, td, SegDesc{j, tlo, nt, 0u}, P, again,
+                                          [&](uint32_t pos, uint2 e) { put_entry(llist, glist, pos, e); });
+            if (cj != c && tid == 0) atomicAdd(&A.stats->internal_errors, 1ull);
+            wait_mem();
+            __syncthreads();
+            zero_fill_emit<OP>(SrcSplit{llist, glist}, c, td, pe, A, P.S.wsum);
+        } else if (multi) {
             zero_fill_emit<OP>(SrcParts{A.ord, P.pbase, P.pofs, nunits}, c, td, pe, A, P.S.wsum);
         } else if (pe.seg) {
             zero_fill_emit<OP>(SrcList{glist}, c, td, pe, A, P.S.wsum);
@@ -953,7 +943,7 @@ __device__ __forceinline__ void recollect_part(const SelectArgs &A, uint32_t rol
     }
     if (tid == 0) {
         st_dev(&A.segcnt[part], min(c2, 0x7FFFFFFFu) | (c2 > part_cap ? 0x80000000u : 0u));
-        if (pe.seg) st_dev(&A.segstart[part], (sd.tile0 + j) * CAPT);      // the part's own place again
+        if (pe.seg) st_dev(&A.segstart[part], (sd.tile0 + j) * CAPT);
     }
     if (!arrive_last(&st->arrive[2], td.nseg, &P.bc)) return;
     tensor_select<OP>(A, td, pe, j, 1, true, true, 0u, false, 0xFFFFFFFFu, tau_new, tprev_new, 0xFFFFFFFFu, false,
@@ -1024,49 +1014,22 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const SelectArgs A)
         // window of the single-workgroup selection: starts at the collection threshold or, when
         // that lies far below (a relaxed hint), 1024 buckets under the previous k-th key
         const uint32_t win_join = max(tau_cur >> 11, max(tprev_cur >> 11, 1024u) - 1024u);
-        const uint32_t win_seg = seg_window_base(tau_cur, tprev_cur);
         uint32_t *verdict = (has_parts && A.repair) ? &st->verdict : nullptr;
         uint32_t status;
         if (pe.seg) {
-            // a tensor that takes the chain: the group's candidates in one list, with every part's
-            // start and count noted for the chain kernels, and the group's window histogram
-            const uint32_t p0 = td.seg_first + sd.sidx * A.gparts;
-            const uint32_t p1 = min(p0 + A.gparts, td.seg_first + td.nseg);
-            uint32_t *gh = A.ghist + (size_t)j * HBINS;
-            for (uint32_t b = tid; b < 2048; b += SEL_THREADS) P.S.h[b] = 0;
-            __syncthreads();
-            const uint32_t ptiles = A.segtab[p0].ntiles;         // tiles per part (the tensor's last part may have fewer)
-            const uint32_t gbase = (sd.tile0 + j) * CAPT;        // below 2^32: n < 2^32
-            cs = join_part(
-                A, td, sd, P, ovf,
-                [&](uint32_t pos, uint2 e) {
-                    st_dev(&plist[pos], e);          // read by the chain kernels, and by a zero fill
-                    const uint32_t hi12 = (e.y & 0x7FFFFFFFu) >> SEG_LOWBITS;
-                    const uint32_t w = (hi12 > win_seg) ? (hi12 - win_seg) : 0u;
-                    atomicAdd(&P.S.h[min(w, SEG_WBINS - 1u)], 1u);
-                },
-                [&](uint32_t tl, uint32_t pos) {
-                    if (tl % ptiles == 0) P.pbase[tl / ptiles] = pos;
-                });
-            for (uint32_t b = tid; b < SEG_WBINS; b += SEL_THREADS) {
-                const uint32_t v = P.S.h[b];
-                if (v) atomicAdd(&gh[b], v);
+            // a tensor that takes the chain: its parts have counted their candidates already, and
+            // one workgroup reads the result
+            if (sd.sidx != 0) return;
+            uint32_t o = 0, mine = 0;
+            for (uint32_t p = tid; p < td.nseg; p += SEL_THREADS) {
+                const uint32_t v = A.segcnt[td.seg_first + p];
+                mine += v & 0x7FFFFFFFu;
+                o |= v >> 31;
             }
-            const uint32_t np = p1 - p0;
-            if (tid < np) {
-                const uint32_t start = P.pbase[tid], end = (tid + 1 < np) ? P.pbase[tid + 1] : cs;
-                st_dev(&A.segstart[p0 + tid], gbase + start);
-                st_dev(&A.segcnt[p0 + tid], (end - start) | (ovf ? 0x80000000u : 0u));
-            }
-            __syncthreads();
-            if (multi) {
-                if (!arrive_last(&st->arrive[0], td.ngrp, &P.bc)) return;
-            } else {
-                wait_mem();       // counts and histogram are read back below
-                __syncthreads();
-            }
-            status = tensor_select<OP>(A, td, pe, j, 0, has_parts, true, cs, ovf, kmin, tau_cur, tprev_cur, win_join,
-                                       true, verdict, P, llist);
+            cs = block_sum(mine, P.S.wsum, SEL_WAVES);
+            ovf = __syncthreads_or((int)o) != 0;
+            status = tensor_select<OP>(A, td, pe, j, 0, false, true, cs, ovf, kmin, tau_cur, tprev_cur, win_join,
+                                       false, verdict, P, llist);
         } else if (multi) {
             cs = join_part(A, td, sd, P, ovf, [&](uint32_t pos, uint2 e) { st_dev(&plist[pos], e); });
             if (tid == 0) st_dev(&A.grpcnt[blockIdx.x], cs | (ovf ? 0x80000000u : 0u));
@@ -1124,7 +1087,10 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const SelectArgs A)
                     const uint32_t v = P.S.h[b];
                     if (v) atomicAdd(&gh[b], v);
                 }
-                if (tid == 0) st_dev(&A.segcnt[part], c2);
+                if (tid == 0) {
+                    st_dev(&A.segcnt[part], c2);
+                    st_dev(&A.segstart[part], (sd.tile0 + j) * CAPT);
+                }
             }
         } else {
             uint2 *glist = plist;

@@ -103,25 +103,25 @@ extern emu::Idx threadIdx, blockIdx, blockDim, gridDim;
 namespace emu {
 
 void to_scheduler();                 // block the current fiber (state already set) and run others
-uint64_t collective(Op op, const void *site, uint64_t a, uint64_t b = 0, uint64_t c = 0, uint64_t d = 0);
+__attribute__((convergent)) uint64_t collective(Op op, const void *site, uint64_t a, uint64_t b = 0, uint64_t c = 0, uint64_t d = 0);
 void launch(dim3 grid, dim3 block, const std::function<void()> &body);
 
 }  // namespace emu
 
 // ---- workgroup / wavefront builtins
 #define EMU_SITE __builtin_return_address(0)
-__attribute__((noinline)) static void __syncthreads() { emu::collective(emu::OP_BARRIER, EMU_SITE, 0); }
-__attribute__((noinline)) static int __syncthreads_or(int p) { return (int)emu::collective(emu::OP_BARRIER_OR, EMU_SITE, p != 0); }
-__attribute__((noinline)) static uint64_t __builtin_amdgcn_ballot_w64(bool p) { return emu::collective(emu::OP_BALLOT, EMU_SITE, p); }
-__attribute__((noinline)) static int __builtin_amdgcn_readlane(int v, int lane) { return (int)emu::collective(emu::OP_READLANE, EMU_SITE, (uint32_t)v, (uint32_t)lane); }
-__attribute__((noinline)) static uint32_t __builtin_amdgcn_readfirstlane(uint32_t v) { return (uint32_t)emu::collective(emu::OP_READFIRST, EMU_SITE, v); }
-__attribute__((noinline)) static int __builtin_amdgcn_update_dpp(int old, int src, int ctrl, int row_mask, int bank_mask, bool bound_ctrl)
+__attribute__((noinline, convergent)) static void __syncthreads() { emu::collective(emu::OP_BARRIER, EMU_SITE, 0); }
+__attribute__((noinline, convergent)) static int __syncthreads_or(int p) { return (int)emu::collective(emu::OP_BARRIER_OR, EMU_SITE, p != 0); }
+__attribute__((noinline, convergent)) static uint64_t __builtin_amdgcn_ballot_w64(bool p) { return emu::collective(emu::OP_BALLOT, EMU_SITE, p); }
+__attribute__((noinline, convergent)) static int __builtin_amdgcn_readlane(int v, int lane) { return (int)emu::collective(emu::OP_READLANE, EMU_SITE, (uint32_t)v, (uint32_t)lane); }
+__attribute__((noinline, convergent)) static uint32_t __builtin_amdgcn_readfirstlane(uint32_t v) { return (uint32_t)emu::collective(emu::OP_READFIRST, EMU_SITE, v); }
+__attribute__((noinline, convergent)) static int __builtin_amdgcn_update_dpp(int old, int src, int ctrl, int row_mask, int bank_mask, bool bound_ctrl)
 {
     (void)bank_mask; (void)bound_ctrl;
     return (int)emu::collective(emu::OP_DPP, EMU_SITE, (uint32_t)old, (uint32_t)src, (uint32_t)ctrl, (uint32_t)row_mask);
 }
-__attribute__((noinline)) static int __builtin_amdgcn_ds_bpermute(int addr, int v) { return (int)emu::collective(emu::OP_BPERMUTE, EMU_SITE, (uint32_t)addr, (uint32_t)v); }
-__attribute__((noinline)) static void __builtin_amdgcn_wave_barrier() { emu::collective(emu::OP_WAVEBAR, EMU_SITE, 0); }
+__attribute__((noinline, convergent)) static int __builtin_amdgcn_ds_bpermute(int addr, int v) { return (int)emu::collective(emu::OP_BPERMUTE, EMU_SITE, (uint32_t)addr, (uint32_t)v); }
+__attribute__((noinline, convergent)) static void __builtin_amdgcn_wave_barrier() { emu::collective(emu::OP_WAVEBAR, EMU_SITE, 0); }
 static inline uint32_t __builtin_amdgcn_mbcnt_lo(uint32_t mask, uint32_t acc)
 {
     const uint32_t lane = threadIdx.x & 63u;
