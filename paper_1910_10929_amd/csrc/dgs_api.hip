@@ -259,13 +259,14 @@ void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out,
             out[j].k = (uint32_t)k;
             out[j].k2 = (uint32_t)k2;
             out[j].outoff = (uint32_t)K;
-            uint64_t k2p = 2 * k + 4ull * isqrt_u32((uint32_t)k) + 16;
-            if (k2p > nj) k2p = nj;
-            out[j].k2_pull = (uint32_t)k2p;
+            uint64_t k2z = 2 * k + 4ull * isqrt_u32((uint32_t)k) + 16;
+            out[j].k2_pull = (uint32_t)std::min(k2z + k / 2, nj);
+            k2z = std::min(k2z, nj);
+            out[j].k2_zero = (uint32_t)k2z;
             bool seg = false;
             if (c->seg_mode != SEG_MODE_NEVER) {
                 if (density > DENSE_DENSITY) seg = true;
-                else if (nj >= SEG_MIN_N) seg = c->seg_mode == SEG_MODE_ALWAYS || std::max(k2, k2p) > SEL_LIST_MAX;
+                else if (nj >= SEG_MIN_N) seg = c->seg_mode == SEG_MODE_ALWAYS || std::max(k2, k2z) > SEL_LIST_MAX;
             }
             out[j].seg = seg ? 1u : 0u;
             // wire form: local indices of b bits each, the tensor's block padded to whole words
@@ -274,7 +275,6 @@ void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out,
             if (b == 0) b = 1;
             out[j].wire_off = (uint32_t)words;      // fits: words <= K, checked by the caller
             out[j].wire_bits = b;
-            out[j].pad2 = 0;
             words += (k * b + 31) / 32;
             active += seg ? 1u : 0u;
             K += k;
@@ -282,7 +282,7 @@ void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out,
         if (active && density <= DENSE_DENSITY)
             for (uint32_t j = 0; j < c->J; ++j) {
                 const uint64_t nj = c->offsets[j + 1] - c->offsets[j];
-                if (out[j].seg || nj < SEL_CROWDED_TILES * TILE || std::max(out[j].k2, out[j].k2_pull) <= SEL_LIST_CROWDED) continue;
+                if (out[j].seg || nj < SEL_CROWDED_TILES * TILE || std::max(out[j].k2, out[j].k2_zero) <= SEL_LIST_CROWDED) continue;
                 out[j].seg = 1u;
                 ++active;
             }

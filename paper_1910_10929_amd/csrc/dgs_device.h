@@ -99,11 +99,11 @@ struct PlanEntry {
     uint32_t k;       // ceil(density * n_j)
     uint32_t k2;      // rank whose key becomes the next predicted threshold (>= k, <= n_j)
     uint32_t outoff;  // sum of k over earlier tensors
-    uint32_t k2_pull; // same for a pull, whose sent entries vanish: about 2k (<= n_j)
+    uint32_t k2_pull; // same for a pull, whose sent entries vanish: about 2.5k (<= n_j)
     uint32_t seg;     // 1: segmented selection at this density
     uint32_t wire_off;   // wire form: first 32-bit word of the tensor's index block (after the values)
     uint32_t wire_bits;  // wire form: bits per local index = bit length of n_j - 1 (>= 1)
-    uint32_t pad2;
+    uint32_t k2_zero; // same for a worker without momentum, whose sent entries vanish too: about 2k (<= n_j)
 };
 
 struct SegDesc {
