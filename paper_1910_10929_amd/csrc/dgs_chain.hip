@@ -141,15 +141,18 @@ __device__ __forceinline__ uint64_t slab_word(uint64_t kind, uint32_t g, uint32_
 __device__ __forceinline__ uint32_t slab_g(uint64_t w) { return (uint32_t)w & 0x7FFFFFFFu; }
 __device__ __forceinline__ uint32_t slab_q(uint64_t w) { return (uint32_t)(w >> 31) & 0x7FFFFFFFu; }
 
-__device__ __forceinline__ void slab_publish(const SelectArgs &A, uint32_t slab, uint64_t w)
+__device__ __forceinline__ void slab_publish(uint2 *word, uint64_t w)
 {
-    st_dev(&A.slabs_done[slab], make_uint2((uint32_t)w, (uint32_t)(w >> 32)));
+    st_dev(word, make_uint2((uint32_t)w, (uint32_t)(w >> 32)));
 }
 
-// Entries above / equal to the k-th key in the tensor's slabs before this one, by one wavefront
-// looking back over up to 64 slabs at a time until one has published its running sum.  Those are
-// blocks with lower indices; bounded by A.spin_limit polls.
-__device__ __forceinline__ void slab_look_back(const SelectArgs &A, uint32_t slab, uint32_t first, uint32_t &g, uint32_t &q)
+// Entries above / equal to the k-th key in the tensor's slabs [first, slab), by one wavefront
+// looking back over up to 64 slabs at a time until one has published its running sum
+// (word_of(i): where slab i publishes).  Those are blocks with lower indices; bounded by
+// A.spin_limit polls.
+template <class WordOf>
+__device__ __forceinline__ void slab_look_back(const SelectArgs &A, uint32_t slab, uint32_t first, WordOf word_of,
+                                               uint32_t &g, uint32_t &q)
 {
     const uint32_t lane = lane_id();
     g = q = 0;
@@ -159,7 +162,7 @@ __device__ __forceinline__ void slab_look_back(const SelectArgs &A, uint32_t sla
         uint64_t have = 0, sums = 0;
         for (uint32_t spin = 0; spin < A.spin_limit; ++spin) {
             if (in && w == 0) {
-                const uint2 x = ld_dev(&A.slabs_done[hi - 1u - lane]);
+                const uint2 x = ld_dev(word_of(hi - 1u - lane));
                 w = ((uint64_t)x.y << 32) | x.x;
             }
             have = ballot64(!in || w != 0);
@@ -201,7 +204,7 @@ __device__ __forceinline__ void rank_slab(const SelectArgs &A, uint32_t slab, co
     uint32_t *glow = A.ghist + (size_t)sd.j * HBINS;
     const uint32_t first = min(wave * CTPW, sd.ntiles);
     const WaveTiles w = wave_tiles(A, td, sd.tile0 + first, min(CTPW, sd.ntiles - first), lists, sd.sidx);
-    if (tid == 0) slab_publish(A, slab, 0);          // nothing published yet (complete before the arrival below)
+    if (tid == 0) slab_publish(&A.slabs_done[slab], 0);          // nothing published yet (complete before the arrival below)
     each_candidate<CTPW>(A, w, [&](uint2 e) {
         if (((e.y & 0x7FFFFFFFu) >> SEG_LOWBITS) == pfx) atomicAdd(&glow[e.y & (SEG_LBINS - 1u)], 1u);
     });
@@ -274,11 +277,11 @@ __device__ __forceinline__ void emit_slab(const SelectArgs &A, uint32_t slab, co
     }
     if (wave == 0) {
         const bool head = (slab == td.cs_first);
-        if (lane == 0) slab_publish(A, slab, slab_word(head ? SLAB_SUM : SLAB_OWN, all & 0xFFFFu, all >> 16));
+        if (lane == 0) slab_publish(&A.slabs_done[slab], slab_word(head ? SLAB_SUM : SLAB_OWN, all & 0xFFFFu, all >> 16));
         uint32_t g, q;
-        slab_look_back(A, slab, td.cs_first, g, q);
+        slab_look_back(A, slab, td.cs_first, [&](uint32_t i) { return &A.slabs_done[i]; }, g, q);
         if (lane == 0) {
-            if (!head) slab_publish(A, slab, slab_word(SLAB_SUM, g + (all & 0xFFFFu), q + (all >> 16)));
+            if (!head) slab_publish(&A.slabs_done[slab], slab_word(SLAB_SUM, g + (all & 0xFFFFu), q + (all >> 16)));
             C.g = g;
             C.q = q;
             if (slab + 1 == td.cs_first + td.ncs && g + (all & 0xFFFFu) + rT != pe.k)      // the tensor's last slab
@@ -379,21 +382,26 @@ void launch_chain(int op, const SelectArgs &a, void *stream, void *ev0, void *ev
 // accumulate pass has counted bits [30:19] of every key of the big tensors and k_pick_dense has
 // found the bucket that holds the k-th one; then, one workgroup per slab of SLAB_TILES tiles of a
 // part (a small tensor is one slab, and that workgroup counts its leading bits too),
-//   refine 1  counts bits [18:8] of the keys in that bucket; the slab arriving last for a tensor
-//             ranks: 23 leading bits of the k-th key
-//   refine 2  counts, per slab, the entries above that prefix and the low 8 bits of those that
-//             share it; the slab arriving last ranks: the exact key, and from every slab's own
-//             counts how many entries it sends and where they go (no list that ties could outgrow)
-//   emit      ordered emission and state fix-up.
+//   refine 1  counts bits [18:11] of the keys in that bucket; the slab arriving last for a tensor
+//             ranks: 20 leading bits of the k-th key
+//   refine 2  counts the low 11 bits of the keys that share them; the slab arriving last ranks:
+//             the exact key, and how many of the entries equal to it are taken
+//   emit      counts its winners, adds up what the slabs before it have published (the chain's
+//             look-back), ordered emission and state fix-up.  Ties need no case of their own.
 // Each pass is bound by memory (4 B/param, mostly from the last-level cache up to a few 1e7
-// parameters) and by having enough of the chip at work: slabs of 16 tiles put 1.6 K workgroups on
-// 25.6M parameters.  ResNet-50 shapes at density 0.1: one workgroup per part (256 tiles and more,
-// element by element) took 1070 + 72 + 361 us for a worker step.
+// parameters), by having enough of the chip at work, and refine 1 by the device-wide atomics that
+// add the slabs' counters up: 256 bins keep those at 200 per slab of 32 tiles (2048 bins per slab
+// of 16 tiles: 400 K on 25.6M parameters, 56 instead of 41 us).  ResNet-50 shapes at density 0.1:
+// one workgroup per part (256 tiles and more, element by element) took 1070 + 72 + 361 us for a
+// worker step, these three 41 + 37 + 80 us.
 
 constexpr uint32_t SLAB_WAVES = SLAB_THREADS / 64;
-constexpr uint32_t TPW = SLAB_TILES / SLAB_WAVES;        // consecutive tiles of one wavefront
-constexpr uint32_t REF1_SHIFT = 8, REF1_BINS = 2048;     // refine 1: key bits [18:8]
-constexpr uint32_t REF2_BINS = 256;                      // refine 2: key bits [7:0]
+constexpr uint32_t TPW = 4;                              // consecutive tiles of one wavefront
+// The emission takes half slabs: its staging area is 8 KB of LDS per wavefront, and workgroups of four
+// wavefronts leave more of them on a compute unit (80 against 97 us, figures as above).
+constexpr uint32_t EMIT_TILES = SLAB_TILES / 2, EMIT_WAVES = EMIT_TILES / TPW, EMIT_THREADS = 64 * EMIT_WAVES;
+constexpr uint32_t REF1_SHIFT = 11, REF1_BINS = 256;     // refine 1: key bits [18:11]
+constexpr uint32_t REF2_BINS = 2048;                     // refine 2: key bits [10:0]
 
 struct Slab {
     TensorDesc td;
@@ -401,36 +409,38 @@ struct Slab {
     uint32_t tile0, ntiles;
 };
 
+template <uint32_t TILES>
 __device__ __forceinline__ bool find_slab(const SelectArgs &A, Slab &s)
 {
-    s.part = A.segtab[blockIdx.x / A.slabs];
-    const uint32_t first = (blockIdx.x % A.slabs) * SLAB_TILES;
+    const uint32_t per = A.slabs * (SLAB_TILES / TILES);
+    s.part = A.segtab[blockIdx.x / per];
+    const uint32_t first = (blockIdx.x % per) * TILES;
     if (first >= s.part.ntiles || !A.plan[s.part.j].seg) return false;
     s.td = A.tdesc[s.part.j];
     s.tile0 = s.part.tile0 + first;
-    s.ntiles = min(SLAB_TILES, s.part.ntiles - first);
+    s.ntiles = min(TILES, s.part.ntiles - first);
     return true;
 }
 
 // Slabs of one full part, and of the whole tensor (only its last part may be shorter).
+template <uint32_t TILES>
 __device__ __forceinline__ uint32_t slabs_per_part(const SelectArgs &A, const TensorDesc &td)
 {
-    return (A.segtab[td.seg_first].ntiles + SLAB_TILES - 1u) / SLAB_TILES;
+    return (A.segtab[td.seg_first].ntiles + TILES - 1u) / TILES;
 }
 
+template <uint32_t TILES>
 __device__ __forceinline__ uint32_t slabs_of_tensor(const SelectArgs &A, const TensorDesc &td)
 {
-    return (td.nseg - 1u) * slabs_per_part(A, td) +
-           (A.segtab[td.seg_first + td.nseg - 1u].ntiles + SLAB_TILES - 1u) / SLAB_TILES;
+    return (td.nseg - 1u) * slabs_per_part<TILES>(A, td) +
+           (A.segtab[td.seg_first + td.nseg - 1u].ntiles + TILES - 1u) / TILES;
 }
 
-// A slab's record, in the ordered-list scratch of its first tile: [0] first output position,
-// [1] ties it sends, [2 + b] entries of the slab at or above (23-bit prefix, low bits b).
-__device__ __forceinline__ uint32_t *slab_record(const SelectArgs &A, uint32_t tile0, uint32_t j)
+// Where a slab of the emission publishes: in the ordered-list scratch of its first tile.
+__device__ __forceinline__ uint2 *dense_word(const SelectArgs &A, uint32_t tile0, uint32_t j)
 {
-    return (uint32_t *)(A.ord + (size_t)(tile0 + j) * CAPT);
+    return A.ord + (size_t)(tile0 + j) * CAPT;
 }
-static_assert(REF2_BINS == SLAB_THREADS && 2 + REF2_BINS + 1 <= 2 * CAPT, "a slab record fits one tile's scratch");
 
 // This wavefront's tiles of the slab, 16 values per lane and tile; bit 4 r + x of in[i] says that
 // value x of row r belongs to the tensor.  All loads are in flight together.
@@ -464,12 +474,11 @@ __global__ __launch_bounds__(SLAB_THREADS) void k_dense_refine(const SelectArgs 
     constexpr uint32_t SHIFT = (LEVEL == 1) ? HSHIFT : REF1_SHIFT;       // the prefix known so far
     constexpr uint32_t LOW = (LEVEL == 1) ? REF1_SHIFT : 0u;
     __shared__ uint32_t h[LEVEL == 1 ? HBINS : BINS];
-    __shared__ uint32_t wsum[SLAB_WAVES];
     __shared__ uint32_t rowsum[64];
     __shared__ int res[6];
     __shared__ uint32_t bc;
     Slab s;
-    if (!find_slab(A, s)) return;
+    if (!find_slab<SLAB_TILES>(A, s)) return;
     const uint32_t j = s.part.j, tid = threadIdx.x;
     SegState *st = &A.segstate[j];
     const bool leading = (LEVEL == 1) && !s.td.big;       // the leading bits are still to be counted
@@ -500,40 +509,24 @@ __global__ __launch_bounds__(SLAB_THREADS) void k_dense_refine(const SelectArgs 
     }
     for (uint32_t b = tid; b < BINS; b += SLAB_THREADS) h[b] = 0;
     __syncthreads();
-    uint32_t above = 0;
 #pragma unroll
     for (uint32_t i = 0; i < TPW; ++i)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            bool hit[4];
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                const bool ok = (in[i] >> (4 * r + x)) & 1u;
-                const uint32_t top = (bits[i][r][x] & 0x7FFFFFFFu) >> SHIFT;
-                hit[x] = ok && top == pfx;
-                if (LEVEL == 2) above += (ok && top > pfx) ? 1u : 0u;
-            }
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
             for (int x = 0; x < 4; ++x)
-                if (hit[x]) atomicAdd(&h[(bits[i][r][x] >> LOW) & (BINS - 1u)], 1u);
-        }
+                if (((in[i] >> (4 * r + x)) & 1u) && ((bits[i][r][x] & 0x7FFFFFFFu) >> SHIFT) == pfx)
+                    atomicAdd(&h[(bits[i][r][x] >> LOW) & (BINS - 1u)], 1u);
     uint32_t *g = A.ghist + (size_t)j * HBINS;
-    if (LEVEL == 2) {
-        const uint32_t G = block_sum(above, wsum, SLAB_WAVES);       // (its barriers also complete h)
-        uint32_t *rec = slab_record(A, s.tile0, j);
-        const uint32_t mine = h[tid];                                // one bin per thread
-        uint32_t tot;
-        const uint32_t below = block_excl_scan<(int)SLAB_WAVES>(mine, wsum, tot);
-        st_dev(&rec[2 + tid], G + tot - below);
-        if (tid == 0) st_dev(&rec[2 + REF2_BINS], G);
-    } else {
-        __syncthreads();
-    }
+    // (the emission's slabs have published nothing yet)
+    if (LEVEL == 2 && tid < SLAB_TILES / EMIT_TILES && tid * EMIT_TILES < s.ntiles)
+        slab_publish(dense_word(A, s.tile0 + tid * EMIT_TILES, j), 0);
+    __syncthreads();
     for (uint32_t b = tid; b < BINS; b += SLAB_THREADS) {
         const uint32_t v = h[b];
         if (v) atomicAdd(&g[b], v);
     }
-    const uint32_t nslabs = slabs_of_tensor(A, s.td);
+    const uint32_t nslabs = slabs_of_tensor<SLAB_TILES>(A, s.td);
     if (!arrive_last(&st->arrive[LEVEL], nslabs, &bc)) return;
 
     // ------------------------------------------------------------------ the tensor's last slab
@@ -552,39 +545,15 @@ __global__ __launch_bounds__(SLAB_THREADS) void k_dense_refine(const SelectArgs 
         }
         return;
     }
-    if (LEVEL == 1) {
-        if (tid == 0) {
-            st->pfx = (pfx << (HSHIFT - REF1_SHIFT)) | (uint32_t)bin;
-            st->r2 = rank;
-        }
-        return;
-    }
-    // slabs in order: ties are taken lowest index first, i.e. earlier slabs first
-    const uint32_t spp = slabs_per_part(A, s.td), ptile0 = A.segtab[s.td.seg_first].tile0,
-                   ptiles = A.segtab[s.td.seg_first].ntiles;
-    uint32_t carry_q = 0, carry_o = 0;
-    for (uint32_t s0 = 0; s0 < nslabs; s0 += SLAB_THREADS) {
-        const uint32_t si = s0 + tid;
-        uint32_t *rec = slab_record(A, ptile0 + (si / spp) * ptiles + (si % spp) * SLAB_TILES, j);
-        uint32_t G = 0, Q = 0;
-        if (si < nslabs) {
-            G = ld_dev(&rec[2 + bin + 1]);
-            Q = ld_dev(&rec[2 + bin]) - G;
-        }
-        uint32_t totq, toto;
-        const uint32_t qb = carry_q + block_excl_scan<(int)SLAB_WAVES>(Q, wsum, totq);
-        const uint32_t take = min(Q, (rank > qb) ? (rank - qb) : 0u);
-        const uint32_t ob = carry_o + block_excl_scan<(int)SLAB_WAVES>(G + take, wsum, toto);
-        if (si < nslabs) {
-            st_dev(&rec[0], ob);
-            st_dev(&rec[1], take);
-        }
-        carry_q += totq;
-        carry_o += toto;
-    }
     if (tid == 0) {
-        st->T = (pfx << REF1_SHIFT) | (uint32_t)bin;
-        if (carry_o != k) atomicAdd(&A.stats->internal_errors, 1ull);
+        const uint32_t key = (pfx << (SHIFT - LOW)) | (uint32_t)bin;
+        if (LEVEL == 1) {
+            st->pfx = key;
+            st->r2 = rank;
+        } else {
+            st->T = key;
+            st->rT = rank;
+        }
     }
 }
 
@@ -592,22 +561,21 @@ __global__ __launch_bounds__(SLAB_THREADS) void k_dense_refine(const SelectArgs 
 // 64-byte lines wherever a line has a winner (at these densities most lines that have one would
 // otherwise be read, merged and written back by the memory side for every 4-byte store).
 template <int OP>
-__global__ __launch_bounds__(SLAB_THREADS) void k_dense_emit(const SelectArgs A)
+__global__ __launch_bounds__(EMIT_THREADS) void k_dense_emit(const SelectArgs A)
 {
-    __shared__ uint2 stage_all[SLAB_WAVES][TILE];
-    __shared__ uint32_t wtot[SLAB_WAVES];
+    __shared__ uint2 stage_all[EMIT_WAVES][TILE];
+    __shared__ uint32_t wtot[EMIT_WAVES];
+    __shared__ uint32_t g_before, q_before;
     Slab s;
-    if (!find_slab(A, s)) return;
+    if (!find_slab<EMIT_TILES>(A, s)) return;
     const SegState *st = &A.segstate[s.part.j];
     const uint32_t status = st->status;
     if (status != SEG_ACTIVE && status != SEG_ALL) return;
     const PlanEntry pe = A.plan[s.part.j];
     const uint32_t lane = lane_id(), wave = uniform(threadIdx.x >> 6);
     const bool all = (status == SEG_ALL);
-    const uint32_t *rec = slab_record(A, s.tile0, s.part.j);
-    // density 1: everything is a "tie" that is sent, at its own position
-    const uint32_t T = all ? 0u : st->T;
-    const uint32_t take = all ? 0u : rec[1];
+    // (density 1: everything is sent, at its own position)
+    const uint32_t T = all ? 0u : st->T, rT = all ? 0u : st->rT;
     uint32_t bits[TPW][4][4], in[TPW];
     load_slab<OP>(A, s, bits, in);
     uint32_t mine = 0;
@@ -622,15 +590,40 @@ __global__ __launch_bounds__(SLAB_THREADS) void k_dense_emit(const SelectArgs A)
                 if (ok && (all || key > T)) ++mine;
                 else if (ok && key == T) mine += 1u << 16;
             }
-    const uint32_t sum = wave_sum(mine);         // at most 4096 of either kind
+    const uint32_t sum = wave_sum(mine);         // at most 4096 of either kind, EMIT_TILES / 4 times that in all
     if (lane == 0) wtot[wave] = sum;
     __syncthreads();
-    uint32_t before = 0;
+    uint32_t before = 0, total = 0;
 #pragma unroll
-    for (uint32_t w = 0; w < SLAB_WAVES; ++w) before += (w < wave) ? wtot[w] : 0u;
-    uint32_t eq = before >> 16;                  // ties seen before this row
-    uint32_t pos = (before & 0xFFFFu) + min(eq, take) +
-                   (all ? max(s.tile0 * TILE, s.td.off) - s.td.off : rec[0]);
+    for (uint32_t w = 0; w < EMIT_WAVES; ++w) {
+        before += (w < wave) ? wtot[w] : 0u;
+        total += wtot[w];
+    }
+    if (wave == 0) {
+        uint32_t g = max(s.tile0 * TILE, s.td.off) - s.td.off, q = 0;
+        if (!all) {
+            const uint32_t j = s.part.j, spp = slabs_per_part<EMIT_TILES>(A, s.td), ptile0 = A.segtab[s.td.seg_first].tile0,
+                           ptiles = A.segtab[s.td.seg_first].ntiles;
+            const uint32_t me = s.part.sidx * spp + (s.tile0 - s.part.tile0) / EMIT_TILES;
+            uint2 *word = dense_word(A, s.tile0, j);
+            if (lane == 0) slab_publish(word, slab_word(me == 0 ? SLAB_SUM : SLAB_OWN, total & 0xFFFFu, total >> 16));
+            slab_look_back(A, me, 0u,
+                           [&](uint32_t i) { return dense_word(A, ptile0 + (i / spp) * ptiles + (i % spp) * EMIT_TILES, j); },
+                           g, q);
+            if (lane == 0) {
+                if (me != 0) slab_publish(word, slab_word(SLAB_SUM, g + (total & 0xFFFFu), q + (total >> 16)));
+                if (me + 1 == slabs_of_tensor<EMIT_TILES>(A, s.td) && g + (total & 0xFFFFu) + rT != pe.k)
+                    atomicAdd(&A.stats->internal_errors, 1ull);
+            }
+        }
+        if (lane == 0) {
+            g_before = g;
+            q_before = q;
+        }
+    }
+    __syncthreads();
+    uint32_t eq = q_before + (before >> 16);     // the tensor's ties before this row: lowest index first, rT of them are taken
+    uint32_t pos = g_before + (before & 0xFFFFu) + min(eq, rT);
     uint2 *stage = stage_all[wave];
 #pragma unroll
     for (uint32_t i = 0; i < TPW; ++i) {
@@ -662,7 +655,7 @@ __global__ __launch_bounds__(SLAB_THREADS) void k_dense_emit(const SelectArgs A)
 #pragma unroll
                 for (int x = 0; x < 4; ++x)
                     if (q[x]) {
-                        f[x] = er < take;
+                        f[x] = er < rT;
                         ++er;
                     }
                 eq += cnt;
@@ -716,15 +709,16 @@ void launch_dense(int op, const SelectArgs &a, void *stream, void *ev0, void *ev
 {
     hipStream_t st = (hipStream_t)stream;
     const dim3 grid(a.nparts * a.slabs), block(SLAB_THREADS);
+    const dim3 egrid(a.nparts * a.slabs * (SLAB_TILES / EMIT_TILES)), eblock(EMIT_THREADS);
     if (op == SEL_PULL_V) {
         launch_k(k_dense_refine<SEL_PULL_V, 1>, grid, block, st, ev0, nullptr, a);
         launch_k(k_dense_refine<SEL_PULL_V, 2>, grid, block, st, nullptr, nullptr, a);
-        launch_k(k_dense_emit<SEL_PULL_V>, grid, block, st, nullptr, ev1, a);
+        launch_k(k_dense_emit<SEL_PULL_V>, egrid, eblock, st, nullptr, ev1, a);
     } else {      // worker and difference row rank the same buffer
         launch_k(k_dense_refine<SEL_PULL, 1>, grid, block, st, ev0, nullptr, a);
         launch_k(k_dense_refine<SEL_PULL, 2>, grid, block, st, nullptr, nullptr, a);
-        if (op == SEL_WORKER) launch_k(k_dense_emit<SEL_WORKER>, grid, block, st, nullptr, ev1, a);
-        else launch_k(k_dense_emit<SEL_PULL>, grid, block, st, nullptr, ev1, a);
+        if (op == SEL_WORKER) launch_k(k_dense_emit<SEL_WORKER>, egrid, eblock, st, nullptr, ev1, a);
+        else launch_k(k_dense_emit<SEL_PULL>, egrid, eblock, st, nullptr, ev1, a);
     }
 }
 

@@ -66,9 +66,9 @@ constexpr uint32_t SEG_LBINS = 1u << SEG_LOWBITS;
 // The chain: tiles of one workgroup (64 / 128 / 256 of them: 405 / 394 / 398 us a round on transformer
 // shapes, 5398 / 5338 / 5368 us at 1 % of 1e9 parameters).
 constexpr uint32_t CSLAB_TILES = SEG_TILES < 128 ? SEG_TILES : 128;
-// Dense requests: tiles of one workgroup (4 wavefronts) of the passes over the tensors themselves.
-constexpr uint32_t SLAB_TILES = 16;
-constexpr uint32_t SLAB_THREADS = 256;
+// Dense requests: tiles of one workgroup of the passes over the tensors themselves, 4 per wavefront.
+constexpr uint32_t SLAB_TILES = SEG_TILES < 32 ? SEG_TILES : 32;
+constexpr uint32_t SLAB_THREADS = SLAB_TILES / 4 * 64;
 static_assert(SLAB_TILES * TILE >= SMALL_N + TILE && SLAB_TILES <= SEG_TILES, "a small tensor is one slab");
 constexpr uint32_t SEG_MAX_PER_TENSOR = 512;       // parts per tensor whose list positions fit the selection's LDS
 // Status of a tensor inside one selection call.
