@@ -109,11 +109,11 @@ Layout make_layout(const uint64_t *offsets, uint32_t J, uint32_t W)
     L.qlist = o;     o = align_up(o + (ntiles + 4) * sizeof(uint32_t));
     L.segtab = o;    o = align_up(o + (nseg_total + 1) * sizeof(SegDesc));
     L.grptab = o;    o = align_up(o + (nseg_total + 1) * sizeof(SegDesc));      // groups <= parts
+    L.cslabs = o;    o = align_up(o + ncs * sizeof(SegDesc));
     L.grpcnt = o;    o = align_up(o + (nseg_total + 1) * sizeof(uint32_t));
     L.segstart = o;  o = align_up(o + (nseg_total + 1) * sizeof(uint32_t));
     L.segcnt = o;    o = align_up(o + (nseg_total + 1) * sizeof(uint32_t));
     L.segstate = o;  o = align_up(o + (size_t)J * sizeof(SegState));
-    L.cslabs = o;    o = align_up(o + ncs * sizeof(SegDesc));
     L.slabs_done = o; o = align_up(o + ncs * sizeof(uint2));
     L.total = o;
     return L;
@@ -242,13 +242,17 @@ struct ProfSlot {
 // Which tensors take the chain kernels behind the selection: those of at least SEG_MIN_N
 // elements whose hinted candidate list is longer than one workgroup selects from
 // (SEL_LIST_MAX), and then also those beyond SEL_LIST_CROWDED.  For a dense request `seg` means the kernels that read the tensors themselves
-// (launch_dense): all of them, unless the option forbids it.
+// (launch_dense): all of them if one is that large, unless the option forbids it.
 void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out, uint64_t *K_out,
                uint32_t *nseg_active, uint64_t *wire_words_out)
 {
     {
         uint64_t K = 0, words = 0;
         uint32_t active = 0;
+        // (a dense request on nothing but small tensors: one launch of one workgroup each, 24 us a step
+        // where the five launches of the dense kernels take 53)
+        bool large = false;
+        for (uint32_t j = 0; j < c->J; ++j) large |= c->offsets[j + 1] - c->offsets[j] >= SEG_MIN_N;
         for (uint32_t j = 0; j < c->J; ++j) {
             const uint64_t nj = c->offsets[j + 1] - c->offsets[j];
             uint64_t k = (uint64_t)std::ceil(density * (double)nj);
@@ -265,7 +269,7 @@ void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out,
             out[j].k2_zero = (uint32_t)k2z;
             bool seg = false;
             if (c->seg_mode != SEG_MODE_NEVER) {
-                if (density > DENSE_DENSITY) seg = true;
+                if (density > DENSE_DENSITY) seg = large;
                 else if (nj >= SEG_MIN_N) seg = c->seg_mode == SEG_MODE_ALWAYS || std::max(k2, k2z) > SEL_LIST_MAX;
             }
             out[j].seg = seg ? 1u : 0u;
@@ -642,17 +646,22 @@ int upload(dgs_ctx *c, void *dst, const void *src, size_t bytes)
     return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, c->stream) == hipSuccess ? DGS_OK : DGS_EHIP;
 }
 
-// Tables up, counters cleared: what a context's workspace holds before its first call.
+// Tables up, counters cleared: what a context's workspace holds before its first call.  tabs != 0: segs,
+// groups and slabs lie in one host block of that many bytes, placed as in the workspace.
 int upload_tables(dgs_ctx *c, const TensorDesc *td, const uint32_t *tau0, const uint32_t *toff, const SegDesc *segs,
-                  const SegDesc *groups, const SegDesc *slabs)
+                  const SegDesc *groups, const SegDesc *slabs, size_t tabs)
 {
     const uint32_t J = c->J, W = c->W;
     int rc = upload(c, c->toff, toff, ((size_t)J + 1) * sizeof(uint32_t));
     if (rc == DGS_OK) rc = upload(c, c->tdesc, td, (size_t)J * sizeof(TensorDesc));
     if (rc == DGS_OK) rc = upload(c, c->tau, tau0, (size_t)(W + 1) * J * sizeof(uint32_t));
-    if (rc == DGS_OK) rc = upload(c, c->segtab, segs, (size_t)c->nseg_total * sizeof(SegDesc));
-    if (rc == DGS_OK) rc = upload(c, c->grptab, groups, (size_t)c->ngroups * sizeof(SegDesc));
-    if (rc == DGS_OK) rc = upload(c, c->cslabs, slabs, (size_t)c->ncslabs * sizeof(SegDesc));
+    if (tabs) {
+        if (rc == DGS_OK) rc = upload(c, c->segtab, segs, tabs);
+    } else {
+        if (rc == DGS_OK) rc = upload(c, c->segtab, segs, (size_t)c->nseg_total * sizeof(SegDesc));
+        if (rc == DGS_OK) rc = upload(c, c->grptab, groups, (size_t)c->ngroups * sizeof(SegDesc));
+        if (rc == DGS_OK) rc = upload(c, c->cslabs, slabs, (size_t)c->ncslabs * sizeof(SegDesc));
+    }
     if (rc != DGS_OK) return rc;
     launch_fill_u32(c->hint2, 0u, (size_t)(W + 1) * J, c->stream);
     launch_fill_u32(c->tprev, 0u, (size_t)(W + 1) * J, c->stream);
@@ -721,19 +730,17 @@ int dgs_create(dgs_ctx **out, const uint64_t *offsets, uint32_t J, uint32_t W, v
     if (env) c->stream_quads = (uint32_t)std::strtoul(env, nullptr, 10);
 
     // host-side plan: tensor and tile descriptors
-    uint32_t nseg_total = 0, ncs = 0;
-    const uint32_t scale = layout_scale(offsets, J);
-    for (uint32_t j = 0; j < J; ++j) {
-        nseg_total += tensor_segments(offsets[j], offsets[j + 1] - offsets[j], scale);
-        if (offsets[j + 1] - offsets[j] >= SEG_MIN_N) ncs += chain_slabs(offsets[j], offsets[j + 1] - offsets[j], scale);
-    }
     std::vector<TensorDesc> td(J);
     std::vector<uint32_t> tau0((size_t)(W + 1) * J);
-    std::vector<SegDesc> segs(nseg_total + 1);
     std::vector<uint32_t> toff(J + 1);
-    std::vector<SegDesc> groups(nseg_total + 1), slabs(ncs + 1);
+    // parts, join groups and chain slabs, as they lie in the workspace: one upload
+    const size_t tabs = L.grpcnt - L.segtab;      // (grpcnt follows them)
+    static_assert(ALIGN % sizeof(SegDesc) == 0, "the tables start at whole entries");
+    std::vector<SegDesc> tab(tabs / sizeof(SegDesc));
+    SegDesc *segs = tab.data(), *groups = segs + (L.grptab - L.segtab) / sizeof(SegDesc),
+            *slabs = segs + (L.cslabs - L.segtab) / sizeof(SegDesc);
     c->nseg.assign(J, 0u);
-    fill_tables(c, td.data(), tau0.data(), toff.data(), segs.data(), groups.data(), slabs.data());
+    fill_tables(c, td.data(), tau0.data(), toff.data(), segs, groups, slabs);
 
     // What a sampling pass visits: every 16th tile of the buffer, and every tile of the tensors of
     // at most 64 tiles, whose ranks are too small to estimate from a sixteenth.
@@ -756,7 +763,7 @@ int dgs_create(dgs_ctx **out, const uint64_t *offsets, uint32_t J, uint32_t W, v
     const size_t stage_bytes = align_up((size_t)NPLAN * J * sizeof(PlanEntry));
     ok = ok && hipHostMalloc((void **)&c->plan_stage, stage_bytes + 64, hipHostMallocDefault) == hipSuccess;
     if (ok) c->host_total = (uint32_t *)((char *)c->plan_stage + stage_bytes);
-    ok = ok && upload_tables(c, td.data(), tau0.data(), toff.data(), segs.data(), groups.data(), slabs.data()) == DGS_OK;
+    ok = ok && upload_tables(c, td.data(), tau0.data(), toff.data(), segs, groups, slabs, tabs) == DGS_OK;
     ok = ok && hipStreamSynchronize(c->stream) == hipSuccess;
     ok = ok && hipGetLastError() == hipSuccess;
     if (!ok) {
@@ -908,7 +915,7 @@ int dgs_worker_step_static(const uint64_t *offsets, uint32_t J, const float *gra
     fill_tables(&c, td, tau0, toff, segs, groups, slabs);
     // every call starts from a clean workspace (the array keeps the previous call's contents);
     // with no threshold hints the step takes the two-pass path
-    rc = upload_tables(&c, td, tau0, toff, segs, groups, slabs);
+    rc = upload_tables(&c, td, tau0, toff, segs, groups, slabs, 0);
     if (rc != DGS_OK) return rc;
     return run_selection(&c, OP_FMA, SEL_WORKER, grad, state, lr, m, density, 0, idx_out, val_out, nnz_out,
                          DGS_PROF_WORKER_STREAM, DGS_PROF_WORKER_SELECT, DGS_PROF_WORKER_SEGMENTED);
