@@ -19,7 +19,7 @@
 // kernel (SEG_LISTS); its slabs then take equal shares of those lists in place of their tiles.
 // Dense requests have no candidates; their passes over the tensors themselves are at the end of
 // this file.
-#include "dgs_select.h"
+#include "dgs_slab.h"
 
 namespace dgs {
 
@@ -131,60 +131,6 @@ __global__ __launch_bounds__(SEL_THREADS) void k_list_window(const SelectArgs A)
     if (tid == 0) A.segcnt[part] = c | (over ? 0x80000000u : 0u);
 }
 
-// What a slab publishes for the slabs behind it: its entries above the k-th key and equal to it
-// (SLAB_OWN), or the same for all slabs of the tensor up to and including it (SLAB_SUM).
-constexpr uint64_t SLAB_OWN = 1ull << 62, SLAB_SUM = 2ull << 62;
-__device__ __forceinline__ uint64_t slab_word(uint64_t kind, uint32_t g, uint32_t q)
-{
-    return kind | ((uint64_t)q << 31) | g;       // 31 bits each: fewer than n / 4 candidates
-}
-__device__ __forceinline__ uint32_t slab_g(uint64_t w) { return (uint32_t)w & 0x7FFFFFFFu; }
-__device__ __forceinline__ uint32_t slab_q(uint64_t w) { return (uint32_t)(w >> 31) & 0x7FFFFFFFu; }
-
-__device__ __forceinline__ void slab_publish(uint2 *word, uint64_t w)
-{
-    st_dev(word, make_uint2((uint32_t)w, (uint32_t)(w >> 32)));
-}
-
-// Entries above / equal to the k-th key in the tensor's slabs [first, slab), by one wavefront
-// looking back over up to 64 slabs at a time until one has published its running sum
-// (word_of(i): where slab i publishes).  Those are blocks with lower indices; bounded by
-// A.spin_limit polls.
-template <class WordOf>
-__device__ __forceinline__ void slab_look_back(const SelectArgs &A, uint32_t slab, uint32_t first, WordOf word_of,
-                                               uint32_t &g, uint32_t &q)
-{
-    const uint32_t lane = lane_id();
-    g = q = 0;
-    for (uint32_t hi = slab; hi > first;) {          // slabs [first, hi) are still to be added
-        const bool in = hi - first > lane;
-        uint64_t w = 0;
-        uint64_t have = 0, sums = 0;
-        for (uint32_t spin = 0; spin < A.spin_limit; ++spin) {
-            if (in && w == 0) {
-                const uint2 x = ld_dev(word_of(hi - 1u - lane));
-                w = ((uint64_t)x.y << 32) | x.x;
-            }
-            have = ballot64(!in || w != 0);
-            sums = ballot64(in && (w & SLAB_SUM) != 0);
-            // everything up to the nearest running sum (or all 64) has been published
-            const uint64_t upto = sums ? (((sums & (0ull - sums)) << 1) - 1ull) : ~0ull;
-            if ((have & upto) == upto) break;
-            __builtin_amdgcn_s_sleep(1);
-        }
-        const uint64_t upto = sums ? (((sums & (0ull - sums)) << 1) - 1ull) : ~0ull;
-        if ((have & upto) != upto) {                 // gave up waiting
-            if (lane == 0) atomicAdd(&A.stats->internal_errors, 1ull);
-            return;
-        }
-        w &= 0ull - ((upto >> lane) & 1ull);         // (lanes beyond `first` hold 0)
-        g += wave_sum(slab_g(w));
-        q += wave_sum(slab_q(w));
-        if (sums) return;
-        hi = (hi - first > 64u) ? hi - 64u : first;
-    }
-}
-
 struct FinishShared {
     uint32_t h[SEG_LBINS];
     uint32_t rowsum[64];
@@ -204,7 +150,7 @@ __device__ __forceinline__ void rank_slab(const SelectArgs &A, uint32_t slab, co
     uint32_t *glow = A.ghist + (size_t)sd.j * HBINS;
     const uint32_t first = min(wave * CTPW, sd.ntiles);
     const WaveTiles w = wave_tiles(A, td, sd.tile0 + first, min(CTPW, sd.ntiles - first), lists, sd.sidx);
-    if (tid == 0) slab_publish(&A.slabs_done[slab], 0);          // nothing published yet (complete before the arrival below)
+    if (tid == 0) slab_publish<false>(&A.slabs_done[slab], 0u, 0u, 0u);      // nothing published yet (complete before the arrival below)
     each_candidate<CTPW>(A, w, [&](uint2 e) {
         if (((e.y & 0x7FFFFFFFu) >> SEG_LOWBITS) == pfx) atomicAdd(&glow[e.y & (SEG_LBINS - 1u)], 1u);
     });
@@ -277,14 +223,15 @@ __device__ __forceinline__ void emit_slab(const SelectArgs &A, uint32_t slab, co
     }
     if (wave == 0) {
         const bool head = (slab == td.cs_first);
-        if (lane == 0) slab_publish(&A.slabs_done[slab], slab_word(head ? SLAB_SUM : SLAB_OWN, all & 0xFFFFu, all >> 16));
+        if (lane == 0) slab_publish<false>(&A.slabs_done[slab], head ? SLAB_SUM : SLAB_OWN, all & 0xFFFFu, all >> 16);
         uint32_t g, q;
-        slab_look_back(A, slab, td.cs_first, [&](uint32_t i) { return &A.slabs_done[i]; }, g, q);
+        slab_look_back<false>(A, slab, td.cs_first, [&](uint32_t i) { return &A.slabs_done[i]; }, g, q);
         if (lane == 0) {
-            if (!head) slab_publish(&A.slabs_done[slab], slab_word(SLAB_SUM, g + (all & 0xFFFFu), q + (all >> 16)));
+            if (!head) slab_publish<false>(&A.slabs_done[slab], SLAB_SUM, g + (all & 0xFFFFu), q + (all >> 16));
             C.g = g;
             C.q = q;
-            if (slab + 1 == td.cs_first + td.ncs && g + (all & 0xFFFFu) + rT != pe.k)      // the tensor's last slab
+            if (slab + 1 == td.cs_first + td.ncs &&                                        // the tensor's last slab
+                (g + (all & 0xFFFFu) + rT != pe.k || q + (all >> 16) < rT))
                 atomicAdd(&A.stats->internal_errors, 1ull);
         }
     }
@@ -436,7 +383,7 @@ __device__ __forceinline__ uint32_t slabs_of_tensor(const SelectArgs &A, const T
            (A.segtab[td.seg_first + td.nseg - 1u].ntiles + TILES - 1u) / TILES;
 }
 
-// Where a slab of the emission publishes: in the ordered-list scratch of its first tile.
+// Where a slab of the emission publishes (two words): in the ordered-list scratch of its first tile.
 __device__ __forceinline__ uint2 *dense_word(const SelectArgs &A, uint32_t tile0, uint32_t j)
 {
     return A.ord + (size_t)(tile0 + j) * CAPT;
@@ -520,7 +467,7 @@ __global__ __launch_bounds__(SLAB_THREADS) void k_dense_refine(const SelectArgs 
     uint32_t *g = A.ghist + (size_t)j * HBINS;
     // (the emission's slabs have published nothing yet)
     if (LEVEL == 2 && tid < SLAB_TILES / EMIT_TILES && tid * EMIT_TILES < s.ntiles)
-        slab_publish(dense_word(A, s.tile0 + tid * EMIT_TILES, j), 0);
+        slab_publish<true>(dense_word(A, s.tile0 + tid * EMIT_TILES, j), 0u, 0u, 0u);
     __syncthreads();
     for (uint32_t b = tid; b < BINS; b += SLAB_THREADS) {
         const uint32_t v = h[b];
@@ -606,13 +553,14 @@ __global__ __launch_bounds__(EMIT_THREADS) void k_dense_emit(const SelectArgs A)
                            ptiles = A.segtab[s.td.seg_first].ntiles;
             const uint32_t me = s.part.sidx * spp + (s.tile0 - s.part.tile0) / EMIT_TILES;
             uint2 *word = dense_word(A, s.tile0, j);
-            if (lane == 0) slab_publish(word, slab_word(me == 0 ? SLAB_SUM : SLAB_OWN, total & 0xFFFFu, total >> 16));
-            slab_look_back(A, me, 0u,
-                           [&](uint32_t i) { return dense_word(A, ptile0 + (i / spp) * ptiles + (i % spp) * EMIT_TILES, j); },
-                           g, q);
+            if (lane == 0) slab_publish<true>(word, me == 0 ? SLAB_SUM : SLAB_OWN, total & 0xFFFFu, total >> 16);
+            slab_look_back<true>(A, me, 0u,
+                                 [&](uint32_t i) { return dense_word(A, ptile0 + (i / spp) * ptiles + (i % spp) * EMIT_TILES, j); },
+                                 g, q);
             if (lane == 0) {
-                if (me != 0) slab_publish(word, slab_word(SLAB_SUM, g + (total & 0xFFFFu), q + (total >> 16)));
-                if (me + 1 == slabs_of_tensor<EMIT_TILES>(A, s.td) && g + (total & 0xFFFFu) + rT != pe.k)
+                if (me != 0) slab_publish<true>(word, SLAB_SUM, g + (total & 0xFFFFu), q + (total >> 16));
+                if (me + 1 == slabs_of_tensor<EMIT_TILES>(A, s.td) &&
+                    (g + (total & 0xFFFFu) + rT != pe.k || q + (total >> 16) < rT))
                     atomicAdd(&A.stats->internal_errors, 1ull);
             }
         }

@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "../../include/dgs.h"
+#include "../../paper_1910_10929_amd/csrc/dgs_slab.h"
 
 extern "C" {
 int dgs_oracle_nnz(const uint64_t *, uint32_t, double, uint64_t *, uint64_t *);
@@ -319,6 +320,46 @@ static void helpers_and_static(uint64_t seed)
     fflush(stdout);
 }
 
+// What an emission's slabs publish and add up, at counts that no buffer of a test could hold: the
+// largest running counts of the two forms, sums and single slabs, more slabs than one look covers.
+template <bool WIDE> static void slab_counts()
+{
+    g_what = WIDE ? "slab words of a dense request" : "slab words of the chain";
+    const std::vector<uint32_t> counts =
+        WIDE ? std::vector<uint32_t>{0u, 5u, 0x7FFFFFFFu, 0x80000000u, 0x80000001u, 0xFFFFFFFFu}
+             : std::vector<uint32_t>{0u, 5u, 0x3FFFFFFFu, 0x40000000u, 0x7FFFFFFFu};
+    dgs::DevStats stats{};
+    dgs::SelectArgs A{};
+    A.stats = &stats;
+    A.spin_limit = 4;
+    for (uint32_t slabs : {1u, 2u, 64u, 65u, 131u})
+        for (uint32_t g0 : counts)
+            for (uint32_t q0 : counts) {
+                // the running sum of the first slab, then slabs of their own that have not summed up yet
+                Buf<uint2> words(2 * slabs);
+                uint32_t want_g = g0, want_q = q0;
+                for (uint32_t i = 0; i < slabs; ++i) {
+                    const uint32_t g = i == 0 ? g0 : (want_g < 0x7FFF0000u || (WIDE && want_g < 0xFFFF0000u) ? 3u : 0u);
+                    const uint32_t q = i == 0 ? q0 : (want_q < 0x7FFF0000u || (WIDE && want_q < 0xFFFF0000u) ? 7u : 0u);
+                    dgs::slab_publish<WIDE>(&words.p[WIDE ? 2 * i : i], i == 0 ? dgs::SLAB_SUM : dgs::SLAB_OWN, g, q);
+                    want_g += i ? g : 0u;
+                    want_q += i ? q : 0u;
+                }
+                uint32_t got_g = 1, got_q = 1;
+                emu::launch(dim3(1), dim3(64), [&] {
+                    uint32_t g, q;
+                    dgs::slab_look_back<WIDE>(A, slabs, 0u, [&](uint32_t i) { return &words.p[WIDE ? 2 * i : i]; }, g, q);
+                    if (threadIdx.x == 0) {
+                        got_g = g;
+                        got_q = q;
+                    }
+                });
+                CHECK(got_g == want_g && got_q == want_q && stats.internal_errors == 0);
+            }
+    printf("%-44s ok\n", g_what.c_str());
+    fflush(stdout);
+}
+
 // Randomised layouts, densities, options, server forms and gradient-scale jumps (which make
 // predictions fail): `soak <first seed> <count>`.
 static void soak(uint64_t seed)
@@ -397,6 +438,8 @@ int main(int argc, char **argv)
         CHECK(st2.repaired_tensors >= 1 && st2.fallback_tensors == 0);
         return 0;
     }
+    slab_counts<false>();
+    slab_counts<true>();
     const std::vector<uint64_t> ragged = {1, 7, 64, 1000, 8192, 8193, 9408, 3, 100003, 20000, 70001, 17, 65537, 12345};
     const std::vector<uint64_t> two = {150000, 64, 66000};
     Opts def, exact, always, never, norepair;

@@ -49,3 +49,37 @@ def test_dense_rounds(oracle, rho, levels):
     for c in (ctx, ctx_sent):
         assert c.stats().internal_errors == 0
         c.close()
+
+
+@pytest.mark.parametrize("kind", ["ties", "above"])
+def test_more_than_2_31_entries_on_one_side_of_the_threshold(kind):
+    """One tensor of more than 2^31 elements: all of them equal to the k-th key, or more than 2^31
+    above it.  The message is the leading run of the row either way."""
+    import torch
+    n, head = (1 << 31) + (1 << 20) + 5, (1 << 31) + 1000
+    off = synth.layout_flat(n)
+    rho = 0.05 if kind == "ties" else (head + 70_000) / n
+    ctx = dgs.Context(off, W=1)
+    K = ctx.nnz(rho)
+    row = torch.zeros((1, n), dtype=torch.float32, device="cuda:0")
+    if kind == "above":
+        assert K > head
+        row[0, :head] = 2.0
+        row[0, head:] = 1.0
+    ctx.server_attach(row)
+    idx, val = torch.zeros(K, dtype=torch.int32, device="cuda:0"), torch.full((K,), 9.0, device="cuda:0")
+    assert ctx.server_pull(0, rho, idx, val) == K
+    step = 1 << 28
+    for a in range(0, K, step):
+        b = min(a + step, K)
+        want = torch.arange(a, b, device="cuda:0").to(torch.int32)       # (the low 32 bits)
+        assert torch.equal(idx[a:b], want)
+        v = val[a:b]
+        if kind == "ties":
+            assert not v.any()
+        else:
+            c = min(max(head - a, 0), b - a)
+            assert (v[:c] == 2.0).all() and (v[c:] == 1.0).all()
+    assert not row[0, :K].any() and (kind == "ties" or (row[0, K:] == 1.0).all())
+    assert ctx.stats().internal_errors == 0
+    ctx.close()
