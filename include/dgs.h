@@ -77,9 +77,12 @@ enum {
                                 the rounding error */
     DGS_OPT_SPIN_LIMIT = 8   /* polls after which a waiting workgroup of the selection gives up
                                 (default 2^20, far beyond any wait that ends); it is then counted
-                                in dgs_stats.internal_errors.  A tensor whose prediction failed in
-                                that launch is then left unselected: after a call that raised
-                                internal_errors the outputs and the context are not to be used */
+                                in dgs_stats.internal_errors.  What waits: the collection after a
+                                failed prediction, and the emission of tensors with long candidate
+                                lists and of dense requests, which waits on every call.  What gave
+                                up is left unselected, or emitted up to the part that gave up: after
+                                a call that raised internal_errors the outputs and the context are
+                                not to be used */
 };
 
 /* Kernel classes reported by dgs_profile_read(). */

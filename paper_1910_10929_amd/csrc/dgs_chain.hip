@@ -174,7 +174,8 @@ __device__ __forceinline__ void rank_slab(const SelectArgs &A, uint32_t slab, co
     }
 }
 
-// EMIT (the other blocks): ordered emission of the slab and the state fix-up.
+// EMIT (the other blocks): ordered emission of the slab and the state fix-up.  A slab that gives up
+// a wait, and every slab of the tensor behind it, emits nothing and leaves the state as it is.
 template <int OP, uint32_t THREADS>
 __device__ __forceinline__ void emit_slab(const SelectArgs &A, uint32_t slab, const SegDesc &sd, const TensorDesc &td,
                                           const PlanEntry &pe, SegState *st, bool lists, FinishShared &C)
@@ -186,7 +187,10 @@ __device__ __forceinline__ void emit_slab(const SelectArgs &A, uint32_t slab, co
     uint2 e[CTPW];
     tile_firsts(A, w, e);                            // on their way while the ranking is awaited
     if (wait_word(&st->ready, A.spin_limit, &C.bc) == 0) {
-        if (tid == 0) atomicAdd(&A.stats->internal_errors, 1ull);
+        if (tid == 0) {
+            slab_publish<false>(&A.slabs_done[slab], SLAB_FAIL, 0u, 0u);
+            atomicAdd(&A.stats->internal_errors, 1ull);
+        }
         return;
     }
     const uint32_t T = uniform(ld_dev(&st->T)), rT = uniform(ld_dev(&st->rT));
@@ -225,17 +229,19 @@ __device__ __forceinline__ void emit_slab(const SelectArgs &A, uint32_t slab, co
         const bool head = (slab == td.cs_first);
         if (lane == 0) slab_publish<false>(&A.slabs_done[slab], head ? SLAB_SUM : SLAB_OWN, all & 0xFFFFu, all >> 16);
         uint32_t g, q;
-        slab_look_back<false>(A, slab, td.cs_first, [&](uint32_t i) { return &A.slabs_done[i]; }, g, q);
+        const bool known = slab_look_back<false>(A, slab, td.cs_first, [&](uint32_t i) { return &A.slabs_done[i]; }, g, q);
         if (lane == 0) {
-            if (!head) slab_publish<false>(&A.slabs_done[slab], SLAB_SUM, g + (all & 0xFFFFu), q + (all >> 16));
+            if (!head) slab_publish<false>(&A.slabs_done[slab], known ? SLAB_SUM : SLAB_FAIL, g + (all & 0xFFFFu), q + (all >> 16));
+            C.bc = known ? 1u : 0u;
             C.g = g;
             C.q = q;
-            if (slab + 1 == td.cs_first + td.ncs &&                                        // the tensor's last slab
+            if (known && slab + 1 == td.cs_first + td.ncs &&                                        // the tensor's last slab
                 (g + (all & 0xFFFFu) + rT != pe.k || q + (all >> 16) < rT))
                 atomicAdd(&A.stats->internal_errors, 1ull);
         }
     }
     __syncthreads();
+    if (C.bc == 0) return;
     uint32_t eq = C.q + (before >> 16);              // the tensor's ties seen so far: lowest index first, rT of them are taken
     uint32_t pos = C.g + (before & 0xFFFFu) + min(eq, rT);
     auto send = [&](uint2 x, float was, bool valid) {             // up to 64 consecutive entries; all lanes call
@@ -512,7 +518,7 @@ __global__ __launch_bounds__(EMIT_THREADS) void k_dense_emit(const SelectArgs A)
 {
     __shared__ uint2 stage_all[EMIT_WAVES][TILE];
     __shared__ uint32_t wtot[EMIT_WAVES];
-    __shared__ uint32_t g_before, q_before;
+    __shared__ uint32_t g_before, q_before, known_before;
     Slab s;
     if (!find_slab<EMIT_TILES>(A, s)) return;
     const SegState *st = &A.segstate[s.part.j];
@@ -548,18 +554,19 @@ __global__ __launch_bounds__(EMIT_THREADS) void k_dense_emit(const SelectArgs A)
     }
     if (wave == 0) {
         uint32_t g = max(s.tile0 * TILE, s.td.off) - s.td.off, q = 0;
+        bool known = true;
         if (!all) {
             const uint32_t j = s.part.j, spp = slabs_per_part<EMIT_TILES>(A, s.td), ptile0 = A.segtab[s.td.seg_first].tile0,
                            ptiles = A.segtab[s.td.seg_first].ntiles;
             const uint32_t me = s.part.sidx * spp + (s.tile0 - s.part.tile0) / EMIT_TILES;
             uint2 *word = dense_word(A, s.tile0, j);
             if (lane == 0) slab_publish<true>(word, me == 0 ? SLAB_SUM : SLAB_OWN, total & 0xFFFFu, total >> 16);
-            slab_look_back<true>(A, me, 0u,
-                                 [&](uint32_t i) { return dense_word(A, ptile0 + (i / spp) * ptiles + (i % spp) * EMIT_TILES, j); },
-                                 g, q);
+            known = slab_look_back<true>(A, me, 0u, [&](uint32_t i) {
+                return dense_word(A, ptile0 + (i / spp) * ptiles + (i % spp) * EMIT_TILES, j);
+            }, g, q);
             if (lane == 0) {
-                if (me != 0) slab_publish<true>(word, SLAB_SUM, g + (total & 0xFFFFu), q + (total >> 16));
-                if (me + 1 == slabs_of_tensor<EMIT_TILES>(A, s.td) &&
+                if (me != 0) slab_publish<true>(word, known ? SLAB_SUM : SLAB_FAIL, g + (total & 0xFFFFu), q + (total >> 16));
+                if (known && me + 1 == slabs_of_tensor<EMIT_TILES>(A, s.td) &&
                     (g + (total & 0xFFFFu) + rT != pe.k || q + (total >> 16) < rT))
                     atomicAdd(&A.stats->internal_errors, 1ull);
             }
@@ -567,9 +574,11 @@ __global__ __launch_bounds__(EMIT_THREADS) void k_dense_emit(const SelectArgs A)
         if (lane == 0) {
             g_before = g;
             q_before = q;
+            known_before = known ? 1u : 0u;
         }
     }
     __syncthreads();
+    if (known_before == 0) return;
     uint32_t eq = q_before + (before >> 16);     // the tensor's ties before this row: lowest index first, rT of them are taken
     uint32_t pos = g_before + (before & 0xFFFFu) + min(eq, rT);
     uint2 *stage = stage_all[wave];

@@ -7,8 +7,9 @@
 namespace dgs {
 
 // A slab's entries above the k-th key and equal to it (SLAB_OWN), or the same for all slabs of the
-// tensor up to and including it (SLAB_SUM); 0: nothing published yet.
-constexpr uint32_t SLAB_OWN = 1u, SLAB_SUM = 2u;
+// tensor up to and including it (SLAB_SUM); SLAB_FAIL: it gave up waiting and emits nothing, and so
+// does every slab behind it; 0: nothing published yet.
+constexpr uint32_t SLAB_OWN = 1u, SLAB_SUM = 2u, SLAB_FAIL = 3u;
 
 struct SlabWord {
     uint32_t kind, g, q;
@@ -43,9 +44,10 @@ __device__ __forceinline__ SlabWord slab_read(const uint2 *word)
 // Entries above / equal to the k-th key in the tensor's slabs [first, slab), by one wavefront
 // looking back over up to 64 slabs at a time until one has published its running sum
 // (word_of(i): where slab i publishes).  Those are blocks with lower indices; bounded by
-// A.spin_limit polls.
+// A.spin_limit polls.  Returns false, in every lane, if it gave up (counted as an internal error) or
+// if a slab before it has: the positions are not known then.
 template <bool WIDE, class WordOf>
-__device__ __forceinline__ void slab_look_back(const SelectArgs &A, uint32_t slab, uint32_t first, WordOf word_of,
+__device__ __forceinline__ bool slab_look_back(const SelectArgs &A, uint32_t slab, uint32_t first, WordOf word_of,
                                                uint32_t &g, uint32_t &q)
 {
     const uint32_t lane = lane_id();
@@ -57,7 +59,7 @@ __device__ __forceinline__ void slab_look_back(const SelectArgs &A, uint32_t sla
         for (uint32_t spin = 0; spin < A.spin_limit; ++spin) {
             if (in && w.kind == 0) w = slab_read<WIDE>(word_of(hi - 1u - lane));
             have = ballot64(!in || w.kind != 0);
-            sums = ballot64(in && w.kind == SLAB_SUM);
+            sums = ballot64(in && w.kind >= SLAB_SUM);
             // everything up to the nearest running sum (or all 64) has been published
             const uint64_t upto = sums ? (((sums & (0ull - sums)) << 1) - 1ull) : ~0ull;
             if ((have & upto) == upto) break;
@@ -66,14 +68,16 @@ __device__ __forceinline__ void slab_look_back(const SelectArgs &A, uint32_t sla
         const uint64_t upto = sums ? (((sums & (0ull - sums)) << 1) - 1ull) : ~0ull;
         if ((have & upto) != upto) {                 // gave up waiting
             if (lane == 0) atomicAdd(&A.stats->internal_errors, 1ull);
-            return;
+            return false;
         }
+        if ((ballot64(w.kind == SLAB_FAIL) & upto) != 0) return false;
         const uint32_t counts = 0u - (uint32_t)((upto >> lane) & 1u);      // (lanes beyond `first` hold 0)
         g += wave_sum(w.g & counts);
         q += wave_sum(w.q & counts);
-        if (sums) return;
+        if (sums) return true;
         hi = (hi - first > 64u) ? hi - 64u : first;
     }
+    return true;
 }
 
 }  // namespace dgs

@@ -8,6 +8,8 @@ extern "C" char __stop_emu_lds[] __attribute__((weak));
 
 namespace emu {
 
+int block_order = 0;
+
 // Minimal stack switch (System V x86-64): callee-saved registers on the old stack, stack
 // pointers exchanged.  (swapcontext would make a system call per switch.)
 extern "C" void emu_stack_switch(void **save_sp, void *load_sp);
@@ -209,8 +211,9 @@ void launch(dim3 grid, dim3 block, const std::function<void()> &body)
     blockDim = Idx{block.x, 1, 1};
     gridDim = Idx{grid.x, grid.y, 1};
     for (uint32_t by = 0; by < grid.y; ++by)
-        for (uint32_t bx = 0; bx < grid.x; ++bx) {
-            blockIdx = Idx{bx, by, 0};
+        for (uint32_t at = 0; at < grid.x; ++at) {
+            const uint32_t half = block_order == 1 ? 0u : (block_order == 2 ? grid.x / 2 : grid.x);
+            blockIdx = Idx{at < half ? at : grid.x - 1 - (at - half), by, 0};
             if (__start_emu_lds && __stop_emu_lds > __start_emu_lds)
                 memset(__start_emu_lds, 0xCD, (size_t)(__stop_emu_lds - __start_emu_lds));   // LDS starts as garbage
             for (uint32_t t = 0; t < m.nthreads; ++t) {

@@ -360,6 +360,50 @@ template <bool WIDE> static void slab_counts()
     fflush(stdout);
 }
 
+// Waits that give up (workgroups run in an order that makes them): nothing is emitted that is not
+// in its place, and an entry is taken out of the state exactly if its pair was written.
+static void gives_up(const char *name, double rho, int seg_mode, int order, uint64_t seed)
+{
+    g_what = name;
+    Layout L({300000, 64, 150001});
+    Rng r(seed);
+    Ctx c(L, 0);
+    Opts o;
+    o.seg_mode = seg_mode;
+    o.repair = 0;
+    set_opts(c, o);
+    const uint64_t K = L.K(rho);
+    Buf<float> g(L.n), s_gpu(L.n), s_ref(L.n);
+    Buf<uint32_t> gi(K), wi(K);
+    Buf<float> gv(K), wv(K);
+    uint64_t k1 = 0, k2 = 0;
+    fill_grad(L, r, g.p, 1.0f, 0);
+    CHECK(dgs_oracle_worker_step(g.p, s_ref.p, L.off.data(), L.J, 0.5f, 0.9f, rho, wi.p, wv.p, &k1) == 0);
+    for (uint64_t e = 0; e < K; ++e) gi.p[e] = 0xFFFFFFFFu;
+    CHECK(dgs_set_option(c.c, DGS_OPT_SPIN_LIMIT, 2) == DGS_OK);
+    emu::block_order = order;
+    CHECK(dgs_worker_step(c.c, g.p, s_gpu.p, nullptr, 0.5f, 0.9f, rho, gi.p, gv.p, &k2) == DGS_OK);
+    emu::block_order = 0;
+    CHECK(c.stats().internal_errors > 0);
+    std::vector<char> sent(L.n, 0);
+    uint64_t missing = 0;
+    for (uint64_t e = 0; e < K; ++e) {
+        if (gi.p[e] == 0xFFFFFFFFu) {
+            ++missing;
+            continue;
+        }
+        CHECK(gi.p[e] == wi.p[e] && memcmp(&gv.p[e], &wv.p[e], 4) == 0);
+        sent[gi.p[e]] = 1;
+    }
+    CHECK(missing > 0 && missing < K);
+    for (uint64_t i = 0; i < L.n; ++i) {
+        const float a = std::fmaf(0.5f, g.p[i], 0.0f), want = sent[i] ? 0.9f * a : a;
+        CHECK(memcmp(&s_gpu.p[i], &want, 4) == 0);
+    }
+    printf("%-44s ok\n", name);
+    fflush(stdout);
+}
+
 // Randomised layouts, densities, options, server forms and gradient-scale jumps (which make
 // predictions fail): `soak <first seed> <count>`.
 static void soak(uint64_t seed)
@@ -440,6 +484,9 @@ int main(int argc, char **argv)
     }
     slab_counts<false>();
     slab_counts<true>();
+    gives_up("dense emission gives up", 0.1, 0, 1, 40);
+    gives_up("chain emission gives up on the slabs before", 0.01, 1, 2, 41);
+    gives_up("chain emission gives up on the ranking", 0.01, 1, 1, 42);
     const std::vector<uint64_t> ragged = {1, 7, 64, 1000, 8192, 8193, 9408, 3, 100003, 20000, 70001, 17, 65537, 12345};
     const std::vector<uint64_t> two = {150000, 64, 66000};
     Opts def, exact, always, never, norepair;

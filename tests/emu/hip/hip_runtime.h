@@ -3,7 +3,8 @@
 // UndefinedBehaviorSanitizer (test infrastructure; see tests/emu/emu_driver.cpp).
 //
 // Model.  A launch runs its workgroups one after the other in block order (so a workgroup
-// that waits for a word set by a lower block finds it set).  The threads of a workgroup are
+// that waits for a word set by a lower block finds it set; emu::block_order can reverse them,
+// which makes such a wait run into its limit).  The threads of a workgroup are
 // fibers; a thread runs until it reaches a synchronisation point -- a workgroup barrier or a
 // wavefront-collective builtin (ballot, readlane, DPP, bpermute, wave barrier) -- where it
 // blocks.  When no thread of the workgroup can run, the pending collectives are resolved per
@@ -102,6 +103,7 @@ extern emu::Idx threadIdx, blockIdx, blockDim, gridDim;
 
 namespace emu {
 
+extern int block_order;              // 0 ascending; 1 descending; 2 ascending in the first half of the grid, descending in the second
 void to_scheduler();                 // block the current fiber (state already set) and run others
 __attribute__((convergent)) uint64_t collective(Op op, const void *site, uint64_t a, uint64_t b = 0, uint64_t c = 0, uint64_t d = 0);
 void launch(dim3 grid, dim3 block, const std::function<void()> &body);
