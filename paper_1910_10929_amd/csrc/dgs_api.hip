@@ -29,7 +29,7 @@ size_t align_up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
 struct Layout {          // byte offsets inside the workspace
     size_t tile_desc, tdesc, plans, tau, hint2, tprev, ghist, tile_cnt, heads, slots, ord, stats, flag;
-    size_t qlist, segtab, grptab, grpcnt, segstart, segcnt, segstate, cslabs, slabs_done, total;
+    size_t qlist, segtab, grptab, grpcnt, segcnt, segstate, cslabs, dslabs, slabs_done, total;
 };
 
 bool check_offsets(const uint64_t *offsets, uint32_t J)
@@ -70,6 +70,12 @@ uint32_t chain_slabs(uint64_t off, uint64_t n, uint32_t scale)
     return (uint32_t)(full * ((per + CSLAB_TILES - 1) / CSLAB_TILES) + (rest + CSLAB_TILES - 1) / CSLAB_TILES);
 }
 
+// Dense slabs of a tensor: runs of SLAB_TILES of its tiles.
+uint32_t dense_slabs(uint64_t off, uint64_t n)
+{
+    return (uint32_t)(((off + n - 1) / TILE - off / TILE + SLAB_TILES) / SLAB_TILES);
+}
+
 uint32_t layout_scale(const uint64_t *offsets, uint32_t J)
 {
     const uint64_t ntiles = (offsets[J] + TILE - 1) / TILE;
@@ -82,12 +88,13 @@ Layout make_layout(const uint64_t *offsets, uint32_t J, uint32_t W)
 {
     const uint64_t n = offsets[J];
     const size_t ntiles = (size_t)((n + TILE - 1) / TILE);
-    size_t nseg_total = 0, ncs = 0;
+    size_t nseg_total = 0, ncs = 0, nds = 0;
     const uint32_t scale = layout_scale(offsets, J);
     for (uint32_t j = 0; j < J; ++j) {
         const uint32_t ns = tensor_segments(offsets[j], offsets[j + 1] - offsets[j], scale);
         nseg_total += ns;
         const uint64_t nj = offsets[j + 1] - offsets[j];
+        nds += dense_slabs(offsets[j], nj);
         if (nj < SEG_MIN_N) continue;
         ncs += chain_slabs(offsets[j], nj, scale);
     }
@@ -103,15 +110,15 @@ Layout make_layout(const uint64_t *offsets, uint32_t J, uint32_t W)
     L.tile_cnt = o;  o = align_up(o + (ntiles + 4) * sizeof(uint32_t));
     L.heads = o;     o = align_up(o + ntiles * HEAD * sizeof(uint2));
     L.slots = o;     o = align_up(o + ntiles * CAPT * sizeof(uint2));
-    L.ord = o;       o = align_up(o + (ntiles + J) * CAPT * sizeof(uint2));
+    L.ord = o;       o = align_up(o + (ntiles + J - 1) * CAPT * sizeof(uint2));   // tensor j from its first tile + j on
     L.stats = o;     o = align_up(o + sizeof(DevStats));
     L.flag = o;      o = align_up(o + 64);
     L.qlist = o;     o = align_up(o + (ntiles + 4) * sizeof(uint32_t));
     L.segtab = o;    o = align_up(o + (nseg_total + 1) * sizeof(SegDesc));
     L.grptab = o;    o = align_up(o + (nseg_total + 1) * sizeof(SegDesc));      // groups <= parts
     L.cslabs = o;    o = align_up(o + ncs * sizeof(SegDesc));
+    L.dslabs = o;    o = align_up(o + nds * sizeof(uint32_t));
     L.grpcnt = o;    o = align_up(o + (nseg_total + 1) * sizeof(uint32_t));
-    L.segstart = o;  o = align_up(o + (nseg_total + 1) * sizeof(uint32_t));
     L.segcnt = o;    o = align_up(o + (nseg_total + 1) * sizeof(uint32_t));
     L.segstate = o;  o = align_up(o + (size_t)J * sizeof(SegState));
     L.slabs_done = o; o = align_up(o + ncs * sizeof(uint2));
@@ -177,15 +184,16 @@ struct dgs_ctx {
     uint32_t nqlist = 0;               // 0: no sampling on this context
     SegDesc *segtab = nullptr;
     SegDesc *grptab = nullptr;
-    uint32_t *grpcnt = nullptr, *segstart = nullptr;
+    uint32_t *grpcnt = nullptr;
     uint32_t ngroups = 0, gparts = 1;  // join groups; parts per group
     uint32_t bgroup = 8;               // parts per re-collecting workgroup (about 2048 tiles)
-    uint32_t slabs = 1;                // slabs of the longest part (dense requests)
     uint32_t *segcnt = nullptr;
     SegState *segstate = nullptr;
     uint2 *slabs_done = nullptr;
     SegDesc *cslabs = nullptr;
     uint32_t ncslabs = 0;              // chain slabs
+    uint32_t *dslabs = nullptr;        // dense slabs: the tensor of each
+    uint32_t ndslabs = 0;
     uint32_t nseg_total = 0;
     HostArr<uint32_t> nseg;            // per tensor: parts (at least one)
     float *diff = nullptr;
@@ -483,7 +491,6 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
     se.segtab = c->segtab;
     se.grptab = c->grptab;
     se.grpcnt = c->grpcnt;
-    se.segstart = c->segstart;
     se.ngroups = c->ngroups;
     se.gparts = c->gparts;
     se.bgroup = c->bgroup;
@@ -514,7 +521,8 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
     se.exact_mode = exact ? 1u : 0u;
     se.repair = (c->repair_round && !dense_req) ? 1u : 0u;   // a dense request has no lists to collect again
     se.spin_limit = c->spin_limit;
-    se.slabs = c->slabs;
+    se.dslabs = c->dslabs;
+    se.ndslabs = c->ndslabs;
     if (!(dense_req && have_seg)) {
         ProfSlot ps(c, prof_select);
         if (have_seg) launch_window(se, c->stream, ps.ev0);
@@ -555,21 +563,21 @@ void carve_workspace(dgs_ctx *c, void *workspace, const Layout &L)
     c->segtab = (SegDesc *)(c->ws + L.segtab);
     c->grptab = (SegDesc *)(c->ws + L.grptab);
     c->grpcnt = (uint32_t *)(c->ws + L.grpcnt);
-    c->segstart = (uint32_t *)(c->ws + L.segstart);
     c->segcnt = (uint32_t *)(c->ws + L.segcnt);
     c->segstate = (SegState *)(c->ws + L.segstate);
     c->cslabs = (SegDesc *)(c->ws + L.cslabs);
+    c->dslabs = (uint32_t *)(c->ws + L.dslabs);
     c->slabs_done = (uint2 *)(c->ws + L.slabs_done);
 }
 
 // Tensor, segment and initial-threshold tables of a layout, into host arrays of J,
-// (W + 1) J, J + 1, (sum of tensor_segments) twice and (sum of chain_slabs) entries; fills c->nseg,
-// c->nseg_total, c->ngroups and c->ncslabs.
+// (W + 1) J, J + 1, (sum of tensor_segments) twice, (sum of chain_slabs) and (sum of dense_slabs)
+// entries; fills c->nseg, c->nseg_total, c->ngroups, c->ncslabs and c->ndslabs.
 void fill_tables(dgs_ctx *c, TensorDesc *td, uint32_t *tau0, uint32_t *toff, SegDesc *segs, SegDesc *groups,
-                 SegDesc *slabs)
+                 SegDesc *slabs, uint32_t *dslabs)
 {
     const uint32_t J = c->J, W = c->W;
-    uint32_t nsegs = 0, ncs = 0;
+    uint32_t nsegs = 0, ncs = 0, nds = 0;
     const uint32_t scale = layout_scale(&c->offsets[0], J);
     for (uint32_t j = 0; j < J; ++j) {
         td[j].off = (uint32_t)c->offsets[j];
@@ -581,7 +589,8 @@ void fill_tables(dgs_ctx *c, TensorDesc *td, uint32_t *tau0, uint32_t *toff, Seg
         td[j].seg_first = nsegs;
         td[j].nseg = ns;
         const bool chain = td[j].n >= SEG_MIN_N;
-        td[j].pad = 0;
+        td[j].ds_first = nds;
+        for (uint32_t s = dense_slabs(c->offsets[j], td[j].n); s; --s) dslabs[nds++] = j;
         td[j].cs_first = ncs;
         c->nseg[j] = ns;
         const uint32_t tlo = td[j].off / TILE, thi = (td[j].off + td[j].n - 1) / TILE;
@@ -594,7 +603,6 @@ void fill_tables(dgs_ctx *c, TensorDesc *td, uint32_t *tau0, uint32_t *toff, Seg
             for (uint32_t t = 0; chain && t < d.ntiles; t += CSLAB_TILES)
                 slabs[ncs++] = SegDesc{j, d.tile0 + t, std::min(CSLAB_TILES, d.ntiles - t), nsegs};
             segs[nsegs++] = d;
-            c->slabs = std::max(c->slabs, (d.ntiles + SLAB_TILES - 1) / SLAB_TILES);
         }
         td[j].ncs = ncs - td[j].cs_first;
         for (uint32_t w = 0; w <= W; ++w) tau0[(size_t)w * J + j] = td[j].big ? 1u : TAU_NEVER;
@@ -602,6 +610,7 @@ void fill_tables(dgs_ctx *c, TensorDesc *td, uint32_t *tau0, uint32_t *toff, Seg
     for (uint32_t j = 0; j <= J; ++j) toff[j] = (uint32_t)c->offsets[j];
     c->nseg_total = nsegs;
     c->ncslabs = ncs;
+    c->ndslabs = nds;
     // re-collecting workgroups: both roles together about as many as the compute units that the
     // tensors' selecting workgroups (at most one per tensor) leave free, each looking after at
     // most 8 consecutive parts
@@ -647,9 +656,9 @@ int upload(dgs_ctx *c, void *dst, const void *src, size_t bytes)
 }
 
 // Tables up, counters cleared: what a context's workspace holds before its first call.  tabs != 0: segs,
-// groups and slabs lie in one host block of that many bytes, placed as in the workspace.
+// groups, slabs and dslabs lie in one host block of that many bytes, placed as in the workspace.
 int upload_tables(dgs_ctx *c, const TensorDesc *td, const uint32_t *tau0, const uint32_t *toff, const SegDesc *segs,
-                  const SegDesc *groups, const SegDesc *slabs, size_t tabs)
+                  const SegDesc *groups, const SegDesc *slabs, const uint32_t *dslabs, size_t tabs)
 {
     const uint32_t J = c->J, W = c->W;
     int rc = upload(c, c->toff, toff, ((size_t)J + 1) * sizeof(uint32_t));
@@ -661,6 +670,7 @@ int upload_tables(dgs_ctx *c, const TensorDesc *td, const uint32_t *tau0, const 
         if (rc == DGS_OK) rc = upload(c, c->segtab, segs, (size_t)c->nseg_total * sizeof(SegDesc));
         if (rc == DGS_OK) rc = upload(c, c->grptab, groups, (size_t)c->ngroups * sizeof(SegDesc));
         if (rc == DGS_OK) rc = upload(c, c->cslabs, slabs, (size_t)c->ncslabs * sizeof(SegDesc));
+        if (rc == DGS_OK) rc = upload(c, c->dslabs, dslabs, (size_t)c->ndslabs * sizeof(uint32_t));
     }
     if (rc != DGS_OK) return rc;
     launch_fill_u32(c->hint2, 0u, (size_t)(W + 1) * J, c->stream);
@@ -733,14 +743,15 @@ int dgs_create(dgs_ctx **out, const uint64_t *offsets, uint32_t J, uint32_t W, v
     std::vector<TensorDesc> td(J);
     std::vector<uint32_t> tau0((size_t)(W + 1) * J);
     std::vector<uint32_t> toff(J + 1);
-    // parts, join groups and chain slabs, as they lie in the workspace: one upload
+    // parts, join groups, chain slabs and dense slabs, as they lie in the workspace: one upload
     const size_t tabs = L.grpcnt - L.segtab;      // (grpcnt follows them)
     static_assert(ALIGN % sizeof(SegDesc) == 0, "the tables start at whole entries");
     std::vector<SegDesc> tab(tabs / sizeof(SegDesc));
     SegDesc *segs = tab.data(), *groups = segs + (L.grptab - L.segtab) / sizeof(SegDesc),
             *slabs = segs + (L.cslabs - L.segtab) / sizeof(SegDesc);
+    uint32_t *dslabs = (uint32_t *)(segs + (L.dslabs - L.segtab) / sizeof(SegDesc));
     c->nseg.assign(J, 0u);
-    fill_tables(c, td.data(), tau0.data(), toff.data(), segs, groups, slabs);
+    fill_tables(c, td.data(), tau0.data(), toff.data(), segs, groups, slabs, dslabs);
 
     // What a sampling pass visits: every 16th tile of the buffer, and every tile of the tensors of
     // at most 64 tiles, whose ranks are too small to estimate from a sixteenth.
@@ -763,7 +774,7 @@ int dgs_create(dgs_ctx **out, const uint64_t *offsets, uint32_t J, uint32_t W, v
     const size_t stage_bytes = align_up((size_t)NPLAN * J * sizeof(PlanEntry));
     ok = ok && hipHostMalloc((void **)&c->plan_stage, stage_bytes + 64, hipHostMallocDefault) == hipSuccess;
     if (ok) c->host_total = (uint32_t *)((char *)c->plan_stage + stage_bytes);
-    ok = ok && upload_tables(c, td.data(), tau0.data(), toff.data(), segs, groups, slabs, tabs) == DGS_OK;
+    ok = ok && upload_tables(c, td.data(), tau0.data(), toff.data(), segs, groups, slabs, dslabs, tabs) == DGS_OK;
     ok = ok && hipStreamSynchronize(c->stream) == hipSuccess;
     ok = ok && hipGetLastError() == hipSuccess;
     if (!ok) {
@@ -885,6 +896,7 @@ int dgs_worker_step_static(const uint64_t *offsets, uint32_t J, const float *gra
     // shorter slab per part: at most T / SEG_TILES full parts and one shorter part per tensor)
     constexpr size_t T = DGS_STATIC_SCRATCH_BYTES / (2 * CAPT * sizeof(uint2)) + DGS_STATIC_MAX_TENSORS;
     static_assert(T / CSLAB_TILES + T / SEG_TILES + DGS_STATIC_MAX_TENSORS <= STATIC_MAX_SLABS, "slab table of a static call");
+    static_assert(T / SLAB_TILES + DGS_STATIC_MAX_TENSORS <= STATIC_MAX_SLABS, "dense slab table of a static call");
     void *ws = nullptr;
     int rc = static_scratch(&ws);
     if (rc != DGS_OK) return rc;
@@ -897,6 +909,7 @@ int dgs_worker_step_static(const uint64_t *offsets, uint32_t J, const float *gra
     uint32_t tau0[DGS_STATIC_MAX_TENSORS], toff[DGS_STATIC_MAX_TENSORS + 1];
     SegDesc segs[STATIC_MAX_SEGS + 1];
     SegDesc groups[STATIC_MAX_SEGS + 1], slabs[STATIC_MAX_SLABS];
+    uint32_t dslabs[STATIC_MAX_SLABS];
     PlanEntry plan[DGS_STATIC_MAX_TENSORS];
     for (uint32_t j = 0; j <= J; ++j) offs[j] = offsets[j];
     dgs_ctx c;
@@ -912,10 +925,10 @@ int dgs_worker_step_static(const uint64_t *offsets, uint32_t J, const float *gra
     c.hint_density.borrow(hint_density);
     c.plan_stage = plan;               // one density per call: only the first cache slot is used
     carve_workspace(&c, ws, L);
-    fill_tables(&c, td, tau0, toff, segs, groups, slabs);
+    fill_tables(&c, td, tau0, toff, segs, groups, slabs, dslabs);
     // every call starts from a clean workspace (the array keeps the previous call's contents);
     // with no threshold hints the step takes the two-pass path
-    rc = upload_tables(&c, td, tau0, toff, segs, groups, slabs, 0);
+    rc = upload_tables(&c, td, tau0, toff, segs, groups, slabs, dslabs, 0);
     if (rc != DGS_OK) return rc;
     return run_selection(&c, OP_FMA, SEL_WORKER, grad, state, lr, m, density, 0, idx_out, val_out, nnz_out,
                          DGS_PROF_WORKER_STREAM, DGS_PROF_WORKER_SELECT, DGS_PROF_WORKER_SEGMENTED);

@@ -51,7 +51,7 @@ __device__ __forceinline__ WaveTiles wave_tiles(const SelectArgs &A, const Tenso
         const uint64_t cnt = A.segcnt[part] & 0x7FFFFFFFu, i = t0 + lane - ps.tile0;
         const uint64_t lo = cnt * i / ps.ntiles, hi = cnt * (i + 1) / ps.ntiles;
         w.n = (uint32_t)(hi - lo);
-        w.start = A.segstart[part] + (uint32_t)lo;
+        w.start = (ps.tile0 + ps.j) * CAPT + (uint32_t)lo;      // below 2^32: n < 2^32
     }
     return w;
 }
@@ -334,7 +334,7 @@ void launch_chain(int op, const SelectArgs &a, void *stream, void *ev0, void *ev
 // Above density 1/32 candidates stop paying off, and the tensors themselves are read again.  The
 // accumulate pass has counted bits [30:19] of every key of the big tensors and k_pick_dense has
 // found the bucket that holds the k-th one; then, one workgroup per slab of SLAB_TILES tiles of a
-// part (a small tensor is one slab, and that workgroup counts its leading bits too),
+// tensor (a small tensor is one slab, and that workgroup counts its leading bits too),
 //   refine 1  counts bits [18:11] of the keys in that bucket; the slab arriving last for a tensor
 //             ranks: 20 leading bits of the k-th key
 //   refine 2  counts the low 11 bits of the keys that share them; the slab arriving last ranks:
@@ -358,35 +358,27 @@ constexpr uint32_t REF2_BINS = 2048;                     // refine 2: key bits [
 
 struct Slab {
     TensorDesc td;
-    SegDesc part;
+    uint32_t j, tlo;          // its tensor, and that tensor's first tile
+    uint32_t idx, count;      // which slab of the tensor it is, of how many (in units of TILES tiles)
     uint32_t tile0, ntiles;
 };
 
+// One block per slab and nothing else: a layout may hold one tensor of a thousand slabs and a
+// hundred thousand of one.  false: the second half of a tensor's last slab is empty.
 template <uint32_t TILES>
 __device__ __forceinline__ bool find_slab(const SelectArgs &A, Slab &s)
 {
-    const uint32_t per = A.slabs * (SLAB_TILES / TILES);
-    s.part = A.segtab[blockIdx.x / per];
-    const uint32_t first = (blockIdx.x % per) * TILES;
-    if (first >= s.part.ntiles || !A.plan[s.part.j].seg) return false;
-    s.td = A.tdesc[s.part.j];
-    s.tile0 = s.part.tile0 + first;
-    s.ntiles = min(TILES, s.part.ntiles - first);
+    constexpr uint32_t PER = SLAB_TILES / TILES;
+    s.j = A.dslabs[blockIdx.x / PER];
+    s.td = A.tdesc[s.j];
+    s.tlo = s.td.off / TILE;
+    const uint32_t nt = (s.td.off + s.td.n - 1u) / TILE - s.tlo + 1u;
+    s.idx = blockIdx.x - s.td.ds_first * PER;
+    s.count = (nt + TILES - 1u) / TILES;
+    if (s.idx >= s.count) return false;
+    s.tile0 = s.tlo + s.idx * TILES;
+    s.ntiles = min(TILES, nt - s.idx * TILES);
     return true;
-}
-
-// Slabs of one full part, and of the whole tensor (only its last part may be shorter).
-template <uint32_t TILES>
-__device__ __forceinline__ uint32_t slabs_per_part(const SelectArgs &A, const TensorDesc &td)
-{
-    return (A.segtab[td.seg_first].ntiles + TILES - 1u) / TILES;
-}
-
-template <uint32_t TILES>
-__device__ __forceinline__ uint32_t slabs_of_tensor(const SelectArgs &A, const TensorDesc &td)
-{
-    return (td.nseg - 1u) * slabs_per_part<TILES>(A, td) +
-           (A.segtab[td.seg_first + td.nseg - 1u].ntiles + TILES - 1u) / TILES;
 }
 
 // Where a slab of the emission publishes (two words): in the ordered-list scratch of its first tile.
@@ -432,7 +424,7 @@ __global__ __launch_bounds__(SLAB_THREADS) void k_dense_refine(const SelectArgs 
     __shared__ uint32_t bc;
     Slab s;
     if (!find_slab<SLAB_TILES>(A, s)) return;
-    const uint32_t j = s.part.j, tid = threadIdx.x;
+    const uint32_t j = s.j, tid = threadIdx.x;
     SegState *st = &A.segstate[j];
     const bool leading = (LEVEL == 1) && !s.td.big;       // the leading bits are still to be counted
     const uint32_t k = A.plan[j].k;
@@ -479,8 +471,7 @@ __global__ __launch_bounds__(SLAB_THREADS) void k_dense_refine(const SelectArgs 
         const uint32_t v = h[b];
         if (v) atomicAdd(&g[b], v);
     }
-    const uint32_t nslabs = slabs_of_tensor<SLAB_TILES>(A, s.td);
-    if (!arrive_last(&st->arrive[LEVEL], nslabs, &bc)) return;
+    if (!arrive_last(&st->arrive[LEVEL], s.count, &bc)) return;
 
     // ------------------------------------------------------------------ the tensor's last slab
     for (uint32_t b = tid; b < BINS; b += SLAB_THREADS) {
@@ -521,10 +512,10 @@ __global__ __launch_bounds__(EMIT_THREADS) void k_dense_emit(const SelectArgs A)
     __shared__ uint32_t g_before, q_before, known_before;
     Slab s;
     if (!find_slab<EMIT_TILES>(A, s)) return;
-    const SegState *st = &A.segstate[s.part.j];
+    const SegState *st = &A.segstate[s.j];
     const uint32_t status = st->status;
     if (status != SEG_ACTIVE && status != SEG_ALL) return;
-    const PlanEntry pe = A.plan[s.part.j];
+    const PlanEntry pe = A.plan[s.j];
     const uint32_t lane = lane_id(), wave = uniform(threadIdx.x >> 6);
     const bool all = (status == SEG_ALL);
     // (density 1: everything is sent, at its own position)
@@ -556,17 +547,13 @@ __global__ __launch_bounds__(EMIT_THREADS) void k_dense_emit(const SelectArgs A)
         uint32_t g = max(s.tile0 * TILE, s.td.off) - s.td.off, q = 0;
         bool known = true;
         if (!all) {
-            const uint32_t j = s.part.j, spp = slabs_per_part<EMIT_TILES>(A, s.td), ptile0 = A.segtab[s.td.seg_first].tile0,
-                           ptiles = A.segtab[s.td.seg_first].ntiles;
-            const uint32_t me = s.part.sidx * spp + (s.tile0 - s.part.tile0) / EMIT_TILES;
-            uint2 *word = dense_word(A, s.tile0, j);
-            if (lane == 0) slab_publish<true>(word, me == 0 ? SLAB_SUM : SLAB_OWN, total & 0xFFFFu, total >> 16);
-            known = slab_look_back<true>(A, me, 0u, [&](uint32_t i) {
-                return dense_word(A, ptile0 + (i / spp) * ptiles + (i % spp) * EMIT_TILES, j);
-            }, g, q);
+            uint2 *word = dense_word(A, s.tile0, s.j);
+            if (lane == 0) slab_publish<true>(word, s.idx == 0 ? SLAB_SUM : SLAB_OWN, total & 0xFFFFu, total >> 16);
+            known = slab_look_back<true>(A, s.idx, 0u, [&](uint32_t i) { return dense_word(A, s.tlo + i * EMIT_TILES, s.j); },
+                                         g, q);
             if (lane == 0) {
-                if (me != 0) slab_publish<true>(word, known ? SLAB_SUM : SLAB_FAIL, g + (total & 0xFFFFu), q + (total >> 16));
-                if (known && me + 1 == slabs_of_tensor<EMIT_TILES>(A, s.td) &&
+                if (s.idx != 0) slab_publish<true>(word, known ? SLAB_SUM : SLAB_FAIL, g + (total & 0xFFFFu), q + (total >> 16));
+                if (known && s.idx + 1 == s.count &&
                     (g + (total & 0xFFFFu) + rT != pe.k || q + (total >> 16) < rT))
                     atomicAdd(&A.stats->internal_errors, 1ull);
             }
@@ -665,8 +652,8 @@ __global__ __launch_bounds__(EMIT_THREADS) void k_dense_emit(const SelectArgs A)
 void launch_dense(int op, const SelectArgs &a, void *stream, void *ev0, void *ev1)
 {
     hipStream_t st = (hipStream_t)stream;
-    const dim3 grid(a.nparts * a.slabs), block(SLAB_THREADS);
-    const dim3 egrid(a.nparts * a.slabs * (SLAB_TILES / EMIT_TILES)), eblock(EMIT_THREADS);
+    const dim3 grid(a.ndslabs), block(SLAB_THREADS);
+    const dim3 egrid(a.ndslabs * (SLAB_TILES / EMIT_TILES)), eblock(EMIT_THREADS);
     if (op == SEL_PULL_V) {
         launch_k(k_dense_refine<SEL_PULL_V, 1>, grid, block, st, ev0, nullptr, a);
         launch_k(k_dense_refine<SEL_PULL_V, 2>, grid, block, st, nullptr, nullptr, a);

@@ -88,7 +88,7 @@ struct TensorDesc {
     uint32_t big;        // n > SMALL_N
     uint32_t seg_first;  // first entry of this tensor in the segment table
     uint32_t nseg;       // segments (0: the tensor never goes segmented)
-    uint32_t pad;
+    uint32_t ds_first;   // its first entry in the table of dense slabs
     uint32_t grp_first;  // first entry of this tensor in the group table
     uint32_t ngrp;       // its join groups (>= 1)
     uint32_t cs_first;   // first entry of this tensor in the table of chain slabs
@@ -182,7 +182,6 @@ struct SelectArgs {
     SegState *segstate;
     uint32_t *segcnt;             // per part: candidates (bit 31: a tile of the part overflowed)
     uint32_t *grpcnt;             // per join group: the same, for the lists joined by groups
-    uint32_t *segstart;           // per part of a tensor that takes the chain and was collected again: where its list starts in ord
     const SegDesc *cslabs;        // chain slabs (sidx: the part they lie in), tensor after tensor
     uint2 *slabs_done;            // per chain slab: what it has published (slab_word)
     uint32_t ncslabs;
@@ -200,7 +199,8 @@ struct SelectArgs {
     uint32_t repair;              // the launch carries the re-collecting workgroups
     uint32_t spin_limit;          // polls before a waiting workgroup gives up
     uint32_t bgroup;              // parts looked after by one re-collecting workgroup
-    uint32_t slabs;               // dense request: slabs (runs of SLAB_TILES tiles) of the longest part
+    const uint32_t *dslabs;       // dense requests: the tensor of every slab (run of SLAB_TILES tiles of a tensor), tensor after tensor
+    uint32_t ndslabs;
 };
 
 // Host-callable launchers (defined next to the kernels).

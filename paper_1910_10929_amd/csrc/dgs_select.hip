@@ -943,7 +943,6 @@ __device__ __forceinline__ void recollect_part(const SelectArgs &A, uint32_t rol
     }
     if (tid == 0) {
         st_dev(&A.segcnt[part], min(c2, 0x7FFFFFFFu) | (c2 > part_cap ? 0x80000000u : 0u));
-        if (pe.seg) st_dev(&A.segstart[part], (sd.tile0 + j) * CAPT);
     }
     if (!arrive_last(&st->arrive[2], td.nseg, &P.bc)) return;
     tensor_select<OP>(A, td, pe, j, 1, true, true, 0u, false, 0xFFFFFFFFu, tau_new, tprev_new, 0xFFFFFFFFu, false,
@@ -1087,10 +1086,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const SelectArgs A)
                     const uint32_t v = P.S.h[b];
                     if (v) atomicAdd(&gh[b], v);
                 }
-                if (tid == 0) {
-                    st_dev(&A.segcnt[part], c2);
-                    st_dev(&A.segstart[part], (sd.tile0 + j) * CAPT);
-                }
+                if (tid == 0) st_dev(&A.segcnt[part], c2);
             }
         } else {
             uint2 *glist = plist;

@@ -83,3 +83,26 @@ def test_more_than_2_31_entries_on_one_side_of_the_threshold(kind):
     assert not row[0, :K].any() and (kind == "ties" or (row[0, K:] == 1.0).all())
     assert ctx.stats().internal_errors == 0
     ctx.close()
+
+
+def test_one_large_tensor_among_half_a_million_small_ones():
+    """The launches hold one workgroup per slab: (parts) x (slabs of the longest part) would be more
+    threads than a grid may have.  Against the selection by one workgroup per tensor."""
+    import torch
+    off = np.concatenate([[0], (1 << 28) + 4 * np.arange(524_300, dtype=np.uint64)]).astype(np.uint64)
+    n, rho = int(off[-1]), 0.3
+    outs = []
+    for mode in (dgs.SEG_AUTO, dgs.SEG_NEVER):
+        gen = torch.Generator(device="cuda:0")
+        gen.manual_seed(6)
+        ctx = dgs.Context(off, W=0)
+        ctx.set_option(dgs.OPT_SEGMENTED, mode)
+        K = ctx.nnz(rho)
+        idx, val = torch.zeros(K, dtype=torch.int32, device="cuda:0"), torch.zeros(K, device="cuda:0")
+        g, s = torch.randn(n, device="cuda:0", generator=gen), torch.zeros(n, device="cuda:0")
+        ctx.worker_step(g, s, 0.1, 0.5, rho, idx, val)
+        assert ctx.stats().internal_errors == 0
+        ctx.close()
+        outs.append((idx, val.view(torch.int32), s.view(torch.int32)))
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
