@@ -289,7 +289,8 @@ int dgs_server_pull_sent(dgs_ctx *ctx, const float *model, uint32_t worker_id, d
  * ascending; afterwards D_k == 0.  nnz is data dependent: the call waits for
  * the stream and writes the count to nnz_out (host).  If the count exceeds
  * `capacity`, nothing is modified, nnz_out still receives the count and
- * DGS_ECAPACITY is returned.
+ * DGS_ECAPACITY is returned.  While the stream is being captured: DGS_ENOTSUP, and nothing is
+ * recorded.
  */
 int dgs_server_pull_all(dgs_ctx *ctx, uint32_t worker_id, uint32_t *idx_out, float *val_out,
                         uint64_t capacity, uint64_t *nnz_out /*host*/);

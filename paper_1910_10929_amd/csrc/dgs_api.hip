@@ -306,18 +306,21 @@ void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out,
 
 int upload(dgs_ctx *c, void *dst, const void *src, size_t bytes);
 
+bool stream_capturing(const dgs_ctx *c)
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
+}
+
 // Returns the cache slot holding the plan for `density`, uploading it if new.  A slot used
 // while the stream was being captured is never evicted afterwards (the captured graph holds
 // its device address), and a plan that would have to be uploaded during capture is refused.
 int get_plan(dgs_ctx *c, double density, uint32_t *slot_out, uint64_t *K_out)
 {
     ++c->tick;
-    bool capturing = false;
-    if (!c->no_alloc) {
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(c->stream, &cs) == hipSuccess) capturing = (cs != hipStreamCaptureStatusNone);
-        else (void)hipGetLastError();
-    }
+    const bool capturing = !c->no_alloc && stream_capturing(c);
     for (uint32_t s = 0; s < NPLAN; ++s) {
         PlanSlot &p = c->plan_slot[s];
         if (p.valid && p.density == density && p.margin == c->margin_pct && p.seg_mode == c->seg_mode) {
@@ -1022,10 +1025,12 @@ namespace {
 
 // Every nonzero of `row` (model == nullptr) or of model - row.  Waits for the count, not for the
 // emission behind it, which the device itself drops if the count exceeds the capacity: the launch
-// does not wait for the host (35 us of idle GPU on 108M parameters).
+// does not wait for the host (35 us of idle GPU on 108M parameters).  A stream that is being captured
+// runs nothing: the event would not be waited for, and the count read would be an earlier call's.
 int pull_all(dgs_ctx *c, float *row, const float *model, uint32_t *idx_out, float *val_out, uint64_t capacity,
              uint64_t *nnz_out)
 {
+    if (stream_capturing(c)) return DGS_ENOTSUP;
     if (!c->counted && hipEventCreate(&c->counted) != hipSuccess) return DGS_EHIP;
     launch_pull_all(row, model, c->n, c->ntiles, c->tile_cnt, c->slots, (uint32_t *)c->heads, c->flag + 8, c->flag + 4,
                     c->host_total, capacity, idx_out, val_out, c->stream, c->counted);

@@ -9,6 +9,7 @@ extern "C" char __stop_emu_lds[] __attribute__((weak));
 namespace emu {
 
 int block_order = 0;
+hipStreamCaptureStatus capture_status = hipStreamCaptureStatusNone;
 
 // Minimal stack switch (System V x86-64): callee-saved registers on the old stack, stack
 // pointers exchanged.  (swapcontext would make a system call per switch.)

@@ -311,6 +311,10 @@ static void helpers_and_static(uint64_t seed)
     CHECK(dgs_server_push(c.c, nullptr, 0, wi.p, wv.p, K) == DGS_OK);
     CHECK(dgs_oracle_server_push(nullptr, row_ref.p, 1, L.n, wi.p, wv.p, K) == 0);
     CHECK(dgs_server_pull_all(c.c, 0, ai.p, av.p, 3, &k2) == DGS_ECAPACITY && k2 == K);
+    emu::capture_status = hipStreamCaptureStatusActive;       // (nothing may run, and there is no count to read)
+    CHECK(dgs_server_pull_all(c.c, 0, ai.p, av.p, L.n, &k2) == DGS_ENOTSUP);
+    emu::capture_status = hipStreamCaptureStatusNone;
+    expect_same_f(row.p, row_ref.p, L.n, "row after a refused pull_all");
     CHECK(dgs_server_pull_all(c.c, 0, ai.p, av.p, L.n, &k2) == DGS_OK);
     CHECK(dgs_oracle_server_pull_all(row_ref.p, L.n, bi.p, bv.p, L.n, &k1) == 0 && k1 == k2);
     expect_same(ai.p, av.p, bi.p, bv.p, k1);
@@ -482,6 +486,7 @@ int main(int argc, char **argv)
         CHECK(st2.repaired_tensors >= 1 && st2.fallback_tensors == 0);
         return 0;
     }
+    helpers_and_static(16);
     slab_counts<false>();
     slab_counts<true>();
     gives_up("dense emission gives up", 0.1, 0, 1, 40);
@@ -540,7 +545,6 @@ int main(int argc, char **argv)
         printed_form("printed server form", two, 0.002, 0.004, 6, def, 14);
         printed_form("printed server form, chain", two, 0.002, 0.004, 5, always, 15);
     }
-    helpers_and_static(16);
     puts("emulated kernels: all scenarios match the oracle");
     return 0;
 }

@@ -122,6 +122,37 @@ def test_an_unplanned_density_is_refused_during_capture(oracle):
     ctx.close()
 
 
+def test_the_pull_that_waits_for_its_count_is_refused_during_capture():
+    """dgs_server_pull_all hands its count to the host; under capture nothing runs, so the call is
+    refused, records nothing and leaves the next eager call its count."""
+    import torch
+    n, dev = 70_001, "cuda:0"
+    s = torch.cuda.Stream(device=dev)
+    with torch.cuda.stream(s):
+        ctx = dgs.Context(synth.layout_flat(n), W=1, device=dev, stream=s)
+        row = torch.zeros((1, n), device=dev)
+        ctx.server_attach(row)
+        idx, val = torch.zeros(n, dtype=torch.int32, device=dev), torch.zeros(n, device=dev)
+        row[0, ::1000] = 1.0
+        assert ctx.server_pull_all(0, idx, val, n) == 71
+        row[0, ::7] = 2.0
+        counter = torch.zeros(1, device=dev)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            counter += 1.0
+            with pytest.raises(dgs.DgsError) as e:
+                ctx.server_pull_all(0, idx, val, n)
+            assert e.value.code == dgs.DGS_ENOTSUP
+        for _ in range(3):
+            graph.replay()
+        s.synchronize()
+        assert counter.item() == 3.0 and int((row != 0).sum()) == (n + 6) // 7
+        assert ctx.server_pull_all(0, idx, val, n) == (n + 6) // 7
+        s.synchronize()
+        assert not row.any()
+    ctx.close()
+
+
 def test_worker_and_server_on_two_streams(oracle):
     """Two contexts on two streams of default priority: the worker's step t+1 is enqueued while
     the server still handles push / pull t; messages are double-buffered and ordered with
