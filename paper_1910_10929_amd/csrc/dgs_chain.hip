@@ -136,7 +136,7 @@ struct FinishShared {
     uint32_t rowsum[64];
     int res[6];
     uint32_t wtot[SEL_WAVES];
-    uint32_t g, q, T, rT, bc;
+    uint32_t g, q, limit, bc;
 };
 
 // RANK (blocks below A.ncslabs): the low key bits of the slab's entries that share the prefix.
@@ -232,7 +232,7 @@ __device__ __forceinline__ void emit_slab(const SelectArgs &A, uint32_t slab, co
         const bool known = slab_look_back<false>(A, slab, td.cs_first, [&](uint32_t i) { return &A.slabs_done[i]; }, g, q);
         if (lane == 0) {
             if (!head) slab_publish<false>(&A.slabs_done[slab], known ? SLAB_SUM : SLAB_FAIL, g + (all & 0xFFFFu), q + (all >> 16));
-            C.bc = known ? 1u : 0u;
+            C.limit = known ? pe.k : 0u;
             C.g = g;
             C.q = q;
             if (known && slab + 1 == td.cs_first + td.ncs &&                                        // the tensor's last slab
@@ -241,9 +241,9 @@ __device__ __forceinline__ void emit_slab(const SelectArgs &A, uint32_t slab, co
         }
     }
     __syncthreads();
-    if (C.bc == 0) return;
     uint32_t eq = C.q + (before >> 16);              // the tensor's ties seen so far: lowest index first, rT of them are taken
     uint32_t pos = C.g + (before & 0xFFFFu) + min(eq, rT);
+    const uint32_t limit = C.limit;
     auto send = [&](uint2 x, float was, bool valid) {             // up to 64 consecutive entries; all lanes call
         const uint32_t key = x.y & 0x7FFFFFFFu;
         bool f = valid && key > T;
@@ -255,7 +255,7 @@ __device__ __forceinline__ void emit_slab(const SelectArgs &A, uint32_t slab, co
         }
         const uint64_t mk = ballot64(f);
         const uint32_t p = pos + mbcnt64(mk);
-        if (f && p < pe.k) {
+        if (f && p < limit) {
             const float v = __uint_as_float(x.y);
             A.out_idx[pe.outoff + p] = x.x;
             A.out_val[pe.outoff + p] = v;

@@ -11,13 +11,40 @@ namespace dgs {
 // does every slab behind it; 0: nothing published yet.
 constexpr uint32_t SLAB_OWN = 1u, SLAB_SUM = 2u, SLAB_FAIL = 3u;
 
-struct SlabWord {
-    uint32_t kind, g, q;
-};
-
 // WIDE: two words, (g, kind) and (q, kind), for counts of any size: a dense request counts every
 // element of its tensor, up to 2^32 - 1 of them.  Otherwise one word with 31 bits for either count:
 // candidates, of which a tensor has fewer than n / 4.
+template <bool WIDE>
+struct SlabWord {
+    uint64_t w = 0;
+    __device__ __forceinline__ uint32_t kind() const { return (uint32_t)(w >> 62); }
+    __device__ __forceinline__ bool published() const { return w != 0; }
+    __device__ __forceinline__ uint32_t g() const { return (uint32_t)w & 0x7FFFFFFFu; }
+    __device__ __forceinline__ uint32_t q() const { return (uint32_t)(w >> 31) & 0x7FFFFFFFu; }
+    __device__ __forceinline__ void read(const uint2 *word)
+    {
+        const uint2 x = ld_dev(word);
+        w = ((uint64_t)x.y << 32) | x.x;
+    }
+};
+
+template <>
+struct SlabWord<true> {
+    uint32_t k = 0, above = 0, equal = 0;
+    __device__ __forceinline__ uint32_t kind() const { return k; }
+    __device__ __forceinline__ bool published() const { return k != 0; }
+    __device__ __forceinline__ uint32_t g() const { return above; }
+    __device__ __forceinline__ uint32_t q() const { return equal; }
+    // (two words of different kinds: the slab is between its two publications, read again)
+    __device__ __forceinline__ void read(const uint2 *word)
+    {
+        const uint2 a = ld_dev(word), b = ld_dev(word + 1);
+        k = (a.y == b.y) ? a.y : 0u;
+        above = a.x;
+        equal = b.x;
+    }
+};
+
 template <bool WIDE>
 __device__ __forceinline__ void slab_publish(uint2 *word, uint32_t kind, uint32_t g, uint32_t q)
 {
@@ -27,18 +54,6 @@ __device__ __forceinline__ void slab_publish(uint2 *word, uint32_t kind, uint32_
     } else {
         st_dev(word, make_uint2(g | (q << 31), (q >> 1) | (kind << 30)));
     }
-}
-
-// (Two words of different kinds: the slab is between its two publications, read again.)
-template <bool WIDE>
-__device__ __forceinline__ SlabWord slab_read(const uint2 *word)
-{
-    const uint2 a = ld_dev(word);
-    if (WIDE) {
-        const uint2 b = ld_dev(word + 1);
-        return SlabWord{a.y == b.y ? a.y : 0u, a.x, b.x};
-    }
-    return SlabWord{a.y >> 30, a.x & 0x7FFFFFFFu, (a.y << 2) >> 1 | a.x >> 31};
 }
 
 // Entries above / equal to the k-th key in the tensor's slabs [first, slab), by one wavefront
@@ -54,12 +69,12 @@ __device__ __forceinline__ bool slab_look_back(const SelectArgs &A, uint32_t sla
     g = q = 0;
     for (uint32_t hi = slab; hi > first;) {          // slabs [first, hi) are still to be added
         const bool in = hi - first > lane;
-        SlabWord w{0u, 0u, 0u};
+        SlabWord<WIDE> w;
         uint64_t have = 0, sums = 0;
         for (uint32_t spin = 0; spin < A.spin_limit; ++spin) {
-            if (in && w.kind == 0) w = slab_read<WIDE>(word_of(hi - 1u - lane));
-            have = ballot64(!in || w.kind != 0);
-            sums = ballot64(in && w.kind >= SLAB_SUM);
+            if (in && !w.published()) w.read(word_of(hi - 1u - lane));
+            have = ballot64(!in || w.published());
+            sums = ballot64(in && w.kind() >= SLAB_SUM);
             // everything up to the nearest running sum (or all 64) has been published
             const uint64_t upto = sums ? (((sums & (0ull - sums)) << 1) - 1ull) : ~0ull;
             if ((have & upto) == upto) break;
@@ -70,11 +85,10 @@ __device__ __forceinline__ bool slab_look_back(const SelectArgs &A, uint32_t sla
             if (lane == 0) atomicAdd(&A.stats->internal_errors, 1ull);
             return false;
         }
-        if ((ballot64(w.kind == SLAB_FAIL) & upto) != 0) return false;
         const uint32_t counts = 0u - (uint32_t)((upto >> lane) & 1u);      // (lanes beyond `first` hold 0)
-        g += wave_sum(w.g & counts);
-        q += wave_sum(w.q & counts);
-        if (sums) return true;
+        g += wave_sum(w.g() & counts);
+        q += wave_sum(w.q() & counts);
+        if (sums) return (ballot64(w.kind() == SLAB_FAIL) & upto) == 0;
         hi = (hi - first > 64u) ? hi - 64u : first;
     }
     return true;
