@@ -282,6 +282,105 @@ __device__ __forceinline__ void emit_slab(const SelectArgs &A, uint32_t slab, co
     }
 }
 
+// SEG_ZERO, both roles: there is nothing to rank, and the emission completes the message with the
+// tensor's z lowest-index zeros.  Candidate i of the tensor (in index order), at local index x, has x - i zeros below
+// it.  While fewer than z, everything up to x is sent, and its position is x; from then on it is z + i.
+// The candidates of a tile that begins with at least z zeros below it come from its list; a tile before
+// that is read element by element, and those are dealt out to the wavefronts one at a time.  Bound by
+// its loads and stores.  Pulls from an empty row / one with 0.9 k nonzeros, us: flat tensor of 1.2e6 at 1 %
+// 30 / 40, of 2^23 at 1 % 62 / 50, of 1e9 at 0.1 % 967 / 1030.  All tiles joined and all pairs written by one
+// workgroup: 30 / 54, 81 / 217, 3030 / 4500; joined by one per 4096 tiles, written by one: 20 / 42 (one launch
+// less), 72 / 236, 1160 / 3150.
+template <int OP, uint32_t THREADS>
+__device__ __forceinline__ void zero_slab(const SelectArgs &A, bool emit, uint32_t slab, const SegDesc &sd,
+                                          const TensorDesc &td, const PlanEntry &pe, SegState *st, FinishShared &C)
+{
+    constexpr uint32_t WAVES = THREADS / 64, CTPW = CSLAB_TILES / WAVES;
+    const uint32_t tid = threadIdx.x, lane = lane_id(), wave = uniform(tid >> 6), end = td.off + td.n;
+    if (!emit) {
+        if (tid == 0) slab_publish<false>(&A.slabs_done[slab], 0u, 0u, 0u);
+        if (arrive_last(&st->arrive[3], td.ncs, &C.bc) && tid == 0) st_dev(&st->ready, 1u);
+        return;
+    }
+    const uint32_t first = min(wave * CTPW, sd.ntiles), nt = min(CTPW, sd.ntiles - first), z = st->r2;
+    const WaveTiles w = wave_tiles(A, td, sd.tile0 + first, nt, false, sd.sidx);
+    const uint32_t upto = wave_incl_scan(w.n);
+    if (lane == 63) C.wtot[wave] = upto;
+    const bool ready = wait_word(&st->ready, A.spin_limit, &C.bc) != 0;
+    uint32_t i0 = 0, all = 0;
+#pragma unroll
+    for (uint32_t x = 0; x < WAVES; ++x) {
+        i0 += (x < wave) ? C.wtot[x] : 0u;
+        all += C.wtot[x];
+    }
+    if (wave == 0) {
+        const bool head = (slab == td.cs_first);
+        if (ready && lane == 0) slab_publish<false>(&A.slabs_done[slab], head ? SLAB_SUM : SLAB_OWN, all, 0u);
+        uint32_t g = 0, q = 0;
+        const bool known = ready && slab_look_back<false>(A, slab, td.cs_first, [&](uint32_t i) { return &A.slabs_done[i]; }, g, q);
+        if (lane == 0) {
+            if (!head || !known) slab_publish<false>(&A.slabs_done[slab], known ? SLAB_SUM : SLAB_FAIL, g + all, 0u);
+            C.limit = known ? pe.k : 0u;
+            C.g = g;
+            if (!ready || (known && slab + 1 == td.cs_first + td.ncs && g + all + z != pe.k))
+                atomicAdd(&A.stats->internal_errors, 1ull);
+        }
+    }
+    __syncthreads();
+    i0 += C.g;
+    const uint32_t limit = C.limit;
+    auto put = [&](uint32_t p, uint32_t ix, float v, float was) {
+        if (p >= limit) return;
+        A.out_idx[pe.outoff + p] = ix;
+        A.out_val[pe.outoff + p] = v;
+        if (!index_ok(A, ix)) return;
+        if (OP == SEL_WORKER) store_scattered(&A.state[ix], A.m * v);
+        else if (OP == SEL_PULL) store_scattered(&A.state[ix], 0.0f);
+        else store_scattered(&A.state[ix], was + v);
+    };
+    auto behind_the_run = [&](uint32_t base, uint32_t before) { return max(base, td.off) - td.off - before >= z; };
+    uint32_t *at = C.h;                              // candidates before every tile of the slab
+    if (lane < nt) at[first + lane] = i0 + upto - w.n;
+#pragma unroll 1
+    for (uint32_t i = 0; i < nt; ++i) {
+        const uint32_t n = tile_n(w, i);
+        if (n != 0 && behind_the_run((w.t0 + i) * TILE, i0)) {
+            const uint32_t start = (uint32_t)__builtin_amdgcn_readlane((int)w.start, (int)i);
+            for (uint32_t q = lane; q < n; q += 64) {
+                const uint2 e = tile_get(A, w, i, start, q);
+                put(z + i0 + q, e.x, __uint_as_float(e.y), (OP == SEL_PULL_V && e.x < A.n) ? A.state[e.x] : 0.0f);
+            }
+        }
+        i0 += n;
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (uint32_t i = wave; i < sd.ntiles; i += WAVES) {
+        const uint32_t base = (sd.tile0 + i) * TILE;
+        uint32_t before0 = at[i];
+        if (behind_the_run(base, before0)) break;
+        // 64 consecutive elements at a time (their pairs leave as whole lines), all loads in flight together
+        constexpr uint32_t ROWS = TILE / 64;
+        float was[ROWS], model[ROWS];
+#pragma unroll
+        for (uint32_t u = 0; u < ROWS; ++u) {
+            const uint32_t ix = min(max(base + u * 64 + lane, td.off), end - 1u);      // (one outside the tensor is not used)
+            was[u] = A.state[ix];
+            if (OP == SEL_PULL_V) model[u] = A.model[ix];
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < ROWS; ++u) {
+            const uint32_t ix = base + u * 64 + lane, local = ix - td.off;
+            const float v = (OP == SEL_PULL_V) ? model[u] - was[u] : was[u];
+            const bool in = ix >= td.off && ix < end, nonzero = in && (__float_as_uint(v) & 0x7FFFFFFFu) != 0;
+            const uint64_t m = ballot64(nonzero);
+            const uint32_t before = before0 + mbcnt64(m);
+            if (in && (nonzero || local - before < z)) put(nonzero ? min(local, z + before) : local, ix, v, was[u]);
+            before0 += (uint32_t)__popcll(m);
+        }
+    }
+}
+
 template <int OP, uint32_t THREADS>
 __global__ __launch_bounds__(THREADS) void k_list_finish(const SelectArgs A)
 {
@@ -293,9 +392,10 @@ __global__ __launch_bounds__(THREADS) void k_list_finish(const SelectArgs A)
     if (!pe.seg) return;
     SegState *st = &A.segstate[sd.j];
     const uint32_t status = st->status;
-    if (status != SEG_ACTIVE && status != SEG_LISTS) return;
+    if (status != SEG_ACTIVE && status != SEG_LISTS && status != SEG_ZERO) return;
     const TensorDesc td = A.tdesc[sd.j];
-    if (emit) emit_slab<OP, THREADS>(A, slab, sd, td, pe, st, status == SEG_LISTS, C);
+    if (__builtin_expect(status == SEG_ZERO, 0)) zero_slab<OP, THREADS>(A, emit, slab, sd, td, pe, st, C);
+    else if (emit) emit_slab<OP, THREADS>(A, slab, sd, td, pe, st, status == SEG_LISTS, C);
     else rank_slab<THREADS>(A, slab, sd, td, st, status == SEG_LISTS, C);
 }
 

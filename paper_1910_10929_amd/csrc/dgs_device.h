@@ -77,9 +77,10 @@ constexpr uint32_t SEG_MAX_PER_TENSOR = 512;       // parts per tensor whose lis
 //   SEG_ACTIVE    the chain kernels finish it (prefix of the k-th key known), reading the tiles' candidates
 //   SEG_LISTS     the same, reading the parts' lists (collected again after a failed prediction)
 //   SEG_ALL       dense request with k_j = n_j: the emission sends every element
+//   SEG_ZERO      fewer candidates than k, every nonzero among them: the chain emits them and the zeros
 //   SEG_PENDING   the prediction failed: the parts collect again with a fresh threshold
 //   SEG_FALLBACK  left to the dense single-workgroup selection
-enum SegStatus { SEG_IDLE = 0, SEG_DONE = 1, SEG_FALLBACK = 2, SEG_PENDING = 4, SEG_ALL = 6, SEG_ACTIVE = 8, SEG_LISTS = 10 };
+enum SegStatus { SEG_IDLE = 0, SEG_DONE = 1, SEG_FALLBACK = 2, SEG_PENDING = 4, SEG_ALL = 6, SEG_ACTIVE = 8, SEG_LISTS = 10, SEG_ZERO = 12 };
 enum SegMode { SEG_MODE_AUTO = 0, SEG_MODE_ALWAYS = 1, SEG_MODE_NEVER = 2 };
 
 struct TensorDesc {
@@ -116,7 +117,7 @@ struct SegDesc {
 struct SegState {        // per tensor, rewritten by every selection
     uint32_t status;     // SegStatus
     uint32_t pfx;        // key >> SEG_LOWBITS of the k-th entry (dense request: its leading bits so far)
-    uint32_t r2;         // its rank among the entries sharing that prefix
+    uint32_t r2;         // its rank among the entries sharing that prefix (SEG_ZERO: the zeros to add)
     uint32_t T;          // the k-th key
     uint32_t rT;         // how many of the entries equal to it are taken (lowest index first)
     uint32_t ready;      // 1: T and rT are in place (chain)
@@ -215,7 +216,7 @@ void launch_pick_dense(const TensorDesc *tdesc, const PlanEntry *plan, uint32_t 
 // fix-up, next hint; failed predictions are collected again inside the same launch).
 void launch_select(int op, const SelectArgs &a, void *stream, void *ev0, void *ev1);
 // Long candidate lists: the parts' window histograms, before the selection kernel, and what
-// remains behind it for tensors left SEG_ACTIVE / SEG_LISTS.
+// remains behind it for tensors left SEG_ACTIVE / SEG_LISTS / SEG_ZERO.
 void launch_window(const SelectArgs &a, void *stream, void *ev0);
 void launch_chain(int op, const SelectArgs &a, void *stream, void *ev0, void *ev1);
 // Dense request: exact k-th keys and emission, reading the tensors themselves.

@@ -696,7 +696,7 @@ __device__ __forceinline__ uint32_t trim_list(const SelectArgs &A, const Src &sr
 
 // What the workgroup that completes a tensor's candidate lists does with them (`round` 0: the
 // streaming pass's candidates, 1: re-collected with a fresh threshold).  Returns the tensor's
-// status: SEG_DONE, SEG_ACTIVE / SEG_LISTS (the chain kernels go on), or SEG_PENDING (round 0
+// status: SEG_DONE, SEG_ACTIVE / SEG_LISTS / SEG_ZERO (the chain kernels go on), or SEG_PENDING (round 0
 // only: collect again).
 //   multi: the lists are global lists of several units -- the tensor's parts (by_parts: counts
 //   in segcnt) or its join groups (counts in grpcnt) -- and are gathered here; otherwise the
@@ -758,17 +758,17 @@ __device__ __forceinline__ uint32_t tensor_select(const SelectArgs &A, const Ten
     if (status == 0 && zerofill) {
         // the message is completed with the tensor's lowest-index zeros
         early = true;
+        status = SEG_DONE;
         if (verdict && tid == 0) st_dev(verdict, 0x100u | (uint32_t)SEG_DONE);
         if (pe.seg && round == 0) {
-            // a nearly empty row: its few candidates are joined here
-            const uint32_t nt = (td.off + td.n - 1u) / TILE - tlo + 1u;
-            bool again;
-            const uint32_t cj = join_part(A, td, SegDesc{j, tlo, nt, 0u}, P, again,
-                                          [&](uint32_t pos, uint2 e) { put_entry(llist, glist, pos, e); });
-            if (cj != c && tid == 0) atomicAdd(&A.stats->internal_errors, 1ull);
-            wait_mem();
-            __syncthreads();
-            zero_fill_emit<OP>(SrcSplit{llist, glist}, c, td, pe, A, P.S.wsum);
+            // the candidates are still in their tiles, and the chain's emission goes through those anyway
+            status = SEG_ZERO;
+            if (tid == 0) {
+                SegState *st = &A.segstate[j];
+                st->r2 = pe.k - c;
+                st->T = st->rT = st->ready = 0;
+                atomicAdd(&A.stats->segmented_tensors, 1ull);
+            }
         } else if (multi) {
             zero_fill_emit<OP>(SrcParts{A.ord, P.pbase, P.pofs, nunits}, c, td, pe, A, P.S.wsum);
         } else if (pe.seg) {
@@ -784,7 +784,6 @@ __device__ __forceinline__ uint32_t tensor_select(const SelectArgs &A, const Ten
             A.tprev[j] = 0u;
         }
         if (tid == 0) atomicAdd(&A.stats->candidates, (unsigned long long)c);
-        status = SEG_DONE;
     } else if (!pe.seg && !ovf && c >= pe.k && c <= list_max && (!multi || have_pbase)) {
         early = true;
         if (verdict && tid == 0) st_dev(verdict, 0x100u | (uint32_t)SEG_DONE);

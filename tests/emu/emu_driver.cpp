@@ -502,6 +502,8 @@ int main(int argc, char **argv)
     const std::vector<float> steady = {1, 1, 1, 1};
     const std::vector<float> jumps = {1, 1, 1e3f, 1e3f, 1e-6f, 1e-6f, 1, 1};
 
+    worker_server("zero fill on the chain", two, 0.02, 0.03, 1.0f, 0.9f, false, {1, 1, 1}, 5, always, 43);
+    printed_form("zero fill on the chain, printed form", two, 0.002, 0.02, 3, always, 44);
     worker_server("ragged, predicted", ragged, 0.004, 0.004, 0.5f, 0.9f, false, steady, 0, def, 1);
     worker_server("scale jumps, residual mode (re-collection)", two, 0.002, 0.004, 1.0f, 0.0f, true, jumps, 0, def, 2);
     worker_server("scale jumps, chain for every large tensor", two, 0.002, 0.002, 1.0f, 0.0f, true, jumps, 0, always, 3);
