@@ -206,6 +206,7 @@ struct dgs_ctx {
     uint64_t tick = 0;
     // which density each hint set was produced for (0 = none yet)
     HostArr<double> hint_density;      // W + 1 entries; entry 0 = worker
+    HostArr<uint32_t> hint_calls;      // ... and how many calls have followed at that density
     bool no_alloc = false;             // tables go up as kernel arguments, nothing is allocated or copied
     // options
     bool force_exact = false, profile = false, validate = false;
@@ -246,6 +247,21 @@ struct ProfSlot {
     void launched() { if (ev0) ++c->prof[kind].used; }
 };
 
+// The rank a pull aims its next threshold at.  Sent entries vanish from the row, and any number of pushes
+// may lie between two pulls of a worker: about 2 k, or 2.5 k so that fewer predictions fail (a failure
+// costs an event 165 us) at the price of longer lists.  A failure is that of any tensor, the longer list
+// that of the largest, so 2.5 k is taken
+//   for layouts of at least PULL_WIDE_TENSORS tensors with lists (servers, us an event at 2 / 2.5 k: 8 equal
+//   tensors of 423 K at 0.2 % 37.7 / 33.0, 70 of 13M in all at 0.2 % 66.1 / 59.8, ResNet-50 shapes with 6
+//   workers at 0.17 % 95.0 / 77.6; 5 tensors 67.3 / 66.2, 4 875 / 940, 3 70.2 / 71.1, one of 300 K / 600 K /
+//   1e6 at 1 % 37.1 / 39.8, 55.8 / 64.4, 83.6 / 101);
+//   for tensors whose list then still fits the LDS of a workgroup, or which take the chain (ResNet-50
+//   shapes at 0.36 / 0.42 %, largest k 8500 / 9900: 125 / 132, 140 / 151);
+//   from the pull number PULL_YOUNG + 1 of a row at a density on: while a row fills up its thresholds rise
+//   and predictions seldom fail (32 workers on ResNet-50 shapes at 0.1 %, pull 2 of every worker 132 / 142,
+//   4 80 / 85, 7 to 10 73 / 76, 11 to 18 72 / 71, later 82 / 71).
+constexpr uint32_t PULL_WIDE_TENSORS = 8, PULL_YOUNG = 10;
+
 // k_j = ceil(density * n_j) in IEEE double; k2 = rank that sets the next predicted threshold.
 // Which tensors take the chain kernels behind the selection: those of at least SEG_MIN_N
 // elements whose hinted candidate list is longer than one workgroup selects from
@@ -260,7 +276,12 @@ void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out,
         // (a dense request on nothing but small tensors: one launch of one workgroup each, 24 us a step
         // where the five launches of the dense kernels take 53)
         bool large = false;
-        for (uint32_t j = 0; j < c->J; ++j) large |= c->offsets[j + 1] - c->offsets[j] >= SEG_MIN_N;
+        uint32_t listed = 0;               // tensors with candidate lists
+        for (uint32_t j = 0; j < c->J; ++j) {
+            const uint64_t nj = c->offsets[j + 1] - c->offsets[j];
+            large |= nj >= SEG_MIN_N;
+            listed += nj > SMALL_N ? 1u : 0u;
+        }
         for (uint32_t j = 0; j < c->J; ++j) {
             const uint64_t nj = c->offsets[j + 1] - c->offsets[j];
             uint64_t k = (uint64_t)std::ceil(density * (double)nj);
@@ -272,9 +293,8 @@ void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out,
             out[j].k2 = (uint32_t)k2;
             out[j].outoff = (uint32_t)K;
             uint64_t k2z = 2 * k + 4ull * isqrt_u32((uint32_t)k) + 16;
-            out[j].k2_pull = (uint32_t)std::min(k2z + k / 2, nj);
             k2z = std::min(k2z, nj);
-            out[j].k2_zero = (uint32_t)k2z;
+            out[j].k2_zero = out[j].k2_pull = (uint32_t)k2z;
             bool seg = false;
             if (c->seg_mode != SEG_MODE_NEVER) {
                 if (density > DENSE_DENSITY) seg = large;
@@ -298,6 +318,11 @@ void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out,
                 out[j].seg = 1u;
                 ++active;
             }
+        for (uint32_t j = 0; j < c->J && listed >= PULL_WIDE_TENSORS; ++j) {
+            const uint64_t nj = c->offsets[j + 1] - c->offsets[j];
+            const uint32_t wide = (uint32_t)std::min<uint64_t>((uint64_t)out[j].k2_zero + out[j].k / 2, nj);
+            if (out[j].seg || wide <= SEL_LDS_LIST) out[j].k2_pull = wide;
+        }
         *nseg_active = active;
         *K_out = K;
         *wire_words_out = words;
@@ -521,6 +546,9 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
     se.nparts = c->nseg_total;
     se.dense = dense_req ? 1u : 0u;
     se.write_hint = dense_req ? 0u : 1u;
+    if (c->hint_density[hint_set] != density) c->hint_calls[hint_set] = 0;
+    se.young = c->hint_calls[hint_set] < PULL_YOUNG ? 1u : 0u;
+    if (se.young && !dense_req) ++c->hint_calls[hint_set];
     se.exact_mode = exact ? 1u : 0u;
     se.repair = (c->repair_round && !dense_req) ? 1u : 0u;   // a dense request has no lists to collect again
     se.spin_limit = c->spin_limit;
@@ -729,6 +757,7 @@ int dgs_create(dgs_ctx **out, const uint64_t *offsets, uint32_t J, uint32_t W, v
     c->offsets.assign(offsets, offsets + J + 1);
     carve_workspace(c, workspace, L);
     c->hint_density.assign((size_t)W + 1, 0.0);
+    c->hint_calls.assign((size_t)W + 1, 0u);
 
     int dev = 0;
     hipDeviceProp_t prop;
@@ -908,6 +937,7 @@ int dgs_worker_step_static(const uint64_t *offsets, uint32_t J, const float *gra
     uint64_t offs[DGS_STATIC_MAX_TENSORS + 1];
     uint32_t nseg[DGS_STATIC_MAX_TENSORS];
     double hint_density[1] = {0.0};
+    uint32_t hint_calls[1] = {0};
     TensorDesc td[DGS_STATIC_MAX_TENSORS];
     uint32_t tau0[DGS_STATIC_MAX_TENSORS], toff[DGS_STATIC_MAX_TENSORS + 1];
     SegDesc segs[STATIC_MAX_SEGS + 1];
@@ -926,6 +956,7 @@ int dgs_worker_step_static(const uint64_t *offsets, uint32_t J, const float *gra
     c.offsets.borrow(offs);
     c.nseg.borrow(nseg);
     c.hint_density.borrow(hint_density);
+    c.hint_calls.borrow(hint_calls);
     c.plan_stage = plan;               // one density per call: only the first cache slot is used
     carve_workspace(&c, ws, L);
     fill_tables(&c, td, tau0, toff, segs, groups, slabs, dslabs);

@@ -100,7 +100,7 @@ struct PlanEntry {
     uint32_t k;       // ceil(density * n_j)
     uint32_t k2;      // rank whose key becomes the next predicted threshold (>= k, <= n_j)
     uint32_t outoff;  // sum of k over earlier tensors
-    uint32_t k2_pull; // same for a pull, whose sent entries vanish: about 2.5k (<= n_j)
+    uint32_t k2_pull; // same for a pull, whose sent entries vanish: 2k to 2.5k (<= n_j), see fill_plan
     uint32_t seg;     // 1: segmented selection at this density
     uint32_t wire_off;   // wire form: first 32-bit word of the tensor's index block (after the values)
     uint32_t wire_bits;  // wire form: bits per local index = bit length of n_j - 1 (>= 1)
@@ -196,6 +196,7 @@ struct SelectArgs {
     uint32_t dense;               // dense request: no candidate lists; tensors with parts take the chain
                                   // reading their own elements, the others select from the state buffer
     uint32_t write_hint;
+    uint32_t young;               // pull: one of the first on this row, which aim at rank k2_zero
     uint32_t exact_mode;          // the threshold came from this call's histogram
     uint32_t repair;              // the launch carries the re-collecting workgroups
     uint32_t spin_limit;          // polls before a waiting workgroup gives up

@@ -465,16 +465,13 @@ __device__ __forceinline__ void select_emit(const Src src, const uint32_t cN, co
 // widened by the ratio of the counts instead.
 template <int OP>
 __device__ __forceinline__ uint32_t hint_rank(const TensorDesc &td, const PlanEntry &pe, bool drift,
-                                              uint32_t c, uint32_t E, float m, uint32_t *Eq)
+                                              uint32_t c, uint32_t E, float m, uint32_t young, uint32_t *Eq)
 {
     *Eq = 0;
     // a pull, or a worker without momentum: sent entries vanish, so even with nothing new
     // before the next call k entries must remain above the hinted key: about 2k for the worker, whose
-    // steps follow each other; 2.5k for a pull, which follows the last one after any number of
-    // pushes (server of 32 workers on ResNet-50 shapes, us an event at 2 / 2.5 / 3 / 4 k: sent rows
-    // 72.0 / 67.2 / 72.1 / 82.5, difference rows 90.0 / 86.1 / 91.2 / 102: a failed prediction costs
-    // 165 us, a thousand more candidates 0.25 us)
-    uint32_t R = (OP != SEL_WORKER) ? pe.k2_pull : (m == 0.0f ? pe.k2_zero : pe.k2);
+    // steps follow each other, and for a pull what the plan and the age of the row say
+    uint32_t R = (OP != SEL_WORKER) ? (young ? pe.k2_zero : pe.k2_pull) : (m == 0.0f ? pe.k2_zero : pe.k2);
     if (OP == SEL_WORKER && drift && E != 0) {
         if (c >= E) {
             *Eq = E;

@@ -471,7 +471,7 @@ __device__ __forceinline__ uint32_t window_step(const SelectArgs &A, const Tenso
     const uint32_t win_base = seg_window_base(tau_cur, tprev_cur);
     const int bin_min = (win_base > (tau_cur >> SEG_LOWBITS)) ? 1 : 0;   // bin 0 mixes in lower keys
     uint32_t R = 0, Eq = 0;
-    if (A.write_hint) R = hint_rank<OP>(td, pe, !exact_mode, c, A.hint2[j], A.m, &Eq);
+    if (A.write_hint) R = hint_rank<OP>(td, pe, !exact_mode, c, A.hint2[j], A.m, A.young, &Eq);
     const bool measurable = (R != 0) && (c >= R);
     const uint32_t qlow = max(c / 4u, min(c, 16u));
     const uint32_t third = measurable ? Eq : ((R != 0 && c != 0) ? (c - qlow + 1u) : 0u);
@@ -527,7 +527,7 @@ __device__ __forceinline__ void dense_select(const SelectArgs &A, const TensorDe
 {
     const uint32_t tid = threadIdx.x;
     uint32_t R = 0, Eq = 0;
-    if (td.big && A.write_hint) R = hint_rank<OP>(td, pe, false, 0u, 0u, A.m, &Eq);
+    if (td.big && A.write_hint) R = hint_rank<OP>(td, pe, false, 0u, 0u, A.m, A.young, &Eq);
     uint32_t tau_next = 0, expect = 0, q_e = 0, t_k = 0;
     if (td.n <= 2 * SEL_LDS_LIST) {
         uint32_t *lv = (uint32_t *)llist;
@@ -567,7 +567,7 @@ __device__ __forceinline__ void list_select(const SelectArgs &A, const TensorDes
 {
     const uint32_t tid = threadIdx.x;
     uint32_t R = 0, Eq = 0;
-    if (A.write_hint) R = hint_rank<OP>(td, pe, !exact_mode, c, hint2_cur, A.m, &Eq);
+    if (A.write_hint) R = hint_rank<OP>(td, pe, !exact_mode, c, hint2_cur, A.m, A.young, &Eq);
     uint32_t tau_next = 0, expect = 0, q_e = 0, t_k = 0;
     // the window placed by the hints serves if no candidate lies below the threshold (none can);
     // a histogram counted on the way then stands as it is
