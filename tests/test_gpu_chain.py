@@ -1,7 +1,7 @@
-"""The chain for long candidate lists at the edges of its work split: tensors of one slab (128
-tiles) and one element more, a last slab of one tile, tensors that share tiles, tiles with more
-than 64 candidates, tie classes that cross slabs; and the form with half-sized workgroups, which
-takes over at 2048 slabs.  Bit for bit against the oracle, or against the single-workgroup
+"""The chain for long candidate lists at the edges of its work split: tensors that fill exactly one
+slab (128 tiles) and one element more, a last slab of one tile, tensors that share tiles, tiles with
+more than 64 candidates, tie classes that cross slabs, messages completed with zeros; and the form
+with half-sized workgroups, which takes over at 2048 slabs.  Bit for bit against the oracle, or against the single-workgroup
 selection where the oracle would take minutes."""
 import numpy as np
 import pytest
@@ -13,10 +13,23 @@ pytestmark = pytest.mark.gpu
 SIZES = [65_536, 3, 131_072, 131_073, 64 * 1024 + 1, 262_144 + 128 * 1024 + 1, 70_001]
 
 
+# tensors that start at a tile: slabs are full, or hold one element more (the 1023 fill the tile up)
+ALIGNED = [128 * 1024, 128 * 1024 + 1, 1023, 256 * 1024, 65_536, 129 * 1024]
+
+
 @pytest.mark.parametrize("kind", ["gaussian", "ties", "crowded"])
 @pytest.mark.parametrize("rho", [0.0005, 0.03])
 def test_chain_slab_edges(oracle, rho, kind):
-    off = synth.offsets_from_sizes(SIZES)
+    _edges(oracle, SIZES, rho, kind)
+
+
+@pytest.mark.parametrize("kind", ["gaussian", "ties"])
+def test_chain_full_slabs(oracle, kind):
+    _edges(oracle, ALIGNED, 0.01, kind)
+
+
+def _edges(oracle, sizes, rho, kind):
+    off = synth.offsets_from_sizes(sizes)
     n = int(off[-1])
     rng = np.random.default_rng(81)
     grads = [synth.gaussian(n, rng) for _ in range(4)]

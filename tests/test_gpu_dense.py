@@ -1,7 +1,8 @@
-"""Dense requests (density above 1/32) at the edges of the kernels that serve them: tensors of
-one workgroup's slab (16 tiles) and one element more, tensors on both sides of the small-tensor
-bound, odd offsets, tie classes that cross slabs, every server form.  Bit for bit against the
-oracle: each value is the result of one correctly rounded operation."""
+"""Dense requests (density above 1/32) at the edges of the kernels that serve them: tensors that fill
+exactly one slab of the refinement (32 tiles) or of the emission (16) and one element more, more
+slabs than one look back covers (64), tensors on both sides of the small-tensor bound, odd offsets,
+tie classes that cross slabs, every server form, counts beyond 2^31, layouts of very uneven tensors.
+Bit for bit against the oracle: each value is the result of one correctly rounded operation."""
 import numpy as np
 import pytest
 
@@ -14,11 +15,24 @@ pytestmark = pytest.mark.gpu
 SIZES = [1, 8192, 8193, 5, 16384, 16385, 262_144, 262_145, 1023, 300_001]
 
 
+# tensors that start at a tile: a slab is full, or holds one element more (the 1023 fill the tile up)
+ALIGNED = [16 * 1024, 32 * 1024, 16 * 1024 + 1, 1023, 32 * 1024 + 1, 1023, 64 * 1024, 1100 * 1024 + 5]
+
+
 @pytest.mark.parametrize("levels", [None, 3], ids=["gaussian", "ties"])
 @pytest.mark.parametrize("rho", [0.0313, 0.37, 1.0])
 def test_dense_rounds(oracle, rho, levels):
+    _rounds(oracle, SIZES, rho, levels)
+
+
+@pytest.mark.parametrize("levels", [None, 3], ids=["gaussian", "ties"])
+def test_dense_rounds_with_full_slabs(oracle, levels):
+    _rounds(oracle, ALIGNED, 0.37, levels)
+
+
+def _rounds(oracle, sizes, rho, levels):
     import torch
-    off = synth.offsets_from_sizes(SIZES)
+    off = synth.offsets_from_sizes(sizes)
     n = int(off[-1])
     rng = np.random.default_rng(91)
     ctx, ctx_sent = dgs.Context(off, W=1), dgs.Context(off, W=1)
