@@ -426,7 +426,8 @@ void launch_pull_all(float *row, const float *model, uint32_t n, uint32_t ntiles
                        st, row, model, n, ntiles, tile_cnt, slots);
     launch_k(k_pull_all_scan, dim3(nc), dim3(1024), st, nullptr, counted, tile_cnt, ntiles, tile_pos, chunk, nc, arrive,
              total, host_total);
-    if (capacity == 0) return;
+    // (no emission from positions that were not written: the caller reports the error)
+    if (hipPeekAtLastError() != hipSuccess || capacity == 0) return;
     constexpr uint32_t per = WAVES_PER_BLOCK * PULL_TPW;
     hipLaunchKernelGGL(k_pull_all_emit, dim3((ntiles + per - 1) / per), dim3(STREAM_THREADS), 0, st, row, model, n,
                        ntiles, tile_cnt, tile_pos, chunk + nc, slots, total, capacity, out_idx, out_val);

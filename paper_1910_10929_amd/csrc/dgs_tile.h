@@ -1,7 +1,7 @@
 // One tile (1024 consecutive elements) of the streaming pass, as one wavefront processes it:
 // loads, fused accumulate (Algorithm 3, "u <- m u + eta grad"), magnitude keys, and either
 // candidate collection against the per-tensor thresholds or the LDS histogram of the keys.
-// Shared by the full pass (k_stream) and the per-segment re-collection (k_seg_restream).
+// Used by k_stream.
 #pragma once
 #include "dgs_wave.h"
 

@@ -9,6 +9,8 @@ extern "C" char __stop_emu_lds[] __attribute__((weak));
 namespace emu {
 
 int block_order = 0;
+hipError_t last_error = hipSuccess;
+bool refuse_stamped = false;
 hipStreamCaptureStatus capture_status = hipStreamCaptureStatusNone;
 
 // Minimal stack switch (System V x86-64): callee-saved registers on the old stack, stack

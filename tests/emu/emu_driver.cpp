@@ -311,6 +311,10 @@ static void helpers_and_static(uint64_t seed)
     CHECK(dgs_server_push(c.c, nullptr, 0, wi.p, wv.p, K) == DGS_OK);
     CHECK(dgs_oracle_server_push(nullptr, row_ref.p, 1, L.n, wi.p, wv.p, K) == 0);
     CHECK(dgs_server_pull_all(c.c, 0, ai.p, av.p, 3, &k2) == DGS_ECAPACITY && k2 == K);
+    emu::refuse_stamped = true;         // (the launch that finds the positions is refused: nothing may be emitted)
+    CHECK(dgs_server_pull_all(c.c, 0, ai.p, av.p, L.n, &k2) == DGS_EHIP);
+    emu::refuse_stamped = false;
+    expect_same_f(row.p, row_ref.p, L.n, "row after a launch that failed");
     emu::capture_status = hipStreamCaptureStatusActive;       // (nothing may run, and there is no count to read)
     CHECK(dgs_server_pull_all(c.c, 0, ai.p, av.p, L.n, &k2) == DGS_ENOTSUP);
     emu::capture_status = hipStreamCaptureStatusNone;

@@ -59,8 +59,10 @@ static inline hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = mall
 static inline hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
 static inline hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 static inline hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int) { p->multiProcessorCount = 4; return hipSuccess; }
-static inline hipError_t hipGetLastError() { return hipSuccess; }
-static inline hipError_t hipEventCreate(hipEvent_t *e) { *e = nullptr; return hipSuccess; }
+namespace emu { extern hipError_t last_error; extern bool refuse_stamped; }      // launches that stamp an event fail
+static inline hipError_t hipPeekAtLastError() { return emu::last_error; }
+static inline hipError_t hipGetLastError() { const hipError_t e = emu::last_error; emu::last_error = hipSuccess; return e; }
+static inline hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t)(uintptr_t)1; return hipSuccess; }
 static inline hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 static inline hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 0.0f; return hipSuccess; }
 namespace emu { extern hipStreamCaptureStatus capture_status; }      // what the next question is answered with
@@ -168,5 +170,9 @@ template <class K, class... A>
 static inline void hipExtLaunchKernelGGL(K kernel, dim3 grid, dim3 block, size_t, hipStream_t, hipEvent_t, hipEvent_t, int,
                                          A... args)
 {
+    if (emu::refuse_stamped) {
+        emu::last_error = hipErrorUnknown;
+        return;
+    }
     emu::launch(grid, block, [=]() { kernel(args...); });
 }
