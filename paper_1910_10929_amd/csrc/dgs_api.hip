@@ -202,7 +202,7 @@ struct dgs_ctx {
     PlanSlot plan_slot[NPLAN];
     PlanEntry *plan_stage = nullptr;   // pinned host, NPLAN * J
     uint32_t *host_total = nullptr;    // pinned host, behind the staging area: the count of a pull without secondary compression
-    hipEvent_t counted = nullptr;      // ... and the event that says it is in place (from the first such pull on)
+    hipEvent_t counted = nullptr;      // ... and the event that says it is in place, made on the stream's device like the rest
     uint64_t tick = 0;
     // which density each hint set was produced for (0 = none yet)
     HostArr<double> hint_density;      // W + 1 entries; entry 0 = worker
@@ -804,6 +804,7 @@ int dgs_create(dgs_ctx **out, const uint64_t *offsets, uint32_t J, uint32_t W, v
     bool ok = true;
     ok = ok && upload(c, c->qlist, qlist.data(), qlist.size() * sizeof(uint32_t)) == DGS_OK;
     const size_t stage_bytes = align_up((size_t)NPLAN * J * sizeof(PlanEntry));
+    ok = ok && hipEventCreate(&c->counted) == hipSuccess;
     ok = ok && hipHostMalloc((void **)&c->plan_stage, stage_bytes + 64, hipHostMallocDefault) == hipSuccess;
     if (ok) c->host_total = (uint32_t *)((char *)c->plan_stage + stage_bytes);
     ok = ok && upload_tables(c, td.data(), tau0.data(), toff.data(), segs, groups, slabs, dslabs, tabs) == DGS_OK;
@@ -811,6 +812,7 @@ int dgs_create(dgs_ctx **out, const uint64_t *offsets, uint32_t J, uint32_t W, v
     ok = ok && hipGetLastError() == hipSuccess;
     if (!ok) {
         if (c->plan_stage) (void)hipHostFree(c->plan_stage);
+        if (c->counted) (void)hipEventDestroy(c->counted);
         delete c;
         return DGS_EHIP;
     }
@@ -1062,7 +1064,6 @@ int pull_all(dgs_ctx *c, float *row, const float *model, uint32_t *idx_out, floa
              uint64_t *nnz_out)
 {
     if (stream_capturing(c)) return DGS_ENOTSUP;
-    if (!c->counted && hipEventCreate(&c->counted) != hipSuccess) return DGS_EHIP;
     launch_pull_all(row, model, c->n, c->ntiles, c->tile_cnt, c->slots, (uint32_t *)c->heads, c->flag + 8, c->flag + 4,
                     c->host_total, capacity, idx_out, val_out, c->stream, c->counted);
     if (hipGetLastError() != hipSuccess) return DGS_EHIP;

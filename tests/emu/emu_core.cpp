@@ -9,6 +9,7 @@ extern "C" char __stop_emu_lds[] __attribute__((weak));
 namespace emu {
 
 int block_order = 0;
+int current_device = 0;
 hipError_t last_error = hipSuccess;
 bool refuse_stamped = false;
 hipStreamCaptureStatus capture_status = hipStreamCaptureStatusNone;

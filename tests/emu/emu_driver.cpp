@@ -310,7 +310,9 @@ static void helpers_and_static(uint64_t seed)
     CHECK(dgs_server_attach(c.c, row.p) == DGS_OK);
     CHECK(dgs_server_push(c.c, nullptr, 0, wi.p, wv.p, K) == DGS_OK);
     CHECK(dgs_oracle_server_push(nullptr, row_ref.p, 1, L.n, wi.p, wv.p, K) == 0);
+    emu::current_device = 1;            // (the caller may have turned to another device since it made the context)
     CHECK(dgs_server_pull_all(c.c, 0, ai.p, av.p, 3, &k2) == DGS_ECAPACITY && k2 == K);
+    emu::current_device = 0;
     emu::refuse_stamped = true;         // (the launch that finds the positions is refused: nothing may be emitted)
     CHECK(dgs_server_pull_all(c.c, 0, ai.p, av.p, L.n, &k2) == DGS_EHIP);
     emu::refuse_stamped = false;

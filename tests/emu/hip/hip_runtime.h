@@ -57,12 +57,15 @@ static inline hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMem
 static inline hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 static inline hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = malloc(n ? n : 1); return *p ? hipSuccess : hipErrorUnknown; }
 static inline hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
-static inline hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+// Two devices, as far as events go: streams belong to device 0, an event to the device that is current
+// when it is created, and a launch that stamps an event of the other device fails.
+namespace emu { extern int current_device; }
+static inline hipError_t hipGetDevice(int *d) { *d = emu::current_device; return hipSuccess; }
 static inline hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int) { p->multiProcessorCount = 4; return hipSuccess; }
 namespace emu { extern hipError_t last_error; extern bool refuse_stamped; }      // launches that stamp an event fail
 static inline hipError_t hipPeekAtLastError() { return emu::last_error; }
 static inline hipError_t hipGetLastError() { const hipError_t e = emu::last_error; emu::last_error = hipSuccess; return e; }
-static inline hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t)(uintptr_t)1; return hipSuccess; }
+static inline hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t)(uintptr_t)(1 + emu::current_device); return hipSuccess; }
 static inline hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 static inline hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 0.0f; return hipSuccess; }
 namespace emu { extern hipStreamCaptureStatus capture_status; }      // what the next question is answered with
@@ -167,10 +170,10 @@ static inline void hipLaunchKernelGGL(K kernel, dim3 grid, dim3 block, size_t, h
     emu::launch(grid, block, [=]() { kernel(args...); });
 }
 template <class K, class... A>
-static inline void hipExtLaunchKernelGGL(K kernel, dim3 grid, dim3 block, size_t, hipStream_t, hipEvent_t, hipEvent_t, int,
+static inline void hipExtLaunchKernelGGL(K kernel, dim3 grid, dim3 block, size_t, hipStream_t, hipEvent_t e0, hipEvent_t e1, int,
                                          A... args)
 {
-    if (emu::refuse_stamped) {
+    if (emu::refuse_stamped || (uintptr_t)e0 > 1u || (uintptr_t)e1 > 1u) {
         emu::last_error = hipErrorUnknown;
         return;
     }
