@@ -184,7 +184,7 @@ int dgs_nnz(const dgs_ctx *ctx, double density, uint64_t *K_out /*host*/);
  * Both buffers given (separate momentum and residual, as in momentum-corrected
  * schemes) is not part of this method: DGS_ENOTSUP.
  *
- * Buffers must be 4-byte aligned; 16-byte alignment gives the fast path.
+ * Buffers must be 4-byte aligned; more alignment is not needed for speed.
  *
  * Graph capture.  Once a call at `density` has been made eagerly on this context (the
  * launch plan of a density is uploaded on its first use, and the first call of a stream

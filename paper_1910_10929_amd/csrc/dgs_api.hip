@@ -265,16 +265,18 @@ constexpr uint32_t PULL_WIDE_TENSORS = 8, PULL_YOUNG = 10;
 // k_j = ceil(density * n_j) in IEEE double; k2 = rank that sets the next predicted threshold.
 // Which tensors take the chain kernels behind the selection: those of at least SEG_MIN_N
 // elements whose hinted candidate list is longer than one workgroup selects from
-// (SEL_LIST_MAX), and then also those beyond SEL_LIST_CROWDED.  For a dense request `seg` means the kernels that read the tensors themselves
-// (launch_dense): all of them if one is that large, unless the option forbids it.
+// (SEL_LIST_MAX), and then also those beyond SEL_LIST_CROWDED.  For a dense request `seg` means
+// the kernels that read the tensors themselves (launch_dense): all tensors if one is that large,
+// unless the option forbids it.
 void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out, uint64_t *K_out,
                uint32_t *nseg_active, uint64_t *wire_words_out)
 {
     {
         uint64_t K = 0, words = 0;
         uint32_t active = 0;
-        // (a dense request on nothing but small tensors: one launch of one workgroup each, 24 us a step
-        // where the five launches of the dense kernels take 53)
+        // A dense request on nothing but small tensors is one launch of one workgroup each.  us a step, so / by the
+        // five launches of the dense kernels: 35 tensors of 1811 elements 15 / 42, 300 of 20 K 73-85 / 86-100, 30 of
+        // 60 K 98-123 / 56-66, 1000 of 60 K 591 / 381: the largest tensor decides, between 20 K and 60 K elements.
         bool large = false;
         uint32_t listed = 0;               // tensors with candidate lists
         for (uint32_t j = 0; j < c->J; ++j) {

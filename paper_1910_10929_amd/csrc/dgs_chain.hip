@@ -3,8 +3,8 @@
 // 16 tiles at a time, all of their first 64 candidates in flight together, and the work is cut into
 // slabs of CSLAB_TILES tiles, so that it fills the chip for any number of tensors.  Joining the
 // candidates into one ordered list first, one workgroup per 4096 tiles, was bound by that
-// workgroup: 92 us of a call on ResNet-50 shapes at 1 % without momentum (now 10 for the window
-// and 23 for the finish), 232 us at 1 % of 1e9 parameters.  At that size each pass reads 240 MB of
+// workgroup: 92 us of a call on ResNet-50 shapes at 1 % without momentum (now 10.6 for the window
+// and 16 for the finish), 232 us at 1 % of 1e9 parameters.  At that size each pass reads 240 MB of
 // candidates and the emission is bound by its scattered 4-byte stores (1e7 of them: 420 us).
 //   window  (before the selection kernel) per part: window histogram of the candidates, in a slot
 //           of its own -- no atomics between workgroups; the selection kernel adds a tensor's
@@ -16,7 +16,8 @@
 //           Algorithms 1-3) and the state fix-up (Eq. 12 / Eq. 6).  Ties need no list and no case
 //           of their own.  Waiting is for blocks with lower indices only, and bounded.
 // A tensor whose prediction failed was collected again into one list per part by the selection
-// kernel (SEG_LISTS); its slabs then take equal shares of those lists in place of their tiles.
+// kernel (SEG_LISTS); its slabs then take equal shares of those lists in place of their tiles.  A tensor
+// with fewer nonzeros than k (SEG_ZERO) has its message completed with zeros by the finish kernel.
 // Dense requests have no candidates; their passes over the tensors themselves are at the end of
 // this file.
 #include "dgs_slab.h"
@@ -420,9 +421,11 @@ void launch_chain(int op, const SelectArgs &a, void *stream, void *ev0, void *ev
     if (a.ncslabs == 0) return;
     // While all slabs run at once (or nearly so) the depth of a workgroup counts: 8 tiles per wavefront.
     // Many rounds of workgroups are better served by twice as many workgroups per compute unit with 16
-    // tiles per wavefront.  Rounds with 1024 / 512 threads: ResNet-50 shapes without momentum at 1 %
-    // (about 260 slabs) 110 / 114 us, transformer shapes (about 900) 394 / 408 us, 1e9 parameters
-    // (7.8 K) at 1 % 5596 / 5338 us.
+    // tiles per wavefront.  Rounds with 1024 / 512 threads, us: ResNet-50 shapes without momentum at 1 %
+    // (about 260 slabs) 110 / 114, transformer shapes (about 900) 394 / 408; one flat tensor at 0.3 / 1 %
+    // with 990 slabs 678 / 694 and 842 / 871, 1530 954 / 942 and 1199 / 1208, 1980 1206 / 1212 and 1554 / 1579,
+    // 3050 1796 / 1781 and 2365 / 2375; 25 equal tensors with 1530 830 / 775 and 1080 / 1047, 3050 1655 / 1535 and
+    // 2209 / 2131; 1e9 parameters (7.8 K) at 1 % 5596 / 5338.
     if (a.ncslabs < 2048u) launch_finish<1024>(op, a, st, ev0, ev1);
     else launch_finish<512>(op, a, st, ev0, ev1);
 }
@@ -446,7 +449,8 @@ void launch_chain(int op, const SelectArgs &a, void *stream, void *ev0, void *ev
 // add the slabs' counters up: 256 bins keep those at 200 per slab of 32 tiles (2048 bins per slab
 // of 16 tiles: 400 K on 25.6M parameters, 56 instead of 41 us).  ResNet-50 shapes at density 0.1:
 // one workgroup per part (256 tiles and more, element by element) took 1070 + 72 + 361 us for a
-// worker step, these three 41 + 37 + 80 us.
+// worker step; these three 41 + 37 + 80 us on a grid of (parts) x (slabs of the longest part), mostly
+// empty workgroups on such a layout, and 32 + 29 + 67 us with one workgroup per slab.
 
 constexpr uint32_t SLAB_WAVES = SLAB_THREADS / 64;
 constexpr uint32_t TPW = 4;                              // consecutive tiles of one wavefront

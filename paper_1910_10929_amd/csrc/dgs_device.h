@@ -35,7 +35,11 @@ constexpr uint32_t HSHIFT = 31 - HBITS;
 constexpr uint32_t SEL_THREADS = 1024;
 constexpr uint32_t SEL_WAVES = SEL_THREADS / 64;
 constexpr uint32_t SEL_LDS_LIST = 16384;           // candidates kept in LDS (128 KB); longer lists continue in global scratch
-constexpr uint32_t SEL_LIST_MAX = 20480;           // longest candidate list one workgroup is planned for
+// Longest candidate list one workgroup is planned for (rank 2 k).  One workgroup / the chain, us: flat tensors
+// of 700 K / 900 K / 1.05M / 1.2M elements at 1 % (lists of 14 / 18 / 21 / 24 K), a round 75.5 / 82.6, 91.3 / 83.5,
+// 105 / 84, 124 / 89, a step without momentum 43 / 40, 57 / 41, 63 / 39, 76 / 43; ResNet-50 shapes at 0.36 / 0.39 /
+// 0.45 % (17 / 18 / 21 K), a round 172 / 186, 178 / 177, 194 / 181, a step 108 / 104, 112 / 95, 119 / 97.
+constexpr uint32_t SEL_LIST_MAX = 20480;
 // ... and where the plan holds a tensor beyond that, so that the chain's launches are there anyway,
 // for tensors of at least SEL_CROWDED_TILES tiles (their join is then what the launch waits for).
 constexpr uint32_t SEL_LIST_CROWDED = 8192, SEL_CROWDED_TILES = 512;
@@ -59,7 +63,6 @@ constexpr uint32_t SEG_TILES = DGS_SEG_TILES;
 #endif
 constexpr uint32_t GROUP_TILES = DGS_GROUP_TILES;
 constexpr uint32_t SEG_MIN_N = 65536;              // smaller tensors never take the chain
-constexpr uint32_t SEG_AUTO_N = 1u << 22;          // (kept for the plan: tensors this large always may)
 constexpr uint32_t SEG_LOWBITS = 12;               // key bits resolved by the second level
 constexpr uint32_t SEG_WBINS = 2048;               // window of key >> SEG_LOWBITS above the threshold
 constexpr uint32_t SEG_LBINS = 1u << SEG_LOWBITS;
@@ -184,7 +187,7 @@ struct SelectArgs {
     uint32_t *segcnt;             // per part: candidates (bit 31: a tile of the part overflowed)
     uint32_t *grpcnt;             // per join group: the same, for the lists joined by groups
     const SegDesc *cslabs;        // chain slabs (sidx: the part they lie in), tensor after tensor
-    uint2 *slabs_done;            // per chain slab: what it has published (slab_word)
+    uint2 *slabs_done;            // per chain slab: what it has published (slab_publish)
     uint32_t ncslabs;
     uint32_t *out_idx;
     float *out_val;

@@ -423,8 +423,8 @@ __device__ __forceinline__ uint32_t dense_compact(const SelectArgs &A, const Ten
 }
 
 // A tensor that takes the chain: its window histogram (c candidates in all; the sum of its parts'
-// own, or, collected again, the one the parts have added to in ghist) -> the 19-bit prefix of the k-th key, its rank among the entries sharing
-// it, and the next hint.  Returns the tensor's status (SEG_ACTIVE / SEG_LISTS, or 0 = failed);
+// own, or, collected again, the one the parts have added to in ghist) -> the 19-bit prefix of the
+// k-th key, its rank among the entries sharing it, and the next hint.  Returns the tensor's status (SEG_ACTIVE / SEG_LISTS, or 0 = failed);
 // thread 0 writes segstate / hints.
 template <int OP>
 __device__ __forceinline__ uint32_t window_step(const SelectArgs &A, const TensorDesc &td, const PlanEntry &pe,

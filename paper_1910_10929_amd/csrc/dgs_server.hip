@@ -247,7 +247,7 @@ void launch_put_words(uint32_t *dst, const uint32_t *src_host, size_t words, voi
 //        finish adds the chunks up and hands the total to the host
 // emit   copies the lists to their place and settles the row; only a tile that outgrew its slots
 //        is read again.  Does nothing if the total exceeds the caller's capacity.
-// 108M parameters, 2 % nonzero: 78 + 6 + 74 us, the emission bound by its scattered 4-byte stores
+// 108M parameters, 2 % nonzero: 78 + 7 + 73 us, the emission bound by its scattered 4-byte stores
 // (element-wise loads in both passes and a scan by one workgroup: 118 + 189 + 135 us, and 35 us in
 // which the GPU waited for the host to see the count).
 
