@@ -438,10 +438,11 @@ void launch_chain(int op, const SelectArgs &a, void *stream, void *ev0, void *ev
 // accumulate pass has counted bits [30:19] of every key of the big tensors and k_pick_dense has
 // found the bucket that holds the k-th one; then, one workgroup per slab of SLAB_TILES tiles of a
 // tensor (a small tensor is one slab, and that workgroup counts its leading bits too),
-//   refine 1  counts bits [18:11] of the keys in that bucket; the slab arriving last for a tensor
-//             ranks: 20 leading bits of the k-th key
-//   refine 2  counts the low 11 bits of the keys that share them; the slab arriving last ranks:
-//             the exact key, and how many of the entries equal to it are taken
+//   refine 1  counts bits [18:11] of the keys in that bucket and writes those keys down, slab by slab;
+//             the slab arriving last for a tensor ranks: 20 leading bits of the k-th key
+//   refine 2  counts the low 11 bits of the keys that share them, among the keys written down (a slab
+//             with too many of them reads its elements again); the slab arriving last ranks: the exact
+//             key, and how many of the entries equal to it are taken
 //   emit      counts its winners, adds up what the slabs before it have published (the chain's
 //             look-back), ordered emission and state fix-up.  Ties need no case of their own.
 // Each pass is bound by memory (4 B/param, mostly from the last-level cache up to a few 1e7
@@ -450,7 +451,9 @@ void launch_chain(int op, const SelectArgs &a, void *stream, void *ev0, void *ev
 // of 16 tiles: 400 K on 25.6M parameters, 56 instead of 41 us).  ResNet-50 shapes at density 0.1:
 // one workgroup per part (256 tiles and more, element by element) took 1070 + 72 + 361 us for a
 // worker step; these three 41 + 37 + 80 us on a grid of (parts) x (slabs of the longest part), mostly
-// empty workgroups on such a layout, and 32 + 29 + 67 us with one workgroup per slab.
+// empty workgroups on such a layout, 32 + 28 + 66 us with one workgroup per slab, and 33 + 13 + 57 us since
+// refine 2 goes through the keys that refine 1 has written down (1.6 % of the elements; writing them costs
+// refine 1 what holding two tiles a wavefront instead of four gains it) and the emission has 128 registers.
 
 constexpr uint32_t SLAB_WAVES = SLAB_THREADS / 64;
 constexpr uint32_t TPW = 4;                              // consecutive tiles of one wavefront
@@ -491,17 +494,39 @@ __device__ __forceinline__ uint2 *dense_word(const SelectArgs &A, uint32_t tile0
     return A.ord + (size_t)(tile0 + j) * CAPT;
 }
 
-// This wavefront's tiles of the slab, 16 values per lane and tile; bit 4 r + x of in[i] says that
-// value x of row r belongs to the tensor.  All loads are in flight together.
-template <int OP>
-__device__ __forceinline__ void load_slab(const SelectArgs &A, const Slab &s, uint32_t (&bits)[TPW][4][4],
-                                          uint32_t (&in)[TPW])
+// The keys that refine 1 hands to refine 2: a stretch of its own for every wavefront that has tiles, in the
+// scratch of the slab's first half (the second half begins with a word of the emission), behind one count
+// each.  The bucket of 1/16 octave around the k-th key of a Gaussian tensor holds 2 % of its elements at
+// density 0.1; there is room for a quarter of a wavefront's (an eighth where its slab has more than 16 tiles).
+constexpr uint32_t KEYS_AT = 16;
+static_assert(KEYS_AT >= 4 + SLAB_WAVES, "two words of the emission and the counts");
+struct SlabKeys {
+    uint32_t *count;          // per wavefront
+    uint32_t *mine;           // this wavefront's keys
+    uint32_t waves, room;     // wavefronts that have tiles, keys of one of them
+};
+__device__ __forceinline__ SlabKeys slab_keys(const SelectArgs &A, const Slab &s)
+{
+    uint32_t *words = (uint32_t *)dense_word(A, s.tile0, s.j);
+    SlabKeys k;
+    k.count = words + KEYS_AT - SLAB_WAVES;
+    k.waves = (s.ntiles + TPW - 1u) / TPW;
+    k.room = (min(s.ntiles, EMIT_TILES) * (2u * CAPT) - KEYS_AT) / k.waves;
+    k.mine = words + KEYS_AT + (threadIdx.x >> 6) * k.room;
+    return k;
+}
+
+// NT of this wavefront's tiles of the slab, from its tile `first` on, 16 values per lane and tile; bit 4 r + x
+// of in[i] says that value x of row r belongs to the tensor.  All loads are in flight together.
+template <int OP, uint32_t NT>
+__device__ __forceinline__ void load_slab(const SelectArgs &A, const Slab &s, uint32_t first, uint32_t (&bits)[NT][4][4],
+                                          uint32_t (&in)[NT])
 {
     const uint32_t lane = lane_id(), wave = uniform(threadIdx.x >> 6);
     const uint32_t lo = s.td.off, hi = s.td.off + s.td.n;
 #pragma unroll
-    for (uint32_t i = 0; i < TPW; ++i) {
-        const uint32_t ti = wave * TPW + i;
+    for (uint32_t i = 0; i < NT; ++i) {
+        const uint32_t ti = wave * TPW + first + i;
         in[i] = 0;
         if (ti >= s.ntiles) {
 #pragma unroll
@@ -516,8 +541,28 @@ __device__ __forceinline__ void load_slab(const SelectArgs &A, const Slab &s, ui
     }
 }
 
+// f(key, belongs) for every element of this wavefront's tiles, 64 at a time (all lanes call), in any order.
+// Two tiles at a time: a kernel that holds all four needs 82 registers and leaves two workgroups on a
+// compute unit, for 800 of them on ResNet-50 shapes one full round and a half.
+template <int OP, class F>
+__device__ __forceinline__ void each_key(const SelectArgs &A, const Slab &s, F f)
+{
+    constexpr uint32_t NT = 2;
+#pragma unroll 1
+    for (uint32_t first = 0; first < TPW; first += NT) {
+        uint32_t bits[NT][4][4], in[NT];
+        load_slab<OP, NT>(A, s, first, bits, in);
+#pragma unroll
+        for (uint32_t i = 0; i < NT; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int x = 0; x < 4; ++x) f(bits[i][r][x] & 0x7FFFFFFFu, ((in[i] >> (4 * r + x)) & 1u) != 0);
+    }
+}
+
 template <int OP, int LEVEL>
-__global__ __launch_bounds__(SLAB_THREADS) void k_dense_refine(const SelectArgs A)
+__global__ __launch_bounds__(SLAB_THREADS, 8) void k_dense_refine(const SelectArgs A)
 {
     constexpr uint32_t BINS = (LEVEL == 1) ? REF1_BINS : REF2_BINS;
     constexpr uint32_t SHIFT = (LEVEL == 1) ? HSHIFT : REF1_SHIFT;       // the prefix known so far
@@ -539,41 +584,57 @@ __global__ __launch_bounds__(SLAB_THREADS) void k_dense_refine(const SelectArgs 
         return;
     }
     uint32_t pfx = st->pfx, r2 = st->r2;
-    uint32_t bits[TPW][4][4], in[TPW];
-    load_slab<OP>(A, s, bits, in);
-    if (leading) {
-        for (uint32_t b = tid; b < HBINS; b += SLAB_THREADS) h[b] = 0;
-        __syncthreads();
-#pragma unroll
-        for (uint32_t i = 0; i < TPW; ++i)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int x = 0; x < 4; ++x)
-                    if ((in[i] >> (4 * r + x)) & 1u) atomicAdd(&h[(bits[i][r][x] & 0x7FFFFFFFu) >> HSHIFT], 1u);
-        find_ranks<(int)HBINS, (int)SLAB_WAVES>(h, k, 0u, 0u, rowsum, res);
-        pfx = (uint32_t)res[0];
-        r2 = (uint32_t)res[1];
-        __syncthreads();
-    }
-    for (uint32_t b = tid; b < BINS; b += SLAB_THREADS) h[b] = 0;
-    __syncthreads();
-#pragma unroll
-    for (uint32_t i = 0; i < TPW; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int x = 0; x < 4; ++x)
-                if (((in[i] >> (4 * r + x)) & 1u) && ((bits[i][r][x] & 0x7FFFFFFFu) >> SHIFT) == pfx)
-                    atomicAdd(&h[(bits[i][r][x] >> LOW) & (BINS - 1u)], 1u);
     uint32_t *g = A.ghist + (size_t)j * HBINS;
+    const SlabKeys keys = slab_keys(A, s);
+    const uint32_t wave = uniform(tid >> 6);
+    bool from_keys = (LEVEL == 2);
+    if (LEVEL == 2)
+        for (uint32_t w = 0; w < keys.waves; ++w) from_keys &= keys.count[w] <= keys.room;
+    if (from_keys) {
+        // one in 256 of them shares the prefix, a few per slab: counted where the slabs' counters are
+        // added up (28 us when the tensors were read again, 15 through counters in LDS, 13)
+        const uint32_t listed = (wave < keys.waves) ? keys.count[wave] : 0u;
+        for (uint32_t q = lane_id(); q < listed; q += 64) {
+            const uint32_t key = keys.mine[q];
+            if ((key >> SHIFT) == pfx) atomicAdd(&g[key & (BINS - 1u)], 1u);
+        }
+    } else {
+        for (uint32_t b = tid; b < (LEVEL == 1 ? HBINS : BINS); b += SLAB_THREADS) h[b] = 0;
+        __syncthreads();
+        if (leading) {
+            each_key<OP>(A, s, [&](uint32_t key, bool in) {
+                if (in) atomicAdd(&h[key >> HSHIFT], 1u);
+            });
+            find_ranks<(int)HBINS, (int)SLAB_WAVES>(h, k, 0u, 0u, rowsum, res);
+            pfx = (uint32_t)res[0];
+            r2 = (uint32_t)res[1];
+            __syncthreads();
+            for (uint32_t b = tid; b < BINS; b += SLAB_THREADS) h[b] = 0;
+            __syncthreads();
+        }
+        uint32_t run = 0;
+        each_key<OP>(A, s, [&](uint32_t key, bool in) {
+            const bool hit = in && (key >> SHIFT) == pfx;
+            const uint64_t m = ballot64(hit);
+            if (m == 0) return;
+            if (hit) {
+                atomicAdd(&h[(key >> LOW) & (BINS - 1u)], 1u);
+                const uint32_t at = run + mbcnt64(m);
+                if (LEVEL == 1 && at < keys.room) keys.mine[at] = key;
+            }
+            run += (uint32_t)__popcll(m);
+        });
+        if (LEVEL == 1 && wave < keys.waves && lane_id() == 0) keys.count[wave] = run;
+    }
     // (the emission's slabs have published nothing yet)
     if (LEVEL == 2 && tid < SLAB_TILES / EMIT_TILES && tid * EMIT_TILES < s.ntiles)
         slab_publish<true>(dense_word(A, s.tile0 + tid * EMIT_TILES, j), 0u, 0u, 0u);
-    __syncthreads();
-    for (uint32_t b = tid; b < BINS; b += SLAB_THREADS) {
-        const uint32_t v = h[b];
-        if (v) atomicAdd(&g[b], v);
+    if (!from_keys) {
+        __syncthreads();
+        for (uint32_t b = tid; b < BINS; b += SLAB_THREADS) {
+            const uint32_t v = h[b];
+            if (v) atomicAdd(&g[b], v);
+        }
     }
     if (!arrive_last(&st->arrive[LEVEL], s.count, &bc)) return;
 
@@ -608,8 +669,10 @@ __global__ __launch_bounds__(SLAB_THREADS) void k_dense_refine(const SelectArgs 
 // Winners are staged per tile in LDS and leave as coalesced runs; the state is written by whole
 // 64-byte lines wherever a line has a winner (at these densities most lines that have one would
 // otherwise be read, merged and written back by the memory side for every 4-byte store).
+// 128 registers let four workgroups share a compute unit (148 by themselves: three, 66 instead of 57 us
+// on ResNet-50 shapes at density 0.1); the printed state's emission would spill 176 of them and keeps its own.
 template <int OP>
-__global__ __launch_bounds__(EMIT_THREADS) void k_dense_emit(const SelectArgs A)
+__global__ __launch_bounds__(EMIT_THREADS, OP == SEL_PULL_V ? 3 : 4) void k_dense_emit(const SelectArgs A)
 {
     __shared__ uint2 stage_all[EMIT_WAVES][TILE];
     __shared__ uint32_t wtot[EMIT_WAVES];
@@ -625,7 +688,7 @@ __global__ __launch_bounds__(EMIT_THREADS) void k_dense_emit(const SelectArgs A)
     // (density 1: everything is sent, at its own position)
     const uint32_t T = all ? 0u : st->T, rT = all ? 0u : st->rT;
     uint32_t bits[TPW][4][4], in[TPW];
-    load_slab<OP>(A, s, bits, in);
+    load_slab<OP, TPW>(A, s, 0u, bits, in);
     uint32_t mine = 0;
 #pragma unroll
     for (uint32_t i = 0; i < TPW; ++i)

@@ -30,6 +30,41 @@ def test_dense_rounds_with_full_slabs(oracle, levels):
     _rounds(oracle, ALIGNED, 0.37, levels)
 
 
+# Tensor sizes whose last slab has 32, 5 and 1 tiles; the keys that one wavefront may write down for the
+# second refinement there (a stretch of the slab's scratch: (min(tiles, 16) * 512 - 16) / wavefronts).
+KEY_ROOM = {96 * 1024: 1022, 69 * 1024: 1272, 65 * 1024: 496}
+
+
+@pytest.mark.parametrize("extra", [-1, 0, 1])
+@pytest.mark.parametrize("n", sorted(KEY_ROOM))
+def test_keys_around_the_threshold_fill_their_room(oracle, n, extra):
+    """Distinct keys in the leading bucket of the k-th one, as many in the last slab's first wavefront (its
+    first four tiles) as may be written down, one fewer and one more; bit for bit against the oracle."""
+    rng = np.random.default_rng(17)
+    tiles = ((n - 1) // 1024) % 32 + 1
+    first = n - tiles * 1024
+    last = first + min(tiles, 4) * 1024               # that wavefront's elements
+    inside = KEY_ROOM[n] + extra
+    a = rng.uniform(0.01, 0.1, n).astype(np.float32)
+    a[rng.permutation(first)[:2000]] = 1.0 + 0.06 * rng.random(2000).astype(np.float32)
+    a[first + rng.permutation(last - first)[:inside]] = 1.0 + 0.06 * rng.random(inside).astype(np.float32)
+    top = np.flatnonzero(a < 0.5)
+    a[rng.permutation(top[top < first])[:n // 10]] = 4.0
+    k = n // 10 + (2000 + inside) // 2
+    off = synth.offsets_from_sizes([n])
+    rho = (k - 0.5) / n
+    ctx = dgs.Context(off, W=0)
+    assert ctx.nnz(rho) == k
+    w = Worker(ctx, density_max=1.0)
+    s_ref = np.zeros(n, np.float32)
+    wi, wv = oracle.worker_step(a, s_ref, off, np.float32(1.0), np.float32(0.5), rho)
+    gi, gv = w.step(a, 1.0, 0.5, rho)
+    assert_pairs_match(gi, gv, wi, wv, f"{inside} keys")
+    assert_state_match(w.state_host(), s_ref, f"{inside} keys")
+    assert ctx.stats().internal_errors == 0
+    ctx.close()
+
+
 def _rounds(oracle, sizes, rho, levels):
     import torch
     off = synth.offsets_from_sizes(sizes)
