@@ -133,6 +133,7 @@ struct PlanSlot {
     int margin = 0;
     int seg_mode = 0;
     uint32_t nseg_active = 0;          // tensors planned as segmented
+    uint32_t kmax = 0;                 // largest k_j
     uint64_t K = 0;
     uint64_t wire_words = 0;           // 32-bit words of the wire form's index area
     uint64_t last_use = 0;
@@ -331,6 +332,8 @@ void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out,
     }
 }
 
+constexpr uint32_t ADD_SENT_K = 1400;      // see run_selection
+
 int upload(dgs_ctx *c, void *dst, const void *src, size_t bytes);
 
 bool stream_capturing(const dgs_ctx *c)
@@ -385,6 +388,8 @@ int get_plan(dgs_ctx *c, double density, uint32_t *slot_out, uint64_t *K_out)
     p.margin = c->margin_pct;
     p.seg_mode = c->seg_mode;
     p.nseg_active = active;
+    p.kmax = 0;
+    for (uint32_t j = 0; j < c->J; ++j) p.kmax = std::max(p.kmax, stage[j].k);
     p.K = K;
     p.wire_words = wire_words;
     p.last_use = c->tick;
@@ -559,7 +564,16 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
     if (!(dense_req && have_seg)) {
         ProfSlot ps(c, prof_select);
         if (have_seg) launch_window(se, c->stream, ps.ev0);
-        launch_select(op_select, se, c->stream, have_seg ? nullptr : ps.ev0, ps.ev1);
+        // The row of the printed state moves behind the selection where that saves more than a launch costs: on a
+        // server with several workers, whose lists are a few times k entries, from about 1400 pairs of a tensor
+        // on.  us an event, in the selection / behind it, largest k_j 700, 1400, 1800, 2400, 3500: one tensor
+        // of 1M elements and 4 workers 24.6 / 25.1, 29.0 / 27.7, 32.4 / 29.9, 37.8 / 33.0, 48.0 / 40.0; eight of
+        // 524 K 27.9 / 28.8, 36.9 / 36.0, 42.0 / 39.2, 48.6 / 44.0, 61.4 / 53.5; a round with one worker, whose
+        // row holds nothing but the message before: 41.1 / 42.9 at 2400, 44.7 / 46.5 at 3500.  (A plan with chain
+        // tensors emits and moves their pairs only later.)
+        se.later = (op_select == SEL_PULL_V && !have_seg && c->W > 1 && c->plan_slot[slot].kmax > ADD_SENT_K) ? 1u : 0u;
+        launch_select(op_select, se, c->stream, have_seg ? nullptr : ps.ev0, se.later ? nullptr : ps.ev1);
+        if (se.later) launch_add_sent(se, (uint32_t)K, c->stream, ps.ev1);
         ps.launched();
     }
     if (have_seg) {

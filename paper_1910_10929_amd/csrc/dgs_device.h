@@ -204,6 +204,7 @@ struct SelectArgs {
     uint32_t repair;              // the launch carries the re-collecting workgroups
     uint32_t spin_limit;          // polls before a waiting workgroup gives up
     uint32_t bgroup;              // parts looked after by one re-collecting workgroup
+    uint32_t later;               // SEL_PULL_V: k_add_sent moves the row behind the selection kernel, which leaves it alone
     const uint32_t *dslabs;       // dense requests: the tensor of every slab (run of SLAB_TILES tiles of a tensor), tensor after tensor
     uint32_t ndslabs;
 };
@@ -219,6 +220,8 @@ void launch_pick_dense(const TensorDesc *tdesc, const PlanEntry *plan, uint32_t 
 // The selection: one launch for every tensor (join, exact k-th key, ordered emission, state
 // fix-up, next hint; failed predictions are collected again inside the same launch).
 void launch_select(int op, const SelectArgs &a, void *stream, void *ev0, void *ev1);
+// SEL_PULL_V with SelectArgs::later: sent_k += G for the K pairs of the message.
+void launch_add_sent(const SelectArgs &a, uint32_t K, void *stream, void *ev1);
 // Long candidate lists: the parts' window histograms, before the selection kernel, and what
 // remains behind it for tensors left SEG_ACTIVE / SEG_LISTS / SEG_ZERO.
 void launch_window(const SelectArgs &a, void *stream, void *ev0);

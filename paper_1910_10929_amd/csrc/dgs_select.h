@@ -21,8 +21,9 @@ __device__ __forceinline__ float row_value(const float *state, const float *mode
 // What a sent entry leaves behind: worker m * a (Eq. 12, state stored as m u); pull on a
 // difference row +0 (Eq. 6 as D_k -= G); pull on model - sent_k: sent_k += G (Eq. 6).
 template <int OP>
-__device__ __forceinline__ void fix_sent(float *state, uint32_t ix, float val, float m)
+__device__ __forceinline__ void fix_sent(float *state, uint32_t ix, float val, float m, bool later = false)
 {
+    if (OP == SEL_PULL_V && later) return;
     if (OP == SEL_WORKER) store_scattered(&state[ix], m * val);
     else if (OP == SEL_PULL) store_scattered(&state[ix], 0.0f);
     else store_scattered(&state[ix], state[ix] + val);
@@ -431,7 +432,7 @@ __device__ __forceinline__ void select_emit(const Src src, const uint32_t cN, co
             // sent_k += G reads the row: all of this thread's reads are issued before the first
             // is needed (one memory round trip instead of one per entry)
             float old[ITEMS];
-            if (OP == SEL_PULL_V) {
+            if (OP == SEL_PULL_V && !A.later) {
 #pragma unroll
                 for (int i = 0; i < ITEMS; ++i) old[i] = (at[i] != 0xFFFFFFFFu) ? A.state[ix[i]] : 0.0f;
             }
@@ -443,7 +444,7 @@ __device__ __forceinline__ void select_emit(const Src src, const uint32_t cN, co
                     A.out_val[outoff + at[i]] = v;
                     if (OP == SEL_WORKER) store_scattered(&A.state[ix[i]], A.m * v);
                     else if (OP == SEL_PULL) store_scattered(&A.state[ix[i]], 0.0f);
-                    else store_scattered(&A.state[ix[i]], old[i] + v);
+                    else if (!A.later) store_scattered(&A.state[ix[i]], old[i] + v);
                 }
             }
         }
@@ -531,14 +532,14 @@ __device__ __forceinline__ void zero_fill_emit(const Src src, const uint32_t c, 
         const float v = row_value<OP>(A.state, A.model, ix);
         A.out_idx[pe.outoff + q] = ix;
         A.out_val[pe.outoff + q] = v;
-        fix_sent<OP>(A.state, ix, v, A.m);
+        fix_sent<OP>(A.state, ix, v, A.m, A.later != 0);
     }
     for (uint32_t p = P + tid; p < c; p += SEL_THREADS) {
         const uint32_t ix = src.index(p);
         const float v = __uint_as_float(src.bits(p));
         A.out_idx[pe.outoff + z + p] = ix;
         A.out_val[pe.outoff + z + p] = v;
-        if (index_ok(A, ix)) fix_sent<OP>(A.state, ix, v, A.m);
+        if (index_ok(A, ix)) fix_sent<OP>(A.state, ix, v, A.m, A.later != 0);
     }
 }
 

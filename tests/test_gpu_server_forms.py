@@ -83,6 +83,21 @@ def test_printed_form_segmented(oracle):
     assert st.segmented_tensors > 0
 
 
+@pytest.mark.parametrize("k", [1400, 1401, 1536, 1537])
+def test_printed_form_on_both_sides_of_the_row_update(oracle, k):
+    """Up to 1400 entries of a tensor the selection moves the row itself, beyond that a launch behind it does
+    (whole workgroups of pairs and one more); messages of a third of the entries, so that the first pulls
+    are completed with zeros, and pulls with nothing new."""
+    off = synth.offsets_from_sizes([300_001, 5000, 17])
+    rho = (k - 0.5) / 300_001
+    run_events(oracle, off, 2, 8, rho / 3, rho, 300 + k, extra=[(0, rho), (1, rho), (1, rho)])
+
+
+def test_printed_form_dense_pulls_of_small_tensors(oracle):
+    off = synth.offsets_from_sizes([60_000, 9000, 8192, 3])
+    run_events(oracle, off, 2, 4, 0.02, 0.3, 311, extra=[(0, 0.5), (1, 1.0), (0, 0.02)])
+
+
 def test_printed_form_full_size_resnet50_shapes(oracle):
     """25,557,032 parameters, 8 workers; pushes shaped like worker messages at density 1e-3."""
     off = synth.layout_resnet50()
