@@ -148,8 +148,25 @@ __device__ __forceinline__ uint32_t *part_hist(const SelectArgs &A, const Tensor
 }
 static_assert(SEG_MIN_N / TILE * 2 * CAPT >= (SEG_MIN_N / TILE / SEG_TILES + 2) * SEG_WBINS, "part histograms fit");
 
+// Window histogram of a list that one workgroup selects from: WIN_BINS buckets of key >> win_shift(op), which
+// leaves that many low bits for a second histogram.  Half an octave for the worker, whose k-th key moves little
+// from step to step; an octave for a pull: with half an octave the k-th key of a server's row that had
+// waited long lay beyond the window, which costs three more passes over the list, 8 to 12 us (mean of the
+// selection in the three server forms of 32 and 6 workers 28.5 -> 24.7, 29.7 -> 26.0, 31.8 -> 26.3 us;
+// the wider second histogram costs 0.3 us where the window had served: a round on ResNet-50 shapes).
+constexpr uint32_t WIN_BINS = 2048;
+constexpr __host__ __device__ uint32_t win_shift(int op) { return op == SEL_WORKER ? 11u : 12u; }
+
+// Its first bucket: the collection threshold or, when that lies far below (a relaxed hint), 1024 buckets
+// under the previous k-th key.
+template <int OP>
+__device__ __forceinline__ uint32_t win_base_of(uint32_t tau_cur, uint32_t t_prev)
+{
+    return max(tau_cur >> win_shift(OP), max(t_prev >> win_shift(OP), WIN_BINS / 2) - WIN_BINS / 2);
+}
+
 struct SelShared {
-    alignas(16) uint32_t h[2048];
+    alignas(16) uint32_t h[4096];      // (the join keeps its tiles in the upper half)
     uint32_t wsum[SEL_WAVES];
     uint32_t rowsum[64];
     int res[6];
@@ -175,13 +192,14 @@ __device__ __forceinline__ void hist_add(uint32_t *h, uint32_t bin, bool valid)
     else if (valid && bin != b0) atomicAdd(&h[bin], 1u);
 }
 
-// Window histogram of candidate keys: bucket (key >> 11) - win_base, everything at or
-// below the base in bucket 0, everything beyond the window in bucket 2047.
+// Window histogram of candidate keys: bucket (key >> win_shift(OP)) - win_base, everything at or
+// below the base in bucket 0, everything beyond the window in the last one.
+template <int OP>
 __device__ __forceinline__ void window_count(uint32_t *h, uint32_t win_base, uint32_t key)
 {
-    const uint32_t hi = key >> 11;
+    const uint32_t hi = key >> win_shift(OP);
     const uint32_t w = (hi > win_base) ? (hi - win_base) : 0u;
-    atomicAdd(&h[min(w, 2047u)], 1u);
+    atomicAdd(&h[min(w, WIN_BINS - 1u)], 1u);
 }
 
 // Next threshold when fewer candidates (c) than the hinted rank R were collected, all at
@@ -204,7 +222,7 @@ __device__ __forceinline__ uint32_t hint_extrapolated(uint32_t kmin, uint32_t c,
 // order and applies the state fix-up.  If R != 0 and R <= cN, also finds the
 // 21-bit key prefix of the entry of rank R: *tau_next = its lower edge (>= 1)
 // and *expect = how many entries lie at or above that edge; otherwise both 0.
-// Candidate lists come with a window: win_base = first bucket (key >> 11), 0xFFFFFFFF for
+// Candidate lists come with a window: win_base = first bucket (key >> win_shift(OP)), 0xFFFFFFFF for
 // other sources; win_min = 1 if entries may lie below the base (bucket 0 is then mixed and
 // cannot hold a result), else 0; win_ready: S.h already holds the window histogram of the
 // entries (window_count); kmin = smallest key of the list.
@@ -225,19 +243,21 @@ __device__ __forceinline__ void select_emit(const Src src, const uint32_t cN, co
     uint32_t pfx = 0;        // key prefix of the k-th entry, `lowbits` bits still unresolved
     uint32_t r2 = 0;         // its rank among the entries sharing that prefix
     uint32_t lowbits = 10;
+    constexpr uint32_t SHIFT = win_shift(OP), LOW_BINS = Src::AGG ? (1u << SHIFT) : 2048u;
+    static_assert(LOW_BINS <= sizeof(S.h) / 4, "low bits of a bucket");
     bool have_prefix = false;
 
     // ---- candidate lists: every key is >= the collection threshold, and the k-th key
-    //      normally lies within a factor ~1.4 of it, or close to the previous call's.  One
-    //      pass over a window of 2047 buckets of key >> 11 (bucket 2047 = everything
-    //      beyond) resolves 20 key bits at once.  A window that was placed by those hints
+    //      normally lies within a factor 1.4 (worker) or 2 of it, or close to the previous call's.
+    //      One pass over a window of 2047 buckets (bucket 2047 = everything beyond) resolves all
+    //      but SHIFT key bits at once.  A window that was placed by those hints
     //      and missed the k-th key is tried once more from the smallest key of the list.
     if (Src::AGG && win_base != 0xFFFFFFFFu) {
         uint32_t base = win_base, bmin = win_min;
         bool counted = win_ready;
         for (int attempt = 0; attempt < 2; ++attempt) {
             if (!counted) {   // otherwise the caller has counted the entries while it built the list
-                for (uint32_t b = tid; b < 2048; b += SEL_THREADS) S.h[b] = 0;
+                for (uint32_t b = tid; b < WIN_BINS; b += SEL_THREADS) S.h[b] = 0;
                 __syncthreads();
                 for (uint32_t pb = 0; pb < cN; pb += 4 * SEL_THREADS) {
                     uint32_t kk[4];
@@ -248,36 +268,36 @@ __device__ __forceinline__ void select_emit(const Src src, const uint32_t cN, co
                     }
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
-                        if (pb + i * SEL_THREADS + tid < cN) window_count(S.h, base, kk[i]);
+                        if (pb + i * SEL_THREADS + tid < cN) window_count<OP>(S.h, base, kk[i]);
                 }
             }
             // third rank: the drift quantile if R is among the candidates; otherwise the entry
             // below which the lowest quarter of the candidates lies (for the extrapolated hint)
             const uint32_t qlow = max(cN / 4u, min(cN, 16u));
             const uint32_t third = measurable ? ((Eq <= cN) ? Eq : 0u) : ((R != 0) ? (cN - qlow + 1u) : 0u);
-            find_ranks<2048, SEL_WAVES>(S.h, k, measurable ? R : k, third, S.rowsum, S.res);
+            find_ranks<WIN_BINS, SEL_WAVES>(S.h, k, measurable ? R : k, third, S.rowsum, S.res);
             const int bk = S.res[0], bR = S.res[2], bE = S.res[4];
             const uint32_t rk = (uint32_t)S.res[1], rR = (uint32_t)S.res[3];
             const int lo = (int)bmin;
-            if (bk >= lo && bk < 2047 && bR >= lo && bR < 2047) {
+            if (bk >= lo && bk < (int)WIN_BINS - 1 && bR >= lo && bR < (int)WIN_BINS - 1) {
                 have_prefix = true;
                 pfx = base + (uint32_t)bk;
                 r2 = rk;
-                lowbits = 11;
+                lowbits = SHIFT;
                 if (measurable) {
-                    const uint32_t edge = (base + (uint32_t)bR) << 11;
+                    const uint32_t edge = (base + (uint32_t)bR) << SHIFT;
                     *tau_next = edge ? edge : 1u;
                     *expect = R - rR + S.h[bR];
-                    if (bE >= lo && bE < 2047) *q_e = (base + (uint32_t)bE) << 11;
-                } else if (R != 0 && bE >= lo && bE < 2047) {
-                    const uint32_t top = (base + (uint32_t)bE + 1u) << 11;   // the lowest quarter ends below it
+                    if (bE >= lo && bE < (int)WIN_BINS - 1) *q_e = (base + (uint32_t)bE) << SHIFT;
+                } else if (R != 0 && bE >= lo && bE < (int)WIN_BINS - 1) {
+                    const uint32_t top = (base + (uint32_t)bE + 1u) << SHIFT;   // the lowest quarter ends below it
                     *tau_next = hint_extrapolated(max(kmin, 1u), cN, R, qlow, top - min(kmin, top - 1u));
                     *expect = R;
                 }
             }
             __syncthreads();
-            if (have_prefix || base == (kmin >> 11)) break;
-            base = kmin >> 11;
+            if (have_prefix || base == (kmin >> SHIFT)) break;
+            base = kmin >> SHIFT;
             bmin = 0;
             counted = false;
         }
@@ -355,7 +375,7 @@ __device__ __forceinline__ void select_emit(const Src src, const uint32_t cN, co
 
     // ---- last pass: the low key bits among the entries sharing the prefix
     const uint32_t lowmask = (1u << lowbits) - 1u;
-    for (uint32_t b = tid; b < 2048; b += SEL_THREADS) S.h[b] = 0;
+    for (uint32_t b = tid; b < LOW_BINS; b += SEL_THREADS) S.h[b] = 0;
     __syncthreads();
     for (uint32_t pb = 0; pb < cN; pb += 4 * SEL_THREADS) {
         uint32_t kk[4];
@@ -368,7 +388,7 @@ __device__ __forceinline__ void select_emit(const Src src, const uint32_t cN, co
         for (int i = 0; i < 4; ++i)
             if ((kk[i] >> lowbits) == pfx) atomicAdd(&S.h[kk[i] & lowmask], 1u);
     }
-    find_ranks<2048, SEL_WAVES>(S.h, r2, 0u, 0u, S.rowsum, S.res);
+    find_ranks<(int)LOW_BINS, SEL_WAVES>(S.h, r2, 0u, 0u, S.rowsum, S.res);
     const int b3 = S.res[0];
     const uint32_t rT = (uint32_t)S.res[1];   // how many entries equal to T are taken (lowest index first)
     __syncthreads();

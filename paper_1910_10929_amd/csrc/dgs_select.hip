@@ -183,8 +183,6 @@ struct PartShared {
     uint32_t pofs[SEG_MAX_PER_TENSOR];        // where every part's global list starts (entries into ord)
     uint32_t wtot[SEL_WAVES];
     uint32_t vbuf[B_GROUP_MAX];               // verdicts of the tensors of a re-collecting workgroup's parts
-    uint32_t tile_pos[SEL_THREADS];           // JOIN: list position and count of every tile of the round
-    uint32_t tile_n[SEL_THREADS];             //       (bit 31: the tile's entries are fetched one by one)
     uint32_t start0;                          //       entries of the previous tensor in a shared first tile
     uint32_t crowd_slot[SEL_THREADS];         //       the round's crowded tiles (which lane has them)
     uint32_t bc;
@@ -211,6 +209,10 @@ __device__ __forceinline__ uint32_t join_part(const SelectArgs &A, const TensorD
     const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = tid & 63u;
     const uint32_t tlo = td.off / TILE;
     const bool head_shared = (td.off % TILE) != 0;
+    // list position and count of every tile of the round (bit 31: the tile's entries are fetched one by
+    // one); the window is counted below them meanwhile
+    static_assert((WIN_BINS + 2 * SEL_THREADS) * 4 <= sizeof(P.S.h), "room for the tiles of a round");
+    uint32_t *tile_pos = P.S.h + WIN_BINS, *tile_n = tile_pos + SEL_THREADS;
     uint32_t base = 0;
     int ovf = 0;
     for (uint32_t r0 = 0; r0 < sd.ntiles; r0 += SEL_THREADS) {
@@ -233,15 +235,15 @@ __device__ __forceinline__ uint32_t join_part(const SelectArgs &A, const TensorD
         const uint32_t excl = block_excl_scan<SEL_WAVES>(n_t | (crowded ? 1u << 19 : 0u), P.S.wsum, total);
         const uint32_t pos = base + (excl & 0x7FFFFu);
         const uint32_t nc = total >> 19, round_n = total & 0x7FFFFu;
-        P.tile_pos[tid] = pos;
-        P.tile_n[tid] = n_t | (crowded ? 0x80000000u : 0u);
+        tile_pos[tid] = pos;
+        tile_n[tid] = n_t | (crowded ? 0x80000000u : 0u);
         if (crowded) P.crowd_slot[excl >> 19] = tid;
         if (head_shared && t == tlo) P.start0 = start;      // (the tensor's first tile, shared with the one before)
         __syncthreads();
 #pragma unroll
         for (uint32_t v = 0; v < 4; ++v) {
             const uint32_t slot = wave * 64u + v * 16u + (lane >> 2);
-            const uint32_t nv = P.tile_n[slot], p = P.tile_pos[slot], e0 = 2u * (lane & 3u);
+            const uint32_t nv = tile_n[slot], p = tile_pos[slot], e0 = 2u * (lane & 3u);
             const uint32_t n = (nv >> 31) ? 0u : nv;
             if (e0 < n) put(p + e0, make_uint2(pf[v].x, pf[v].y));
             if (e0 + 1 < n) put(p + e0 + 1, make_uint2(pf[v].z, pf[v].w));
@@ -250,7 +252,7 @@ __device__ __forceinline__ uint32_t join_part(const SelectArgs &A, const TensorD
             // a few crowded tiles: a wavefront copies one at a time
             for (uint32_t q = wave; q < nc; q += SEL_WAVES) {
                 const uint32_t slot = P.crowd_slot[q], tc = sd.tile0 + r0 + slot;
-                const uint32_t n_c = P.tile_n[slot] & 0x7FFFFFFFu, pc = P.tile_pos[slot];
+                const uint32_t n_c = tile_n[slot] & 0x7FFFFFFFu, pc = tile_pos[slot];
                 const uint32_t st0 = (head_shared && tc == tlo) ? P.start0 : 0u;
                 const uint2 *hd = A.heads + (size_t)tc * HEAD;
                 const uint2 *sl = A.slots + (size_t)tc * CAPT;
@@ -272,15 +274,15 @@ __device__ __forceinline__ uint32_t join_part(const SelectArgs &A, const TensorD
                         uint32_t lo = 0, hi = SEL_THREADS;
                         while (hi - lo > 1) {
                             const uint32_t mid = (lo + hi) >> 1;
-                            if (P.tile_pos[mid] <= q) lo = mid;
+                            if (tile_pos[mid] <= q) lo = mid;
                             else hi = mid;
                         }
-                        if (P.tile_n[lo] >> 31) {
+                        if (tile_n[lo] >> 31) {
                             const uint32_t tc = sd.tile0 + r0 + lo;
                             const uint32_t st0 = (head_shared && tc == tlo) ? P.start0 : 0u;
                             take[u] = true;
                             e[u] = tile_entry(A.heads + (size_t)tc * HEAD, A.slots + (size_t)tc * CAPT,
-                                              st0 + (q - P.tile_pos[lo]));
+                                              st0 + (q - tile_pos[lo]));
                         }
                     }
                 }
@@ -571,10 +573,10 @@ __device__ __forceinline__ void list_select(const SelectArgs &A, const TensorDes
     uint32_t tau_next = 0, expect = 0, q_e = 0, t_k = 0;
     // the window placed by the hints serves if no candidate lies below the threshold (none can);
     // a histogram counted on the way then stands as it is
-    const bool anchored = (win_join != 0xFFFFFFFFu) && (kmin != 0xFFFFFFFFu) && (kmin >> 11) >= (tau_cur >> 11);
+    const bool anchored = (win_join != 0xFFFFFFFFu) && (kmin != 0xFFFFFFFFu) && (kmin >> win_shift(OP)) >= (tau_cur >> win_shift(OP));
     const bool win_ready = win_counted && anchored;
-    const uint32_t win_base = (kmin == 0xFFFFFFFFu) ? 0xFFFFFFFFu : (anchored ? win_join : (kmin >> 11));
-    const uint32_t win_min = (anchored && win_join > (kmin >> 11)) ? 1u : 0u;   // entries below the window
+    const uint32_t win_base = (kmin == 0xFFFFFFFFu) ? 0xFFFFFFFFu : (anchored ? win_join : (kmin >> win_shift(OP)));
+    const uint32_t win_min = (anchored && win_join > (kmin >> win_shift(OP))) ? 1u : 0u;   // entries below the window
     if (c <= SEL_LDS_LIST) {
         SrcList src{llist};
         select_emit<OP, 4>(src, c, pe.k, R, Eq, win_base, win_min, win_ready, kmin, P.S, A, pe.outoff,
@@ -810,7 +812,7 @@ __device__ __forceinline__ uint32_t tensor_select(const SelectArgs &A, const Ten
                     if (q < c) {
                         put_entry(llist, glist, q, e[u]);
                         km = min(km, e[u].y & 0x7FFFFFFFu);
-                        if (count_win) window_count(P.S.h, win_join, e[u].y & 0x7FFFFFFFu);
+                        if (count_win) window_count<OP>(P.S.h, win_join, e[u].y & 0x7FFFFFFFu);
                     }
                 }
             }
@@ -1011,7 +1013,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const SelectArgs A)
         bool ovf = false;
         // window of the single-workgroup selection: starts at the collection threshold or, when
         // that lies far below (a relaxed hint), 1024 buckets under the previous k-th key
-        const uint32_t win_join = max(tau_cur >> 11, max(tprev_cur >> 11, 1024u) - 1024u);
+        const uint32_t win_join = win_base_of<OP>(tau_cur, tprev_cur);
         uint32_t *verdict = (has_parts && A.repair) ? &st->verdict : nullptr;
         uint32_t status;
         if (pe.seg) {
@@ -1042,7 +1044,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const SelectArgs A)
             cs = join_part(A, td, sd, P, ovf, [&](uint32_t pos, uint2 e) {
                 put_entry(llist, glist, pos, e);
                 kmin = min(kmin, e.y & 0x7FFFFFFFu);
-                window_count(P.S.h, win_join, e.y & 0x7FFFFFFFu);
+                window_count<OP>(P.S.h, win_join, e.y & 0x7FFFFFFFu);
             });
             kmin = wave_min_to_last(kmin);
             if (lane_id() == 63) atomicMin(&P.S.kmin, kmin);

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 from paper_1910_10929_amd import dgs, synth
-from harness import assert_pairs_match, assert_state_match, to_dev, to_host_u32
+from harness import Server, assert_pairs_match, assert_state_match, to_dev, to_host_u32
 
 pytestmark = pytest.mark.gpu
 
@@ -96,6 +96,39 @@ def test_printed_form_on_both_sides_of_the_row_update(oracle, k):
 def test_printed_form_dense_pulls_of_small_tensors(oracle):
     off = synth.offsets_from_sizes([60_000, 9000, 8192, 3])
     run_events(oracle, off, 2, 4, 0.02, 0.3, 311, extra=[(0, 0.5), (1, 1.0), (0, 0.02)])
+
+
+@pytest.mark.parametrize("factor", [1.3, 1.9, 2.2, 9.0])
+@pytest.mark.parametrize("form", ["sent", "diff"])
+def test_pulls_whose_threshold_key_moves(oracle, form, factor):
+    """The k-th key of a pull inside the window that the pull before has placed (an octave), in the octave
+    above it and beyond: messages that grow by `factor` once a row has settled, and shrink again."""
+    off = synth.offsets_from_sizes([300_001, 70_000, 9000])
+    n, W, rho = int(off[-1]), 2, 0.004
+    rng = np.random.default_rng(43)
+    scales = synth.tensor_scales(3, 44)
+    kj, _ = oracle.nnz(off, rho)
+    ctx = dgs.Context(off, W=W)
+    model0 = synth.gaussian(n, rng)
+    model_ref, rows = model0.copy(), np.tile(model0, (W, 1)) if form == "sent" else np.zeros((W, n), np.float32)
+    srv = SentServer(ctx, model0) if form == "sent" else Server(ctx, model0)
+    for e, f in enumerate([1.0] * 6 + [factor] * 3 + [1.0] * 2):
+        idx, val = synth.sparse_payload(off, kj, scales, rng)
+        val = (val * np.float32(f)).astype(np.float32)
+        k = e % W
+        if form == "sent":
+            oracle.server_push_model(model_ref, idx, val)
+            srv.push(idx, val)
+            want = oracle.server_pull_sent(model_ref, rows, k, off, rho)
+        else:
+            oracle.server_push(model_ref, rows, idx, val)
+            srv.push(k, idx, val)
+            want = oracle.server_pull(rows, k, off, rho)
+        assert_pairs_match(*srv.pull(k, rho), *want, f"event {e}")
+        got = (srv.sent if form == "sent" else srv.diff).cpu().numpy()
+        assert_state_match(got[k], rows[k], f"row {e}")
+    assert ctx.stats().internal_errors == 0
+    ctx.close()
 
 
 def test_printed_form_full_size_resnet50_shapes(oracle):
