@@ -567,13 +567,18 @@ __global__ __launch_bounds__(SLAB_THREADS, 8) void k_dense_refine(const SelectAr
     constexpr uint32_t BINS = (LEVEL == 1) ? REF1_BINS : REF2_BINS;
     constexpr uint32_t SHIFT = (LEVEL == 1) ? HSHIFT : REF1_SHIFT;       // the prefix known so far
     constexpr uint32_t LOW = (LEVEL == 1) ? REF1_SHIFT : 0u;
-    __shared__ uint32_t h[LEVEL == 1 ? HBINS : BINS];
+    __shared__ __align__(16) uint32_t h[LEVEL == 1 ? HBINS : BINS];
     __shared__ uint32_t rowsum[64];
     __shared__ int res[6];
     __shared__ uint32_t bc;
+    const uint32_t tid = threadIdx.x;
+    if (LEVEL == 2) {      // (before anything that has to be waited for)
+        for (uint32_t b = 4u * tid; b < BINS; b += 4u * SLAB_THREADS) *(uint4 *)&h[b] = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+    }
     Slab s;
     if (!find_slab<SLAB_TILES>(A, s)) return;
-    const uint32_t j = s.j, tid = threadIdx.x;
+    const uint32_t j = s.j;
     SegState *st = &A.segstate[j];
     const bool leading = (LEVEL == 1) && !s.td.big;       // the leading bits are still to be counted
     const uint32_t k = A.plan[j].k;
@@ -591,16 +596,20 @@ __global__ __launch_bounds__(SLAB_THREADS, 8) void k_dense_refine(const SelectAr
     if (LEVEL == 2)
         for (uint32_t w = 0; w < keys.waves; ++w) from_keys &= keys.count[w] <= keys.room;
     if (from_keys) {
-        // one in 256 of them shares the prefix, a few per slab: counted where the slabs' counters are
-        // added up (28 us when the tensors were read again, 15 through counters in LDS, 13)
+        // A smooth tensor has a few keys per slab that share the prefix (one in 256 of those written down), but
+        // all of them do where keys are tied: quantised ones, or ones that had 16 bits.  So they are counted in LDS
+        // and a slab adds at most once to a word: adds of the whole device to one word follow each other at 11 ns
+        // (64M parameters with 1 % ties, all three passes: 7485 us with an add per key, 262 so).
         const uint32_t listed = (wave < keys.waves) ? keys.count[wave] : 0u;
         for (uint32_t q = lane_id(); q < listed; q += 64) {
             const uint32_t key = keys.mine[q];
-            if ((key >> SHIFT) == pfx) atomicAdd(&g[key & (BINS - 1u)], 1u);
+            if ((key >> SHIFT) == pfx) atomicAdd(&h[key & (BINS - 1u)], 1u);
         }
     } else {
-        for (uint32_t b = tid; b < (LEVEL == 1 ? HBINS : BINS); b += SLAB_THREADS) h[b] = 0;
-        __syncthreads();
+        if (LEVEL == 1) {
+            for (uint32_t b = tid; b < HBINS; b += SLAB_THREADS) h[b] = 0;
+            __syncthreads();
+        }
         if (leading) {
             each_key<OP>(A, s, [&](uint32_t key, bool in) {
                 if (in) atomicAdd(&h[key >> HSHIFT], 1u);
@@ -629,12 +638,16 @@ __global__ __launch_bounds__(SLAB_THREADS, 8) void k_dense_refine(const SelectAr
     // (the emission's slabs have published nothing yet)
     if (LEVEL == 2 && tid < SLAB_TILES / EMIT_TILES && tid * EMIT_TILES < s.ntiles)
         slab_publish<true>(dense_word(A, s.tile0 + tid * EMIT_TILES, j), 0u, 0u, 0u);
-    if (!from_keys) {
-        __syncthreads();
-        for (uint32_t b = tid; b < BINS; b += SLAB_THREADS) {
-            const uint32_t v = h[b];
-            if (v) atomicAdd(&g[b], v);
-        }
+    __syncthreads();
+    // (16 bytes a thread: with 2048 counters read and cleared one by one this pass takes 15 us instead of 13)
+    static_assert(LEVEL == 2 || BINS <= SLAB_THREADS, "a counter each");
+    if (LEVEL == 1 && tid < BINS && h[tid]) atomicAdd(&g[tid], h[tid]);
+    for (uint32_t b = 4u * tid; LEVEL == 2 && b < BINS; b += 4u * SLAB_THREADS) {
+        const uint4 v = *(const uint4 *)&h[b];
+        if (v.x) atomicAdd(&g[b], v.x);
+        if (v.y) atomicAdd(&g[b + 1], v.y);
+        if (v.z) atomicAdd(&g[b + 2], v.z);
+        if (v.w) atomicAdd(&g[b + 3], v.w);
     }
     if (!arrive_last(&st->arrive[LEVEL], s.count, &bc)) return;
 

@@ -1,5 +1,6 @@
 // Scheduler of the host emulation (see hip/hip_runtime.h).
 #include <hip/hip_runtime.h>
+#include <unordered_map>
 
 emu::Idx threadIdx, blockIdx, blockDim, gridDim;
 
@@ -13,6 +14,22 @@ int current_device = 0;
 hipError_t last_error = hipSuccess;
 bool refuse_stamped = false;
 hipStreamCaptureStatus capture_status = hipStreamCaptureStatusNone;
+
+bool count_adds = false;
+static std::unordered_map<const void *, uint64_t> adds;
+
+void count_add(const void *p)
+{
+    if ((const char *)p < __start_emu_lds || (const char *)p >= __stop_emu_lds) ++adds[p];
+}
+
+uint64_t most_adds()
+{
+    uint64_t most = 0;
+    for (const auto &a : adds) most = std::max(most, a.second);
+    adds.clear();
+    return most;
+}
 
 // Minimal stack switch (System V x86-64): callee-saved registers on the old stack, stack
 // pointers exchanged.  (swapcontext would make a system call per switch.)

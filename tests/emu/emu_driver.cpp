@@ -414,6 +414,43 @@ static void gives_up(const char *name, double rho, int seg_mode, int order, uint
     fflush(stdout);
 }
 
+// Dense requests whose k-th key is shared by a part of the tensor (quantised gradients, or ones that were
+// rounded to 16 bits): results against the oracle, and no word of global memory is added to more often than
+// once per slab and refinement and once per streaming workgroup.
+static void tied_dense(const char *name, double share, double rho, uint64_t seed)
+{
+    g_what = name;
+    Layout L({300000, 64, 5000});       // (one tensor that the accumulate pass counts)
+    Rng r(seed);
+    Ctx c(L, 0);
+    const uint64_t K = L.K(rho);
+    Buf<float> g(L.n), s_gpu(L.n), s_ref(L.n);
+    Buf<uint32_t> gi(K), wi(K);
+    Buf<float> gv(K), wv(K);
+    fill_grad(L, r, g.p, 1.0f, 0);
+    for (uint32_t j = 0; j < L.J; ++j) {
+        const uint64_t lo = L.off[j], n = L.off[j + 1] - lo;
+        std::vector<float> a(n);
+        for (uint64_t i = 0; i < n; ++i) a[i] = std::fabs(g.p[lo + i]);
+        std::sort(a.begin(), a.end());
+        const float v = a[(size_t)((1.0 - rho + share / 2) * (double)n)];
+        for (uint64_t i = 0; i < n; ++i)
+            if (r.uni() < share) g.p[lo + i] = (r.u32() & 1u) ? v : -v;
+    }
+    uint64_t k1 = 0, k2 = 0;
+    CHECK(dgs_oracle_worker_step(g.p, s_ref.p, L.off.data(), L.J, 1.0f, 0.9f, rho, wi.p, wv.p, &k1) == 0);
+    emu::count_adds = true;
+    CHECK(dgs_worker_step(c.c, g.p, s_gpu.p, nullptr, 1.0f, 0.9f, rho, gi.p, gv.p, &k2) == DGS_OK);
+    emu::count_adds = false;
+    const uint64_t slabs = 300000 / (dgs::SLAB_TILES * dgs::TILE) + 1, streaming = L.n / 4096 + 1;
+    CHECK(emu::most_adds() <= 2 * slabs + streaming);
+    expect_same(gi.p, gv.p, wi.p, wv.p, K);
+    expect_same_f(s_gpu.p, s_ref.p, L.n, "state");
+    CHECK(c.stats().internal_errors == 0);
+    printf("%-44s ok\n", name);
+    fflush(stdout);
+}
+
 // Randomised layouts, densities, options, server forms and gradient-scale jumps (which make
 // predictions fail): `soak <first seed> <count>`.
 static void soak(uint64_t seed)
@@ -498,6 +535,9 @@ int main(int argc, char **argv)
     gives_up("dense emission gives up", 0.1, 0, 1, 40);
     gives_up("chain emission gives up on the slabs before", 0.01, 1, 2, 41);
     gives_up("chain emission gives up on the ranking", 0.01, 1, 1, 42);
+    tied_dense("dense request, 1 in 1000 share the k-th key", 0.001, 0.1, 45);
+    tied_dense("dense request, 12 % share the k-th key", 0.12, 0.1, 46);
+    tied_dense("dense request, 20 % share the k-th key of 90 %", 0.2, 0.9, 47);
     const std::vector<uint64_t> ragged = {1, 7, 64, 1000, 8192, 8193, 9408, 3, 100003, 20000, 70001, 17, 65537, 12345};
     const std::vector<uint64_t> two = {150000, 64, 66000};
     Opts def, exact, always, never, norepair;

@@ -155,7 +155,18 @@ using std::min;
 static inline float fmaxf_(float a, float b) { return a > b ? a : b; }
 
 // ---- atomics (one thread runs at a time)
-template <class T> static inline T atomicAdd(T *p, T v) { T o = *p; *p = o + v; return o; }
+namespace emu {
+extern bool count_adds;              // atomicAdd calls are counted per word of global memory (not LDS)
+void count_add(const void *p);
+uint64_t most_adds();                // the highest of those counts; starts over
+}
+template <class T> static inline T atomicAdd(T *p, T v)
+{
+    if (emu::count_adds) emu::count_add(p);
+    T o = *p;
+    *p = o + v;
+    return o;
+}
 template <class T> static inline T atomicMin(T *p, T v) { T o = *p; if (v < o) *p = v; return o; }
 template <class T> static inline T atomicOr(T *p, T v) { T o = *p; *p = o | v; return o; }
 // __hip_atomic_load / _store / _fetch_add are compiler builtins that also exist for the host.

@@ -65,6 +65,39 @@ def test_keys_around_the_threshold_fill_their_room(oracle, n, extra):
     ctx.close()
 
 
+@pytest.mark.parametrize("tied", [True, False], ids=["tied", "distinct"])
+@pytest.mark.parametrize("each", [1, 64, 800])
+def test_keys_that_share_all_but_the_last_bits(oracle, each, tied):
+    """Keys with the k-th one's 20 leading bits, `each` of them in every wavefront's four tiles, equal or all
+    different in the last bits (as far as 2048 values go); 800 of 4096 still fit the room of the keys written
+    down.  One wavefront has one more."""
+    rng = np.random.default_rng(each)
+    waves, n = 3 * 8, 3 * 32 * 1024
+    a = rng.uniform(0.01, 0.1, n).astype(np.float32)
+    prefix = np.float32(1.03).view(np.uint32) & np.uint32(0xFFFFF800)
+    total = 0
+    for w in range(waves):
+        where, c = w * 4096 + rng.permutation(4096), each + (w == 13)
+        low = np.full(c, 77) if tied else np.resize(rng.permutation(2048), c)
+        a[where[:c]] = (prefix + low.astype(np.uint32)).view(np.float32)
+        a[where[c:c + 500]] = 4.0
+        total += c
+    a *= rng.choice(np.float32([-1, 1]), n)
+    k = waves * 500 + (total + 1) // 2
+    off = synth.offsets_from_sizes([n])
+    rho = (k - 0.5) / n
+    ctx = dgs.Context(off, W=0)
+    assert ctx.nnz(rho) == k
+    w = Worker(ctx, density_max=1.0)
+    s_ref = np.zeros(n, np.float32)
+    wi, wv = oracle.worker_step(a, s_ref, off, np.float32(1.0), np.float32(0.5), rho)
+    gi, gv = w.step(a, 1.0, 0.5, rho)
+    assert_pairs_match(gi, gv, wi, wv, f"{each} keys")
+    assert_state_match(w.state_host(), s_ref, f"{each} keys")
+    assert ctx.stats().internal_errors == 0
+    ctx.close()
+
+
 def _rounds(oracle, sizes, rho, levels):
     import torch
     off = synth.offsets_from_sizes(sizes)
