@@ -1111,11 +1111,12 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const SelectArgs A)
 
 // Pull on the printed state: sent_k += G, a thread per pair, behind the selection kernel.  A tensor's selection
 // runs on one compute unit, and what that can have in flight bounds a scattered read and write of its row:
-// 7.6 us for 2360 pairs, which the whole chip does in the 4 us of this launch (32-worker server on ResNet-50
-// shapes 72.7 -> 68.8 us an event).  Only what the row still shows is added: a pair that a selection
-// has failed to write (counted as an internal error) moves nothing.
+// 7.6 us for 2360 pairs, which the whole chip does in the 5 us of this launch (32-worker server on ResNet-50
+// shapes 72.7 -> 68.8 us an event).  The row follows the message whatever becomes of the model meanwhile.  Only in
+// a context that has counted an internal error may the message hold pairs that no selection has written:
+// there, what the row does not show is not added.
 __global__ __launch_bounds__(256) void k_add_sent(float *sent, const float *model, uint32_t n, const uint32_t *idx,
-                                                  const float *val, uint32_t K)
+                                                  const float *val, uint32_t K, const DevStats *stats)
 {
     const uint32_t e = blockIdx.x * 256 + threadIdx.x;
     if (e >= K) return;
@@ -1123,13 +1124,14 @@ __global__ __launch_bounds__(256) void k_add_sent(float *sent, const float *mode
     const float v = val[e];
     if (ix >= n) return;
     const float old = sent[ix];
-    if (__float_as_uint(model[ix] - old) == __float_as_uint(v)) store_scattered(&sent[ix], old + v);
+    if (stats->internal_errors != 0 && __float_as_uint(model[ix] - old) != __float_as_uint(v)) return;
+    store_scattered(&sent[ix], old + v);
 }
 
 void launch_add_sent(const SelectArgs &a, uint32_t K, void *stream, void *ev1)
 {
     launch_k(k_add_sent, dim3((K + 255u) / 256u), dim3(256), (hipStream_t)stream, nullptr, ev1, a.state, a.model, a.n,
-             (const uint32_t *)a.out_idx, (const float *)a.out_val, K);
+             (const uint32_t *)a.out_idx, (const float *)a.out_val, K, (const DevStats *)a.stats);
 }
 
 void launch_select(int op, const SelectArgs &a, void *stream, void *ev0, void *ev1)

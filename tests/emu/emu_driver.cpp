@@ -451,6 +451,47 @@ static void tied_dense(const char *name, double share, double rho, uint64_t seed
     fflush(stdout);
 }
 
+// The launch behind a selection on the printed state: the row follows the message, also where the model has moved
+// on since the values were taken; an index outside the row is skipped; and where an internal error has been
+// counted, a pair that the row does not show (one that no selection has written) moves nothing.
+static void row_update()
+{
+    g_what = "row update behind the selection";
+    const uint32_t n = 1000, K = 300;
+    Rng r(50);
+    for (unsigned long long errors : {0ull, 1ull}) {
+        Buf<float> sent(n), want(n), model(n), val(K);
+        Buf<uint32_t> idx(K);
+        for (uint32_t i = 0; i < n; ++i) {
+            want.p[i] = sent.p[i] = r.gauss();
+            model.p[i] = r.gauss();
+        }
+        for (uint32_t e = 0; e < K; ++e) {
+            idx.p[e] = 3 * e + 1;
+            if (e == 10) model.p[31] = INFINITY;
+            if (e == 11) model.p[34] = NAN;
+            val.p[e] = model.p[idx.p[e]] - sent.p[idx.p[e]];
+            const bool other = (e % 5) == 4;
+            if (other) model.p[idx.p[e]] += 1.0f;
+            if (e == 7 || e == 299) idx.p[e] = e == 7 ? n : 0xFFFFFFFFu;
+            else if (!other || errors == 0) want.p[idx.p[e]] += val.p[e];
+        }
+        dgs::DevStats stats{};
+        stats.internal_errors = errors;
+        dgs::SelectArgs A{};
+        A.state = sent.p;
+        A.model = model.p;
+        A.n = n;
+        A.out_idx = idx.p;
+        A.out_val = val.p;
+        A.stats = &stats;
+        dgs::launch_add_sent(A, K, nullptr, nullptr);
+        expect_same_f(sent.p, want.p, n, errors ? "row after an error" : "row");
+    }
+    printf("%-44s ok\n", g_what.c_str());
+    fflush(stdout);
+}
+
 // Randomised layouts, densities, options, server forms and gradient-scale jumps (which make
 // predictions fail): `soak <first seed> <count>`.
 static void soak(uint64_t seed)
@@ -538,6 +579,7 @@ int main(int argc, char **argv)
     tied_dense("dense request, 1 in 1000 share the k-th key", 0.001, 0.1, 45);
     tied_dense("dense request, 12 % share the k-th key", 0.12, 0.1, 46);
     tied_dense("dense request, 20 % share the k-th key of 90 %", 0.2, 0.9, 47);
+    row_update();
     const std::vector<uint64_t> ragged = {1, 7, 64, 1000, 8192, 8193, 9408, 3, 100003, 20000, 70001, 17, 65537, 12345};
     const std::vector<uint64_t> two = {150000, 64, 66000};
     Opts def, exact, always, never, norepair;
