@@ -216,7 +216,7 @@ static dgs_stats worker_server(const char *name, const std::vector<uint64_t> &si
 
 // the printed server form (model + sent_k) with two workers, pulls at another density
 static void printed_form(const char *name, const std::vector<uint64_t> &sizes, double rho_up, double rho_down,
-                         int events, const Opts &o, uint64_t seed)
+                         int events, const Opts &o, uint64_t seed, int flavour = 0)
 {
     g_what = name;
     Layout L(sizes);
@@ -231,7 +231,7 @@ static void printed_form(const char *name, const std::vector<uint64_t> &sizes, d
     CHECK(dgs_server_attach_sent(c.c, sent_gpu.p) == DGS_OK);
     for (int e = 0; e < events; ++e) {
         g_what = std::string(name) + " event " + std::to_string(e);
-        fill_grad(L, r, g.p, e == 3 ? 1e-3f : 1.0f, 0);
+        fill_grad(L, r, g.p, e == 3 ? 1e-3f : 1.0f, flavour);
         uint64_t k1 = 0, k2 = 0;
         CHECK(dgs_oracle_worker_step(g.p, s_ref.p, L.off.data(), L.J, 1.0f, 0.9f, rho_up, wi.p, wv.p, &k1) == 0);
         const uint32_t w = (uint32_t)(e % 3 == 2 ? 0 : e % 2);
@@ -492,6 +492,50 @@ static void row_update()
     fflush(stdout);
 }
 
+// A pull on the printed state whose prediction fails and whose collection gives up waiting, with the row updated
+// behind the selection: a tensor moves exactly if its pairs were written in this call.
+static void pull_gives_up(uint64_t seed)
+{
+    g_what = "pull on the printed state gives up";
+    Layout L({150000, 64, 300000});
+    Rng r(seed);
+    Ctx c(L, 2);
+    Opts o;
+    o.seg_mode = 2;
+    set_opts(c, o);
+    const double rho = 0.01;
+    const uint64_t K = L.K(rho);
+    Buf<float> model(L.n), sent(2 * L.n), want(2 * L.n);
+    Buf<uint32_t> gi(K), wi(K);
+    Buf<float> gv(K), wv(K);
+    uint64_t k1 = 0, k2 = 0;
+    CHECK(dgs_server_attach_sent(c.c, sent.p) == DGS_OK);
+    for (int call = 0; call < 3; ++call) {
+        // (the last model: the first tensor as before, the others so close to the row that nothing reaches the threshold)
+        for (uint64_t i = 0; i < L.n; ++i)
+            model.p[i] = (call == 2 && i >= L.off[1]) ? sent.p[i] + 1e-6f * r.gauss() : sent.p[i] + r.gauss();
+        CHECK(dgs_oracle_server_pull_sent(model.p, want.p, L.off.data(), L.J, rho, wi.p, wv.p, &k1) == 0);
+        if (call == 2) {
+            CHECK(dgs_set_option(c.c, DGS_OPT_SPIN_LIMIT, 2) == DGS_OK);
+            emu::block_order = 1;
+        }
+        CHECK(dgs_server_pull_sent(c.c, model.p, 0, rho, gi.p, gv.p, &k2) == DGS_OK && k1 == K && k2 == K);
+        emu::block_order = 0;
+        if (call == 2) break;
+        expect_same(gi.p, gv.p, wi.p, wv.p, K);
+        expect_same_f(sent.p, want.p, L.n, "row");
+    }
+    CHECK(c.stats().internal_errors > 0);
+    const uint64_t done = L.off[1];      // the first tensor's prediction holds
+    expect_same(gi.p, gv.p, wi.p, wv.p, 1500);
+    expect_same_f(sent.p, want.p, done, "row of the tensor that was selected");
+    uint64_t moved = 0;
+    for (uint64_t i = L.off[2]; i < L.n; ++i) moved += sent.p[i] != want.p[i];
+    CHECK(moved > 2900);                 // (its 3000 entries are not written: nothing moves)
+    printf("%-44s ok\n", g_what.c_str());
+    fflush(stdout);
+}
+
 // Randomised layouts, densities, options, server forms and gradient-scale jumps (which make
 // predictions fail): `soak <first seed> <count>`.
 static void soak(uint64_t seed)
@@ -592,6 +636,12 @@ int main(int argc, char **argv)
 
     worker_server("zero fill on the chain", two, 0.02, 0.03, 1.0f, 0.9f, false, {1, 1, 1}, 5, always, 43);
     printed_form("zero fill on the chain, printed form", two, 0.002, 0.02, 3, always, 44);
+    // (more than 1400 pairs in a tensor: the row is updated behind the selection)
+    printed_form("printed form, row behind the selection", two, 0.01, 0.02, 5, never, 51);
+    printed_form("the same, completed with zeros", two, 0.002, 0.02, 4, never, 52);
+    printed_form("the same, dense pulls of small tensors", {20000, 64, 9000, 5000}, 0.05, 0.3, 3, def, 53);
+    printed_form("the same, infinities and NaNs", two, 0.01, 0.01, 4, never, 54, 7);
+    pull_gives_up(55);
     worker_server("ragged, predicted", ragged, 0.004, 0.004, 0.5f, 0.9f, false, steady, 0, def, 1);
     worker_server("scale jumps, residual mode (re-collection)", two, 0.002, 0.004, 1.0f, 0.0f, true, jumps, 0, def, 2);
     worker_server("scale jumps, chain for every large tensor", two, 0.002, 0.002, 1.0f, 0.0f, true, jumps, 0, always, 3);

@@ -93,6 +93,44 @@ def test_printed_form_on_both_sides_of_the_row_update(oracle, k):
     run_events(oracle, off, 2, 8, rho / 3, rho, 300 + k, extra=[(0, rho), (1, rho), (1, rho)])
 
 
+@pytest.mark.parametrize("k", [1400, 1401])
+def test_printed_form_with_infinities_and_nans(oracle, k):
+    """A few entries of the model become infinite or NaN, on both sides of where the row is updated: they are
+    sent, the row follows, and from then on their difference is NaN.  NaN equal to NaN, all else bit for bit."""
+    off = synth.offsets_from_sizes([300_001, 5000, 17])
+    n, rho, W = int(off[-1]), (k - 0.5) / 300_001, 2
+    rng = np.random.default_rng(312)
+    kj, _ = oracle.nnz(off, rho)
+    scales = synth.tensor_scales(3, 45)
+    ctx = dgs.Context(off, W=W)
+    model_ref = synth.gaussian(n, rng)
+    rows_ref = np.tile(model_ref, (W, 1))
+    srv = SentServer(ctx, model_ref)
+
+    def same(got, want, what):
+        odd = np.isnan(want)
+        assert np.array_equal(np.isnan(got), odd), what
+        assert np.array_equal(got[~odd].view(np.uint32), want[~odd].view(np.uint32)), what
+
+    for e in range(8):
+        idx, val = synth.sparse_payload(off, kj, scales, rng)
+        if e in (2, 5):
+            val[::40] = np.inf
+            val[1::80] = -np.inf
+            val[2::200] = np.nan
+        oracle.server_push_model(model_ref, idx, val)
+        srv.push(idx, val)
+        wi, wv = oracle.server_pull_sent(model_ref, rows_ref, e % W, off, rho)
+        gi, gv = srv.pull(e % W, rho)
+        assert np.array_equal(gi, wi), f"event {e}"
+        same(gv, wv, f"event {e}: values")
+        same(srv.model.cpu().numpy(), model_ref, f"event {e}: model")
+        same(srv.sent.cpu().numpy().ravel(), rows_ref.ravel(), f"event {e}: rows")
+    assert np.isnan(rows_ref).any() and np.isinf(model_ref).any()
+    assert ctx.stats().internal_errors == 0
+    ctx.close()
+
+
 def test_printed_form_dense_pulls_of_small_tensors(oracle):
     off = synth.offsets_from_sizes([60_000, 9000, 8192, 3])
     run_events(oracle, off, 2, 4, 0.02, 0.3, 311, extra=[(0, 0.5), (1, 1.0), (0, 0.02)])

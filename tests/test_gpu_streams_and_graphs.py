@@ -86,6 +86,59 @@ def test_step_replayed_from_a_graph(oracle):
     ctx.close()
 
 
+@pytest.mark.parametrize("rho_up", [0.006, 0.002])
+def test_pull_on_the_printed_state_replayed_from_a_graph(oracle, rho_up):
+    """dgs_server_push_model + dgs_server_pull_sent of a server with two workers, captured where the row is updated
+    by a launch of its own behind the selection (more than 1400 pairs in a tensor): every replay against
+    the oracle, messages as dense as the pull and sparser ones."""
+    import torch
+    off = synth.offsets_from_sizes([300_001, 64, 9408, 70_001, 5])
+    n, rho, W = int(off[-1]), 0.006, 2
+    dev = "cuda:0"
+    rng = np.random.default_rng(85)
+    scales = synth.tensor_scales(5, 84)
+    kj, K_up = oracle.nnz(off, rho_up)
+    model_ref = synth.gaussian(n, rng)
+    rows_ref = np.tile(model_ref, (W, 1))
+    s = torch.cuda.Stream(device=dev)
+    ctx = dgs.Context(off, W=W, device=dev, stream=s)
+    K = ctx.nnz(rho)
+    with torch.cuda.stream(s):
+        model, rows = torch.from_numpy(model_ref.copy()).to(dev), torch.from_numpy(rows_ref.copy()).to(dev)
+        idx, val = torch.zeros(K_up, dtype=torch.int32, device=dev), torch.zeros(K_up, device=dev)
+        pidx, pval = torch.zeros(K, dtype=torch.int32, device=dev), torch.zeros(K, device=dev)
+        ctx.server_attach_sent(rows)
+
+        def enqueue(w):
+            ctx.server_push_model(model, idx, val, K_up)
+            ctx.server_pull_sent(model, w, rho, pidx, pval)
+
+        def event(w, go, tag):
+            i, v = synth.sparse_payload(off, kj, scales, rng)
+            idx.copy_(torch.from_numpy(i.view(np.int32)))
+            val.copy_(torch.from_numpy(v))
+            go()
+            oracle.server_push_model(model_ref, i, v)
+            wi, wv = oracle.server_pull_sent(model_ref, rows_ref, w, off, rho)
+            s.synchronize()
+            assert_pairs_match(to_host_u32(pidx), pval.cpu().numpy(), wi, wv, tag)
+            assert_state_match(rows.cpu().numpy().ravel(), rows_ref.ravel(), f"{tag}: rows")
+            (rows.sum() + model.sum()).item()                 # eager work and a host wait in between
+
+        graphs = []
+        for w in range(W):
+            for t in range(2):
+                event(w, lambda: enqueue(w), f"eager {w} {t}")
+            graphs.append(torch.cuda.CUDAGraph())
+            with torch.cuda.graph(graphs[w], stream=s):
+                enqueue(w)
+        for t in range(8):
+            event(t % W, graphs[t % W].replay, f"replay {t}")
+    assert_state_match(model.cpu().numpy(), model_ref, "model")
+    assert ctx.stats().internal_errors == 0
+    ctx.close()
+
+
 def test_an_unplanned_density_is_refused_during_capture(oracle):
     """Planning a density copies its tables to the device, which a stream capture must not contain:
     a call with a density that has no cached plan returns DGS_ENOTSUP while the stream is being
