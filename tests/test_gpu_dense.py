@@ -172,23 +172,24 @@ def test_one_large_tensor_costs_what_several_do():
     of one tensor meet on its counters (1.10 times the time; 1.46 with the count of finished slabs on the
     line that each of them begins by reading)."""
     import torch
-    n, us = 240_000_000, []
+    n = 240_000_000
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(9)
     row = torch.randn(n, device="cuda:0", generator=gen)
     idx, val = torch.zeros(n // 10 + 64, dtype=torch.int32, device="cuda:0"), torch.zeros(n // 10 + 64, device="cuda:0")
-    for off in (synth.layout_flat(n), synth.layout_equal(n, 24)):
-        ctx = dgs.Context(off, W=1)
-        ctx.set_option(dgs.OPT_PROFILE, 1)
-        times = []
-        for _ in range(7):
+    ctxs = [dgs.Context(off, W=1) for off in (synth.layout_flat(n), synth.layout_equal(n, 24))]
+    times = [[], []]
+    for _ in range(7):                                  # (in turn, so that both see the same clocks)
+        for ctx, t in zip(ctxs, times):
+            ctx.set_option(dgs.OPT_PROFILE, 1)
             diff = row.clone()
             ctx.server_attach(diff)
             ctx.server_pull(0, 0.1, idx, val)
-            times.append(ctx.profile_read(dgs.PROF_PULL_SEGMENTED)[1])
+            t.append(ctx.profile_read(dgs.PROF_PULL_SEGMENTED)[1])
+    for ctx in ctxs:
         assert ctx.stats().internal_errors == 0
         ctx.close()
-        us.append(1e3 * float(np.median(times[1:])))
+    us = [1e3 * float(np.median(t[1:])) for t in times]
     print("one tensor %.0f us, 24 tensors %.0f us" % tuple(us))
     assert us[0] < 1.25 * us[1]
 
