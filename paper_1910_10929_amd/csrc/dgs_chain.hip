@@ -497,7 +497,8 @@ __device__ __forceinline__ uint2 *dense_word(const SelectArgs &A, uint32_t tile0
 // The keys that refine 1 hands to refine 2: a stretch of its own for every wavefront that has tiles, in the
 // scratch of the slab's first half (the second half begins with a word of the emission), behind one count
 // each.  The bucket of 1/16 octave around the k-th key of a Gaussian tensor holds 2 % of its elements at
-// density 0.1; there is room for a quarter of a wavefront's (an eighth where its slab has more than 16 tiles).
+// density 0.1; there is room for half of a wavefront's elements in slabs of up to 16 tiles (2 CAPT words for
+// the TILE elements of a tile), falling to a quarter in a full slab of 32.
 constexpr uint32_t KEYS_AT = 16;
 static_assert(KEYS_AT >= 4 + SLAB_WAVES, "two words of the emission and the counts");
 struct SlabKeys {

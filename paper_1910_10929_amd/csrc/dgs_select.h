@@ -219,9 +219,10 @@ __device__ __forceinline__ uint32_t hint_extrapolated(uint32_t kmin, uint32_t c,
 }
 
 // Exact selection over `cN` ordered entries of `src`; emits the k winners in
-// order and applies the state fix-up.  If R != 0 and R <= cN, also finds the
-// 21-bit key prefix of the entry of rank R: *tau_next = its lower edge (>= 1)
-// and *expect = how many entries lie at or above that edge; otherwise both 0.
+// order and applies the state fix-up.  If R != 0 and R <= cN, also finds a key
+// prefix of the entry of rank R -- 31 - win_shift(OP) bits where the window resolved
+// it, 21 from the passes without one: *tau_next = its lower edge (>= 1) and
+// *expect = how many entries lie at or above that edge; otherwise both 0.
 // Candidate lists come with a window: win_base = first bucket (key >> win_shift(OP)), 0xFFFFFFFF for
 // other sources; win_min = 1 if entries may lie below the base (bucket 0 is then mixed and
 // cannot hold a result), else 0; win_ready: S.h already holds the window histogram of the

@@ -799,7 +799,7 @@ __device__ __forceinline__ uint32_t tensor_select(const SelectArgs &A, const Ten
             // gather the parts' lists into one (positions beyond the LDS list land in the first
             // part's global list: on dead space, or on the very entry that is being moved)
             const bool count_win = (win_join != 0xFFFFFFFFu);   // the hinted window is counted on the way
-            for (uint32_t b = tid; b < 2048; b += SEL_THREADS) P.S.h[b] = 0;
+            for (uint32_t b = tid; b < WIN_BINS; b += SEL_THREADS) P.S.h[b] = 0;
             if (tid == 0) P.S.kmin = 0xFFFFFFFFu;
             __syncthreads();
             const SrcParts src{A.ord, P.pbase, P.pofs, nunits};
@@ -1043,7 +1043,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const SelectArgs A)
             status = tensor_select<OP>(A, td, pe, j, 0, true, false, cs, ovf, kmin, tau_cur, tprev_cur, win_join, true,
                                        verdict, P, llist);
         } else {
-            for (uint32_t b = tid; b < 2048; b += SEL_THREADS) P.S.h[b] = 0;
+            for (uint32_t b = tid; b < WIN_BINS; b += SEL_THREADS) P.S.h[b] = 0;
             if (tid == 0) P.S.kmin = 0xFFFFFFFFu;
             __syncthreads();
             uint2 *glist = plist;
