@@ -250,17 +250,19 @@ struct ProfSlot {
 
 // The rank a pull aims its next threshold at.  Sent entries vanish from the row, and any number of pushes
 // may lie between two pulls of a worker: about 2 k, or 2.5 k so that fewer predictions fail (a failure
-// costs an event 165 us) at the price of longer lists.  A failure is that of any tensor, the longer list
+// costs an event about 100 us) at the price of longer lists.  A failure is that of any tensor, the longer list
 // that of the largest, so 2.5 k is taken
 //   for layouts of at least PULL_WIDE_TENSORS tensors with lists (servers, us an event at 2 / 2.5 k: 8 equal
-//   tensors of 423 K at 0.2 % 37.7 / 33.0, 70 of 13M in all at 0.2 % 66.1 / 59.8, ResNet-50 shapes with 6
-//   workers at 0.17 % 95.0 / 77.6; 5 tensors 67.3 / 66.2, 4 875 / 940, 3 70.2 / 71.1, one of 300 K / 600 K /
-//   1e6 at 1 % 37.1 / 39.8, 55.8 / 64.4, 83.6 / 101);
+//   tensors of 423 K at 0.2 % 31.6 / 25.9, 70 of 13M in all at 0.2 % 58.6 / 48.1, ResNet-50 shapes with 6
+//   workers at 0.17 % 79.9 / 67.9; one tensor of 300 K / 600 K at 1 % 31.9 / 30.9, 42.2 / 43.1.  The line was drawn
+//   with slower joins of long lists; now 3 to 5 tensors of 423 K would gain from it too: 27.3 / 23.4, 27.9 / 23.4,
+//   30.4 / 24.5);
 //   for tensors whose list then still fits the LDS of a workgroup, or which take the chain (ResNet-50
-//   shapes at 0.36 / 0.42 %, largest k 8500 / 9900: 125 / 132, 140 / 151);
+//   shapes at 0.36 / 0.42 %, largest k 8500 / 9900, with the wide rank for the others alone / for all: 93.9 / 95.2,
+//   102.5 / 105.0 on the printed state, 100.1 / 102.4, 112.5 / 117.0 on difference rows);
 //   from the pull number PULL_YOUNG + 1 of a row at a density on: while a row fills up its thresholds rise
-//   and predictions seldom fail (32 workers on ResNet-50 shapes at 0.1 %, pull 2 of every worker 132 / 142,
-//   4 80 / 85, 7 to 10 73 / 76, 11 to 18 72 / 71, later 82 / 71).
+//   and predictions seldom fail (32 workers on ResNet-50 shapes at 0.1 % in regular turns, pull 2 of every worker
+//   103 / 106, 3 72 / 79, 5 to 10 58.6 / 59.3, 11 to 18 59 / 59; later, in random order, 73 / 60).
 constexpr uint32_t PULL_WIDE_TENSORS = 8, PULL_YOUNG = 10;
 
 // k_j = ceil(density * n_j) in IEEE double; k2 = rank that sets the next predicted threshold.
@@ -565,10 +567,10 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
         ProfSlot ps(c, prof_select);
         if (have_seg) launch_window(se, c->stream, ps.ev0);
         // The row of the printed state moves behind the selection where that saves more than a launch costs: on a
-        // server with several workers, whose lists are a few times k entries, from about 1400 pairs of a tensor
-        // on.  us an event, in the selection / behind it, largest k_j 700, 1400, 1800, 2400, 3500: one tensor
-        // of 1M elements and 4 workers 24.6 / 25.1, 29.0 / 27.7, 32.4 / 29.9, 37.8 / 33.0, 48.0 / 40.0; eight of
-        // 524 K 27.9 / 28.8, 36.9 / 36.0, 42.0 / 39.2, 48.6 / 44.0, 61.4 / 53.5; a round with one worker, whose
+        // server with several workers, whose lists are a few times k entries, clearly from 1400 pairs of a tensor
+        // on.  us an event, in the selection / behind it, largest k_j 700, 1000, 1400, 1800, 2400, 3500: one tensor
+        // of 1M elements and 4 workers 23.0 / 23.4, 25.3 / 25.1, 27.9 / 26.2, 30.2 / 27.2, 34.1 / 28.9, 40.8 / 31.9; eight of
+        // 524 K 24.5 / 25.1, 27.1 / 27.0, 30.5 / 28.5, 33.4 / 30.1, 38.3 / 33.1, 47.1 / 38.1; a round with one worker, whose
         // row holds nothing but the message before: 41.1 / 42.9 at 2400, 44.7 / 46.5 at 3500.  (A plan with chain
         // tensors emits and moves their pairs only later.)
         se.later = (op_select == SEL_PULL_V && !have_seg && c->W > 1 && c->plan_slot[slot].kmax > ADD_SENT_K) ? 1u : 0u;

@@ -36,12 +36,15 @@ constexpr uint32_t SEL_THREADS = 1024;
 constexpr uint32_t SEL_WAVES = SEL_THREADS / 64;
 constexpr uint32_t SEL_LDS_LIST = 16384;           // candidates kept in LDS (128 KB); longer lists continue in global scratch
 // Longest candidate list one workgroup is planned for (rank 2 k).  One workgroup / the chain, us: flat tensors
-// of 700 K / 900 K / 1.05M / 1.2M elements at 1 % (lists of 14 / 18 / 21 / 24 K), a round 75.5 / 82.6, 91.3 / 83.5,
-// 105 / 84, 124 / 89, a step without momentum 43 / 40, 57 / 41, 63 / 39, 76 / 43; ResNet-50 shapes at 0.36 / 0.39 /
-// 0.45 % (17 / 18 / 21 K), a round 172 / 186, 178 / 177, 194 / 181, a step 108 / 104, 112 / 95, 119 / 97.
+// of 700 K / 900 K / 1.05M / 1.2M elements at 1 % (lists of 14 / 18 / 21 / 24 K), a round 63 / 84, 79 / 88,
+// 88 / 88, 98 / 90, a step without momentum 34 / 40, 46 / 42, 51 / 41, 60 / 44; ResNet-50 shapes at 0.36 / 0.39 /
+// 0.45 % (17 / 18 / 21 K), a round 153 / 178, 158 / 173, 167 / 175, a step 89 / 96, 92 / 92, 99 / 93.
 constexpr uint32_t SEL_LIST_MAX = 20480;
 // ... and where the plan holds a tensor beyond that, so that the chain's launches are there anyway,
-// for tensors of at least SEL_CROWDED_TILES tiles (their join is then what the launch waits for).
+// for tensors of at least SEL_CROWDED_TILES tiles (their join is then what the launch waits for).  us with the
+// line at 4096 / 8192 / without one: ResNet-50 shapes at 1 %, a round 193 / 192 / 204, a step without momentum 93 / 93 / 101,
+// at 0.6 % 177 / 184 / 197 and 95 / 100 / 108; 40 tensors of 30M in all at 1 % 222 / 222 / 241, transformer shapes
+// at 0.4 % 505 / 499 / 487.  From 64 tiles on instead of 512 the same within 1 %, from 1024 on 11 to 19 us more at 1 %.
 constexpr uint32_t SEL_LIST_CROWDED = 8192, SEL_CROWDED_TILES = 512;
 constexpr uint32_t SEL_LIST_HARD = 65536;          // longest it accepts when a tail has grown beyond the plan
 // Above this density candidates stop paying off; such requests select densely.
