@@ -446,7 +446,8 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
     sa.tau = tau;
     sa.tile_cnt = c->tile_cnt;
     sa.heads = c->heads;
-    sa.slots = c->slots;
+    sa.near = c->slots;
+    sa.far = c->slots + (size_t)c->ntiles * (NEAR - HEAD);
     sa.ghist = c->ghist;
     sa.n = c->n;
     sa.ntiles = c->ntiles;
@@ -534,7 +535,8 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
     se.tau = tau;
     se.tile_cnt = c->tile_cnt;
     se.heads = c->heads;
-    se.slots = c->slots;
+    se.near0 = (uint32_t)(sa.near - c->heads);
+    se.far0 = (uint32_t)(sa.far - c->heads);
     se.ord = c->ord;
     se.hint2 = c->hint2 + (size_t)hint_set * c->J;
     se.tprev = tprev;

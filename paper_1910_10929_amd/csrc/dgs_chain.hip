@@ -1,10 +1,10 @@
 // The chain: tensors whose candidate lists are too long for one workgroup to join and select from.
 // The candidates stay where the streaming pass has left them, tile by tile; one wavefront takes 8 or
-// 16 tiles at a time, all of their first 64 candidates in flight together, and the work is cut into
+// 16 tiles, all of their first 64 candidates in flight together, four tiles to an instruction, and the work is cut into
 // slabs of CSLAB_TILES tiles, so that it fills the chip for any number of tensors.  Joining the
 // candidates into one ordered list first, one workgroup per 4096 tiles, was bound by that
-// workgroup: 92 us of a call on ResNet-50 shapes at 1 % without momentum (now 10.6 for the window
-// and 16 for the finish), 232 us at 1 % of 1e9 parameters.  At that size each pass reads 240 MB of
+// workgroup: 92 us of a call on ResNet-50 shapes at 1 % without momentum (now 7 for the window
+// and 15 for the finish), 232 us at 1 % of 1e9 parameters.  At that size each pass reads 240 MB of
 // candidates and the emission is bound by its scattered 4-byte stores (1e7 of them: 420 us).
 //   window  (before the selection kernel) per part: window histogram of the candidates, in a slot
 //           of its own -- no atomics between workgroups; the selection kernel adds a tensor's
@@ -67,37 +67,93 @@ __device__ __forceinline__ uint2 tile_get(const SelectArgs &A, const WaveTiles &
 {
     const uint32_t p = start + q;
     if (w.lists) return A.ord[p];
-    return (p < HEAD) ? A.heads[(size_t)(w.t0 + i) * HEAD + p] : A.slots[(size_t)(w.t0 + i) * CAPT + p];
+    return *candidate(A, w.t0 + i, p);
 }
 
-// The first 64 candidates of every tile, candidate `lane` of tile i in e[i].
-template <uint32_t CTPW>
-__device__ __forceinline__ void tile_firsts(const SelectArgs &A, const WaveTiles &w, uint2 (&e)[CTPW])
+// A wavefront takes four tiles at a time, 16 lanes each, and a lane two of a tile's candidates: one 16-byte load for
+// the first NEAR of each, and one for as many more where one of the four tiles has more.  (64 lanes on one tile, a
+// candidate each: every instruction of these passes works on the 10 to 30 candidates of one tile then, and
+// they are bound by instructions: a round on one tensor of 2^20 elements at 1 % 85.0 us, 73.4 so; the window histogram of
+// 1e9 parameters at 1 % 122 us, 73 so.)
+static_assert(NEAR == 32 && HEAD % 2 == 0, "16 lanes, two candidates each");
+constexpr uint32_t PAIRS = 2 * NEAR;      // candidates of a tile that are held in registers
+
+__device__ __forceinline__ uint32_t shuffle(uint32_t v, uint32_t from)
+{
+    return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * from), (int)v);
+}
+
+// This lane's candidates of tile 4 i + lane / 16: positions at, at + 1, NEAR + at and NEAR + at + 1 of its list, of which
+// n are the tensor's from `start` on (for the ordered lists: start 0, positions count from the share's first).
+struct LanePair {
+    uint32_t n, start, at;
+    __device__ __forceinline__ bool has(uint32_t x) const { return at + x - start < n; }
+};
+
+__device__ __forceinline__ LanePair lane_pair(const WaveTiles &w, uint32_t i)
+{
+    const uint32_t lane = lane_id(), t = 4u * i + (lane >> 4);
+    LanePair p;
+    p.n = shuffle(w.n, t);
+    p.start = w.lists ? 0u : shuffle(w.start, t);
+    p.at = 2u * (lane & 15u);
+    return p;
+}
+
+// The tiles (bit i: tile i) that hold candidates at position `from` or behind it.
+__device__ __forceinline__ uint64_t deep_tiles(const WaveTiles &w, uint32_t from)
+{
+    return ballot64(w.n != 0 && (w.lists ? 0u : w.start) + w.n > from);
+}
+__device__ __forceinline__ bool deep_group(uint64_t deep, uint32_t i) { return ((deep >> (4u * i)) & 0xFull) != 0; }
+
+// Those candidates for NT tiles: e[i][0] the first NEAR positions, e[i][1] the next.
+template <uint32_t NT>
+__device__ __forceinline__ void tile_firsts(const SelectArgs &A, const WaveTiles &w, uint4 (&e)[NT / 4][2])
 {
     const uint32_t lane = lane_id();
+    static_assert(NT % 4 == 0, "four tiles at a time");
+    const uint64_t deep = deep_tiles(w, NEAR);
 #pragma unroll
-    for (uint32_t i = 0; i < CTPW; ++i) {
-        const uint32_t start = (uint32_t)__builtin_amdgcn_readlane((int)w.start, (int)i);
-        e[i] = (lane < tile_n(w, i)) ? tile_get(A, w, i, start, lane) : make_uint2(0u, 0u);
+    for (uint32_t i = 0; i < NT / 4; ++i) {
+        LanePair p = lane_pair(w, i);
+        const uint32_t from = w.lists ? shuffle(w.start, 4u * i + (lane >> 4)) : 0u;
+#pragma unroll
+        for (uint32_t u = 0; u < 2; ++u, p.at += NEAR) {
+            e[i][u] = make_uint4(0u, 0u, 0u, 0u);
+            if (u == 1 && !deep_group(deep, i)) continue;
+            if (w.lists) {
+                const uint2 a = p.has(0) ? A.ord[from + p.at] : make_uint2(0u, 0u);
+                const uint2 b = p.has(1) ? A.ord[from + p.at + 1u] : make_uint2(0u, 0u);
+                e[i][u] = make_uint4(a.x, a.y, b.x, b.y);
+            } else if (p.has(0) || p.has(1)) {
+                e[i][u] = *(const uint4 *)candidate(A, w.t0 + 4u * i + (lane >> 4), p.at);      // (both in the same line)
+            }
+        }
     }
 }
 
 // f(entry) for every candidate, in no particular order (lanes diverge inside f).
-template <uint32_t CTPW, class F>
-__device__ __forceinline__ void each_candidate(const SelectArgs &A, const WaveTiles &w, F f)
+template <uint32_t NT, class F>
+__device__ __forceinline__ void each_candidate(const SelectArgs &A, const WaveTiles &w, const uint4 (&e)[NT / 4][2], F f)
 {
     const uint32_t lane = lane_id();
-    uint2 e[CTPW];
-    tile_firsts(A, w, e);
+    const uint64_t deep = deep_tiles(w, NEAR);
 #pragma unroll
-    for (uint32_t i = 0; i < CTPW; ++i)
-        if (lane < tile_n(w, i)) f(e[i]);
-#pragma unroll 1
-    for (uint32_t i = 0; i < CTPW; ++i) {
-        const uint32_t n = tile_n(w, i);
-        if (n <= 64) continue;
+    for (uint32_t i = 0; i < NT / 4; ++i) {
+        LanePair p = lane_pair(w, i);
+        if (p.has(0)) f(make_uint2(e[i][0].x, e[i][0].y));
+        if (p.has(1)) f(make_uint2(e[i][0].z, e[i][0].w));
+        if (!deep_group(deep, i)) continue;
+        p.at += NEAR;
+        if (p.has(0)) f(make_uint2(e[i][1].x, e[i][1].y));
+        if (p.has(1)) f(make_uint2(e[i][1].z, e[i][1].w));
+    }
+    for (uint64_t m = deep_tiles(w, PAIRS); m != 0; m &= m - 1ull) {
+        const uint32_t i = (uint32_t)__ffsll((unsigned long long)m) - 1u, n = tile_n(w, i);
         const uint32_t start = (uint32_t)__builtin_amdgcn_readlane((int)w.start, (int)i);
-        for (uint32_t q = 64 + lane; q < n; q += 64) f(tile_get(A, w, i, start, q));
+        const uint32_t skip = w.lists ? PAIRS : PAIRS - min(start, PAIRS);
+        for (uint32_t q = skip + lane; q < n; q += 64) f(tile_get(A, w, i, start, q));
     }
 }
 
@@ -119,8 +175,10 @@ __global__ __launch_bounds__(SEL_THREADS) void k_list_window(const SelectArgs A)
         const WaveTiles w = wave_tiles(A, td, sd.tile0 + t, min(WINDOW_TPW, sd.ntiles - t), false, part);
         mine += w.n;
         ovf |= w.ovf;
-        each_candidate<WINDOW_TPW>(A, w, [&](uint2 e) {
-            const uint32_t hi12 = (e.y & 0x7FFFFFFFu) >> SEG_LOWBITS;
+        uint4 e[WINDOW_TPW / 4][2];
+        tile_firsts<WINDOW_TPW>(A, w, e);
+        each_candidate<WINDOW_TPW>(A, w, e, [&](uint2 x) {
+            const uint32_t hi12 = (x.y & 0x7FFFFFFFu) >> SEG_LOWBITS;
             const uint32_t b = (hi12 > win) ? (hi12 - win) : 0u;
             atomicAdd(&h[min(b, SEG_WBINS - 1u)], 1u);
         });
@@ -132,8 +190,11 @@ __global__ __launch_bounds__(SEL_THREADS) void k_list_window(const SelectArgs A)
     if (tid == 0) A.segcnt[part] = c | (over ? 0x80000000u : 0u);
 }
 
+// Tiles of one wavefront of a slab.
+constexpr uint32_t slab_tpw(uint32_t threads) { return CSLAB_TILES / (threads / 64) < 4 ? 4u : CSLAB_TILES / (threads / 64); }
+
 struct FinishShared {
-    uint32_t h[SEG_LBINS];
+    alignas(8) uint32_t h[SEG_LBINS];      // (an emission stages its winners there)
     uint32_t rowsum[64];
     int res[6];
     uint32_t wtot[SEL_WAVES];
@@ -145,15 +206,17 @@ template <uint32_t THREADS>
 __device__ __forceinline__ void rank_slab(const SelectArgs &A, uint32_t slab, const SegDesc &sd, const TensorDesc &td,
                                           SegState *st, bool lists, FinishShared &C)
 {
-    constexpr uint32_t CTPW = CSLAB_TILES / (THREADS / 64);      // tiles of one wavefront
+    constexpr uint32_t CTPW = slab_tpw(THREADS);
     const uint32_t tid = threadIdx.x, wave = uniform(tid >> 6);
     const uint32_t pfx = st->pfx;
     uint32_t *glow = A.ghist + (size_t)sd.j * HBINS;
     const uint32_t first = min(wave * CTPW, sd.ntiles);
     const WaveTiles w = wave_tiles(A, td, sd.tile0 + first, min(CTPW, sd.ntiles - first), lists, sd.sidx);
     if (tid == 0) slab_publish<false>(&A.slabs_done[slab], 0u, 0u, 0u);      // nothing published yet (complete before the arrival below)
-    each_candidate<CTPW>(A, w, [&](uint2 e) {
-        if (((e.y & 0x7FFFFFFFu) >> SEG_LOWBITS) == pfx) atomicAdd(&glow[e.y & (SEG_LBINS - 1u)], 1u);
+    uint4 e[CTPW / 4][2];
+    tile_firsts<CTPW>(A, w, e);
+    each_candidate<CTPW>(A, w, e, [&](uint2 x) {
+        if (((x.y & 0x7FFFFFFFu) >> SEG_LOWBITS) == pfx) atomicAdd(&glow[x.y & (SEG_LBINS - 1u)], 1u);
     });
     if (!arrive_last(&st->arrive[3], td.ncs, &C.bc)) return;
     // the tensor's last slab: exact k-th key and tie budget
@@ -181,12 +244,12 @@ template <int OP, uint32_t THREADS>
 __device__ __forceinline__ void emit_slab(const SelectArgs &A, uint32_t slab, const SegDesc &sd, const TensorDesc &td,
                                           const PlanEntry &pe, SegState *st, bool lists, FinishShared &C)
 {
-    constexpr uint32_t WAVES = THREADS / 64, CTPW = CSLAB_TILES / WAVES;
+    constexpr uint32_t WAVES = THREADS / 64, CTPW = slab_tpw(THREADS);
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = uniform(tid >> 6);
     const uint32_t first = min(wave * CTPW, sd.ntiles);
     const WaveTiles w = wave_tiles(A, td, sd.tile0 + first, min(CTPW, sd.ntiles - first), lists, sd.sidx);
-    uint2 e[CTPW];
-    tile_firsts(A, w, e);                            // on their way while the ranking is awaited
+    uint4 e[CTPW / 4][2];
+    tile_firsts<CTPW>(A, w, e);                      // on their way while the ranking is awaited
     if (wait_word(&st->ready, A.spin_limit, &C.bc) == 0) {
         if (tid == 0) {
             slab_publish<false>(&A.slabs_done[slab], SLAB_FAIL, 0u, 0u);
@@ -197,28 +260,12 @@ __device__ __forceinline__ void emit_slab(const SelectArgs &A, uint32_t slab, co
     const uint32_t T = uniform(ld_dev(&st->T)), rT = uniform(ld_dev(&st->rT));
     // entries above T (low half) and equal to it (high half) of this wavefront: a few thousand at most
     uint32_t mine = 0;
-#pragma unroll
-    for (uint32_t i = 0; i < CTPW; ++i) {
-        const uint32_t key = e[i].y & 0x7FFFFFFFu;
-        if (lane < tile_n(w, i)) mine += (key > T ? 1u : 0u) + (key == T ? 0x10000u : 0u);
-    }
-#pragma unroll 1
-    for (uint32_t i = 0; i < CTPW; ++i) {
-        const uint32_t n = tile_n(w, i), start = (uint32_t)__builtin_amdgcn_readlane((int)w.start, (int)i);
-        for (uint32_t q = 64 + lane; q < n; q += 64) {
-            const uint32_t key = tile_get(A, w, i, start, q).y & 0x7FFFFFFFu;
-            mine += (key > T ? 1u : 0u) + (key == T ? 0x10000u : 0u);
-        }
-    }
+    each_candidate<CTPW>(A, w, e, [&](uint2 x) {
+        const uint32_t key = x.y & 0x7FFFFFFFu;
+        mine += (key > T ? 1u : 0u) + (key == T ? 0x10000u : 0u);
+    });
     const uint32_t sum = wave_sum(mine);
     if (lane == 0) C.wtot[wave] = sum;
-    // sent_k += G reads the row: all of these reads are in flight before the first is needed
-    float old[CTPW];
-    if (OP == SEL_PULL_V) {
-#pragma unroll
-        for (uint32_t i = 0; i < CTPW; ++i)
-            old[i] = (lane < tile_n(w, i) && (e[i].y & 0x7FFFFFFFu) >= T && e[i].x < A.n) ? A.state[e[i].x] : 0.0f;
-    }
     __syncthreads();
     uint32_t before = 0, all = 0;
 #pragma unroll
@@ -245,40 +292,93 @@ __device__ __forceinline__ void emit_slab(const SelectArgs &A, uint32_t slab, co
     uint32_t eq = C.q + (before >> 16);              // the tensor's ties seen so far: lowest index first, rT of them are taken
     uint32_t pos = C.g + (before & 0xFFFFu) + min(eq, rT);
     const uint32_t limit = C.limit;
-    auto send = [&](uint2 x, float was, bool valid) {             // up to 64 consecutive entries; all lanes call
-        const uint32_t key = x.y & 0x7FFFFFFFu;
-        bool f = valid && key > T;
-        const bool tie = valid && key == T;
-        const uint64_t mq = ballot64(tie);
-        if (mq != 0) {
-            if (tie) f = eq + mbcnt64(mq) < rT;
-            eq += (uint32_t)__popcll(mq);
-        }
-        const uint64_t mk = ballot64(f);
-        const uint32_t p = pos + mbcnt64(mk);
-        if (f && p < limit) {
-            const float v = __uint_as_float(x.y);
-            A.out_idx[pe.outoff + p] = x.x;
-            A.out_val[pe.outoff + p] = v;
-            if (index_ok(A, x.x)) {
-                if (OP == SEL_WORKER) store_scattered(&A.state[x.x], A.m * v);
-                else if (OP == SEL_PULL) store_scattered(&A.state[x.x], 0.0f);
-                else store_scattered(&A.state[x.x], was + v);
-            }
-        }
-        pos += (uint32_t)__popcll(mk);
+    auto write = [&](uint32_t p, uint2 x, float was) {
+        if (p >= limit) return;
+        const float v = __uint_as_float(x.y);
+        A.out_idx[pe.outoff + p] = x.x;
+        A.out_val[pe.outoff + p] = v;
+        if (!index_ok(A, x.x)) return;
+        if (OP == SEL_WORKER) store_scattered(&A.state[x.x], A.m * v);
+        else if (OP == SEL_PULL) store_scattered(&A.state[x.x], 0.0f);
+        else store_scattered(&A.state[x.x], was + v);
     };
+    constexpr uint32_t STAGED = SEG_LBINS / 2 / WAVES;            // entries of a wavefront in C.h
+    uint2 *stage = (uint2 *)C.h + wave * STAGED;
+    const uint64_t deep = deep_tiles(w, NEAR), deeper = deep_tiles(w, PAIRS);
 #pragma unroll
-    for (uint32_t i = 0; i < CTPW; ++i) {
-        const uint32_t n = tile_n(w, i);
-        if (n == 0) continue;                                     // (wave-uniform, like all of this loop)
-        send(e[i], OP == SEL_PULL_V ? old[i] : 0.0f, lane < n);
-        const uint32_t start = (uint32_t)__builtin_amdgcn_readlane((int)w.start, (int)i);
-        for (uint32_t q0 = 64; q0 < n; q0 += 64) {
-            const bool valid = q0 + lane < n;
-            const uint2 x = valid ? tile_get(A, w, i, start, q0 + lane) : make_uint2(0u, 0u);
-            const float was = (OP == SEL_PULL_V && valid && x.x < A.n) ? A.state[x.x] : 0.0f;
-            send(x, was, valid);
+    for (uint32_t i = 0; i < CTPW / 4; ++i) {                     // (wave-uniform, like all of this loop)
+        if (!deep_group(deeper, i)) {
+            // four tiles; in each, the lanes' pairs of the first NEAR positions come before those of the next
+            const bool more = deep_group(deep, i);
+            LanePair p = lane_pair(w, i);
+            const uint64_t low = (1ull << (lane & 48u)) - 1ull, up = low | (0xFFFFull << (lane & 48u));
+            bool v[4], f[4];
+            uint64_t mk[4];
+#pragma unroll
+            for (uint32_t x = 0; x < 4; ++x) {
+                const uint32_t bits = (x & 1u) ? e[i][x / 2].w : e[i][x / 2].y;
+                if (x == 2) p.at += NEAR;
+                v[x] = (x < 2 || more) && p.has(x & 1u);
+                f[x] = v[x] && (bits & 0x7FFFFFFFu) == T;
+                mk[x] = ballot64(f[x]);
+            }
+            auto rank = [&](uint32_t x) {                         // marked entries before entry x of this lane
+                uint32_t r;
+                if (x < 2) r = mbcnt64(mk[0]) + mbcnt64(mk[1]) + (uint32_t)(__popcll(mk[2] & low) + __popcll(mk[3] & low));
+                else r = mbcnt64(mk[2]) + mbcnt64(mk[3]) + (uint32_t)(__popcll(mk[0] & up) + __popcll(mk[1] & up));
+                return r + ((x & 1u) && f[x - 1] ? 1u : 0u);
+            };
+            uint32_t tied[4] = {0, 0, 0, 0};
+            const bool ties = (mk[0] | mk[1] | mk[2] | mk[3]) != 0;
+            if (ties) {
+#pragma unroll
+                for (uint32_t x = 0; x < 4; ++x) tied[x] = eq + rank(x);
+                eq += (uint32_t)(__popcll(mk[0]) + __popcll(mk[1]) + __popcll(mk[2]) + __popcll(mk[3]));
+            }
+#pragma unroll
+            for (uint32_t x = 0; x < 4; ++x) {
+                const uint32_t bits = (x & 1u) ? e[i][x / 2].w : e[i][x / 2].y;
+                f[x] = v[x] && ((bits & 0x7FFFFFFFu) > T || (f[x] && tied[x] < rT));
+                mk[x] = ballot64(f[x]);
+            }
+            // The winners meet in LDS and leave 64 at a time: neighbours in the message by neighbouring lanes, and winners
+            // of one line of the state in one store (1 % of 1e9 parameters: 524 / 439 us, and 584 / 508 straight from
+            // the registers).
+            const uint32_t won = (uint32_t)(__popcll(mk[0]) + __popcll(mk[1]) + __popcll(mk[2]) + __popcll(mk[3]));
+            const bool fits = won <= STAGED;
+#pragma unroll
+            for (uint32_t x = 0; x < 4; ++x) {
+                if (x >= 2 && !more) break;
+                const uint2 c = (x & 1u) ? make_uint2(e[i][x / 2].z, e[i][x / 2].w) : make_uint2(e[i][x / 2].x, e[i][x / 2].y);
+                if (!f[x]) continue;
+                const uint32_t r = rank(x);
+                if (fits) stage[r] = c;
+                else write(pos + r, c, (OP == SEL_PULL_V && c.x < A.n) ? A.state[c.x] : 0.0f);
+            }
+            __builtin_amdgcn_wave_barrier();
+            for (uint32_t r = lane; fits && r < won; r += 64) {
+                const uint2 c = stage[r];
+                write(pos + r, c, (OP == SEL_PULL_V && c.x < A.n) ? A.state[c.x] : 0.0f);
+            }
+            __builtin_amdgcn_wave_barrier();
+            pos += won;
+            continue;
+        }
+#pragma unroll 1
+        for (uint32_t t = 4u * i; t < 4u * i + 4u; ++t) {         // one of the four has more than that: a tile at a time
+            const uint32_t n = tile_n(w, t), start = (uint32_t)__builtin_amdgcn_readlane((int)w.start, (int)t);
+            for (uint32_t q0 = 0; q0 < n; q0 += 64) {
+                const bool valid = q0 + lane < n;
+                const uint2 x = valid ? tile_get(A, w, t, start, q0 + lane) : make_uint2(0u, 0u);
+                const float was = (OP == SEL_PULL_V && valid && x.x < A.n) ? A.state[x.x] : 0.0f;
+                const uint32_t key = x.y & 0x7FFFFFFFu;
+                const uint64_t mt = ballot64(valid && key == T);
+                const bool f = valid && (key > T || (key == T && eq + mbcnt64(mt) < rT));
+                eq += (uint32_t)__popcll(mt);
+                const uint64_t mf = ballot64(f);
+                if (f) write(pos + mbcnt64(mf), x, was);
+                pos += (uint32_t)__popcll(mf);
+            }
         }
     }
 }
@@ -296,7 +396,7 @@ template <int OP, uint32_t THREADS>
 __device__ __forceinline__ void zero_slab(const SelectArgs &A, bool emit, uint32_t slab, const SegDesc &sd,
                                           const TensorDesc &td, const PlanEntry &pe, SegState *st, FinishShared &C)
 {
-    constexpr uint32_t WAVES = THREADS / 64, CTPW = CSLAB_TILES / WAVES;
+    constexpr uint32_t WAVES = THREADS / 64, CTPW = slab_tpw(THREADS);
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = uniform(tid >> 6), end = td.off + td.n;
     if (!emit) {
         if (tid == 0) slab_publish<false>(&A.slabs_done[slab], 0u, 0u, 0u);

@@ -102,6 +102,13 @@ __device__ __forceinline__ uint32_t quad_bits(const SelectArgs &A, uint32_t e0, 
     return in;
 }
 
+// Candidate p of tile t.
+__device__ __forceinline__ const uint2 *candidate(const SelectArgs &A, uint32_t t, uint32_t p)
+{
+    const uint32_t far = A.far0 + t * (CAPT - NEAR) + (p - NEAR), near = A.near0 + t * (NEAR - HEAD) + (p - HEAD);
+    return A.heads + ((p < HEAD) ? t * HEAD + p : (p < NEAR ? near : far));      // (below 2^31: at most 2^22 tiles)
+}
+
 // What a tile's counter word says about tensor td's candidates in tile t: how many, and after
 // how many of the previous tensor's (a first tile shared with it).  An overflowed tile, or a
 // count beyond the slots (a corrupted word), sets ovf and counts as empty.

@@ -188,12 +188,6 @@ struct PartShared {
     uint32_t bc;
 };
 
-// Entry e of a crowded or border tile: heads for q < HEAD, slots beyond.
-__device__ __forceinline__ uint2 tile_entry(const uint2 *hd, const uint2 *sl, uint32_t q)
-{
-    return (q < HEAD) ? hd[q] : sl[q];
-}
-
 // JOIN of a run of tiles: the candidates of tensor j in tiles [sd.tile0, sd.tile0 + sd.ntiles),
 // in index order, through `put(position, entry)`.  Returns the count; `ovf` is set if a tile had
 // overflowed its slots.  Rounds of SEL_THREADS tiles.  Every lane takes one tile's count; a
@@ -264,10 +258,8 @@ __device__ __forceinline__ uint32_t join_part(const SelectArgs &A, const TensorD
             for (uint32_t q = wave; q < nc; q += SEL_WAVES) {
                 const uint32_t slot = P.crowd_slot[q], nv = tile_n[slot], tc = sd.tile0 + r0 + slot;
                 const uint32_t skip = (nv >> 31) ? 0u : HEAD, from = skip ? HEAD : P.start0;
-                const uint2 *hd = A.heads + (size_t)tc * HEAD;
-                const uint2 *sl = A.slots + (size_t)tc * CAPT;
                 for (uint32_t i = skip + lane; i < (nv & 0x7FFFFFFFu); i += 64)
-                    put(tile_pos[slot] + i, tile_entry(hd, sl, from + i - skip));
+                    put(tile_pos[slot] + i, *candidate(A, tc, from + i - skip));
             }
             nc = 0;
         }
@@ -298,7 +290,7 @@ __device__ __forceinline__ uint32_t join_part(const SelectArgs &A, const TensorD
 #pragma unroll
                 for (uint32_t u = 0; u < CU; ++u)
                     if (i < left[u])
-                        e[u] = tile_entry(A.heads + (size_t)tile[u] * HEAD, A.slots + (size_t)tile[u] * CAPT, from[u] + i);
+                        e[u] = *candidate(A, tile[u], from[u] + i);
 #pragma unroll
                 for (uint32_t u = 0; u < CU; ++u)
                     if (i < left[u]) put(at[u] + i, e[u]);

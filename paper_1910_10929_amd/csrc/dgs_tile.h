@@ -85,7 +85,6 @@ __device__ __forceinline__ void tile_tail(const StreamArgs &A, const uint32_t *_
         const uint32_t tauA = tau[tA];
         const uint32_t tauB = (begB != 0xFFFFFFFFu) ? tau[tB] : TAU_NEVER;
         uint2 *myheads = A.heads + (size_t)t * HEAD;
-        uint2 *myslots = A.slots + (size_t)t * CAPT;
         uint32_t run = 0, runA = 0;
         const bool simple = full && !straddle;     // wave-uniform: one tensor, no ragged end
 #pragma unroll
@@ -119,7 +118,7 @@ __device__ __forceinline__ void tile_tail(const StreamArgs &A, const uint32_t *_
                     if (f[j]) {
                         const uint2 ent = make_uint2(e0 + j, __float_as_uint(a[r][j]));
                         if (p < STAGE) stage[p] = ent;
-                        else if (p < CAPT) myslots[p] = ent;
+                        else if (p < CAPT) A.far[(size_t)t * (CAPT - NEAR) + (p - NEAR)] = ent;
                         ++p;
                     }
                 }
@@ -140,7 +139,8 @@ __device__ __forceinline__ void tile_tail(const StreamArgs &A, const uint32_t *_
         if (nst > HEAD) {   // wave-uniform and rare: the spill lines of a crowded tile
             const uint32_t nlines = (nst + HEAD - 1u) / HEAD;
             if (lane >= HEAD && lane < nlines * HEAD)
-                myslots[lane] = (lane < nst) ? stage[lane] : make_uint2(0u, 0u);
+                *(lane < NEAR ? A.near + (size_t)t * (NEAR - HEAD) + (lane - HEAD)
+                              : A.far + (size_t)t * (CAPT - NEAR) + (lane - NEAR)) = (lane < nst) ? stage[lane] : make_uint2(0u, 0u);
         }
         if (!straddle) runA = run;
         if (lane == 0)
