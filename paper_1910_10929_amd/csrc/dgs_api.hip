@@ -30,6 +30,7 @@ size_t align_up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 struct Layout {          // byte offsets inside the workspace
     size_t tile_desc, tdesc, plans, tau, hint2, tprev, ghist, tile_cnt, heads, slots, ord, stats, flag;
     size_t qlist, segtab, grptab, grpcnt, segcnt, segstate, cslabs, dslabs, slabs_done, total;
+    size_t plan_bytes;   // of one plan: its entries and, where the chain is part of the selection's launch, that launch's tables
 };
 
 bool check_offsets(const uint64_t *offsets, uint32_t J)
@@ -84,11 +85,12 @@ uint32_t layout_scale(const uint64_t *offsets, uint32_t J)
     return (uint32_t)(s < 1 ? 1 : (s > 64 ? 64 : s));
 }
 
-Layout make_layout(const uint64_t *offsets, uint32_t J, uint32_t W)
+// one_call: for a single call without hints -- one plan, no list of tiles to sample.
+Layout make_layout(const uint64_t *offsets, uint32_t J, uint32_t W, bool one_call = false)
 {
     const uint64_t n = offsets[J];
     const size_t ntiles = (size_t)((n + TILE - 1) / TILE);
-    size_t nseg_total = 0, ncs = 0, nds = 0;
+    size_t nseg_total = 0, ncs = 0, nds = 0, nwin = 0;
     const uint32_t scale = layout_scale(offsets, J);
     for (uint32_t j = 0; j < J; ++j) {
         const uint32_t ns = tensor_segments(offsets[j], offsets[j + 1] - offsets[j], scale);
@@ -97,12 +99,18 @@ Layout make_layout(const uint64_t *offsets, uint32_t J, uint32_t W)
         nds += dense_slabs(offsets[j], nj);
         if (nj < SEG_MIN_N) continue;
         ncs += chain_slabs(offsets[j], nj, scale);
+        nwin += window_blocks(ns, WINDOW_MAX_ONE);
     }
     Layout L;
     size_t o = 0;
+    L.plan_bytes = (size_t)J * sizeof(PlanEntry);
+    // (a run of parts has at least one slab)
+    const size_t cap = std::min<size_t>(ncs, CHAIN_HERE_ONE);
+    L.plan_bytes += std::min(nwin, cap) * sizeof(SegDesc) + (cap * sizeof(uint32_t) + 15) / 16 * 16;
+    static_assert(sizeof(PlanEntry) % sizeof(SegDesc) == 0 && sizeof(SegDesc) == 16, "tables behind the entries");
     L.tile_desc = o; o = align_up(o + ((size_t)J + 1) * sizeof(uint32_t));   // tensor offsets
     L.tdesc = o;     o = align_up(o + (size_t)J * sizeof(TensorDesc));
-    L.plans = o;     o = align_up(o + (size_t)NPLAN * J * sizeof(PlanEntry));
+    L.plans = o;     o = align_up(o + (one_call ? 1 : NPLAN) * L.plan_bytes);
     L.tau = o;       o = align_up(o + (size_t)(W + 1) * J * sizeof(uint32_t));
     L.hint2 = o;     o = align_up(o + (size_t)(W + 1) * J * sizeof(uint32_t));
     L.tprev = o;     o = align_up(o + (size_t)(W + 1) * J * sizeof(uint32_t));
@@ -113,7 +121,7 @@ Layout make_layout(const uint64_t *offsets, uint32_t J, uint32_t W)
     L.ord = o;       o = align_up(o + (ntiles + J - 1) * CAPT * sizeof(uint2));   // tensor j from its first tile + j on
     L.stats = o;     o = align_up(o + sizeof(DevStats));
     L.flag = o;      o = align_up(o + 64);
-    L.qlist = o;     o = align_up(o + (ntiles + 4) * sizeof(uint32_t));
+    L.qlist = o;     o = align_up(o + (one_call ? 0 : ntiles + 4) * sizeof(uint32_t));
     L.segtab = o;    o = align_up(o + (nseg_total + 1) * sizeof(SegDesc));
     L.grptab = o;    o = align_up(o + (nseg_total + 1) * sizeof(SegDesc));      // groups <= parts
     L.cslabs = o;    o = align_up(o + ncs * sizeof(SegDesc));
@@ -133,6 +141,8 @@ struct PlanSlot {
     int margin = 0;
     int seg_mode = 0;
     uint32_t nseg_active = 0;          // tensors planned as segmented
+    uint32_t nwin = 0, nslab = 0;      // entries of the selection launch's tables (0: the chain has launches of its own)
+    uint32_t window_max = 0;
     uint32_t kmax = 0;                 // largest k_j
     uint64_t K = 0;
     uint64_t wire_words = 0;           // 32-bit words of the wire form's index area
@@ -170,7 +180,7 @@ struct dgs_ctx {
     // device views
     uint32_t *toff = nullptr;
     TensorDesc *tdesc = nullptr;
-    PlanEntry *plans = nullptr;
+    char *plans = nullptr;             // NPLAN * L.plan_bytes
     uint32_t *tau = nullptr;
     uint32_t *hint2 = nullptr;
     uint32_t *tprev = nullptr;
@@ -201,7 +211,7 @@ struct dgs_ctx {
     float *sent = nullptr;             // W rows: what each worker has been sent (model - sent_k form)
     // plan cache
     PlanSlot plan_slot[NPLAN];
-    PlanEntry *plan_stage = nullptr;   // pinned host, NPLAN * J
+    char *plan_stage = nullptr;        // pinned host, NPLAN * L.plan_bytes
     uint32_t *host_total = nullptr;    // pinned host, behind the staging area: the count of a pull without secondary compression
     hipEvent_t counted = nullptr;      // ... and the event that says it is in place, made on the stream's device like the rest
     uint64_t tick = 0;
@@ -346,6 +356,40 @@ bool stream_capturing(const dgs_ctx *c)
     return false;
 }
 
+// The tables of a selection launch that holds the chain's workgroups, behind the plan's entries: the runs of parts
+// whose window histogram a workgroup counts, and the slabs, of the tensors that take the chain.  None of either if
+// there are more than `most` slabs.
+void chain_tables(const dgs_ctx *c, PlanEntry *plan, uint32_t most, uint32_t window_max, uint32_t *nwin, uint32_t *nslab)
+{
+    const uint32_t scale = layout_scale(&c->offsets[0], c->J);
+    uint32_t nw = 0, ns = 0;
+    for (uint32_t j = 0; j < c->J; ++j)
+        if (plan[j].seg) {
+            ns += chain_slabs(c->offsets[j], c->offsets[j + 1] - c->offsets[j], scale);
+            if (ns > most) return;
+        }
+    SegDesc *win = (SegDesc *)(plan + c->J);
+    for (uint32_t j = 0; j < c->J; ++j) {
+        if (!plan[j].seg) continue;
+        const uint64_t off = c->offsets[j], n = c->offsets[j + 1] - off;
+        const uint32_t per = part_tiles(off, n, scale), run = window_parts(c->nseg[j], window_max);
+        const uint32_t tlo = (uint32_t)(off / TILE), tiles = (uint32_t)((off + n - 1) / TILE) - tlo + 1u;
+        for (uint32_t s = 0; s < c->nseg[j]; s += run)
+            win[nw++] = SegDesc{j, tlo + s * per, std::min(run * per, tiles - s * per), s};
+    }
+    uint32_t *slab = (uint32_t *)(win + nw), first = 0;
+    ns = 0;
+    for (uint32_t j = 0; j < c->J; ++j) {
+        const uint64_t off = c->offsets[j], n = c->offsets[j + 1] - off;
+        if (n < SEG_MIN_N) continue;
+        const uint32_t count = chain_slabs(off, n, scale);
+        for (uint32_t s = 0; plan[j].seg && s < count; ++s) slab[ns++] = first + s;
+        first += count;
+    }
+    *nwin = nw;
+    *nslab = ns;
+}
+
 // Returns the cache slot holding the plan for `density`, uploading it if new.  A slot used
 // while the stream was being captured is never evicted afterwards (the captured graph holds
 // its device address), and a plan that would have to be uploaded during capture is refused.
@@ -376,14 +420,23 @@ int get_plan(dgs_ctx *c, double density, uint32_t *slot_out, uint64_t *K_out)
         // the staging area of this slot may still feed an earlier upload
         if (hipStreamSynchronize(c->stream) != hipSuccess) return DGS_EHIP;
     }
-    PlanEntry *stage = c->plan_stage + (size_t)victim * c->J;
+    char *stage_at = c->plan_stage + (size_t)victim * c->L.plan_bytes;
+    PlanEntry *stage = (PlanEntry *)stage_at;
     uint64_t K = 0, wire_words = 0;
     uint32_t active = 0;
     fill_plan(c, density, c->margin_pct, stage, &K, &active, &wire_words);
     if (K >= (1ull << 32)) return DGS_EINVAL;
-    const int rc = upload(c, c->plans + (size_t)victim * c->J, stage, (size_t)c->J * sizeof(PlanEntry));
+    uint32_t nwin = 0, nslab = 0;
+    const uint32_t window_max = (active == 1) ? WINDOW_MAX_ONE : WINDOW_MAX;
+    if (active && density <= DENSE_DENSITY)
+        chain_tables(c, stage, active == 1 ? CHAIN_HERE_ONE : CHAIN_HERE, window_max, &nwin, &nslab);
+    const int rc = upload(c, c->plans + (size_t)victim * c->L.plan_bytes, stage_at,
+                          (size_t)c->J * sizeof(PlanEntry) + nwin * sizeof(SegDesc) + nslab * sizeof(uint32_t));
     if (rc != DGS_OK) return rc;
     PlanSlot &p = c->plan_slot[victim];
+    p.nwin = nwin;
+    p.nslab = nslab;
+    p.window_max = window_max;
     p.valid = true;
     p.captured = false;
     p.density = density;
@@ -399,6 +452,8 @@ int get_plan(dgs_ctx *c, double density, uint32_t *slot_out, uint64_t *K_out)
     *K_out = K;
     return DGS_OK;
 }
+
+const PlanEntry *plan_at(const dgs_ctx *c, uint32_t slot) { return (const PlanEntry *)(c->plans + (size_t)slot * c->L.plan_bytes); }
 
 bool aligned4(const void *p) { return ((uintptr_t)p & 3u) == 0; }
 
@@ -436,7 +491,7 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
     const bool dense_req = density > DENSE_DENSITY;
     const bool exact = !dense_req && (c->force_exact || c->force_sample || c->hint_density[hint_set] != density);
     uint32_t *tau = c->tau + (size_t)hint_set * c->J;
-    const PlanEntry *plan = c->plans + (size_t)slot * c->J;
+    const PlanEntry *plan = plan_at(c, slot);
 
     StreamArgs sa{};
     sa.grad = grad;
@@ -567,7 +622,13 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
     se.ndslabs = c->ndslabs;
     if (!(dense_req && have_seg)) {
         ProfSlot ps(c, prof_select);
-        if (have_seg) launch_window(se, c->stream, ps.ev0);
+        se.nwin = c->plan_slot[slot].nwin;
+        se.nslab = c->plan_slot[slot].nslab;
+        se.window_max = c->plan_slot[slot].window_max;
+        se.wintab = (const SegDesc *)(plan + c->J);
+        se.slabtab = (const uint32_t *)(se.wintab + se.nwin);
+        const bool window = have_seg && se.nwin == 0;
+        if (window) launch_window(se, c->stream, ps.ev0);
         // The row of the printed state moves behind the selection where that saves more than a launch costs: on a
         // server with several workers, whose lists are a few times k entries, clearly from 1400 pairs of a tensor
         // on.  us an event, in the selection / behind it, largest k_j 700, 1000, 1400, 1800, 2400, 3500: one tensor
@@ -576,11 +637,11 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
         // row holds nothing but the message before: 41.1 / 42.9 at 2400, 44.7 / 46.5 at 3500.  (A plan with chain
         // tensors emits and moves their pairs only later.)
         se.later = (op_select == SEL_PULL_V && !have_seg && c->W > 1 && c->plan_slot[slot].kmax > ADD_SENT_K) ? 1u : 0u;
-        launch_select(op_select, se, c->stream, have_seg ? nullptr : ps.ev0, se.later ? nullptr : ps.ev1);
+        launch_select(op_select, se, c->stream, window ? nullptr : ps.ev0, se.later ? nullptr : ps.ev1);
         if (se.later) launch_add_sent(se, (uint32_t)K, c->stream, ps.ev1);
         ps.launched();
     }
-    if (have_seg) {
+    if (have_seg && se.nwin == 0) {
         ProfSlot ps(c, prof_seg);
         if (dense_req) launch_dense(op_select, se, c->stream, ps.ev0, ps.ev1);
         else launch_chain(op_select, se, c->stream, ps.ev0, ps.ev1);
@@ -599,7 +660,7 @@ void carve_workspace(dgs_ctx *c, void *workspace, const Layout &L)
     c->L = L;
     c->toff = (uint32_t *)(c->ws + L.tile_desc);
     c->tdesc = (TensorDesc *)(c->ws + L.tdesc);
-    c->plans = (PlanEntry *)(c->ws + L.plans);
+    c->plans = c->ws + L.plans;
     c->tau = (uint32_t *)(c->ws + L.tau);
     c->hint2 = (uint32_t *)(c->ws + L.hint2);
     c->tprev = (uint32_t *)(c->ws + L.tprev);
@@ -823,10 +884,10 @@ int dgs_create(dgs_ctx **out, const uint64_t *offsets, uint32_t J, uint32_t W, v
     c->nqlist = (uint32_t)qlist.size();
     bool ok = true;
     ok = ok && upload(c, c->qlist, qlist.data(), qlist.size() * sizeof(uint32_t)) == DGS_OK;
-    const size_t stage_bytes = align_up((size_t)NPLAN * J * sizeof(PlanEntry));
+    const size_t stage_bytes = align_up(NPLAN * L.plan_bytes);
     ok = ok && hipEventCreate(&c->counted) == hipSuccess;
     ok = ok && hipHostMalloc((void **)&c->plan_stage, stage_bytes + 64, hipHostMallocDefault) == hipSuccess;
-    if (ok) c->host_total = (uint32_t *)((char *)c->plan_stage + stage_bytes);
+    if (ok) c->host_total = (uint32_t *)(c->plan_stage + stage_bytes);
     ok = ok && upload_tables(c, td.data(), tau0.data(), toff.data(), segs, groups, slabs, dslabs, tabs) == DGS_OK;
     ok = ok && hipStreamSynchronize(c->stream) == hipSuccess;
     ok = ok && hipGetLastError() == hipSuccess;
@@ -940,7 +1001,7 @@ int dgs_worker_step_static(const uint64_t *offsets, uint32_t J, const float *gra
     if (!aligned4(grad) || !aligned4(state) || !aligned4(idx_out) || !aligned4(val_out)) return DGS_EINVAL;
     // limits: the tables live on this call's stack, the workspace in the static array
     if (J > DGS_STATIC_MAX_TENSORS) return DGS_ECAPACITY;
-    const Layout L = make_layout(offsets, J, 0);
+    const Layout L = make_layout(offsets, J, 0, true);
     if (L.total > DGS_STATIC_SCRATCH_BYTES) return DGS_ECAPACITY;
     uint32_t nseg_total = 0;
     for (uint32_t j = 0; j < J; ++j)
@@ -965,7 +1026,8 @@ int dgs_worker_step_static(const uint64_t *offsets, uint32_t J, const float *gra
     SegDesc segs[STATIC_MAX_SEGS + 1];
     SegDesc groups[STATIC_MAX_SEGS + 1], slabs[STATIC_MAX_SLABS];
     uint32_t dslabs[STATIC_MAX_SLABS];
-    PlanEntry plan[DGS_STATIC_MAX_TENSORS];
+    alignas(16) char plan[DGS_STATIC_MAX_TENSORS * sizeof(PlanEntry) + STATIC_MAX_SEGS * sizeof(SegDesc) +
+                          STATIC_MAX_SLABS * sizeof(uint32_t)];
     for (uint32_t j = 0; j <= J; ++j) offs[j] = offsets[j];
     dgs_ctx c;
     c.no_alloc = true;
@@ -1171,7 +1233,7 @@ int dgs_encode(dgs_ctx *c, double density, const uint32_t *idx, const float *val
     if (K + words >= (1ull << 32)) return DGS_EINVAL;      // (the value area is at most K words)
     if (c->validate) launch_fill_u32(c->flag, 0u, 1, c->stream);
     ProfSlot ps(c, DGS_PROF_ENCODE);
-    launch_wire_pack(c->tdesc, c->plans + (size_t)slot * c->J, c->J, (uint32_t)K, (uint32_t)words,
+    launch_wire_pack(c->tdesc, plan_at(c, slot), c->J, (uint32_t)K, (uint32_t)words,
                      c->wire_value_bits, idx, val, (uint32_t *)wire, c->validate ? c->flag : nullptr, c->stream, ps.ev0, ps.ev1);
     ps.launched();
     if (hipGetLastError() != hipSuccess) return DGS_EHIP;
@@ -1194,7 +1256,7 @@ int dgs_decode(dgs_ctx *c, double density, const void *wire, uint32_t *idx_out, 
     if (rc != DGS_OK) return rc;
     if (c->validate) launch_fill_u32(c->flag, 0u, 1, c->stream);
     ProfSlot ps(c, DGS_PROF_DECODE);
-    launch_wire_unpack(c->tdesc, c->plans + (size_t)slot * c->J, c->J, (uint32_t)K, c->wire_value_bits,
+    launch_wire_unpack(c->tdesc, plan_at(c, slot), c->J, (uint32_t)K, c->wire_value_bits,
                        (const uint32_t *)wire, idx_out, val_out, c->validate ? c->flag : nullptr, c->stream, ps.ev0, ps.ev1);
     ps.launched();
     if (hipGetLastError() != hipSuccess) return DGS_EHIP;

@@ -80,6 +80,22 @@ constexpr uint32_t CSLAB_TILES = SEG_TILES < 128 ? SEG_TILES : 128;
 constexpr uint32_t SLAB_TILES = SEG_TILES < 32 ? SEG_TILES : 32;
 constexpr uint32_t SLAB_THREADS = SLAB_TILES / 4 * 64;
 static_assert(SLAB_TILES * TILE >= SMALL_N + TILE && SLAB_TILES <= SEG_TILES, "a small tensor is one slab");
+// The chain in the selection's launch, for plans of at most CHAIN_HERE slabs, or CHAIN_HERE_ONE of a single tensor: two
+// launches less, and the chain runs beside the joins.  Beyond that the workgroups of one launch, one to a compute unit,
+// are too few.  us in one launch / in three: one tensor of 2^20 elements at 1 % (8 slabs) a round 57.0 / 68.7, ResNet-50
+// shapes without momentum (130) 77.0 / 86.2, a server for them 115.4 / 136.5, transformer shapes at 0.1 % (180) 367 / 377;
+// one tensor of 30M at 0.3 % (230) 178.5 / 182, of 100M at 0.1 and 1 % (763) 437 / 458 and 594 / 613, of 250M at 0.3 %
+// (1900) 1098 / 1069; 8 tensors of 96M in all at 1 % (732) 514.5 / 515, transformer shapes at 1 % (800) 603 / 587, 24
+// tensors of 240M 1278 / 1243.
+// (A CPU test build with small parts has layouts on either side of the line.)
+constexpr uint32_t CHAIN_HERE = SEG_TILES < 128 ? 12 : 512, CHAIN_HERE_ONE = SEG_TILES < 128 ? 16 : 1024;
+// There one workgroup counts the window histogram of a run of parts, so that a tensor has at most WINDOW_MAX histograms
+// (the compute unit that adds them up reads 29 bytes a ns), or WINDOW_MAX_ONE where it is the only one (transformer
+// shapes with 16 / 32 / 64 of them 373.5 / 367 / 367.8 us; one tensor of 100M at 0.1 % 510 / 457 / 437; 8 of 96M 521 /
+// 514 / 531).
+constexpr uint32_t WINDOW_MAX = 32, WINDOW_MAX_ONE = 64;
+constexpr uint32_t window_parts(uint32_t nseg, uint32_t most) { return (nseg + most - 1u) / most; }
+constexpr uint32_t window_blocks(uint32_t nseg, uint32_t most) { return (nseg + window_parts(nseg, most) - 1u) / window_parts(nseg, most); }
 constexpr uint32_t SEG_MAX_PER_TENSOR = 512;       // parts per tensor whose list positions fit the selection's LDS
 // Status of a tensor inside one selection call.
 //   SEG_IDLE      nothing decided yet
@@ -124,20 +140,29 @@ struct SegDesc {
     uint32_t sidx;    // index of the segment within its tensor
 };
 
+constexpr uint32_t CHAIN_STATUS_SHIFT = 20, KEY_READY = 0x80000000u;      // (pfx: 31 - SEG_LOWBITS bits)
+
 struct SegState {        // per tensor, rewritten by every selection
     uint32_t status;     // SegStatus
     uint32_t pfx;        // key >> SEG_LOWBITS of the k-th entry (dense request: its leading bits so far)
     uint32_t r2;         // its rank among the entries sharing that prefix (SEG_ZERO: the zeros to add)
     uint32_t T;          // the k-th key
     uint32_t rT;         // how many of the entries equal to it are taken (lowest index first)
-    uint32_t ready;      // 1: T and rT are in place (chain)
-    uint32_t pad0, pad1;
     // Hand-over between the workgroups of one launch (all zero between launches):
-    uint32_t arrive[4];  // parts that have finished: [0] join, [1] re-histogram, [2] re-collection, [3] chain prefix
     uint32_t verdict;    // 0 = not decided; else 0x100 | SegStatus, written by the last joining part
     uint32_t tau_ready;  // 1: the fresh threshold of a pending tensor is in place
+    uint32_t pad0;
+    uint2 chain;         // the chain in the selection's launch: 0 = not decided; else r2, and status << CHAIN_STATUS_SHIFT | pfx
+    uint2 key;           // chain: 0 = not ranked; else rT, and KEY_READY | T (one store either, which needs no second)
+    uint32_t pad1[20];
+    // What is counted in, on a line of its own: a line that is added to all the time is fetched anew by everybody who
+    // polls a word of it (transformer shapes, 180 slabs of one tensor: the arrivals alone took 7 us).
+    uint32_t arrive[4];  // parts that have finished: [0] join, [1] re-histogram, [2] re-collection, [3] chain prefix
     uint32_t seen[2];    // readers of verdict / tau_ready that have passed (the last one clears)
+    uint32_t chain_seen; // the same for chain and key
+    uint32_t pad2[25];
 };
+static_assert(sizeof(SegState) == 256, "two lines of 128 bytes");
 
 struct DevStats {
     unsigned long long fallback_tensors;
@@ -215,6 +240,12 @@ struct SelectArgs {
     uint32_t later;               // SEL_PULL_V: k_add_sent moves the row behind the selection kernel, which leaves it alone
     const uint32_t *dslabs;       // dense requests: the tensor of every slab (run of SLAB_TILES tiles of a tensor), tensor after tensor
     uint32_t ndslabs;
+    // The chain in the selection's launch: its workgroups' runs of parts (sidx: the first part; ntiles: of the whole
+    // run), and the slabs of the tensors that take it.  nwin = 0: it has launches of its own.
+    const SegDesc *wintab;
+    const uint32_t *slabtab;
+    uint32_t nwin, nslab;
+    uint32_t window_max;          // histograms of a tensor at most
 };
 
 // Host-callable launchers (defined next to the kernels).

@@ -2,7 +2,7 @@
 // exact k-th largest magnitude with the lowest-index tie rule ("thr <- R% of |x|" in
 // Algorithms 1-3), the ordered emission ("encode()"), the state fix-up (Eq. 12 / Eq. 6) and
 // the next threshold hint -- all tensors in one launch.
-#include "dgs_select.h"
+#include "dgs_chain.h"
 
 namespace dgs {
 
@@ -433,25 +433,34 @@ __device__ __forceinline__ uint32_t dense_compact(const SelectArgs &A, const Ten
 // own, or, collected again, the one the parts have added to in ghist) -> the 19-bit prefix of the
 // k-th key, its rank among the entries sharing it, and the next hint.  Returns the tensor's status (SEG_ACTIVE / SEG_LISTS, or 0 = failed);
 // thread 0 writes segstate / hints.
-template <int OP>
+template <int OP, bool HERE>
 __device__ __forceinline__ uint32_t window_step(const SelectArgs &A, const TensorDesc &td, const PlanEntry &pe,
-                                                uint32_t j, uint32_t c, bool ovf, uint32_t tau_cur, uint32_t tprev_cur,
-                                                bool exact_mode, bool lists, PartShared &P)
+                                                uint32_t j, uint32_t &c, bool &ovf, uint32_t tau_cur, uint32_t tprev_cur,
+                                                uint32_t hint2_cur, bool exact_mode, bool lists, PartShared &P)
 {
     const uint32_t tid = threadIdx.x;
     uint32_t *h = P.S.h;
     uint32_t *gh = A.ghist + (size_t)j * HBINS;
-    uint32_t mylow = 0xFFFFFFFFu;
+    uint32_t mylow = 0xFFFFFFFFu, cnt = 0;
     if (tid == 0) P.S.kmin = 0xFFFFFFFFu;
+    if (HERE && !lists && tid < window_blocks(td.nseg, A.window_max)) cnt = ld_dev(&A.segcnt[td.seg_first + tid * window_parts(td.nseg, A.window_max)]);
     if (!lists) {
         // four counters per load, every other part: a tensor of 90 parts costs a thread 45 loads
         static_assert(SEG_WBINS == 2 * SEL_THREADS, "two threads per four counters");
         const uint32_t b4 = tid & (SEL_THREADS / 2 - 1u), half = tid / (SEL_THREADS / 2);
         const uint4 *ph = (const uint4 *)part_hist(A, td, j, 0) + b4;
         uint4 sum = make_uint4(0, 0, 0, 0);
+        const uint32_t nh = HERE ? window_blocks(td.nseg, A.window_max) : td.nseg;
 #pragma unroll 8
-        for (uint32_t s = half; s < td.nseg; s += 2) {
-            const uint4 v = ph[(size_t)s * (SEG_WBINS / 4)];
+        for (uint32_t s = half; s < nh; s += 2) {
+            uint4 v;
+            if (HERE) {      // written in this launch
+                const uint2 *p = (const uint2 *)(ph + (size_t)s * (SEG_WBINS / 4));
+                const uint2 a = ld_dev(p), b = ld_dev(p + 1);
+                v = make_uint4(a.x, a.y, b.x, b.y);
+            } else {
+                v = ph[(size_t)s * (SEG_WBINS / 4)];
+            }
             sum.x += v.x;
             sum.y += v.y;
             sum.z += v.z;
@@ -474,11 +483,16 @@ __device__ __forceinline__ uint32_t window_step(const SelectArgs &A, const Tenso
         }
         if (v && mylow == 0xFFFFFFFFu) mylow = b;
     }
-    if (mylow != 0xFFFFFFFFu) atomicMin(&P.S.kmin, mylow);
+    mylow = wave_min_to_last(mylow);
+    if (lane_id() == 63 && mylow != 0xFFFFFFFFu) atomicMin(&P.S.kmin, mylow);
+    if (HERE && !lists) {
+        c = block_sum(cnt & 0x7FFFFFFFu, P.S.wsum, SEL_WAVES);
+        ovf = __syncthreads_or((int)(cnt >> 31)) != 0;
+    }
     const uint32_t win_base = seg_window_base(tau_cur, tprev_cur);
     const int bin_min = (win_base > (tau_cur >> SEG_LOWBITS)) ? 1 : 0;   // bin 0 mixes in lower keys
     uint32_t R = 0, Eq = 0;
-    if (A.write_hint) R = hint_rank<OP>(td, pe, !exact_mode, c, A.hint2[j], A.m, A.young, &Eq);
+    if (A.write_hint) R = hint_rank<OP>(td, pe, !exact_mode, c, hint2_cur, A.m, A.young, &Eq);
     const bool measurable = (R != 0) && (c >= R);
     const uint32_t qlow = max(c / 4u, min(c, 16u));
     const uint32_t third = measurable ? Eq : ((R != 0 && c != 0) ? (c - qlow + 1u) : 0u);
@@ -490,8 +504,8 @@ __device__ __forceinline__ uint32_t window_step(const SelectArgs &A, const Tenso
         SegState *st = &A.segstate[j];
         st->pfx = win_base + (uint32_t)bk;
         st->r2 = (uint32_t)P.S.res[1];
-        st->T = 0;
-        st->ready = 0;
+        // (the slabs go on while the hint is worked out)
+        if (HERE && !lists) st_dev(&st->chain, make_uint2(st->r2, ((uint32_t)SEG_ACTIVE << CHAIN_STATUS_SHIFT) | st->pfx));
         atomicAdd(&A.stats->candidates, (unsigned long long)c);
         atomicAdd(&A.stats->segmented_tensors, 1ull);
         if (A.write_hint) {
@@ -825,7 +839,7 @@ __device__ __forceinline__ uint32_t trim_list(const SelectArgs &A, const Src &sr
 //   (null: nobody waits); a success is published as soon as it is certain, before the work.
 //   tau_cur, tprev_cur: the threshold the lists were collected with and the anchor of the window
 //   histograms (handed in: in round 1 they were published by another workgroup of this launch).
-template <int OP>
+template <int OP, bool HERE>
 __device__ __forceinline__ uint32_t tensor_select(const SelectArgs &A, const TensorDesc &td, const PlanEntry &pe,
                                                   uint32_t j, int round, bool multi, bool by_parts, uint32_t c0,
                                                   bool ovf0, uint32_t kmin0, uint32_t tau_cur, uint32_t tprev_cur,
@@ -870,9 +884,9 @@ __device__ __forceinline__ uint32_t tensor_select(const SelectArgs &A, const Ten
     }
     uint32_t status = 0;
     bool early = false;      // the verdict went out before the work
+    if (pe.seg) status = window_step<OP, HERE>(A, td, pe, j, c, ovf, tau_cur, tprev_cur, hint2_cur, exact_mode, round != 0, P);
     // every nonzero is in the lists
     const bool zerofill = !ovf && c < pe.k && tau_cur <= 1u && (!multi || have_pbase);
-    if (pe.seg) status = window_step<OP>(A, td, pe, j, c, ovf, tau_cur, tprev_cur, exact_mode, round != 0, P);
     if (status == 0 && zerofill) {
         // the message is completed with the tensor's lowest-index zeros
         early = true;
@@ -884,7 +898,7 @@ __device__ __forceinline__ uint32_t tensor_select(const SelectArgs &A, const Ten
             if (tid == 0) {
                 SegState *st = &A.segstate[j];
                 st->r2 = pe.k - c;
-                st->T = st->rT = st->ready = 0;
+                st->pfx = 0;
                 atomicAdd(&A.stats->segmented_tensors, 1ull);
             }
         } else if (multi) {
@@ -974,6 +988,15 @@ __device__ __forceinline__ uint32_t tensor_select(const SelectArgs &A, const Ten
         atomicAdd(&A.stats->repaired_tensors, 1ull);
     }
     if (tid == 0) A.segstate[j].status = status;
+    if (HERE && pe.seg && status != SEG_PENDING && status != SEG_ACTIVE) {      // the slabs of this launch go on
+        wait_mem();
+        __syncthreads();
+        if (tid == 0) {
+            SegState *st = &A.segstate[j];
+            const bool done = status == SEG_DONE;
+            st_dev(&st->chain, make_uint2(done ? 0u : st->r2, (status << CHAIN_STATUS_SHIFT) | (done ? 0u : st->pfx)));
+        }
+    }
     if (verdict && !early) {
         wait_mem();
         __syncthreads();
@@ -990,7 +1013,7 @@ __device__ __forceinline__ uint32_t tensor_select(const SelectArgs &A, const Ten
 
 // RE-HISTOGRAM (role 1) or RE-COLLECTION (role 2) of one part of a tensor that the JOIN left
 // pending (the caller has seen that verdict).
-template <int OP>
+template <int OP, bool HERE>
 __device__ __forceinline__ void recollect_part(const SelectArgs &A, uint32_t role, uint32_t part, PartShared &P,
                                                uint2 *llist)
 {
@@ -1062,21 +1085,45 @@ __device__ __forceinline__ void recollect_part(const SelectArgs &A, uint32_t rol
         st_dev(&A.segcnt[part], min(c2, 0x7FFFFFFFu) | (c2 > part_cap ? 0x80000000u : 0u));
     }
     if (!arrive_last(&st->arrive[2], td.nseg, &P.bc)) return;
-    tensor_select<OP>(A, td, pe, j, 1, true, true, 0u, false, 0xFFFFFFFFu, tau_new, tprev_new, 0xFFFFFFFFu, false,
+    tensor_select<OP, HERE>(A, td, pe, j, 1, true, true, 0u, false, 0xFFFFFFFFu, tau_new, tprev_new, 0xFFFFFFFFu, false,
                       nullptr, P, llist);
 }
 
-template <int OP>
+// The chain's first part inside the selection's launch: the window histogram of a run of parts of a tensor.  The
+// workgroup that arrives last for the tensor returns true.
+__device__ __forceinline__ bool window_run(const SelectArgs &A, const SegDesc &run, const TensorDesc &td, uint32_t tau_cur,
+                                           uint32_t tprev_cur, PartShared &P)
+{
+    const uint32_t tid = threadIdx.x, per = window_parts(td.nseg, A.window_max), nb = window_blocks(td.nseg, A.window_max);
+    bool ovf;
+    const uint32_t c = window_tiles(A, td, run.tile0, run.ntiles, seg_window_base(tau_cur, tprev_cur), P.S.h, P.S.wsum, ovf);
+    uint2 *out = (uint2 *)part_hist(A, td, run.j, run.sidx / per);
+    for (uint32_t b = tid; b < SEG_WBINS / 2; b += SEL_THREADS) st_dev(&out[b], make_uint2(P.S.h[2 * b], P.S.h[2 * b + 1]));
+    if (tid == 0) st_dev(&A.segcnt[td.seg_first + run.sidx], c | (ovf ? 0x80000000u : 0u));
+    return arrive_last(&A.segstate[run.j].arrive[0], nb, &P.bc);
+}
+
+// HERE: the chain's workgroups are in this launch, for the tensors that take it: before the others one per run of parts
+// (the window histograms), behind them two per slab.  (They have no use for most of the LDS, but with 128 registers
+// there is one workgroup on a compute unit anyway.)
+template <int OP, bool HERE>
 __global__ __launch_bounds__(SEL_THREADS) void k_select(const SelectArgs A)
 {
     __shared__ PartShared P;
     __shared__ uint2 llist[SEL_LDS_LIST];
     const uint32_t tid = threadIdx.x;
-    if (blockIdx.x >= A.ngroups) {
+    const bool window = HERE && blockIdx.x < A.nwin;
+    const uint32_t block = HERE ? blockIdx.x - A.nwin : blockIdx.x;      // (of the roles behind those)
+    if (!window && block >= A.ngroups) {
         // RE-HISTOGRAM / RE-COLLECTION: this workgroup looks after up to B_GROUP parts, nb apart,
         // so that the parts of one failed tensor are spread over as many workgroups as there are
         const uint32_t nb = (A.nparts + A.bgroup - 1) / A.bgroup;
-        const uint32_t b = blockIdx.x - A.ngroups;
+        const uint32_t b = block - A.ngroups, standby = A.repair ? 2u * nb : 0u;
+        if (HERE && b >= standby) {
+            const uint32_t s = b - standby;
+            finish_slab<OP, SEL_THREADS, true>(A, s >= A.nslab, A.slabtab[s < A.nslab ? s : s - A.nslab], *(FinishShared *)llist);
+            return;
+        }
         const uint32_t role = (b < nb) ? 1u : 2u;
         const uint32_t first = (role == 1) ? b : b - nb;
         // the verdicts of the tensors these parts belong to: lane i waits for part i's tensor and
@@ -1101,10 +1148,10 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const SelectArgs A)
         }
         __syncthreads();
         for (uint32_t i = 0; i < A.bgroup; ++i)
-            if ((P.vbuf[i] & 0xFFu) == SEG_PENDING) recollect_part<OP>(A, role, first + i * nb, P, llist);
+            if ((P.vbuf[i] & 0xFFu) == SEG_PENDING) recollect_part<OP, HERE>(A, role, first + i * nb, P, llist);
         return;
     }
-    const SegDesc sd = A.grptab[blockIdx.x];      // this workgroup's join group
+    const SegDesc sd = window ? A.wintab[blockIdx.x] : A.grptab[block];      // this workgroup's join group, or run of parts
     const uint32_t j = sd.j;
     const TensorDesc td = A.tdesc[j];
     const PlanEntry pe = A.plan[j];
@@ -1117,6 +1164,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const SelectArgs A)
 
     {
         // ------------------------------------------------------------------ JOIN
+        if (HERE && !window && pe.seg) return;
         if (!td.big || A.dense) {
             if (sd.sidx != 0) return;
             if (tid == 0) st->status = SEG_DONE;
@@ -1137,22 +1185,26 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const SelectArgs A)
         if (pe.seg) {
             // a tensor that takes the chain: its parts have counted their candidates already, and
             // one workgroup reads the result
-            if (sd.sidx != 0) return;
-            uint32_t o = 0, mine = 0;
-            for (uint32_t p = tid; p < td.nseg; p += SEL_THREADS) {
-                const uint32_t v = A.segcnt[td.seg_first + p];
-                mine += v & 0x7FFFFFFFu;
-                o |= v >> 31;
+            if (HERE) {
+                if (!window_run(A, sd, td, tau_cur, tprev_cur, P)) return;
+            } else {
+                if (sd.sidx != 0) return;
+                uint32_t o = 0, mine = 0;
+                for (uint32_t p = tid; p < td.nseg; p += SEL_THREADS) {
+                    const uint32_t v = A.segcnt[td.seg_first + p];
+                    mine += v & 0x7FFFFFFFu;
+                    o |= v >> 31;
+                }
+                cs = block_sum(mine, P.S.wsum, SEL_WAVES);
+                ovf = __syncthreads_or((int)o) != 0;
             }
-            cs = block_sum(mine, P.S.wsum, SEL_WAVES);
-            ovf = __syncthreads_or((int)o) != 0;
-            status = tensor_select<OP>(A, td, pe, j, 0, false, true, cs, ovf, kmin, tau_cur, tprev_cur, win_join,
+            status = tensor_select<OP, HERE>(A, td, pe, j, 0, false, true, cs, ovf, kmin, tau_cur, tprev_cur, win_join,
                                        false, verdict, P, llist);
         } else if (multi) {
             cs = join_part(A, td, sd, P, ovf, [&](uint32_t pos, uint2 e) { st_dev(&plist[pos], e); });
-            if (tid == 0) st_dev(&A.grpcnt[blockIdx.x], cs | (ovf ? 0x80000000u : 0u));
+            if (tid == 0) st_dev(&A.grpcnt[block], cs | (ovf ? 0x80000000u : 0u));
             if (!arrive_last(&st->arrive[0], td.ngrp, &P.bc)) return;
-            status = tensor_select<OP>(A, td, pe, j, 0, true, false, cs, ovf, kmin, tau_cur, tprev_cur, win_join, true,
+            status = tensor_select<OP, HERE>(A, td, pe, j, 0, true, false, cs, ovf, kmin, tau_cur, tprev_cur, win_join, true,
                                        verdict, P, llist);
         } else {
             for (uint32_t b = tid; b < WIN_BINS; b += SEL_THREADS) P.S.h[b] = 0;
@@ -1169,7 +1221,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const SelectArgs A)
             wait_mem();
             __syncthreads();
             kmin = P.S.kmin;
-            status = tensor_select<OP>(A, td, pe, j, 0, false, false, cs, ovf, kmin, tau_cur, tprev_cur, win_join, true,
+            status = tensor_select<OP, HERE>(A, td, pe, j, 0, false, false, cs, ovf, kmin, tau_cur, tprev_cur, win_join, true,
                                        verdict, P, llist);
         }
         if (has_parts) return;        // the re-collecting workgroups have the verdict
@@ -1214,7 +1266,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const SelectArgs A)
         wait_mem();
         __syncthreads();
         // kmin unknown (0 keeps the window honest: it is counted again from the list)
-        tensor_select<OP>(A, td, pe, j, 1, false, true, c2, c2 > cap, tau_new, tau_new, tprev_new, 0xFFFFFFFFu, false,
+        tensor_select<OP, HERE>(A, td, pe, j, 1, false, true, c2, c2 > cap, tau_new, tau_new, tprev_new, 0xFFFFFFFFu, false,
                           nullptr, P, llist);
         return;
     }
@@ -1246,15 +1298,22 @@ void launch_add_sent(const SelectArgs &a, uint32_t K, void *stream, void *ev1)
              (const uint32_t *)a.out_idx, (const float *)a.out_val, K, (const DevStats *)a.stats);
 }
 
+template <int OP>
+static void launch_select_t(const SelectArgs &a, hipStream_t st, void *ev0, void *ev1)
+{
+    const uint32_t nb = (a.nparts + a.bgroup - 1) / a.bgroup;
+    const uint32_t blocks = a.ngroups + (a.repair ? 2u * nb : 0u);
+    if (a.nwin) launch_k(k_select<OP, true>, dim3(a.nwin + blocks + 2u * a.nslab), dim3(SEL_THREADS), st, ev0, ev1, a);
+    else launch_k(k_select<OP, false>, dim3(blocks), dim3(SEL_THREADS), st, ev0, ev1, a);
+}
+
 void launch_select(int op, const SelectArgs &a, void *stream, void *ev0, void *ev1)
 {
     hipStream_t st = (hipStream_t)stream;
     if (a.ngroups == 0) return;
-    const uint32_t nb = (a.nparts + a.bgroup - 1) / a.bgroup;
-    const dim3 grid(a.ngroups + (a.repair ? 2u * nb : 0u)), block(SEL_THREADS);
-    if (op == SEL_WORKER) launch_k(k_select<SEL_WORKER>, grid, block, st, ev0, ev1, a);
-    else if (op == SEL_PULL) launch_k(k_select<SEL_PULL>, grid, block, st, ev0, ev1, a);
-    else launch_k(k_select<SEL_PULL_V>, grid, block, st, ev0, ev1, a);
+    if (op == SEL_WORKER) launch_select_t<SEL_WORKER>(a, st, ev0, ev1);
+    else if (op == SEL_PULL) launch_select_t<SEL_PULL>(a, st, ev0, ev1);
+    else launch_select_t<SEL_PULL_V>(a, st, ev0, ev1);
 }
 
 }  // namespace dgs

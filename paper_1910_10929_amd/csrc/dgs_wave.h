@@ -134,6 +134,24 @@ __device__ __forceinline__ uint32_t wait_word(const uint32_t *p, uint32_t limit,
     return *bc;
 }
 
+// The same for two words that are written in one store, of which the second says that they are.
+__device__ __forceinline__ uint2 wait_pair(const uint2 *p, uint32_t limit, uint32_t *bc)
+{
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint2 v = make_uint2(0u, 0u);
+        for (uint32_t spin = 0; spin < limit; ++spin) {
+            v = ld_dev(p);
+            if (v.y != 0) break;
+            __builtin_amdgcn_s_sleep(4);
+        }
+        bc[0] = v.x;
+        bc[1] = v.y;
+    }
+    __syncthreads();
+    return make_uint2(bc[0], bc[1]);
+}
+
 // `count` readers of a hand-over word have passed; whoever completes the `readers` clears the
 // word and the count for the next launch.  Call from one thread.
 __device__ __forceinline__ void reader_done(uint32_t *seen, uint32_t readers, uint32_t count, uint32_t *word)
