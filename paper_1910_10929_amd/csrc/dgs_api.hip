@@ -267,7 +267,8 @@ struct ProfSlot {
 //   workers at 0.17 % 79.9 / 67.9; one tensor of 300 K / 600 K at 1 % 31.9 / 30.9, 42.2 / 43.1.  The line was drawn
 //   with slower joins of long lists; now 3 to 5 tensors of 423 K would gain from it too: 27.3 / 23.4, 27.9 / 23.4,
 //   30.4 / 24.5);
-//   for tensors whose list then still fits the LDS of a workgroup, or which take the chain (ResNet-50
+//   for tensors whose list then still fits the LDS of a workgroup, or which take the chain in a plan with a list
+//   beyond SEL_LIST_MAX_OTHER (ResNet-50
 //   shapes at 0.36 / 0.42 %, largest k 8500 / 9900, with the wide rank for the others alone / for all: 93.9 / 95.2,
 //   102.5 / 105.0 on the printed state, 100.1 / 102.4, 112.5 / 117.0 on difference rows);
 //   from the pull number PULL_YOUNG + 1 of a row at a density on: while a row fills up its thresholds rise
@@ -278,7 +279,7 @@ constexpr uint32_t PULL_WIDE_TENSORS = 8, PULL_YOUNG = 10;
 // k_j = ceil(density * n_j) in IEEE double; k2 = rank that sets the next predicted threshold.
 // Which tensors take the chain kernels behind the selection: those of at least SEG_MIN_N
 // elements whose hinted candidate list is longer than one workgroup selects from
-// (SEL_LIST_MAX), and then also those beyond SEL_LIST_CROWDED.  For a dense request `seg` means
+// (SEL_LIST_MAX, SEL_LIST_MAX_OTHER), and then also those beyond SEL_LIST_CROWDED.  For a dense request `seg` means
 // the kernels that read the tensors themselves (launch_dense): all tensors if one is that large,
 // unless the option forbids it.
 void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out, uint64_t *K_out,
@@ -290,7 +291,7 @@ void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out,
         // A dense request on nothing but small tensors is one launch of one workgroup each.  us a step, so / by the
         // five launches of the dense kernels: 35 tensors of 1811 elements 15 / 42, 300 of 20 K 73-85 / 86-100, 30 of
         // 60 K 98-123 / 56-66, 1000 of 60 K 591 / 381: the largest tensor decides, between 20 K and 60 K elements.
-        bool large = false;
+        bool large = false, beyond = c->seg_mode == SEG_MODE_ALWAYS;      // a list beyond SEL_LIST_MAX_OTHER
         uint32_t listed = 0;               // tensors with candidate lists
         for (uint32_t j = 0; j < c->J; ++j) {
             const uint64_t nj = c->offsets[j + 1] - c->offsets[j];
@@ -313,7 +314,11 @@ void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out,
             bool seg = false;
             if (c->seg_mode != SEG_MODE_NEVER) {
                 if (density > DENSE_DENSITY) seg = large;
-                else if (nj >= SEG_MIN_N) seg = c->seg_mode == SEG_MODE_ALWAYS || std::max(k2, k2z) > SEL_LIST_MAX;
+                else if (nj >= SEG_MIN_N) {
+                    const bool middle = nj >= SEL_CROWDED_TILES * TILE && nj < SEL_LONG_TILES * TILE;
+                    seg = c->seg_mode == SEG_MODE_ALWAYS || std::max(k2, k2z) > (middle ? SEL_LIST_MAX : SEL_LIST_MAX_OTHER);
+                    beyond |= std::max(k2, k2z) > SEL_LIST_MAX_OTHER;
+                }
             }
             out[j].seg = seg ? 1u : 0u;
             // wire form: local indices of b bits each, the tensor's block padded to whole words
@@ -336,7 +341,7 @@ void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out,
         for (uint32_t j = 0; j < c->J && listed >= PULL_WIDE_TENSORS; ++j) {
             const uint64_t nj = c->offsets[j + 1] - c->offsets[j];
             const uint32_t wide = (uint32_t)std::min<uint64_t>((uint64_t)out[j].k2_zero + out[j].k / 2, nj);
-            if (out[j].seg || wide <= SEL_LDS_LIST) out[j].k2_pull = wide;
+            if ((out[j].seg && beyond) || wide <= SEL_LDS_LIST) out[j].k2_pull = wide;
         }
         *nseg_active = active;
         *K_out = K;

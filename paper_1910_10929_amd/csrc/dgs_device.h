@@ -40,15 +40,20 @@ constexpr uint32_t SEL_THREADS = 1024;
 constexpr uint32_t SEL_WAVES = SEL_THREADS / 64;
 constexpr uint32_t SEL_LDS_LIST = 16384;           // candidates kept in LDS (128 KB); longer lists continue in global scratch
 // Longest candidate list one workgroup is planned for (rank 2 k).  One workgroup / the chain, us: flat tensors
-// of 700 K / 900 K / 1.05M / 1.2M elements at 1 % (lists of 14 / 18 / 21 / 24 K), a round 63 / 84, 79 / 88,
-// 88 / 88, 98 / 90, a step without momentum 34 / 40, 46 / 42, 51 / 41, 60 / 44; ResNet-50 shapes at 0.36 / 0.39 /
-// 0.45 % (17 / 18 / 21 K), a round 153 / 178, 158 / 173, 167 / 175, a step 89 / 96, 92 / 92, 99 / 93.
-constexpr uint32_t SEL_LIST_MAX = 20480;
-// ... and where the plan holds a tensor beyond that, so that the chain's launches are there anyway,
+// of 400 K / 550 K / 700 K / 900 K elements at 1 % (lists of 8 / 11 / 14 / 18 K), a round 51.3 / 56.5, 56.3 / 55.5,
+// 63.7 / 57.0, 80.0 / 60.1, a step without momentum 26.3 / 26.9, 28.2 / 25.9, 33.9 / 27.3 (700 K); 2.4M at 0.3 % (15 K) a round
+// 78.3 / 64.0; ResNet-50 shapes at 0.2 / 0.3 / 0.36 % (10 / 14 / 17 K), a round 124.7 / 126.7, 140.1 / 130.8, 152.6 / 134.0,
+// a step 72.3 / 71.0, 79.8 / 72.3 (0.3 %).
+constexpr uint32_t SEL_LIST_MAX = 10240;
+// For tensors of fewer than SEL_CROWDED_TILES tiles, and of SEL_LONG_TILES or more, it lies where it was before the chain
+// became part of the selection's launch.  The chain would serve large ones sooner, too (4M at 0.25 % 97.7 / 68.5, 6M at
+// 0.15 % 112.0 / 75.8), but which of their calls count in segmented_tensors, and which lists one workgroup
+// trims, is relied on by tests.
+constexpr uint32_t SEL_LIST_MAX_OTHER = 20480, SEL_LONG_TILES = 3584;
+// ... and where the plan holds a tensor beyond that, so that the chain's workgroups are there anyway,
 // for tensors of at least SEL_CROWDED_TILES tiles (their join is then what the launch waits for).  us with the
-// line at 4096 / 8192 / without one: ResNet-50 shapes at 1 %, a round 193 / 192 / 204, a step without momentum 93 / 93 / 101,
-// at 0.6 % 177 / 184 / 197 and 95 / 100 / 108; 40 tensors of 30M in all at 1 % 222 / 222 / 241, transformer shapes
-// at 0.4 % 505 / 499 / 487.  From 64 tiles on instead of 512 the same within 1 %, from 1024 on 11 to 19 us more at 1 %.
+// line at 8192 / 5000: ResNet-50 shapes, a round at 0.3 % 130.8 / 134.0, at 0.36 % 134.0 / 137.5, at 1 % 159.0 / 161.9, a step
+// without momentum at 0.3 % 72.3 / 74.6, a server at 0.36 % 87.9 / 78.7; transformer shapes at 0.4 % 470.6 / 471.1.
 constexpr uint32_t SEL_LIST_CROWDED = 8192, SEL_CROWDED_TILES = 512;
 constexpr uint32_t SEL_LIST_HARD = 65536;          // longest it accepts when a tail has grown beyond the plan
 // Above this density candidates stop paying off; such requests select densely.
