@@ -668,11 +668,11 @@ __device__ __forceinline__ void dense_select(const SelectArgs &A, const TensorDe
             lv[p] = __float_as_uint(row_value<OP>(A.state, A.model, td.off + p));
         __syncthreads();
         SrcDenseLds src{lv, td.off};
-        select_emit<OP, 4>(src, td.n, pe.k, R, 0u, 0xFFFFFFFFu, 0u, false, 0xFFFFFFFFu, P.S, A, pe.outoff,
+        select_emit<OP, 2>(src, td.n, pe.k, R, 0u, 0xFFFFFFFFu, 0u, false, 0xFFFFFFFFu, P.S, A, pe.outoff,
                            &tau_next, &expect, &q_e, &t_k);
     } else {
         SrcDense<OP> src{A.state, A.model, td.off};
-        select_emit<OP, 8>(src, td.n, pe.k, R, 0u, 0xFFFFFFFFu, 0u, false, 0xFFFFFFFFu, P.S, A, pe.outoff,
+        select_emit<OP, 4>(src, td.n, pe.k, R, 0u, 0xFFFFFFFFu, 0u, false, 0xFFFFFFFFu, P.S, A, pe.outoff,
                            &tau_next, &expect, &q_e, &t_k);
     }
     if (td.big && A.write_hint && tid == 0) {
@@ -709,11 +709,11 @@ __device__ __forceinline__ void list_select(const SelectArgs &A, const TensorDes
     const uint32_t win_min = (anchored && win_join > (kmin >> win_shift(OP))) ? 1u : 0u;   // entries below the window
     if (c <= SEL_LDS_LIST) {
         SrcList src{llist};
-        select_emit<OP, 4>(src, c, pe.k, R, Eq, win_base, win_min, win_ready, kmin, P.S, A, pe.outoff,
+        select_emit<OP, 3>(src, c, pe.k, R, Eq, win_base, win_min, win_ready, kmin, P.S, A, pe.outoff,
                            &tau_next, &expect, &q_e, &t_k);
     } else {
         SrcSplit src{llist, glist};     // the list outgrew LDS: its tail is read from global scratch
-        select_emit<OP, 8>(src, c, pe.k, R, Eq, win_base, win_min, win_ready, kmin, P.S, A, pe.outoff,
+        select_emit<OP, 4>(src, c, pe.k, R, Eq, win_base, win_min, win_ready, kmin, P.S, A, pe.outoff,
                            &tau_next, &expect, &q_e, &t_k);
     }
     if (A.write_hint && tid == 0) {
