@@ -1233,7 +1233,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const SelectArgs A)
         pick_from_hist<SEL_WAVES>(lh, pe, P.S.rowsum, P.S.res, tau_new, tprev_new);
         if (tid == 0) {
             A.tau[j] = tau_new;
-            A.tprev[j] = tprev_new;
+            st_dev(&A.tprev[j], tprev_new);      // (the chain's ranking writes this word in the same launch)
             P.bc = tau_new;
         }
         __syncthreads();

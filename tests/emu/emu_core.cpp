@@ -31,6 +31,66 @@ uint64_t most_adds()
     return most;
 }
 
+// The watched buffer: what it held when the running workgroup began, and per word which workgroup of the launch has
+// written it with an ordinary store (block index + 1), or that the running one has written it device-wide.
+static uint32_t *watched = nullptr;
+static size_t watched_words = 0;
+static std::vector<uint32_t> before, owner;
+static std::vector<bool> through;
+static std::vector<size_t> through_list;
+static uint64_t mixed = 0;
+
+void watch(void *p, size_t bytes)
+{
+    watched = (uint32_t *)p;
+    watched_words = p ? bytes / 4 : 0;
+    before.assign(watched, watched + watched_words);
+    owner.assign(watched_words, 0u);
+    through.assign(watched_words, false);
+    through_list.clear();
+}
+
+uint64_t mixed_words() { return mixed; }
+
+void device_access(const void *p, size_t bytes, bool write)
+{
+    const uint32_t *w = (const uint32_t *)p;
+    if (w < watched || w >= watched + watched_words) return;
+    for (size_t i = (size_t)(w - watched), e = i + bytes / 4; i < e; ++i) {
+        if (owner[i] != 0 && owner[i] != blockIdx.x + 1u && mixed++ == 0)
+            fprintf(stderr, "emu: word %zu: written with an ordinary store by workgroup %u, %s device-wide by %u\n", i,
+                    owner[i] - 1u, write ? "written" : "read", blockIdx.x);
+        if (write && !through[i]) {
+            through[i] = true;
+            through_list.push_back(i);
+        }
+    }
+}
+
+// What the running workgroup has changed so far: its own from here on, or (keep = false) in memory.
+static void settle(bool keep)
+{
+    constexpr size_t RUN = 1024;
+    for (size_t lo = 0; lo < watched_words; lo += RUN) {
+        const size_t n = std::min(RUN, watched_words - lo);
+        if (memcmp(watched + lo, before.data() + lo, n * 4) == 0) continue;
+        for (size_t i = lo; i < lo + n; ++i) {
+            if (watched[i] == before[i]) continue;
+            before[i] = watched[i];
+            if (!through[i]) owner[i] = keep ? blockIdx.x + 1u : 0u;
+        }
+    }
+    for (size_t i : through_list) through[i] = false;
+    through_list.clear();
+}
+
+void write_back()
+{
+    settle(false);
+    for (uint32_t &o : owner)
+        if (o == blockIdx.x + 1u) o = 0u;
+}
+
 // Minimal stack switch (System V x86-64): callee-saved registers on the old stack, stack
 // pointers exchanged.  (swapcontext would make a system call per switch.)
 extern "C" void emu_stack_switch(void **save_sp, void *load_sp);
@@ -229,6 +289,7 @@ void launch(dim3 grid, dim3 block, const std::function<void()> &body)
     for (uint32_t t = 0; t < m.nthreads; ++t)
         if (!m.fibers[t].stack) m.fibers[t].stack = (char *)malloc(STACK_BYTES);
     m.body = body;
+    if (watched) watch(watched, watched_words * 4);      // (whatever was written before is in memory)
     blockDim = Idx{block.x, 1, 1};
     gridDim = Idx{grid.x, grid.y, 1};
     for (uint32_t by = 0; by < grid.y; ++by)
@@ -250,6 +311,7 @@ void launch(dim3 grid, dim3 block, const std::function<void()> &body)
                 f.op = OP_NONE;
             }
             run_block(m);
+            if (watched) settle(true);
         }
 }
 

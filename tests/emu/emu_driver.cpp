@@ -101,8 +101,14 @@ struct Ctx {
         ws.reset(bytes);
         memset(ws.p, 0xA5, bytes);      // the library must not rely on a cleared workspace
         CHECK(dgs_create(&c, L.off.data(), L.J, W, ws.p, bytes, nullptr) == DGS_OK);
+        emu::watch(ws.p, bytes);
     }
-    ~Ctx() { dgs_destroy(c); }
+    ~Ctx()
+    {
+        emu::watch(nullptr, 0);
+        dgs_destroy(c);
+        CHECK(emu::mixed_words() == 0);
+    }
     dgs_stats stats()
     {
         dgs_stats s;
@@ -592,6 +598,16 @@ int main(int argc, char **argv)
         // one flat tensor of 2^20 elements at density 0.01, as the smallest benchmark configuration
         Opts o;
         worker_server("flat 2^20", {1u << 20}, 0.01, 0.01, 1.0f, 0.9f, false, {1, 1, 1}, 0, o, 20);
+        return 0;
+    }
+    if (argc > 1 && std::string(argv[1]) == "parts") {
+        // (built with the library's own part size) Tensors of one part that take the chain and whose scale jumps: the
+        // join's workgroup collects them again, and the ranking of the same launch leaves the k-th key
+        Opts o;
+        o.seg_mode = 1;
+        const dgs_stats st = worker_server("chain tensors of one part, collected again", {70001, 64, 131072}, 0.004, 0.01, 1.0f,
+                                           0.0f, true, {1, 1e-6f, 1, 1e3f, 1e-6f, 1}, 0, o, 60);
+        CHECK(st.repaired_tensors >= 1 && st.fallback_tensors == 0);
         return 0;
     }
     if (argc > 1 && std::string(argv[1]) == "rounds") {

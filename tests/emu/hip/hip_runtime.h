@@ -11,7 +11,10 @@
 // wavefront and call site among the lanes waiting there (the lanes that took the same branch:
 // the hardware's exec mask), then barriers.  LDS (`__shared__`) is static storage, global
 // memory is host memory, atomics are plain operations.  Cross-die cache effects are NOT
-// modelled: this checks indexing, synchronisation structure and results, not memory ordering.
+// modelled: this checks indexing, synchronisation structure and results, not memory ordering --
+// except for one rule, on a buffer that is watched (emu::watch): a word that one workgroup has
+// written with an ordinary store is neither written nor read device-wide by another workgroup of
+// the same launch, whose store an older copy in the first one's cache could shadow.
 #pragma once
 #include <algorithm>
 #include <cmath>
@@ -143,7 +146,8 @@ static inline uint32_t __builtin_amdgcn_mbcnt_hi(uint32_t mask, uint32_t acc)
     return acc + (uint32_t)__builtin_popcount(mask & m);
 }
 static inline void __builtin_amdgcn_s_sleep(int) {}
-#define __builtin_amdgcn_fence(...) ((void)0)
+namespace emu { void write_back(); }
+#define __builtin_amdgcn_fence(...) emu::write_back()
 
 // ---- scalar helpers
 static inline uint32_t __float_as_uint(float f) { uint32_t u; memcpy(&u, &f, 4); return u; }
@@ -159,17 +163,27 @@ namespace emu {
 extern bool count_adds;              // atomicAdd calls are counted per word of global memory (not LDS)
 void count_add(const void *p);
 uint64_t most_adds();                // the highest of those counts; starts over
+void watch(void *p, size_t bytes);   // a buffer of 4-byte words (null: none)
+void device_access(const void *p, size_t bytes, bool write);
+uint64_t mixed_words();              // accesses against the rule so far; the first one is printed
 }
 template <class T> static inline T atomicAdd(T *p, T v)
 {
     if (emu::count_adds) emu::count_add(p);
+    emu::device_access(p, sizeof(T), true);
     T o = *p;
     *p = o + v;
     return o;
 }
-template <class T> static inline T atomicMin(T *p, T v) { T o = *p; if (v < o) *p = v; return o; }
-template <class T> static inline T atomicOr(T *p, T v) { T o = *p; *p = o | v; return o; }
-// __hip_atomic_load / _store / _fetch_add are compiler builtins that also exist for the host.
+template <class T> static inline T atomicMin(T *p, T v) { emu::device_access(p, sizeof(T), true); T o = *p; if (v < o) *p = v; return o; }
+template <class T> static inline T atomicOr(T *p, T v) { emu::device_access(p, sizeof(T), true); T o = *p; *p = o | v; return o; }
+// (compiler builtins under these names also exist for the host)
+template <class T, class V> static inline void emu_store(T *p, V v) { emu::device_access(p, sizeof(T), true); *p = (T)v; }
+template <class T> static inline T emu_load(const T *p) { emu::device_access(p, sizeof(T), false); return *p; }
+template <class T, class V> static inline T emu_fetch_add(T *p, V v) { emu::device_access(p, sizeof(T), true); const T o = *p; *p = o + (T)v; return o; }
+#define __hip_atomic_store(p, v, order, scope) emu_store(p, v)
+#define __hip_atomic_load(p, order, scope) emu_load(p)
+#define __hip_atomic_fetch_add(p, v, order, scope) emu_fetch_add(p, v)
 #ifndef __HIP_MEMORY_SCOPE_AGENT
 #define __HIP_MEMORY_SCOPE_AGENT 4
 #endif

@@ -85,6 +85,17 @@ def test_kernels_on_the_cpu_under_asan_ubsan(tmp_path):
     assert "all scenarios match the oracle" in r.stdout
 
 
+def test_words_handed_over_in_a_launch_are_written_through(tmp_path):
+    """Tensors of one part (the library's own part size) that take the chain and are collected again by the workgroup
+    that found their prediction failed: no word of the workspace that it writes with an ordinary store is written or
+    read device-wide by another workgroup of the launch."""
+    exe = build_emulated_kernels(str(tmp_path), seg_tiles=256, group_tiles=4096)
+    r = subprocess.run([exe, "parts"], capture_output=True, text=True, env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0"),
+                       timeout=600)
+    assert r.returncode == 0, r.stdout[-3000:] + r.stderr[-6000:]
+    assert "emu: word" not in r.stderr and "collected again" in r.stdout
+
+
 def test_oracle_pins_against_ubsan_build():
     env = dict(os.environ, DGS_ORACLE_SANITIZE="1")
     r = subprocess.run([sys.executable, "-m", "pytest", "-x", "-q", "-p", "no:cacheprovider",
