@@ -482,6 +482,147 @@ __device__ __forceinline__ void select_emit(const Src src, const uint32_t cN, co
     if (run_sel != k && tid == 0) atomicAdd(&A.stats->internal_errors, 1ull);
 }
 
+// A small tensor (at most SMALL_N elements) straight from its buffer, 8 consecutive elements per thread in registers.
+// Keys are counted only within an octave of the k-th key of the previous selection on this stream: one pass and one
+// rank search give all but 12 bits of the new one, and the bucket it falls into mostly holds nothing but winners.
+// (Counting every element, most lanes of a wavefront add to the same few counters, the zeros of a difference row
+// all to one: 9 to 10 us on 7600 elements, which the whole launch waited for.)  Where the window has no answer -- no
+// previous call, a k-th key that has moved further -- the nonzero keys are counted by their upper 12 bits, and those
+// that share them with the k-th by the next 12.  us a call, generic passes over the elements in LDS / window / window
+// that missed: worker steps on 60 tensors of 500 to 8192 elements 20.4 / 15.3 / 19.9, 200 of 8192 24.4 / 20.9 / 24.8, 20 of 1000
+// 16.3 / 16.0 / 17.7; pulls on the printed state of the 60 23.3 / - / 21.1; first calls on the 60 27.0 / - / 21.0 (two
+// kernels more).  A miss that left the registers and began again with the generic passes: 26.0, 30.5, 19.0; 29.5; 28.2.
+// Returns whether the window held the k-th key (uniform; tests ask).
+template <int OP>
+__device__ __forceinline__ bool small_select(const SelectArgs &A, const TensorDesc &td, const PlanEntry &pe, uint32_t j,
+                                             SelShared &S)
+{
+    constexpr uint32_t ITEMS = SMALL_N / SEL_THREADS, BINS = 4096, SHIFT = 12;
+    static_assert(BINS * 4 <= sizeof(S.h) && (1u << SHIFT) == BINS && ITEMS % 4 == 0, "one histogram for all levels");
+    static_assert(HSHIFT > SHIFT && HSHIFT - SHIFT <= SHIFT && HBINS == BINS, "two passes leave fewer bits than a window");
+    const uint32_t tid = threadIdx.x, p0 = tid * ITEMS;
+    const uint32_t t_prev = A.tprev[j];
+    uint32_t bits[ITEMS];
+    float row[OP == SEL_PULL_V ? ITEMS : 1];      // sent_k, which the values are not
+#pragma unroll
+    for (uint32_t x = 0; x < ITEMS; x += 4) {
+        if (p0 + x + 4u <= td.n) {
+            const f32x4 s = *(const f32x4_any *)(A.state + td.off + p0 + x);
+            f32x4 v = s;
+            if (OP == SEL_PULL_V) v = *(const f32x4_any *)(A.model + td.off + p0 + x) - s;
+#pragma unroll
+            for (int y = 0; y < 4; ++y) {
+                bits[x + y] = __float_as_uint(v[y]);
+                if (OP == SEL_PULL_V) row[x + y] = s[y];
+            }
+        } else {
+#pragma unroll
+            for (int y = 0; y < 4; ++y) {
+                const bool in = p0 + x + y < td.n;
+                const float s = in ? A.state[td.off + p0 + x + y] : 0.0f;
+                bits[x + y] = __float_as_uint((OP == SEL_PULL_V && in) ? A.model[td.off + p0 + x + y] - s : s);
+                if (OP == SEL_PULL_V) row[x + y] = s;
+            }
+        }
+    }
+    // f(key) for the nonzero keys of this thread (elements beyond the tensor read as 0), into cleared counters
+    auto count = [&](auto f) {
+        for (uint32_t b = tid; b < BINS; b += SEL_THREADS) S.h[b] = 0;
+        __syncthreads();
+#pragma unroll
+        for (uint32_t i = 0; i < ITEMS; ++i) {
+            const uint32_t key = bits[i] & 0x7FFFFFFFu;
+            if (key != 0) f(key);
+        }
+    };
+    const uint32_t base = max(t_prev >> SHIFT, BINS / 2) - BINS / 2;
+    uint32_t seen = 0;                            // nonzero keys (low half), those in the window or above it
+    count([&](uint32_t key) {
+        ++seen;
+        const uint32_t hi = key >> SHIFT;
+        if (t_prev != 0 && hi >= base) {
+            seen += 1u << 16;
+            atomicAdd(&S.h[min(hi - base, BINS - 1u)], 1u);
+        }
+    });
+    seen = block_sum(seen, S.wsum, SEL_WAVES);
+    const uint32_t nonzero = seen & 0xFFFFu;
+    uint32_t T = 0, rT = pe.k - nonzero;          // (the message is completed with the lowest-index zeros)
+    const bool near = (seen >> 16) >= pe.k && S.h[BINS - 1u] < pe.k;      // (the last bucket is open)
+    if (nonzero >= pe.k) {
+        // the k-th key is in bucket bk: its bits above the `low` lowest, its rank among the keys that share them
+        uint32_t pfx, r2, low;
+        int bk;
+        if (near) {
+            find_ranks<(int)BINS, SEL_WAVES>(S.h, pe.k, 0u, 0u, S.rowsum, S.res);
+            bk = S.res[0];
+            r2 = (uint32_t)S.res[1];
+            pfx = base + (uint32_t)bk;
+            low = SHIFT;
+        } else {
+            __syncthreads();
+            count([&](uint32_t key) { atomicAdd(&S.h[key >> HSHIFT], 1u); });
+            find_ranks<(int)BINS, SEL_WAVES>(S.h, pe.k, 0u, 0u, S.rowsum, S.res);
+            const uint32_t top = (uint32_t)S.res[0], r1 = (uint32_t)S.res[1];
+            low = HSHIFT - SHIFT;
+            __syncthreads();
+            count([&](uint32_t key) {
+                if ((key >> HSHIFT) == top) atomicAdd(&S.h[(key >> low) & (BINS - 1u)], 1u);
+            });
+            find_ranks<(int)BINS, SEL_WAVES>(S.h, r1, 0u, 0u, S.rowsum, S.res);
+            bk = S.res[0];
+            r2 = (uint32_t)S.res[1];
+            pfx = (top << SHIFT) | (uint32_t)bk;
+        }
+        if (S.h[bk] == r2 && pfx != 0) {
+            T = (pfx << low) - 1u;                // the whole bucket is sent
+            rT = 0;
+        } else {
+            __syncthreads();
+            count([&](uint32_t key) {
+                if ((key >> low) == pfx) atomicAdd(&S.h[key & ((1u << low) - 1u)], 1u);
+            });
+            find_ranks<(int)BINS, SEL_WAVES>(S.h, r2, 0u, 0u, S.rowsum, S.res);
+            T = (pfx << low) | (uint32_t)S.res[0];
+            rT = (uint32_t)S.res[1];
+        }
+    }
+    uint32_t g = 0, q = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < ITEMS; ++i) {
+        const uint32_t key = bits[i] & 0x7FFFFFFFu;
+        if (p0 + i < td.n) {
+            g += key > T ? 1u : 0u;
+            q += key == T ? 1u : 0u;
+        }
+    }
+    uint32_t total;
+    const uint32_t before = block_excl_scan<SEL_WAVES>(g | (q << 16), S.wsum, total);
+    uint32_t eq = before >> 16, above = before & 0xFFFFu;      // ties: lowest index first, rT of them are taken
+#pragma unroll
+    for (uint32_t i = 0; i < ITEMS; ++i) {
+        const uint32_t key = bits[i] & 0x7FFFFFFFu;
+        const bool in = p0 + i < td.n, tie = in && key == T, over = in && key > T;
+        const uint32_t pos = above + min(eq, rT);
+        if ((over || (tie && eq < rT)) && pos < pe.k) {
+            const uint32_t ix = td.off + p0 + i;
+            const float v = __uint_as_float(bits[i]);
+            A.out_idx[pe.outoff + pos] = ix;
+            A.out_val[pe.outoff + pos] = v;
+            if (OP == SEL_WORKER) store_scattered(&A.state[ix], A.m * v);
+            else if (OP == SEL_PULL) store_scattered(&A.state[ix], 0.0f);
+            else if (!A.later) store_scattered(&A.state[ix], row[i] + v);
+        }
+        above += over ? 1u : 0u;
+        eq += tie ? 1u : 0u;
+    }
+    if (tid == 0) {
+        if ((total & 0xFFFFu) + min(total >> 16, rT) != pe.k) atomicAdd(&A.stats->internal_errors, 1ull);
+        A.tprev[j] = T;
+    }
+    return near;
+}
+
 // Rank (from the top) whose key becomes the next predicted threshold, and how the
 // drift since the current threshold was set is measured.
 //   c: candidates collected at the current threshold; E: candidates that threshold was

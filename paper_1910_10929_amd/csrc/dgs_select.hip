@@ -539,118 +539,7 @@ __device__ __forceinline__ uint32_t window_step(const SelectArgs &A, const Tenso
     return !ok ? 0u : (lists ? (uint32_t)SEG_LISTS : (uint32_t)SEG_ACTIVE);
 }
 
-// A small tensor (at most SMALL_N elements), 8 consecutive elements per thread in registers.  Keys are counted
-// only within an octave of the k-th key of the previous selection on this stream: one pass and one rank search give
-// all but 12 bits of the new one, and the bucket it falls into mostly holds nothing but winners.  The generic passes
-// of dense_select count every element, and most lanes of a wavefront then add to the same few counters (the zeros
-// of a difference row all to one): 9 to 10 us of them on 7600 elements, which the whole launch waited for (a round
-// of nine odd tensors of 270 K elements in all 48.5 -> 41.4 us, an event of a server with 70 tensors 49.0 -> 46.7).
-// Returns false, with nothing written, where the hint does not reach: no previous call at this density, a k-th
-// key that has moved by more than an octave.
-template <int OP>
-__device__ __forceinline__ bool small_select(const SelectArgs &A, const TensorDesc &td, const PlanEntry &pe, uint32_t j,
-                                             PartShared &P)
-{
-    constexpr uint32_t ITEMS = SMALL_N / SEL_THREADS, BINS = 4096, SHIFT = 12;
-    static_assert(BINS * 4 <= sizeof(P.S.h) && (1u << SHIFT) == BINS && ITEMS % 4 == 0, "one histogram for both levels");
-    const uint32_t tid = threadIdx.x, p0 = tid * ITEMS;
-    const uint32_t t_prev = A.tprev[j];
-    uint32_t bits[ITEMS];
-    float row[OP == SEL_PULL_V ? ITEMS : 1];      // sent_k, which the values are not
-#pragma unroll
-    for (uint32_t x = 0; x < ITEMS; x += 4) {
-        if (p0 + x + 4u <= td.n) {
-            const f32x4 s = *(const f32x4_any *)(A.state + td.off + p0 + x);
-            f32x4 v = s;
-            if (OP == SEL_PULL_V) v = *(const f32x4_any *)(A.model + td.off + p0 + x) - s;
-#pragma unroll
-            for (int y = 0; y < 4; ++y) {
-                bits[x + y] = __float_as_uint(v[y]);
-                if (OP == SEL_PULL_V) row[x + y] = s[y];
-            }
-        } else {
-#pragma unroll
-            for (int y = 0; y < 4; ++y) {
-                const bool in = p0 + x + y < td.n;
-                const float s = in ? A.state[td.off + p0 + x + y] : 0.0f;
-                bits[x + y] = __float_as_uint((OP == SEL_PULL_V && in) ? A.model[td.off + p0 + x + y] - s : s);
-                if (OP == SEL_PULL_V) row[x + y] = s;
-            }
-        }
-    }
-    for (uint32_t b = tid; b < BINS; b += SEL_THREADS) P.S.h[b] = 0;
-    __syncthreads();
-    const uint32_t base = max(t_prev >> SHIFT, BINS / 2) - BINS / 2;
-    uint32_t nonzero = 0;
-#pragma unroll
-    for (uint32_t i = 0; i < ITEMS; ++i) {
-        const uint32_t key = bits[i] & 0x7FFFFFFFu, hi = key >> SHIFT;      // (elements beyond the tensor read as 0)
-        nonzero += key != 0 ? 1u : 0u;
-        if (t_prev != 0 && key != 0 && hi >= base) atomicAdd(&P.S.h[min(hi - base, BINS - 1u)], 1u);
-    }
-    nonzero = block_sum(nonzero, P.S.wsum, SEL_WAVES);
-    uint32_t T = 0, rT = pe.k - nonzero;          // (the message is completed with the lowest-index zeros)
-    if (nonzero >= pe.k) {
-        if (t_prev == 0) return false;
-        find_ranks<(int)BINS, SEL_WAVES>(P.S.h, pe.k, 0u, 0u, P.S.rowsum, P.S.res);
-        const int bk = P.S.res[0];
-        const uint32_t r2 = (uint32_t)P.S.res[1];
-        if (bk < 0 || bk >= (int)BINS - 1) return false;
-        const uint32_t pfx = base + (uint32_t)bk;
-        if (P.S.h[bk] == r2 && pfx != 0) {
-            T = (pfx << SHIFT) - 1u;              // the whole bucket is sent
-            rT = 0;
-        } else {
-            __syncthreads();
-            for (uint32_t b = tid; b < BINS; b += SEL_THREADS) P.S.h[b] = 0;
-            __syncthreads();
-#pragma unroll
-            for (uint32_t i = 0; i < ITEMS; ++i) {
-                const uint32_t key = bits[i] & 0x7FFFFFFFu;
-                if (key != 0 && (key >> SHIFT) == pfx) atomicAdd(&P.S.h[key & (BINS - 1u)], 1u);
-            }
-            find_ranks<(int)BINS, SEL_WAVES>(P.S.h, r2, 0u, 0u, P.S.rowsum, P.S.res);
-            T = (pfx << SHIFT) | (uint32_t)P.S.res[0];
-            rT = (uint32_t)P.S.res[1];
-        }
-    }
-    uint32_t g = 0, q = 0;
-#pragma unroll
-    for (uint32_t i = 0; i < ITEMS; ++i) {
-        const uint32_t key = bits[i] & 0x7FFFFFFFu;
-        if (p0 + i < td.n) {
-            g += key > T ? 1u : 0u;
-            q += key == T ? 1u : 0u;
-        }
-    }
-    uint32_t total;
-    const uint32_t before = block_excl_scan<SEL_WAVES>(g | (q << 16), P.S.wsum, total);
-    uint32_t eq = before >> 16, above = before & 0xFFFFu;      // ties: lowest index first, rT of them are taken
-#pragma unroll
-    for (uint32_t i = 0; i < ITEMS; ++i) {
-        const uint32_t key = bits[i] & 0x7FFFFFFFu;
-        const bool in = p0 + i < td.n, tie = in && key == T, over = in && key > T;
-        const uint32_t pos = above + min(eq, rT);
-        if ((over || (tie && eq < rT)) && pos < pe.k) {
-            const uint32_t ix = td.off + p0 + i;
-            const float v = __uint_as_float(bits[i]);
-            A.out_idx[pe.outoff + pos] = ix;
-            A.out_val[pe.outoff + pos] = v;
-            if (OP == SEL_WORKER) store_scattered(&A.state[ix], A.m * v);
-            else if (OP == SEL_PULL) store_scattered(&A.state[ix], 0.0f);
-            else if (!A.later) store_scattered(&A.state[ix], row[i] + v);
-        }
-        above += over ? 1u : 0u;
-        eq += tie ? 1u : 0u;
-    }
-    if (tid == 0) {
-        if ((total & 0xFFFFu) + min(total >> 16, rT) != pe.k) atomicAdd(&A.stats->internal_errors, 1ull);
-        A.tprev[j] = T;
-    }
-    return true;
-}
-
-// Selection of a whole tensor straight from the buffers by this one workgroup: small tensors,
+// Selection of a whole tensor straight from the buffers by this one workgroup:
 // dense requests on tensors outside the chain, and whatever the re-collection could not
 // resolve.  Exact for any data; slow on large tensors.
 template <int OP>
@@ -684,8 +573,8 @@ __device__ __forceinline__ void dense_select(const SelectArgs &A, const TensorDe
         if (tn >= 0x7F800000u) tn = 0x7F7FFFFFu;
         A.tau[j] = tn;
         A.hint2[j] = expect;
+        A.tprev[j] = t_k;
     }
-    if (A.write_hint && tid == 0) A.tprev[j] = t_k;
 }
 
 // The tensor's candidates are in `llist` (first SEL_LDS_LIST) and `glist` (beyond): exact
@@ -1168,9 +1057,8 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const SelectArgs A)
         if (!td.big || A.dense) {
             if (sd.sidx != 0) return;
             if (tid == 0) st->status = SEG_DONE;
-            if (!A.dense && !A.exact_mode && small_select<OP>(A, td, pe, j, P)) return;
-            __syncthreads();
-            dense_select<OP>(A, td, pe, j, td.big ? A.tau[j] : TAU_NEVER, P, llist);
+            if (A.dense) dense_select<OP>(A, td, pe, j, td.big ? A.tau[j] : TAU_NEVER, P, llist);
+            else small_select<OP>(A, td, pe, j, P.S);
             return;
         }
         const uint32_t tau_cur = A.tau[j];

@@ -12,6 +12,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -542,6 +543,89 @@ static void pull_gives_up(uint64_t seed)
     fflush(stdout);
 }
 
+// The selection of a small tensor, called by itself with a previous k-th key of its choice: the window around that key
+// (which branch was taken is asked for), a key that has moved by more than an octave either way, no previous key; a
+// bucket that holds nothing but winners, ties inside one, the lowest keys of all, fewer nonzeros than k; sizes around
+// what a thread and the workgroup hold.
+template <int OP> static void small_branches()
+{
+    g_what = OP == dgs::SEL_WORKER ? "small tensors by branch, worker"
+                                   : (OP == dgs::SEL_PULL ? "small tensors by branch, difference row" : "small tensors by branch, printed state");
+    Rng r(70 + OP);
+    static const uint32_t sizes[] = {1, 8, 9, 1024, 4097, 8192};
+    for (uint32_t n : sizes)
+        for (int kind = 0; kind < (n < 1024u ? 2 : 6); ++kind)
+            for (uint32_t k : {(n + 99u) / 100u, n < 1024u ? n : (n + 1u) / 2u}) {
+                if ((OP != dgs::SEL_PULL || n == 1024u) && (kind > 1 || (n != 9u && n != 4097u))) continue;
+                const uint64_t off[2] = {0, n};
+                std::vector<float> value(n);
+                for (uint32_t i = 0; i < n; ++i) {
+                    float v = r.gauss();
+                    if (kind == 1) v = std::round(2.0f * v);                                 // ties, zeros among them
+                    if (kind == 2 && r.u32() % 4u != 0) v = 0.0f;                             // few nonzeros
+                    if (kind == 3) v = (float)((int)(r.u32() % 2001u) - 1000) * 1e-45f;       // the lowest keys
+                    if (kind == 4) v = 1.5f;
+                    if (kind == 5) v = r.u32() % 3u ? INFINITY : (r.u32() & 1u ? NAN : 3e38f);
+                    value[i] = v;
+                }
+                std::vector<uint32_t> keys(n);
+                for (uint32_t i = 0; i < n; ++i) keys[i] = __float_as_uint(value[i]) & 0x7FFFFFFFu;
+                std::sort(keys.begin(), keys.end(), std::greater<uint32_t>());
+                const uint32_t T = keys[k - 1];
+                // what comes out is the oracle's pull of a row that holds the values
+                Buf<float> row(n), wv(k);
+                Buf<uint32_t> wi(k);
+                uint64_t K = 0;
+                for (uint32_t i = 0; i < n; ++i) row.p[i] = value[i];
+                CHECK(dgs_oracle_server_pull(row.p, off, 1, (double)k / (double)n * (1.0 - 1e-9), wi.p, wv.p, &K) == 0 && K == k);
+                for (uint32_t t_prev : {0u, T, T + (3u << 23), T > (4u << 23) ? T - (3u << 23) : 1u}) {
+                    Buf<float> state(n), model(n), gv(k);
+                    Buf<uint32_t> gi(k), tprev(1);
+                    for (uint32_t i = 0; i < n; ++i) (OP == dgs::SEL_PULL_V ? model.p : state.p)[i] = value[i];
+                    tprev.p[0] = t_prev;
+                    dgs::DevStats stats{};
+                    dgs::SelectArgs A{};
+                    A.state = state.p;
+                    A.model = model.p;
+                    A.n = n;
+                    A.m = 0.5f;
+                    A.out_idx = gi.p;
+                    A.out_val = gv.p;
+                    A.tprev = tprev.p;
+                    A.stats = &stats;
+                    dgs::TensorDesc td{};
+                    td.n = n;
+                    dgs::PlanEntry pe{};
+                    pe.k = k;
+                    bool near = false;
+                    emu::launch(dim3(1), dim3(dgs::SEL_THREADS), [&] {
+                        __shared__ dgs::SelShared S;
+                        const bool in_window = dgs::small_select<OP>(A, td, pe, 0u, S);
+                        if (threadIdx.x == 0) near = in_window;
+                    });
+                    expect_same(gi.p, gv.p, wi.p, wv.p, k);
+                    CHECK(stats.internal_errors == 0);
+                    // the window begins 2048 buckets of 2^12 keys below the previous key's bucket, and its last bucket is open
+                    const uint32_t b = t_prev >> 12, base = (b > 2048u ? b : 2048u) - 2048u;
+                    CHECK(near == (T != 0 && t_prev != 0 && (T >> 12) >= base && (T >> 12) - base < 4095u));
+                    // the next call's anchor: the k-th key, or the one below its bucket where the whole bucket is sent
+                    const uint32_t low = near ? 12u : 7u;
+                    CHECK(T == 0 ? tprev.p[0] == 0
+                                 : tprev.p[0] == T || (tprev.p[0] == (T >> low << low) - 1u && (k == n || keys[k] <= tprev.p[0])));
+                    std::vector<char> sent(n, 0);
+                    for (uint32_t e = 0; e < k; ++e) sent[gi.p[e]] = 1;
+                    for (uint32_t i = 0; i < n; ++i) {
+                        const float v = value[i];
+                        const float want = OP == dgs::SEL_PULL_V ? (sent[i] ? 0.0f + v : 0.0f)
+                                                                 : (!sent[i] ? v : (OP == dgs::SEL_WORKER ? 0.5f * v : 0.0f));
+                        CHECK(memcmp(&state.p[i], &want, 4) == 0 || (std::isnan(want) && std::isnan(state.p[i])));
+                    }
+                }
+            }
+    printf("%-44s ok\n", g_what.c_str());
+    fflush(stdout);
+}
+
 // Randomised layouts, densities, options, server forms and gradient-scale jumps (which make
 // predictions fail): `soak <first seed> <count>`.
 static void soak(uint64_t seed)
@@ -600,6 +684,12 @@ int main(int argc, char **argv)
         worker_server("flat 2^20", {1u << 20}, 0.01, 0.01, 1.0f, 0.9f, false, {1, 1, 1}, 0, o, 20);
         return 0;
     }
+    if (argc > 1 && std::string(argv[1]) == "small") {
+        small_branches<dgs::SEL_WORKER>();
+        small_branches<dgs::SEL_PULL>();
+        small_branches<dgs::SEL_PULL_V>();
+        return 0;
+    }
     if (argc > 1 && std::string(argv[1]) == "parts") {
         // (built with the library's own part size) Tensors of one part that take the chain and whose scale jumps: the
         // join's workgroup collects them again, and the ranking of the same launch leaves the k-th key
@@ -640,6 +730,9 @@ int main(int argc, char **argv)
     tied_dense("dense request, 12 % share the k-th key", 0.12, 0.1, 46);
     tied_dense("dense request, 20 % share the k-th key of 90 %", 0.2, 0.9, 47);
     row_update();
+    small_branches<dgs::SEL_WORKER>();
+    small_branches<dgs::SEL_PULL>();
+    small_branches<dgs::SEL_PULL_V>();
     const std::vector<uint64_t> ragged = {1, 7, 64, 1000, 8192, 8193, 9408, 3, 100003, 20000, 70001, 17, 65537, 12345};
     const std::vector<uint64_t> two = {150000, 64, 66000};
     Opts def, exact, always, never, norepair;
