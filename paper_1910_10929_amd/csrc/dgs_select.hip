@@ -210,8 +210,9 @@ __device__ __forceinline__ uint32_t join_part(const SelectArgs &A, const TensorD
     uint32_t base = 0;
     int ovf = 0;
     // lines of this wavefront's 64 tiles: load v covers tiles 16 v .. 16 v + 15.  A round's are fetched as soon as
-    // those before are in place, while the crowded tiles are copied (a round on ResNet-50 shapes 129.6 -> 129.1 us; a
-    // second set of registers, fetched a whole round ahead, 130.1: one compute unit takes in 29 bytes a ns at most).
+    // those before are in place, while the crowded tiles are copied: a round on ResNet-50 shapes 111.1 -> 110.0 us, an
+    // event of a server with 12 sent rows 59.5 -> 59.1 (each side as two copies, whose medians agreed to 0.2).  A second
+    // set of registers, fetched a whole round ahead, brought no more: one compute unit takes in 29 bytes a ns at most.
     uint4 pf[4];
     uint32_t w;
     auto fetch = [&](uint32_t r0) {
@@ -556,10 +557,16 @@ __device__ __forceinline__ void dense_select(const SelectArgs &A, const TensorDe
         for (uint32_t p = tid; p < td.n; p += SEL_THREADS)
             lv[p] = __float_as_uint(row_value<OP>(A.state, A.model, td.off + p));
         __syncthreads();
+        // Entries per thread, 2 / 3 / 4 of them, us a dense call: 300 tensors of 20 K at 0.1, worker 85.4 / 82.3 / 81.3,
+        // difference row 67.3 / 64.8 / 63.5, printed state 73.9 / 71.5 / 70.4; at 0.5 76.8 / 77.4 / 79.9, 68.4 / 68.7 / 71.2,
+        // 74.9 / 74.0 / 74.8; 200 of 30 K at 0.5 60.0 / 60.3 / 62.8, 52.7 / 52.7 / 55.3, 56.5 / 54.6 / 56.7.  (1: 3 to 10 us
+        // more, 8: up to 24 us more at 0.5.)
         SrcDenseLds src{lv, td.off};
-        select_emit<OP, 2>(src, td.n, pe.k, R, 0u, 0xFFFFFFFFu, 0u, false, 0xFFFFFFFFu, P.S, A, pe.outoff,
+        select_emit<OP, OP == SEL_PULL_V ? 4 : 3>(src, td.n, pe.k, R, 0u, 0xFFFFFFFFu, 0u, false, 0xFFFFFFFFu, P.S, A, pe.outoff,
                            &tau_next, &expect, &q_e, &t_k);
     } else {
+        // (4 / 8 a thread: 8 tensors of 60 K at 0.1, worker 102.9 / 116.2, printed state 109.7 / 134.1; one of 2.4M that
+        // falls back 833.7 / 924.5)
         SrcDense<OP> src{A.state, A.model, td.off};
         select_emit<OP, 4>(src, td.n, pe.k, R, 0u, 0xFFFFFFFFu, 0u, false, 0xFFFFFFFFu, P.S, A, pe.outoff,
                            &tau_next, &expect, &q_e, &t_k);
@@ -597,11 +604,17 @@ __device__ __forceinline__ void list_select(const SelectArgs &A, const TensorDes
     const uint32_t win_base = (kmin == 0xFFFFFFFFu) ? 0xFFFFFFFFu : (anchored ? win_join : (kmin >> win_shift(OP)));
     const uint32_t win_min = (anchored && win_join > (kmin >> win_shift(OP))) ? 1u : 0u;   // entries below the window
     if (c <= SEL_LDS_LIST) {
+        // Entries per thread, 2 / 3 / 4 of them: a round on ResNet-50 shapes 111.0 / 109.8 / 111.2 us, an event of a server with
+        // 32 sent rows 59.8 / 59.5 / 59.9, with difference rows 83.0 / 82.8 / 83.2; 70 odd tensors, 6 workers 45.4 / 45.1 /
+        // 45.6.  (Every instance of the emission costs the kernel scalar registers, which it spills: 194 to 243 of them,
+        // 400 to 431 with 4, 8, 4 and 8 here and in the other three, where the round takes 115.0.)
         SrcList src{llist};
         select_emit<OP, 3>(src, c, pe.k, R, Eq, win_base, win_min, win_ready, kmin, P.S, A, pe.outoff,
                            &tau_next, &expect, &q_e, &t_k);
     } else {
-        SrcSplit src{llist, glist};     // the list outgrew LDS: its tail is read from global scratch
+        // The list outgrew LDS: its tail is read from global scratch.  (4 / 8 a thread: 1.2M elements at 1 % by one workgroup,
+        // worker 53.6 / 56.5, printed state 88.0 / 92.3)
+        SrcSplit src{llist, glist};
         select_emit<OP, 4>(src, c, pe.k, R, Eq, win_base, win_min, win_ready, kmin, P.S, A, pe.outoff,
                            &tau_next, &expect, &q_e, &t_k);
     }
