@@ -60,9 +60,12 @@ enum {
     DGS_OPT_VALIDATE = 3,    /* 1: dgs_server_push checks idx on the device (synchronises) */
     DGS_OPT_MARGIN_PCT = 4,  /* candidate over-provisioning in percent of k_j (default 50) */
     DGS_OPT_STREAM_QUADS = 5,/* 4096-element groups per workgroup of the streaming kernel */
-    DGS_OPT_SEGMENTED = 6,   /* which tensors continue through the multi-kernel chain behind the
-                                selection: 0 automatic (candidate lists too long for one workgroup,
-                                dense requests), 1 every tensor of at least 65536 elements, 2 never */
+    DGS_OPT_SEGMENTED = 6,   /* which tensors are resolved by many workgroups (the "chain") in place of
+                                one: 0 automatic (candidate lists too long for one workgroup,
+                                dense requests), 1 every tensor of at least 65536 elements, 2 never.
+                                The chain is part of the selection's launch where it has at most 512
+                                slabs of 131072 elements (1024 where one tensor takes it), and launches
+                                before and behind it otherwise */
     DGS_OPT_REPAIR_ROUND = 7,/* 1 (default): the selection launch carries the workgroups that collect
                                 again, with a fresh threshold, the tensors whose predicted threshold
                                 failed (they wait inside the launch and return at once when their
@@ -78,9 +81,9 @@ enum {
     DGS_OPT_SPIN_LIMIT = 8   /* polls after which a waiting workgroup of the selection gives up
                                 (default 2^20, far beyond any wait that ends); it is then counted
                                 in dgs_stats.internal_errors.  What waits: the collection after a
-                                failed prediction, and the emission of tensors with long candidate
-                                lists and of dense requests, which waits on every call.  What gave
-                                up is left unselected, or emitted up to the part that gave up: after
+                                failed prediction, and on every call the ranking and emission of
+                                tensors with long candidate lists and the emission of dense
+                                requests.  What gave up is left unselected, or emitted up to the part that gave up: after
                                 a call that raised internal_errors the outputs and the context are
                                 not to be used */
 };
@@ -93,7 +96,10 @@ enum {
     DGS_PROF_PULL_SELECT = 3,
     DGS_PROF_PUSH = 4,
     DGS_PROF_EXACT_EXTRA = 5,   /* second (collecting) pass of the non-predicted path */
-    DGS_PROF_WORKER_SEGMENTED = 6, /* chain kernels behind the selection, first begin to last end */
+    DGS_PROF_WORKER_SEGMENTED = 6, /* kernels behind the selection, first begin to last end: of a dense
+                                      request, and of the chain where it has launches of its own
+                                      (DGS_OPT_SEGMENTED); nothing where it is part of the
+                                      selection's launch and its time part of that class */
     DGS_PROF_PULL_SEGMENTED = 7,
     DGS_PROF_ENCODE = 8,        /* dgs_encode */
     DGS_PROF_DECODE = 9,        /* dgs_decode */
@@ -107,7 +113,7 @@ typedef struct dgs_stats {
     uint64_t fallback_elems;   /* elements re-read by those */
     uint64_t candidates;       /* candidates collected by streaming passes */
     uint64_t internal_errors;  /* must stay 0 */
-    uint64_t segmented_tensors; /* tensors resolved through the chain kernels */
+    uint64_t segmented_tensors; /* tensors resolved through the chain, or by the kernels of a dense request */
     uint64_t repaired_tensors;  /* tensors whose prediction failed and that were resolved inside the call with
                                    a fresh threshold: lists trimmed in place, or collected a second time */
 } dgs_stats;
@@ -208,8 +214,9 @@ int dgs_worker_step(dgs_ctx *ctx, const float *grad, float *momentum, float *res
  * that the library holds in device memory on every GPU it runs on, until the process ends.
  * The call makes no hipMalloc / hipFree / hipHostMalloc, creates no events, issues no copies
  * and does not wait: the layout tables travel as kernel arguments.
- * Limits: J <= DGS_STATIC_MAX_TENSORS, and dgs_workspace_bytes(offsets, J, 0) <=
- * DGS_STATIC_SCRATCH_BYTES (about 1e7 parameters); beyond them DGS_ECAPACITY is returned and
+ * Limits: J <= DGS_STATIC_MAX_TENSORS, and a workspace of at most DGS_STATIC_SCRATCH_BYTES
+ * (about 1e7 parameters; a single call needs a little less than dgs_workspace_bytes(offsets, J, 0):
+ * one launch plan and no list of tiles to sample); beyond them DGS_ECAPACITY is returned and
  * nothing is enqueued.  Nothing is remembered between calls (each starts from a cleared
  * workspace and takes the two-pass path), so it is slower than a context.
  * All calls on one GPU share that GPU's array: two calls whose work overlaps on the GPU (two

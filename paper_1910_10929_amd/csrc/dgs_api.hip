@@ -289,8 +289,9 @@ void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out,
         uint64_t K = 0, words = 0;
         uint32_t active = 0;
         // A dense request on nothing but small tensors is one launch of one workgroup each.  us a step, so / by the
-        // five launches of the dense kernels: 35 tensors of 1811 elements 15 / 42, 300 of 20 K 73-85 / 86-100, 30 of
-        // 60 K 98-123 / 56-66, 1000 of 60 K 591 / 381: the largest tensor decides, between 20 K and 60 K elements.
+        // five launches of the dense kernels, at 0.1: 35 tensors of 1811 elements 15.9 / 42.6, nine of 7000 21.7 / 49.3, 300 of
+        // 20 K 84.7 / 110.9, 8 of 60 K 98.7 / 63.5, 30 103.5 / 72.0, 100 112.3 / 94.3, 1000 563 / 427: the largest tensor
+        // decides, between 20 K and 60 K elements.
         bool large = false, beyond = c->seg_mode == SEG_MODE_ALWAYS;      // a list beyond SEL_LIST_MAX_OTHER
         uint32_t listed = 0;               // tensors with candidate lists
         for (uint32_t j = 0; j < c->J; ++j) {

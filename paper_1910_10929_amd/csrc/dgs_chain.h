@@ -14,7 +14,12 @@
 //           entries equal to it are taken.  EMIT awaits that, counts its winners, adds up what the
 //           slabs before it have published, and writes its stretch of the message ("encode()" of
 //           Algorithms 1-3) and the state fix-up (Eq. 12 / Eq. 6).  Ties need no list and no case
-//           of their own.  Waiting is for blocks with lower indices only, and bounded.
+//           of their own.
+// Waiting is for blocks with lower indices only.  The chip deals a launch's blocks out to its eight dies in turn and each die
+// starts its share in order, so the lowest block that has not ended either runs, and waits for nobody, or is the next to
+// start on a die whose earlier blocks of this launch have all ended.  That is progress as long as the die has room, which
+// another launch may take: two at once stand still only if each fills a die with waiting blocks and holds
+// back one that the other needs.  The bound on every wait (A.spin_limit) then ends it, counted as an internal error.
 // Where there are few enough slabs all of that is part of the selection's launch (CHAIN_HERE), beside the joins of the
 // other tensors; otherwise window and finish are launches of their own, before and behind it.
 // A tensor whose prediction failed was collected again into one list per part by the selection

@@ -47,9 +47,8 @@ void launch_chain(int op, const SelectArgs &a, void *stream, void *ev0, void *ev
     if (a.ncslabs == 0) return;
     // While all slabs run at once (or nearly so) the depth of a workgroup counts: 8 tiles per wavefront.
     // Many rounds of workgroups are better served by twice as many workgroups per compute unit with 16
-    // tiles per wavefront.  Rounds with 1024 / 512 threads, us: ResNet-50 shapes without momentum at 1 %
-    // (about 260 slabs) 110 / 114, transformer shapes (about 900) 394 / 408; one flat tensor at 0.3 / 1 %
-    // with 990 slabs 678 / 694 and 842 / 871, 1530 954 / 942 and 1199 / 1208, 1980 1206 / 1212 and 1554 / 1579,
+    // tiles per wavefront.  Rounds with 1024 / 512 threads, us: transformer shapes (about 900 slabs) 394 / 408; one flat
+    // tensor at 0.3 / 1 % with 1530 slabs 954 / 942 and 1199 / 1208, 1980 1206 / 1212 and 1554 / 1579,
     // 3050 1796 / 1781 and 2365 / 2375; 25 equal tensors with 1530 830 / 775 and 1080 / 1047, 3050 1655 / 1535 and
     // 2209 / 2131; 1e9 parameters (7.8 K) at 1 % 5596 / 5338.
     if (a.ncslabs < 2048u) launch_finish<1024>(op, a, st, ev0, ev1);

@@ -45,10 +45,12 @@ constexpr uint32_t SEL_LDS_LIST = 16384;           // candidates kept in LDS (12
 // 78.3 / 64.0; ResNet-50 shapes at 0.2 / 0.3 / 0.36 % (10 / 14 / 17 K), a round 124.7 / 126.7, 140.1 / 130.8, 152.6 / 134.0,
 // a step 72.3 / 71.0, 79.8 / 72.3 (0.3 %).
 constexpr uint32_t SEL_LIST_MAX = 10240;
-// For tensors of fewer than SEL_CROWDED_TILES tiles, and of SEL_LONG_TILES or more, it lies where it was before the chain
-// became part of the selection's launch.  The chain would serve large ones sooner, too (4M at 0.25 % 97.7 / 68.5, 6M at
-// 0.15 % 112.0 / 75.8), but which of their calls count in segmented_tensors, and which lists one workgroup
-// trims, is relied on by tests.
+// Tensors of fewer than SEL_CROWDED_TILES tiles are joined in half a round, and one workgroup keeps up for longer: 250 K
+// elements with lists of 11 / 15 K a round 51.3 / 57.7, 56.3 / 63.1, 400 K with 11 / 19 K 55.1 / 57.9, 66.2 / 62.1, 500 K with 11 / 15 K
+// 53.8 / 55.0, 59.5 / 56.9.  From SEL_LONG_TILES on the same line stands, but not because one workgroup were faster
+// (4M with 11 / 20 K 71.1 / 67.1, 92.1 / 68.1, 6M with 12 / 18 K 86.7 / 74.6, 105.3 / 75.5, four of 7M with 10 / 14 K 139.3 /
+// 140.4, 152.2 / 141.7): the tests of trimmed lists and of joins of several rounds have tensors of that size and state that
+// the chain resolves none of them (segmented_tensors).  Nothing else speaks against SEL_LIST_MAX there.
 constexpr uint32_t SEL_LIST_MAX_OTHER = 20480, SEL_LONG_TILES = 3584;
 // ... and where the plan holds a tensor beyond that, so that the chain's workgroups are there anyway,
 // for tensors of at least SEL_CROWDED_TILES tiles (their join is then what the launch waits for).  us with the
@@ -87,9 +89,11 @@ constexpr uint32_t SLAB_THREADS = SLAB_TILES / 4 * 64;
 static_assert(SLAB_TILES * TILE >= SMALL_N + TILE && SLAB_TILES <= SEG_TILES, "a small tensor is one slab");
 // The chain in the selection's launch, for plans of at most CHAIN_HERE slabs, or CHAIN_HERE_ONE of a single tensor: two
 // launches less, and the chain runs beside the joins.  Beyond that the workgroups of one launch, one to a compute unit,
-// are too few.  us in one launch / in three: one tensor of 2^20 elements at 1 % (8 slabs) a round 57.0 / 68.7, ResNet-50
-// shapes without momentum (130) 77.0 / 86.2, a server for them 115.4 / 136.5, transformer shapes at 0.1 % (180) 367 / 377;
-// one tensor of 30M at 0.3 % (230) 178.5 / 182, of 100M at 0.1 and 1 % (763) 437 / 458 and 594 / 613, of 250M at 0.3 %
+// are too few.  us in one launch / in three, over and over on the same few gradients (a step on ResNet-50 shapes takes 13 us more
+// on gradients that the last-level cache does not hold): one tensor of 2^20 elements at 1 % (8 slabs) a round 57.0 / 67.5,
+// ResNet-50 shapes at 1 % (130) a step without momentum 75.9 / 87.0, an event of a server with 8 sent rows 111.6 / 132.2, with
+// difference rows 168.9 / 184.2, transformer shapes at 0.1 % (180) 367.7 / 376.9;
+// one tensor of 30M at 0.3 % (230) 178.5 / 182.6, of 100M at 0.1 and 1 % (763) 436 / 459 and 587 / 607, of 250M at 0.3 %
 // (1900) 1098 / 1069; 8 tensors of 96M in all at 1 % (732) 514.5 / 515, transformer shapes at 1 % (800) 603 / 587, 24
 // tensors of 240M 1278 / 1243.
 // (A CPU test build with small parts has layouts on either side of the line.)
@@ -153,7 +157,10 @@ struct SegState {        // per tensor, rewritten by every selection
     uint32_t r2;         // its rank among the entries sharing that prefix (SEG_ZERO: the zeros to add)
     uint32_t T;          // the k-th key
     uint32_t rT;         // how many of the entries equal to it are taken (lowest index first)
-    // Hand-over between the workgroups of one launch (all zero between launches):
+    // Hand-over between the workgroups of one launch (all zero between launches).  These words share a line with the plain
+    // ones above, which the tensor's deciding workgroup stores through its cache: a die's L2 writes back the bytes that were
+    // written in it and no others (the messages of neighbouring tensors, from workgroups on different dies, rely on
+    // the same), and these words are only ever accessed past it.
     uint32_t verdict;    // 0 = not decided; else 0x100 | SegStatus, written by the last joining part
     uint32_t tau_ready;  // 1: the fresh threshold of a pending tensor is in place
     uint32_t pad0;

@@ -149,17 +149,19 @@ void launch_pick_dense(const TensorDesc *tdesc, const PlanEntry *plan, uint32_t 
 // the selection kernel
 // ---------------------------------------------------------------------------
 //
-// Grid: block b < G is the JOIN of join group b (1024 threads; a group is a tensor, or up to
-// GROUP_TILES tiles of one).  With the re-collecting roles enabled, nb = ceil(P / bgroup)
+// Grid, where the chain has launches of its own or there is none: block b < G is the JOIN of join group b (1024 threads; a
+// group is a tensor, or up to GROUP_TILES tiles of one).  With the re-collecting roles enabled, nb = ceil(P / bgroup)
 // RE-HISTOGRAM blocks follow (P: the number of parts), then as many RE-COLLECTION blocks; block
 // b of a role looks after parts b, b + nb, b + 2 nb, ... in turn, so the parts of one tensor
 // lie in different blocks.  These blocks act on tensors of several parts whose prediction
-// failed, and pass over everything else.
+// failed, and pass over everything else.  Where the chain is part of the launch, one block per run of parts of the
+// tensors that take it comes before all of these (its window histogram; the last of a tensor goes on as that tensor's JOIN,
+// whose own block leaves at once), and two blocks per slab (ranking, then emission) come behind.
 //
 //   JOIN      compacts the candidates the streaming pass left in the part's tiles into one
 //             ordered list.  The workgroup that arrives last for a tensor (the only one, for a
 //             tensor of one part) gathers the parts' lists and SELECTS: exact k-th key, ordered
-//             emission, state fix-up, next hint.  A tensor planned for the chain kernels only
+//             emission, state fix-up, next hint.  A tensor planned for the chain only
 //             gets its key window resolved here.  Lists that are complete but beyond one
 //             workgroup's reach are trimmed on the way (threshold from their own histogram).
 //             If the prediction failed otherwise (fewer candidates than k, an overflowed tile)
@@ -172,8 +174,8 @@ void launch_pick_dense(const TensorDesc *tdesc, const PlanEntry *plan, uint32_t 
 //             (one value filling the tensor, say) is selected from the buffers by that one
 //             workgroup -- slow, never wrong.
 //
-// Waiting is only ever for blocks with a lower index, which the hardware dispatches first,
-// and every wait is bounded (A.spin_limit polls).
+// Waiting is only ever for blocks with a lower index, and every wait is bounded (A.spin_limit polls); why that
+// makes progress is stated at the chain (dgs_chain.h).
 
 constexpr uint32_t B_GROUP_MAX = 8;   // most parts one re-collecting workgroup looks after
 
