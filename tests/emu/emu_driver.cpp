@@ -135,6 +135,11 @@ static void fill_grad(const Layout &L, Rng &r, float *g, float scale, int flavou
                 if (q < 140) v = INFINITY;
                 else if (q == 999) v = NAN;
             }
+            if (flavour == 8) {      // 20 entries in every tile, 60 far larger ones in runs of four tiles: winners side by side
+                const uint64_t t = i / dgs::TILE, e = (i * 619u + t) % dgs::TILE;
+                const bool run = t % 16u >= 8u && t % 16u < 12u;
+                v = e < (run ? 60u : 20u) ? (run ? 20.0f : 1.0f) * (1.0f + (float)r.uni()) * sj : 0.0f;
+            }
             g[i] = v;
         }
     }
@@ -684,6 +689,13 @@ int main(int argc, char **argv)
         worker_server("flat 2^20", {1u << 20}, 0.01, 0.01, 1.0f, 0.9f, false, {1, 1, 1}, 0, o, 20);
         return 0;
     }
+    if (argc > 1 && std::string(argv[1]) == "winners") {
+        Opts a;
+        a.seg_mode = 1;
+        worker_server("winners side by side, chain", {150000, 64, 66000}, 0.02, 0.02, 1.0f, 0.5f, false, {1, 1, 1}, 8, a, 61);
+        printed_form("winners side by side, printed form", {150000, 64, 66000}, 0.02, 0.02, 3, a, 62, 8);
+        return 0;
+    }
     if (argc > 1 && std::string(argv[1]) == "small") {
         small_branches<dgs::SEL_WORKER>();
         small_branches<dgs::SEL_PULL>();
@@ -743,6 +755,8 @@ int main(int argc, char **argv)
     const std::vector<float> steady = {1, 1, 1, 1};
     const std::vector<float> jumps = {1, 1, 1e3f, 1e3f, 1e-6f, 1e-6f, 1, 1};
 
+    worker_server("winners side by side, chain", {150000, 64, 66000}, 0.02, 0.02, 1.0f, 0.5f, false, {1, 1, 1}, 8, always, 61);
+    printed_form("winners side by side, printed form", {150000, 64, 66000}, 0.02, 0.02, 3, always, 62, 8);
     worker_server("zero fill on the chain", two, 0.02, 0.03, 1.0f, 0.9f, false, {1, 1, 1}, 5, always, 43);
     printed_form("zero fill on the chain, printed form", two, 0.002, 0.02, 3, always, 44);
     // (more than 1400 pairs in a tensor: the row is updated behind the selection)

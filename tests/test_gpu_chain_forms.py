@@ -35,6 +35,11 @@ def contents(kind, n, rng, count):
         elif kind == "crowded":
             for tile in (9, 20, 63, 64, 127, 128, 129, 200, 201, 202, 203, 400):      # up to 250 entries of a tile far above the rest
                 v[tile * 1024 + rng.choice(1024, int(rng.integers(60, 250)), replace=False)] *= np.float32(40.0)
+        elif kind == "side by side":        # 60 winners in each of four tiles, no tile beyond 64 candidates
+            at = np.arange(n)
+            tile, run = at // 1024, (at // 1024) % 16
+            few = (at * 619 + tile) % 1024 < np.where((run >= 8) & (run < 12), 60, 20)
+            v = np.where(few, np.sign(v) * np.where((run >= 8) & (run < 12), 20, 1) * (1 + np.abs(v) / 8), 0).astype(np.float32)
         elif kind == "jumps":
             v *= np.float32([1.0, 1.0, 1e-6, 1e3, 1.0, 1e-6][t % 6])
         elif kind == "zeros":
@@ -85,7 +90,7 @@ def run_calls(oracle, op, kind, form, repair, rho=0.01, calls=6):
 
 
 @pytest.mark.parametrize("form", ["in-launch", "separate"])
-@pytest.mark.parametrize("kind", ["gaussian", "ties", "crowded", "zeros"])
+@pytest.mark.parametrize("kind", ["gaussian", "ties", "crowded", "side by side", "zeros"])
 @pytest.mark.parametrize("op", ["worker", "diff", "sent"])
 def test_both_forms(oracle, op, kind, form):
     run_calls(oracle, op, kind, form, 1)
