@@ -689,19 +689,6 @@ int main(int argc, char **argv)
         worker_server("flat 2^20", {1u << 20}, 0.01, 0.01, 1.0f, 0.9f, false, {1, 1, 1}, 0, o, 20);
         return 0;
     }
-    if (argc > 1 && std::string(argv[1]) == "winners") {
-        Opts a;
-        a.seg_mode = 1;
-        worker_server("winners side by side, chain", {150000, 64, 66000}, 0.02, 0.02, 1.0f, 0.5f, false, {1, 1, 1}, 8, a, 61);
-        printed_form("winners side by side, printed form", {150000, 64, 66000}, 0.02, 0.02, 3, a, 62, 8);
-        return 0;
-    }
-    if (argc > 1 && std::string(argv[1]) == "small") {
-        small_branches<dgs::SEL_WORKER>();
-        small_branches<dgs::SEL_PULL>();
-        small_branches<dgs::SEL_PULL_V>();
-        return 0;
-    }
     if (argc > 1 && std::string(argv[1]) == "parts") {
         // (built with the library's own part size) Tensors of one part that take the chain and whose scale jumps: the
         // join's workgroup collects them again, and the ranking of the same launch leaves the k-th key
@@ -710,6 +697,12 @@ int main(int argc, char **argv)
         const dgs_stats st = worker_server("chain tensors of one part, collected again", {70001, 64, 131072}, 0.004, 0.01, 1.0f,
                                            0.0f, true, {1, 1e-6f, 1, 1e3f, 1e-6f, 1}, 0, o, 60);
         CHECK(st.repaired_tensors >= 1 && st.fallback_tensors == 0);
+        worker_server("winners side by side, chain", {150000, 64, 66000}, 0.02, 0.02, 1.0f, 0.5f, false, {1, 1, 1}, 8, o, 61);
+        printed_form("winners side by side, printed form", {150000, 64, 66000}, 0.02, 0.02, 3, o, 62, 8);
+        small_branches<dgs::SEL_WORKER>();
+        small_branches<dgs::SEL_PULL>();
+        small_branches<dgs::SEL_PULL_V>();
+        puts("parts, winners and small tensors: all as expected");
         return 0;
     }
     if (argc > 1 && std::string(argv[1]) == "rounds") {
@@ -742,9 +735,6 @@ int main(int argc, char **argv)
     tied_dense("dense request, 12 % share the k-th key", 0.12, 0.1, 46);
     tied_dense("dense request, 20 % share the k-th key of 90 %", 0.2, 0.9, 47);
     row_update();
-    small_branches<dgs::SEL_WORKER>();
-    small_branches<dgs::SEL_PULL>();
-    small_branches<dgs::SEL_PULL_V>();
     const std::vector<uint64_t> ragged = {1, 7, 64, 1000, 8192, 8193, 9408, 3, 100003, 20000, 70001, 17, 65537, 12345};
     const std::vector<uint64_t> two = {150000, 64, 66000};
     Opts def, exact, always, never, norepair;
@@ -755,8 +745,6 @@ int main(int argc, char **argv)
     const std::vector<float> steady = {1, 1, 1, 1};
     const std::vector<float> jumps = {1, 1, 1e3f, 1e3f, 1e-6f, 1e-6f, 1, 1};
 
-    worker_server("winners side by side, chain", {150000, 64, 66000}, 0.02, 0.02, 1.0f, 0.5f, false, {1, 1, 1}, 8, always, 61);
-    printed_form("winners side by side, printed form", {150000, 64, 66000}, 0.02, 0.02, 3, always, 62, 8);
     worker_server("zero fill on the chain", two, 0.02, 0.03, 1.0f, 0.9f, false, {1, 1, 1}, 5, always, 43);
     printed_form("zero fill on the chain, printed form", two, 0.002, 0.02, 3, always, 44);
     // (more than 1400 pairs in a tensor: the row is updated behind the selection)
