@@ -115,7 +115,8 @@ typedef struct dgs_stats {
     uint64_t internal_errors;  /* must stay 0 */
     uint64_t segmented_tensors; /* tensors resolved through the chain, or by the kernels of a dense request */
     uint64_t repaired_tensors;  /* tensors whose prediction failed and that were resolved inside the call with
-                                   a fresh threshold: lists trimmed in place, or collected a second time */
+                                   a fresh threshold or window: lists trimmed in place, candidates
+                                   counted again, or collected a second time */
 } dgs_stats;
 
 /*

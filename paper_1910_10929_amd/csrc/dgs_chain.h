@@ -163,13 +163,14 @@ __device__ __forceinline__ void each_candidate(const SelectArgs &A, const WaveTi
     }
 }
 
-// The window histogram of the candidates in tiles [tile0, tile0 + ntiles) of a tensor, into h (SEG_WBINS counters
-// in LDS, zeroed here).  Returns their number; `over`: a tile had overflowed.
-__device__ __forceinline__ uint32_t window_tiles(const SelectArgs &A, const TensorDesc &td, uint32_t tile0, uint32_t ntiles,
-                                                 uint32_t win, uint32_t *h, uint32_t *wsum, bool &over)
+// How many of the candidates in tiles [tile0, tile0 + ntiles) of a tensor fall into each of `bins` buckets, into h (counters
+// in LDS, zeroed here): bin(key).  Returns their number; `over`: a tile had overflowed.
+template <class Bin>
+__device__ __forceinline__ uint32_t count_tiles(const SelectArgs &A, const TensorDesc &td, uint32_t tile0, uint32_t ntiles,
+                                                uint32_t *h, uint32_t bins, uint32_t *wsum, bool &over, Bin bin)
 {
     const uint32_t tid = threadIdx.x, wave = uniform(tid >> 6);
-    for (uint32_t b = tid; b < SEG_WBINS; b += SEL_THREADS) h[b] = 0;
+    for (uint32_t b = tid; b < bins; b += SEL_THREADS) h[b] = 0;
     __syncthreads();
     uint32_t mine = 0;
     int ovf = 0;
@@ -179,15 +180,21 @@ __device__ __forceinline__ uint32_t window_tiles(const SelectArgs &A, const Tens
         ovf |= w.ovf;
         uint4 e[WINDOW_TPW / 4][2];
         tile_firsts<WINDOW_TPW>(A, w, e);
-        each_candidate<WINDOW_TPW>(A, w, e, [&](uint2 x) {
-            const uint32_t hi12 = (x.y & 0x7FFFFFFFu) >> SEG_LOWBITS;
-            const uint32_t b = (hi12 > win) ? (hi12 - win) : 0u;
-            atomicAdd(&h[min(b, SEG_WBINS - 1u)], 1u);
-        });
+        each_candidate<WINDOW_TPW>(A, w, e, [&](uint2 x) { atomicAdd(&h[bin(x.y & 0x7FFFFFFFu)], 1u); });
     }
     const uint32_t c = block_sum(mine, wsum, SEL_WAVES);
     over = __syncthreads_or(ovf) != 0;
     return c;
+}
+
+// The window histogram: SEG_WBINS buckets of key >> SEG_LOWBITS from `win` on, what lies below in the first, beyond in the last.
+__device__ __forceinline__ uint32_t window_tiles(const SelectArgs &A, const TensorDesc &td, uint32_t tile0, uint32_t ntiles,
+                                                 uint32_t win, uint32_t *h, uint32_t *wsum, bool &over)
+{
+    return count_tiles(A, td, tile0, ntiles, h, SEG_WBINS, wsum, over, [&](uint32_t key) {
+        const uint32_t hi = key >> SEG_LOWBITS;
+        return min((hi > win) ? (hi - win) : 0u, SEG_WBINS - 1u);
+    });
 }
 
 // Tiles of one wavefront of a slab.

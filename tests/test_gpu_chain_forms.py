@@ -104,6 +104,53 @@ def test_failed_predictions(oracle, op, repair, form):
     assert (st.repaired_tensors if repair else st.fallback_tensors) >= 2
 
 
+@pytest.mark.parametrize("form", ["in-launch", "separate"])
+@pytest.mark.parametrize("op", ["worker", "diff", "sent"])
+def test_missed_windows(oracle, op, form):
+    """Values that double from call to call on a fresh row: the k-th key lies more than an octave above the hinted threshold, but
+    no tile overflows.  In the selection's launch the candidates are counted again; without the re-collecting workgroups nothing
+    but the slow selection from the buffers could resolve such a tensor otherwise, and that must stay unused there."""
+    import torch
+    off = synth.offsets_from_sizes(FRONT + ([65_536] * OTHERS if form == "separate" else []))
+    front, rho, dev = synth.offsets_from_sizes(FRONT), 0.001, "cuda:0"
+    n, nf, Kf = int(off[-1]), int(front[-1]), int(sum(np.ceil(rho * s) for s in FRONT))
+    ctx = dgs.Context(off, W=0 if op == "worker" else 1)
+    ctx.set_option(dgs.OPT_SEGMENTED, dgs.SEG_ALWAYS)
+    ctx.set_option(dgs.OPT_REPAIR_ROUND, 0)
+    K = ctx.nnz(rho)
+    idx, val = torch.zeros(K, dtype=torch.int32, device=dev), torch.zeros(K, device=dev)
+    row = torch.zeros((1, n), device=dev)
+    others = torch.randn(n, device=dev, generator=torch.Generator(device=dev).manual_seed(8))
+    if op != "worker":
+        (ctx.server_attach if op == "diff" else ctx.server_attach_sent)(row)
+    rng = np.random.default_rng(94)
+    for t, scale in enumerate([1, 1, 2, 4, 8]):
+        v = (rng.standard_normal(nf) * scale).astype(np.float32)
+        given = others.clone()
+        given[:nf].copy_(torch.from_numpy(v))
+        ref = np.zeros((1, nf), np.float32)
+        row.zero_()
+        if op == "worker":
+            wi, wv = oracle.worker_step(v, ref[0], front, np.float32(1.0), np.float32(0.0), rho)
+            ctx.worker_step(given, row[0], 1.0, 0.0, rho, idx, val, residual_mode=True)
+        elif op == "diff":
+            ref[0] = v
+            row[0] = given
+            wi, wv = oracle.server_pull(ref, 0, front, rho)
+            ctx.server_pull(0, rho, idx, val)
+        else:
+            wi, wv = oracle.server_pull_sent(v, ref, 0, front, rho)
+            ctx.server_pull_sent(given, 0, rho, idx, val)
+        torch.cuda.synchronize()
+        assert_pairs_match(to_host_u32(idx)[:Kf], val.cpu().numpy()[:Kf], wi, wv, f"call {t}")
+        assert_state_match(row[0, :nf].cpu().numpy(), ref[0], f"state {t}")
+    st = ctx.stats()
+    assert st.internal_errors == 0
+    if form == "in-launch":
+        assert st.repaired_tensors >= 2 and st.fallback_tensors == 0
+    ctx.close()
+
+
 SLABS256 = 256 * 128 * 1024      # elements of 256 full slabs
 
 
