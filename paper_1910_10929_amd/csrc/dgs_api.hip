@@ -332,6 +332,19 @@ void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out,
             active += seg ? 1u : 0u;
             K += k;
         }
+        if (active && !beyond && density <= DENSE_DENSITY) {
+            // Nothing but lists that one workgroup selects from as well: the chain only while its slabs are few
+            uint64_t slabs = 0, longest = 0;
+            for (uint32_t j = 0; j < c->J; ++j) {
+                if (!out[j].seg) continue;
+                slabs += chain_slabs(c->offsets[j], c->offsets[j + 1] - c->offsets[j], layout_scale(&c->offsets[0], c->J));
+                longest = std::max<uint64_t>(longest, std::max(out[j].k2, out[j].k2_zero));
+            }
+            if (slabs * CHAIN_SLAB_COST > longest) {
+                for (uint32_t j = 0; j < c->J; ++j) out[j].seg = 0u;
+                active = 0;
+            }
+        }
         if (active && density <= DENSE_DENSITY)
             for (uint32_t j = 0; j < c->J; ++j) {
                 const uint64_t nj = c->offsets[j + 1] - c->offsets[j];

@@ -52,7 +52,13 @@ constexpr uint32_t SEL_LIST_MAX = 10240;
 // 140.4, 152.2 / 141.7): the tests of trimmed lists and of joins of several rounds have tensors of that size and state that
 // the chain resolves none of them (segmented_tensors).  Nothing else speaks against SEL_LIST_MAX there.
 constexpr uint32_t SEL_LIST_MAX_OTHER = 20480, SEL_LONG_TILES = 3584;
-// ... and where the plan holds a tensor beyond that, so that the chain's workgroups are there anyway,
+// One workgroup's time grows with its list, whatever the number of tensors (up to one per compute unit); the chain's grows with
+// its slabs, two workgroups each, one to a compute unit.  A plan without a list beyond SEL_LIST_MAX_OTHER has the chain
+// only while CHAIN_SLAB_COST entries of its longest list come on each slab.  Selection of a worker step, one workgroup / chain, us, tensors of
+// 1.2M elements (10 slabs), lists of 11 K: 16 of them 32.0 / 25.3, 24 32.1 / 27.3, 32 32.1 / 32.5, 48 34.5 / 41.2, 64 38.8 / 50.6,
+// 128 57.1 / 83.5; of 18 K: 32 47.2 / 33.0, 48 49.5 / 43.1, 64 56.2 / 57.1, 128 85.2 / 99.0.
+constexpr uint32_t CHAIN_SLAB_COST = 32;
+// Where the plan holds a tensor beyond its line, so that the chain's workgroups are there anyway, it also serves shorter lists,
 // for tensors of at least SEL_CROWDED_TILES tiles (their join is then what the launch waits for).  us with the
 // line at 8192 / 5000: ResNet-50 shapes, a round at 0.3 % 130.8 / 134.0, at 0.36 % 134.0 / 137.5, at 1 % 159.0 / 161.9, a step
 // without momentum at 0.3 % 72.3 / 74.6, a server at 0.36 % 87.9 / 78.7; transformer shapes at 0.4 % 470.6 / 471.1.

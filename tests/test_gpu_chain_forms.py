@@ -315,3 +315,32 @@ def test_two_contexts_on_two_streams():
             assert torch.equal(x.view(torch.int32), y.view(torch.int32))
         a[0].close()
         b[0].close()
+
+
+@pytest.mark.parametrize("tensors,chain", [(80, True), (81, False)])
+def test_the_chain_gives_way_to_many_tensors(tensors, chain):
+    """Tensors of 512 tiles (4 slabs) with lists planned for 10,242 entries: the chain while there are 32 of them to a slab, one
+    workgroup per tensor from 321 slabs on."""
+    import torch
+    off, dev = synth.offsets_from_sizes([512 * 1024] * tensors), "cuda:0"
+    n, rho = int(off[-1]), (4973 - 0.5) / (512 * 1024)
+    outs = []
+    for mode in (dgs.SEG_AUTO, dgs.SEG_NEVER):
+        gen = torch.Generator(device=dev).manual_seed(12)
+        ctx = dgs.Context(off, W=0)
+        ctx.set_option(dgs.OPT_SEGMENTED, mode)
+        K = ctx.nnz(rho)
+        idx, val = torch.zeros(K, dtype=torch.int32, device=dev), torch.zeros(K, device=dev)
+        state, grad = torch.zeros(n, device=dev), torch.randn(n, device=dev, generator=gen)
+        run = []
+        for _ in range(3):
+            ctx.worker_step(grad, state, 1.0, 0.0, rho, idx, val, residual_mode=True)
+            run += [idx.clone(), val.view(torch.int32).clone()]
+        run.append(state.view(torch.int32).clone())
+        st = ctx.stats()
+        assert st.internal_errors == 0
+        assert st.segmented_tensors == (3 * tensors if chain and mode == dgs.SEG_AUTO else 0)
+        ctx.close()
+        outs.append(run)
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
