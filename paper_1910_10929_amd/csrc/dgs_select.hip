@@ -1054,9 +1054,20 @@ __device__ __forceinline__ bool window_run(const SelectArgs &A, const SegDesc &r
 // HERE: the chain's workgroups are in this launch, for the tensors that take it: before the others one per run of parts
 // (the window histograms), behind them two per slab.  (They have no use for most of the LDS, but with 128 registers
 // there is one workgroup on a compute unit anyway.)
+// (The tables that a workgroup starts with come as arguments of their own, which are in registers then.)
 template <int OP, bool HERE>
-__global__ __launch_bounds__(SEL_THREADS) void k_select(const SelectArgs A)
+__global__ __launch_bounds__(SEL_THREADS) void k_select(const SegDesc *grptab, const TensorDesc *tdesc, const PlanEntry *plan,
+                                                        uint32_t *tau, uint32_t *tprev, uint32_t ngroups, uint32_t nwin,
+                                                        const SelectArgs rest)
 {
+    SelectArgs A = rest;
+    A.grptab = grptab;
+    A.tdesc = tdesc;
+    A.plan = plan;
+    A.tau = tau;
+    A.tprev = tprev;
+    A.ngroups = ngroups;
+    A.nwin = nwin;
     __shared__ PartShared P;
     __shared__ uint2 llist[SEL_LDS_LIST];
     const uint32_t tid = threadIdx.x;
@@ -1250,8 +1261,10 @@ static void launch_select_t(const SelectArgs &a, hipStream_t st, void *ev0, void
 {
     const uint32_t nb = (a.nparts + a.bgroup - 1) / a.bgroup;
     const uint32_t blocks = a.ngroups + (a.repair ? 2u * nb : 0u);
-    if (a.nwin) launch_k(k_select<OP, true>, dim3(a.nwin + blocks + 2u * a.nslab), dim3(SEL_THREADS), st, ev0, ev1, a);
-    else launch_k(k_select<OP, false>, dim3(blocks), dim3(SEL_THREADS), st, ev0, ev1, a);
+    if (a.nwin) launch_k(k_select<OP, true>, dim3(a.nwin + blocks + 2u * a.nslab), dim3(SEL_THREADS), st, ev0, ev1, a.grptab, a.tdesc,
+                         a.plan, a.tau, a.tprev, a.ngroups, a.nwin, a);
+    else launch_k(k_select<OP, false>, dim3(blocks), dim3(SEL_THREADS), st, ev0, ev1, a.grptab, a.tdesc, a.plan, a.tau, a.tprev,
+                  a.ngroups, a.nwin, a);
 }
 
 void launch_select(int op, const SelectArgs &a, void *stream, void *ev0, void *ev1)
