@@ -703,9 +703,9 @@ void carve_workspace(dgs_ctx *c, void *workspace, const Layout &L)
 
 // Tensor, segment and initial-threshold tables of a layout, into host arrays of J,
 // (W + 1) J, J + 1, (sum of tensor_segments) twice, (sum of chain_slabs) and (sum of dense_slabs)
-// entries; fills c->nseg, c->nseg_total, c->ngroups, c->ncslabs and c->ndslabs.
+// entries (order: scratch of J); fills c->nseg, c->nseg_total, c->ngroups, c->ncslabs and c->ndslabs.
 void fill_tables(dgs_ctx *c, TensorDesc *td, uint32_t *tau0, uint32_t *toff, SegDesc *segs, SegDesc *groups,
-                 SegDesc *slabs, uint32_t *dslabs)
+                 SegDesc *slabs, uint32_t *dslabs, uint32_t *order)
 {
     const uint32_t J = c->J, W = c->W;
     uint32_t nsegs = 0, ncs = 0, nds = 0;
@@ -750,12 +750,16 @@ void fill_tables(dgs_ctx *c, TensorDesc *td, uint32_t *tau0, uint32_t *toff, Seg
     c->bgroup = std::min<uint32_t>(8u, std::max<uint32_t>(1u, (nsegs + per_role - 1u) / per_role));
     // Join groups: runs of `gparts` consecutive parts (about GROUP_TILES tiles).  The launch takes
     // the groups of the tensors with several groups first: those tensors end with a gather and
-    // a selection by the last group to arrive, the critical path of the launch.
+    // a selection by the last group to arrive, the critical path of the launch.  The others follow by size: a die
+    // starts a workgroup of 16 wavefronts every 0.15 us, and the launch waits for the largest tensors.
     const uint32_t gparts = std::max<uint32_t>(1u, GROUP_TILES / (SEG_TILES * scale));
     c->gparts = gparts;
     uint32_t g = 0;
+    for (uint32_t j = 0; j < J; ++j) order[j] = j;
+    std::sort(order, order + J, [&](uint32_t a, uint32_t b) { return td[a].n != td[b].n ? td[a].n > td[b].n : a < b; });
     for (uint32_t pass = 0; pass < 2; ++pass)
-        for (uint32_t j = 0; j < J; ++j) {
+        for (uint32_t i = 0; i < J; ++i) {
+            const uint32_t j = order[i];
             const uint32_t ng = (td[j].nseg + gparts - 1) / gparts;
             if ((pass == 0) != (ng > 1)) continue;
             td[j].grp_first = g;
@@ -883,7 +887,8 @@ int dgs_create(dgs_ctx **out, const uint64_t *offsets, uint32_t J, uint32_t W, v
             *slabs = segs + (L.cslabs - L.segtab) / sizeof(SegDesc);
     uint32_t *dslabs = (uint32_t *)(segs + (L.dslabs - L.segtab) / sizeof(SegDesc));
     c->nseg.assign(J, 0u);
-    fill_tables(c, td.data(), tau0.data(), toff.data(), segs, groups, slabs, dslabs);
+    std::vector<uint32_t> order(J);
+    fill_tables(c, td.data(), tau0.data(), toff.data(), segs, groups, slabs, dslabs, order.data());
 
     // What a sampling pass visits: every 16th tile of the buffer, and every tile of the tensors of
     // at most 64 tiles, whose ranks are too small to estimate from a sixteenth.
@@ -1062,7 +1067,8 @@ int dgs_worker_step_static(const uint64_t *offsets, uint32_t J, const float *gra
     c.hint_calls.borrow(hint_calls);
     c.plan_stage = plan;               // one density per call: only the first cache slot is used
     carve_workspace(&c, ws, L);
-    fill_tables(&c, td, tau0, toff, segs, groups, slabs, dslabs);
+    uint32_t order[DGS_STATIC_MAX_TENSORS];
+    fill_tables(&c, td, tau0, toff, segs, groups, slabs, dslabs, order);
     // every call starts from a clean workspace (the array keeps the previous call's contents);
     // with no threshold hints the step takes the two-pass path
     rc = upload_tables(&c, td, tau0, toff, segs, groups, slabs, dslabs, 0);

@@ -182,7 +182,7 @@ __device__ __forceinline__ uint32_t count_tiles(const SelectArgs &A, const Tenso
         tile_firsts<WINDOW_TPW>(A, w, e);
         each_candidate<WINDOW_TPW>(A, w, e, [&](uint2 x) { atomicAdd(&h[bin(x.y & 0x7FFFFFFFu)], 1u); });
     }
-    const uint32_t c = block_sum(mine, wsum, SEL_WAVES);
+    const uint32_t c = block_sum<SEL_WAVES>(mine, wsum);
     over = __syncthreads_or(ovf) != 0;
     return c;
 }
@@ -266,12 +266,8 @@ __device__ __forceinline__ void emit_slab(const SelectArgs &A, uint32_t slab, co
     const uint32_t sum = wave_sum(mine);
     if (lane == 0) C.wtot[wave] = sum;
     __syncthreads();
-    uint32_t before = 0, all = 0;
-#pragma unroll
-    for (uint32_t x = 0; x < WAVES; ++x) {
-        before += (x < wave) ? C.wtot[x] : 0u;
-        all += C.wtot[x];
-    }
+    uint32_t all;
+    const uint32_t before = sum_waves<(int)WAVES>(C.wtot, all);
     if (wave == 0) {
         const bool head = (slab == td.cs_first);
         if (lane == 0) slab_publish<false>(&A.slabs_done[slab], head ? SLAB_SUM : SLAB_OWN, all & 0xFFFFu, all >> 16);

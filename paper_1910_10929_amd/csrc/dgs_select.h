@@ -545,7 +545,7 @@ __device__ __forceinline__ bool small_select(const SelectArgs &A, const TensorDe
             atomicAdd(&S.h[min(hi - base, BINS - 1u)], 1u);
         }
     });
-    seen = block_sum(seen, S.wsum, SEL_WAVES);
+    seen = block_sum<SEL_WAVES>(seen, S.wsum);
     const uint32_t nonzero = seen & 0xFFFFu;
     uint32_t T = 0, rT = pe.k - nonzero;          // (the message is completed with the lowest-index zeros)
     const bool near = (seen >> 16) >= pe.k && S.h[BINS - 1u] < pe.k;      // (the last bucket is open)
@@ -694,7 +694,7 @@ __device__ __forceinline__ void zero_fill_emit(const Src src, const uint32_t c, 
     const uint32_t z = pe.k - c;
     uint32_t mine = 0;
     for (uint32_t p = tid; p < c; p += SEL_THREADS) mine += ((src.index(p) - td.off - p) < z) ? 1u : 0u;
-    const uint32_t P = block_sum(mine, wsum, SEL_WAVES);
+    const uint32_t P = block_sum<SEL_WAVES>(mine, wsum);
     const uint32_t X = z + P;
     for (uint32_t q = tid; q < X; q += SEL_THREADS) {
         const uint32_t ix = td.off + q;

@@ -62,7 +62,7 @@ __global__ __launch_bounds__(256) void k_pick(const TensorDesc *tdesc, const Pla
     }
     PlanEntry pe = plan[j];
     if (sample) {
-        const uint32_t total = block_sum(mine, wsum, 4);
+        const uint32_t total = block_sum<4>(mine, wsum);
         // from here on the histogram is that of the nonzero keys, as in a full pass (bucket 0 held
         // the zeros; keys below 2^19, denormals of about 1e-39, go with them)
         if (threadIdx.x == 0) h[0] = 0;
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(1024) void k_pick_dense(const TensorDesc *tdesc, co
         mine += v;
         g[b] = 0;   // leave the histogram clean for the next use
     }
-    const uint32_t nonzero = block_sum(mine, wsum, SEL_WAVES);
+    const uint32_t nonzero = block_sum<SEL_WAVES>(mine, wsum);
     if (threadIdx.x == 0) h[0] += td.n - nonzero;
     const uint32_t k = plan[j].k;
     find_ranks<HBINS, SEL_WAVES>(h, k, 0u, 0u, rowsum, res);
@@ -531,7 +531,7 @@ __device__ __forceinline__ uint32_t window_step(const SelectArgs &A, const Tenso
     mylow = wave_min_to_last(mylow);
     if (lane_id() == 63 && mylow != 0xFFFFFFFFu) atomicMin(&P.S.kmin, mylow);
     if (HERE && !lists) {
-        c = block_sum(cnt & 0x7FFFFFFFu, P.S.wsum, SEL_WAVES);
+        c = block_sum<SEL_WAVES>(cnt & 0x7FFFFFFFu, P.S.wsum);
         ovf = __syncthreads_or((int)(cnt >> 31)) != 0;
     }
     const uint32_t win_base = seg_window_base(tau_cur, tprev_cur);
@@ -738,7 +738,7 @@ __device__ __forceinline__ uint32_t trim_list(const SelectArgs &A, const Src &sr
     for (uint32_t b = tid; b < 2048; b += SEL_THREADS)
         if (b >= (t >> 20)) reach += P.S.h[b];
     __syncthreads();
-    const uint32_t c2 = block_sum(reach, P.S.wsum, SEL_WAVES);
+    const uint32_t c2 = block_sum<SEL_WAVES>(reach, P.S.wsum);
     __syncthreads();
     if (c2 < pe.k || c2 > list_max) return 0u;
     if (verdict && tid == 0) st_dev(verdict, 0x100u | (uint32_t)SEG_DONE);
@@ -1153,7 +1153,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const SegDesc *grptab, c
                     mine += v & 0x7FFFFFFFu;
                     o |= v >> 31;
                 }
-                cs = block_sum(mine, P.S.wsum, SEL_WAVES);
+                cs = block_sum<SEL_WAVES>(mine, P.S.wsum);
                 ovf = __syncthreads_or((int)o) != 0;
             }
             status = tensor_select<OP, HERE>(A, td, pe, j, 0, false, true, cs, ovf, kmin, tau_cur, tprev_cur, win_join,
