@@ -82,13 +82,17 @@ enum {
                                 (default 2^20, far beyond any wait that ends); it is then counted
                                 in dgs_stats.internal_errors.  What waits: the collection after a
                                 failed prediction, and on every call the ranking and emission of
-                                tensors with long candidate lists and the emission of dense
-                                requests.  What gave up is left unselected, or emitted up to the part that gave up: after
+                                tensors with long candidate lists, the emission of dense
+                                requests and the selection of calls that are one launch (which
+                                calls with a limit below 1024 are not).  What gave up is left unselected, or emitted up to the part that gave up: after
                                 a call that raised internal_errors the outputs and the context are
                                 not to be used */
 };
 
-/* Kernel classes reported by dgs_profile_read(). */
+/*
+ * Kernel classes reported by dgs_profile_read().  A call on a layout small enough to be one launch (up to
+ * 4 M elements or so, at densities of at most 1/32) is counted under _SELECT alone.
+ */
 enum {
     DGS_PROF_WORKER_STREAM = 0, /* accumulate + candidate pass over grad/state */
     DGS_PROF_WORKER_SELECT = 1,

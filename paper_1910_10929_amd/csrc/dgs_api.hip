@@ -29,7 +29,7 @@ size_t align_up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
 struct Layout {          // byte offsets inside the workspace
     size_t tile_desc, tdesc, plans, tau, hint2, tprev, ghist, tile_cnt, heads, slots, ord, stats, flag;
-    size_t qlist, segtab, grptab, grpcnt, segcnt, segstate, cslabs, dslabs, slabs_done, total;
+    size_t qlist, segtab, grptab, grpcnt, segcnt, segstate, cslabs, dslabs, steptab, ranktab, emittab, stepflag, slabs_done, total;
     size_t plan_bytes;   // of one plan: its entries and, where the chain is part of the selection's launch, that launch's tables
 };
 
@@ -85,6 +85,30 @@ uint32_t layout_scale(const uint64_t *offsets, uint32_t J)
     return (uint32_t)(s < 1 ? 1 : (s > 64 ? 64 : s));
 }
 
+// A whole call in one launch: how its layout is cut into units (bt tiles each; 0: it is not).
+struct StepCut {
+    uint32_t bt, units, ranks, emits;
+};
+
+// Units as small as the compute units allow, one each: a unit's loads are what its compute unit takes longest for.
+StepCut step_cut(const uint64_t *offsets, uint32_t J)
+{
+    for (uint32_t bt = 4; bt <= 16; bt *= 2) {
+        uint64_t units = 0, ranks = 0, emits = 0, most = 0;
+        for (uint32_t j = 0; j < J && units <= STEP_UNITS_FEW; ++j) {
+            const uint64_t n = offsets[j + 1] - offsets[j];
+            const uint64_t u = (n > SMALL_N) ? (n + (uint64_t)bt * TILE - 1) / ((uint64_t)bt * TILE) : 1;
+            units += u;
+            most = std::max(most, u);
+            ranks += (n > SMALL_N) ? 1 : 0;
+            if (n >= SEG_MIN_N) emits += (u + SEL_WAVES - 1) / SEL_WAVES;
+        }
+        const bool fits = bt < 16 ? units + ranks + emits <= STEP_BLOCKS : units <= (J <= STEP_FEW ? STEP_UNITS_FEW : STEP_UNITS);
+        if (fits && most <= SEG_MAX_PER_TENSOR) return StepCut{bt, (uint32_t)units, (uint32_t)ranks, (uint32_t)emits};
+    }
+    return StepCut{};
+}
+
 // one_call: for a single call without hints -- one plan, no list of tiles to sample.
 Layout make_layout(const uint64_t *offsets, uint32_t J, uint32_t W, bool one_call = false)
 {
@@ -126,8 +150,13 @@ Layout make_layout(const uint64_t *offsets, uint32_t J, uint32_t W, bool one_cal
     L.grptab = o;    o = align_up(o + (nseg_total + 1) * sizeof(SegDesc));      // groups <= parts
     L.cslabs = o;    o = align_up(o + ncs * sizeof(SegDesc));
     L.dslabs = o;    o = align_up(o + nds * sizeof(uint32_t));
+    const StepCut cut = one_call ? StepCut{} : step_cut(offsets, J);
+    L.steptab = o;   o = align_up(o + cut.units * sizeof(StepUnit));
+    L.ranktab = o;   o = align_up(o + cut.ranks * sizeof(SegDesc));
+    L.emittab = o;   o = align_up(o + cut.emits * sizeof(SegDesc));
     L.grpcnt = o;    o = align_up(o + (nseg_total + 1) * sizeof(uint32_t));
     L.segcnt = o;    o = align_up(o + (nseg_total + 1) * sizeof(uint32_t));
+    L.stepflag = o;  o = align_up(o + 2 * cut.units * sizeof(uint32_t));
     L.segstate = o;  o = align_up(o + (size_t)J * sizeof(SegState));
     L.slabs_done = o; o = align_up(o + ncs * sizeof(uint2));
     L.total = o;
@@ -144,6 +173,7 @@ struct PlanSlot {
     uint32_t nwin = 0, nslab = 0;      // entries of the selection launch's tables (0: the chain has launches of its own)
     uint32_t window_max = 0;
     uint32_t kmax = 0;                 // largest k_j
+    bool step = false, emits = false;  // a predicted call may be one launch; it has emitting workgroups then
     uint64_t K = 0;
     uint64_t wire_words = 0;           // 32-bit words of the wire form's index area
     uint64_t last_use = 0;
@@ -205,6 +235,10 @@ struct dgs_ctx {
     uint32_t ncslabs = 0;              // chain slabs
     uint32_t *dslabs = nullptr;        // dense slabs: the tensor of each
     uint32_t ndslabs = 0;
+    StepUnit *steptab = nullptr;
+    SegDesc *ranktab = nullptr, *emittab = nullptr;
+    uint32_t *stepflag = nullptr;
+    StepCut cut{};                     // a whole call in one launch (no tables: bt = 0)
     uint32_t nseg_total = 0;
     HostArr<uint32_t> nseg;            // per tensor: parts (at least one)
     float *diff = nullptr;
@@ -363,6 +397,26 @@ void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out,
     }
 }
 
+// Whether a predicted call at this plan may be one launch: every list that it expects leaves a fifth of what the ranking workgroup
+// holds free.  (Its threads are dealt out to a power of two of units.  One tensor of 600 K elements at 2 %, 147 units and
+// lists of 18 to 24 K: a worker step 40.6 us in one launch, which reads the lists again, 31.1 in several.)
+bool step_plan(const dgs_ctx *c, const PlanEntry *plan, double density, bool *emits)
+{
+    *emits = false;
+    if (c->cut.bt == 0 || density > DENSE_DENSITY || c->seg_mode != SEG_MODE_AUTO) return false;
+    for (uint32_t j = 0; j < c->J; ++j) {
+        const uint64_t n = c->offsets[j + 1] - c->offsets[j], units = (n + c->cut.bt * TILE - 1) / (c->cut.bt * TILE);
+        if (n < SEG_MIN_N || plan[j].k <= STEP_EMIT_K) continue;      // (a list that does not fit is selected from LDS)
+        *emits = true;
+        uint64_t slots = 1;
+        while (slots < units) slots *= 2;
+        const uint64_t longest = std::max(plan[j].k2, std::max(plan[j].k2_zero, plan[j].k2_pull));
+        if (longest * 5 * slots > 4ull * STEP_ITEMS_KEYS * SEL_THREADS * units) return false;
+    }
+    return true;
+}
+
+constexpr uint32_t STEP_MIN_SPINS = 1024;
 constexpr uint32_t ADD_SENT_K = 1400;      // see run_selection
 
 int upload(dgs_ctx *c, void *dst, const void *src, size_t bytes);
@@ -466,6 +520,7 @@ int get_plan(dgs_ctx *c, double density, uint32_t *slot_out, uint64_t *K_out)
     for (uint32_t j = 0; j < c->J; ++j) p.kmax = std::max(p.kmax, stage[j].k);
     p.K = K;
     p.wire_words = wire_words;
+    p.step = step_plan(c, stage, density, &p.emits);
     p.last_use = c->tick;
     *slot_out = victim;
     *K_out = K;
@@ -509,6 +564,9 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
     const int op_again = (op_stream == OP_SUB) ? OP_SUB : OP_IDENT;
     const bool dense_req = density > DENSE_DENSITY;
     const bool exact = !dense_req && (c->force_exact || c->force_sample || c->hint_density[hint_set] != density);
+    // A small layout's predicted call is one launch.  (It rests on waits: not where those are bounded to next to nothing.)
+    const bool step = !dense_req && !exact && c->plan_slot[slot].step && c->repair_round && c->stream_quads == 0 &&
+                      c->spin_limit >= STEP_MIN_SPINS;
     uint32_t *tau = c->tau + (size_t)hint_set * c->J;
     const PlanEntry *plan = plan_at(c, slot);
 
@@ -532,7 +590,9 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
 
     const bool have_seg = c->plan_slot[slot].nseg_active != 0;
     uint32_t *tprev = c->tprev + (size_t)hint_set * c->J;
-    if (dense_req && have_seg) {
+    if (step) {
+        // (accumulates by itself)
+    } else if (dense_req && have_seg) {
         // dense request: the accumulate pass also histograms the keys, which
         // gives the leading bits of each k-th key; the rest is found by reading the tensors again
         ProfSlot ps(c, prof_stream);
@@ -639,7 +699,21 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
     se.spin_limit = c->spin_limit;
     se.dslabs = c->dslabs;
     se.ndslabs = c->ndslabs;
-    if (!(dense_req && have_seg)) {
+    se.steptab = c->steptab;
+    se.ranktab = c->ranktab;
+    se.emittab = c->emittab;
+    se.stepflag = c->stepflag;
+    se.nstep = c->cut.units;
+    se.nrank = c->cut.ranks;
+    se.nemit = c->plan_slot[slot].emits ? c->cut.emits : 0u;
+    se.multi = c->nseg_total > c->J ? 1u : 0u;
+    se.grad = grad;
+    se.lr = lr;
+    if (step) {
+        ProfSlot ps(c, prof_select);
+        launch_step(op_select, se, c->stream, ps.ev0, ps.ev1);
+        ps.launched();
+    } else if (!(dense_req && have_seg)) {
         ProfSlot ps(c, prof_select);
         se.nwin = c->plan_slot[slot].nwin;
         se.nslab = c->plan_slot[slot].nslab;
@@ -660,7 +734,7 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
         if (se.later) launch_add_sent(se, (uint32_t)K, c->stream, ps.ev1);
         ps.launched();
     }
-    if (have_seg && se.nwin == 0) {
+    if (!step && have_seg && se.nwin == 0) {
         ProfSlot ps(c, prof_seg);
         if (dense_req) launch_dense(op_select, se, c->stream, ps.ev0, ps.ev1);
         else launch_chain(op_select, se, c->stream, ps.ev0, ps.ev1);
@@ -698,6 +772,10 @@ void carve_workspace(dgs_ctx *c, void *workspace, const Layout &L)
     c->segstate = (SegState *)(c->ws + L.segstate);
     c->cslabs = (SegDesc *)(c->ws + L.cslabs);
     c->dslabs = (uint32_t *)(c->ws + L.dslabs);
+    c->steptab = (StepUnit *)(c->ws + L.steptab);
+    c->ranktab = (SegDesc *)(c->ws + L.ranktab);
+    c->stepflag = (uint32_t *)(c->ws + L.stepflag);
+    c->emittab = (SegDesc *)(c->ws + L.emittab);
     c->slabs_done = (uint2 *)(c->ws + L.slabs_done);
 }
 
@@ -778,6 +856,35 @@ void fill_tables(dgs_ctx *c, TensorDesc *td, uint32_t *tau0, uint32_t *toff, Seg
     c->ngroups = g;
 }
 
+// Units, ranking and emitting workgroups of a whole call in one launch, the largest tensors first: their ranking is what
+// the launch waits for.
+void fill_step_tables(const dgs_ctx *c, StepUnit *units, SegDesc *ranks, SegDesc *emits)
+{
+    std::vector<uint32_t> order(c->J);
+    for (uint32_t j = 0; j < c->J; ++j) order[j] = j;
+    auto size = [&](uint32_t j) { return (uint32_t)(c->offsets[j + 1] - c->offsets[j]); };
+    std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return size(a) > size(b); });
+    uint32_t nu = 0, nr = 0, ne = 0;
+    const uint32_t bt = c->cut.bt;
+    for (const uint32_t j : order) {
+        const uint32_t off = (uint32_t)c->offsets[j], n = size(j);
+        if (n <= SMALL_N) {
+            units[nu++] = StepUnit{j, off, n, n, 0, 0, 0, 0};
+            continue;
+        }
+        const uint32_t per = bt * TILE, count = (n + per - 1) / per;
+        const uint32_t tlo = off / TILE, tiles = (off + n - 1) / TILE - tlo + 1;
+        ranks[nr++] = SegDesc{j, nu, count, 0};
+        if (n >= SEG_MIN_N)
+            for (uint32_t u = 0; u < count; u += SEL_WAVES)
+                emits[ne++] = SegDesc{j, nu + u, std::min(SEL_WAVES, count - u), u / SEL_WAVES};
+        // (the tensor has at least as many tiles in the scratch as its elements need)
+        for (uint32_t u = 0; u < count; ++u)
+            units[nu++] = StepUnit{j, off + u * per, std::min(per, n - u * per), n, (tlo + j + bt * u) * CAPT,
+                                   std::min(bt, tiles - bt * u) * CAPT - STEP_LINE, bt / 4, 0};
+    }
+}
+
 // Host -> device: a copy on the stream, or -- for the context that must not allocate or copy
 // -- kernels that carry the bytes as their arguments.
 int upload(dgs_ctx *c, void *dst, const void *src, size_t bytes)
@@ -791,7 +898,7 @@ int upload(dgs_ctx *c, void *dst, const void *src, size_t bytes)
 }
 
 // Tables up, counters cleared: what a context's workspace holds before its first call.  tabs != 0: segs,
-// groups, slabs and dslabs lie in one host block of that many bytes, placed as in the workspace.
+// groups, slabs, dslabs and the tables of a whole call in one launch lie in one host block of that many bytes, placed as in the workspace.
 int upload_tables(dgs_ctx *c, const TensorDesc *td, const uint32_t *tau0, const uint32_t *toff, const SegDesc *segs,
                   const SegDesc *groups, const SegDesc *slabs, const uint32_t *dslabs, size_t tabs)
 {
@@ -814,6 +921,7 @@ int upload_tables(dgs_ctx *c, const TensorDesc *td, const uint32_t *tau0, const 
     launch_fill_u32(c->tile_cnt, 0u, (size_t)c->ntiles + 4, c->stream);
     launch_fill_u32((uint32_t *)c->stats, 0u, sizeof(DevStats) / 4, c->stream);
     launch_fill_u32(c->flag, 0u, 16, c->stream);
+    launch_fill_u32(c->stepflag, 0u, 2 * (size_t)c->cut.units, c->stream);
     launch_fill_u32((uint32_t *)c->segstate, 0u, (size_t)J * sizeof(SegState) / 4, c->stream);
     return hipGetLastError() == hipSuccess ? DGS_OK : DGS_EHIP;
 }
@@ -879,7 +987,7 @@ int dgs_create(dgs_ctx **out, const uint64_t *offsets, uint32_t J, uint32_t W, v
     std::vector<TensorDesc> td(J);
     std::vector<uint32_t> tau0((size_t)(W + 1) * J);
     std::vector<uint32_t> toff(J + 1);
-    // parts, join groups, chain slabs and dense slabs, as they lie in the workspace: one upload
+    // parts, join groups, chain slabs, dense slabs and the units of a call in one launch, as they lie in the workspace: one upload
     const size_t tabs = L.grpcnt - L.segtab;      // (grpcnt follows them)
     static_assert(ALIGN % sizeof(SegDesc) == 0, "the tables start at whole entries");
     std::vector<SegDesc> tab(tabs / sizeof(SegDesc));
@@ -887,6 +995,11 @@ int dgs_create(dgs_ctx **out, const uint64_t *offsets, uint32_t J, uint32_t W, v
             *slabs = segs + (L.cslabs - L.segtab) / sizeof(SegDesc);
     uint32_t *dslabs = (uint32_t *)(segs + (L.dslabs - L.segtab) / sizeof(SegDesc));
     c->nseg.assign(J, 0u);
+    c->cut = step_cut(offsets, J);
+    static_assert(sizeof(StepUnit) == 2 * sizeof(SegDesc), "among the other tables");
+    if (c->cut.bt)
+        fill_step_tables(c, (StepUnit *)(segs + (L.steptab - L.segtab) / sizeof(SegDesc)), segs + (L.ranktab - L.segtab) / sizeof(SegDesc),
+                         segs + (L.emittab - L.segtab) / sizeof(SegDesc));
     std::vector<uint32_t> order(J);
     fill_tables(c, td.data(), tau0.data(), toff.data(), segs, groups, slabs, dslabs, order.data());
 

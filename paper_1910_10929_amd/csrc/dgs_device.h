@@ -122,6 +122,19 @@ constexpr uint32_t SEG_MAX_PER_TENSOR = 512;       // parts per tensor whose lis
 //   SEG_PENDING   the prediction failed: the parts collect again with a fresh threshold
 //   SEG_FALLBACK  left to the dense single-workgroup selection
 enum SegStatus { SEG_IDLE = 0, SEG_DONE = 1, SEG_FALLBACK = 2, SEG_PENDING = 4, SEG_ALL = 6, SEG_ACTIVE = 8, SEG_LISTS = 10, SEG_ZERO = 12 };
+// A whole call in one launch (k_step): units of 4 or 8 tiles while all workgroups, STEP_BLOCKS, have a compute unit each;
+// then of 16, up to STEP_UNITS of them, or STEP_UNITS_FEW of at most STEP_FEW tensors.  us, streaming pass and selection / one launch: a worker step on
+// one tensor of 100 K elements at 0.1 % 14.8 / 11.1, of 1M at 1 % 25.3 / 23.4, of 4M at 0.1 % 31.8 / 24.7, on 64 of 500 K in all at 1 %
+// 13.9 / 12.1, 8 of 4M at 1 % 30.4 / 25.9, 24 of 4M at 1 % (264 units) 23.9 / 24.5; an event of a server with 4 difference rows 16.0 /
+// 13.4, 33.7 / 28.4, 34.3 / 25.2, 15.9 / 13.4, 45.8 / 37.1, 31.5 / 31.6.  Beyond: 8 of 5M at 0.3 % (312) a round 49.3 / 53.3, 8 of 6M at 0.1 % an
+// event 22.3 / 23.0, 200 mixed of 4M a step 21.5 / 22.6; but 3 of 5M at 0.3 % (306) a round 66.7 / 59.5, one of 8M at 0.1 % (489) 102.4 / 91.1.
+// (The CPU test build with small parts keeps to the kernels that larger layouts take.)
+constexpr uint32_t STEP_BLOCKS = SEG_TILES < 128 ? 0 : 256, STEP_UNITS = SEG_TILES < 128 ? 0 : 272, STEP_UNITS_FEW = SEG_TILES < 128 ? 0 : 512;
+constexpr uint32_t STEP_FEW = 4;
+// Where a tensor of at least SEG_MIN_N elements has more than STEP_EMIT_K pairs, those tensors have emitting workgroups.
+constexpr uint32_t STEP_EMIT_K = 2500;
+constexpr uint32_t STEP_ITEMS = 16, STEP_ITEMS_KEYS = 32;      // entries, or keys, that a thread of the ranking holds in registers
+constexpr uint32_t STEP_DONE = 0xFFFFFFFFu;          // SegState::key.x: nothing for the emitting workgroups to do
 enum SegMode { SEG_MODE_AUTO = 0, SEG_MODE_ALWAYS = 1, SEG_MODE_NEVER = 2 };
 
 struct TensorDesc {
@@ -157,6 +170,19 @@ struct SegDesc {
 
 constexpr uint32_t CHAIN_STATUS_SHIFT = 20, KEY_READY = 0x80000000u;      // (pfx: 31 - SEG_LOWBITS bits)
 
+// A unit of a whole call in one launch: a run of elements of one tensor (a small tensor is one), and where in the
+// ordered-list scratch its list lies: one line, then room for `cap` values, then for as many indices.
+struct StepUnit {
+    uint32_t j, e0, count;        // its tensor, first element, elements
+    uint32_t n;                   // elements of the tensor
+    uint32_t ord0;                // its list in SelectArgs::ord
+    uint32_t cap;                 // a quarter of its elements, less the line
+    uint32_t rows;                // rows of 256 elements of a wavefront: 1, 2 or 4 (16 such wavefronts are a unit)
+    uint32_t pad;
+};
+constexpr uint32_t STEP_LINE = 16;                   // words; the second two of a run's first unit: what the run publishes
+constexpr uint32_t STEP_READY = 0x80000000u, STEP_OVER = 0x40000000u;      // (over: more than there was room for)
+
 struct SegState {        // per tensor, rewritten by every selection
     uint32_t status;     // SegStatus
     uint32_t pfx;        // key >> SEG_LOWBITS of the k-th entry (dense request: its leading bits so far)
@@ -171,13 +197,14 @@ struct SegState {        // per tensor, rewritten by every selection
     uint32_t tau_ready;  // 1: the fresh threshold of a pending tensor is in place
     uint32_t pad0;
     uint2 chain;         // the chain in the selection's launch: 0 = not decided; else r2, and status << CHAIN_STATUS_SHIFT | pfx
-    uint2 key;           // chain: 0 = not ranked; else rT, and KEY_READY | T (one store either, which needs no second)
+    uint2 key;           // chain, and k_step's emission: 0 = not ranked; else rT, and KEY_READY | T (one store either, which needs
+                         // no second)
     uint32_t pad1[20];
     // What is counted in, on a line of its own: a line that is added to all the time is fetched anew by everybody who
     // polls a word of it (transformer shapes, 180 slabs of one tensor: the arrivals alone took 7 us).
     uint32_t arrive[4];  // parts that have finished: [0] join, [1] re-histogram, [2] re-collection, [3] chain prefix
     uint32_t seen[2];    // readers of verdict / tau_ready that have passed (the last one clears)
-    uint32_t chain_seen; // the same for chain and key
+    uint32_t chain_seen; // the same for chain and key (k_step: key alone)
     uint32_t pad2[25];
 };
 static_assert(sizeof(SegState) == 256, "two lines of 128 bytes");
@@ -264,6 +291,15 @@ struct SelectArgs {
     const uint32_t *slabtab;
     uint32_t nwin, nslab;
     uint32_t window_max;          // histograms of a tensor at most
+    // A whole call in one launch (k_step).
+    const StepUnit *steptab;      // its units: nstep of them, a tensor's one after the other
+    const SegDesc *ranktab;       // its ranking workgroups (tile0: the tensor's first unit in steptab, ntiles: how many), nrank of them
+    const SegDesc *emittab;       // the runs of up to SEL_WAVES units that an emitting workgroup takes (sidx: which run of the tensor)
+    uint32_t *stepflag;           // per unit, for the ranking: 0, or STEP_READY and the entries of its list; then as many for the emission
+    uint32_t nstep, nrank, nemit;
+    uint32_t multi;               // some tensor has several parts
+    const float *grad;            // SEL_WORKER
+    float lr;
 };
 
 // Host-callable launchers (defined next to the kernels).
@@ -281,6 +317,8 @@ void launch_select(int op, const SelectArgs &a, void *stream, void *ev0, void *e
 void launch_add_sent(const SelectArgs &a, uint32_t K, void *stream, void *ev1);
 // Long candidate lists: the parts' window histograms, before the selection kernel, and what
 // remains behind it for tensors left SEG_ACTIVE / SEG_LISTS / SEG_ZERO.
+// A whole worker step or pull.
+void launch_step(int op, const SelectArgs &a, void *stream, void *ev0, void *ev1);
 void launch_window(const SelectArgs &a, void *stream, void *ev0);
 void launch_chain(int op, const SelectArgs &a, void *stream, void *ev0, void *ev1);
 // Dense request: exact k-th keys and emission, reading the tensors themselves.

@@ -11,10 +11,12 @@ namespace dgs {
 // ---------------------------------------------------------------------------
 
 // The value the selection ranks at flat index ix, read from the buffers themselves
-// (dense sources, zero fill): the state / difference row, or model - sent_k.
-template <int OP>
+// (dense sources, zero fill): the state / difference row, or model - sent_k.  WRITTEN: another workgroup
+// of this launch may have stored the worker's state.
+template <int OP, bool WRITTEN = false>
 __device__ __forceinline__ float row_value(const float *state, const float *model, uint32_t ix)
 {
+    if (WRITTEN && OP == SEL_WORKER) return __uint_as_float(ld_dev((const uint32_t *)state + ix));
     return (OP == SEL_PULL_V) ? (model[ix] - state[ix]) : state[ix];
 }
 
@@ -38,7 +40,7 @@ __device__ __forceinline__ bool index_ok(const SelectArgs &A, uint32_t ix)
     return false;
 }
 
-template <int OP>
+template <int OP, bool WRITTEN>
 struct SrcDense {          // the tensor itself: position p <-> element off + p
     static constexpr bool AGG = false;
     const float *base;
@@ -46,7 +48,7 @@ struct SrcDense {          // the tensor itself: position p <-> element off + p
     uint32_t off;
     __device__ __forceinline__ uint32_t bits(uint32_t p) const
     {
-        return __float_as_uint(row_value<OP>(base, model, off + p));
+        return __float_as_uint(row_value<OP, WRITTEN>(base, model, off + p));
     }
     __device__ __forceinline__ uint32_t index(uint32_t p) const { return off + p; }
 };
@@ -78,12 +80,19 @@ struct SrcSplit {          // a list whose first SEL_LDS_LIST entries are in LDS
 // The four consecutive elements e0 .. e0 + 3 (e0 a multiple of 4) of the ranked row as bit
 // patterns, and which of them belong to the tensor [lo, hi): one 16-byte load per buffer where
 // the quad lies inside the tensor, element by element at a tensor border.
-template <int OP>
+// (All lanes of a wavefront call together, in the same tile.)
+template <int OP, bool WRITTEN = false>
 __device__ __forceinline__ uint32_t quad_bits(const SelectArgs &A, uint32_t e0, uint32_t lo, uint32_t hi,
                                               uint32_t (&bits)[4])
 {
+    const uint32_t base = (WRITTEN && OP == SEL_WORKER) ? uniform(e0 / TILE * TILE) : 0u;
     if (e0 >= lo && e0 + 3u < hi) {
-        f32x4 v = *(const f32x4_any *)(A.state + e0);
+        f32x4 v;
+        if (WRITTEN && OP == SEL_WORKER) {
+            v = load_through16(A.state + base, (e0 - base) * 4u);
+        } else {
+            v = *(const f32x4_any *)(A.state + e0);
+        }
         if (OP == SEL_PULL_V) v = *(const f32x4_any *)(A.model + e0) - v;      // one fp32 subtraction per element
         bits[0] = __float_as_uint(v.x);
         bits[1] = __float_as_uint(v.y);
@@ -96,7 +105,7 @@ __device__ __forceinline__ uint32_t quad_bits(const SelectArgs &A, uint32_t e0, 
     for (int x = 0; x < 4; ++x) {
         const uint32_t e = e0 + x;
         const bool ok = e >= lo && e < hi;
-        bits[x] = ok ? __float_as_uint(row_value<OP>(A.state, A.model, e)) : 0u;
+        bits[x] = ok ? __float_as_uint(row_value<OP, WRITTEN>(A.state, A.model, e)) : 0u;
         in |= ok ? (1u << x) : 0u;
     }
     return in;
@@ -172,12 +181,15 @@ __device__ __forceinline__ uint32_t win_base_of(uint32_t tau_cur, uint32_t t_pre
     return max(tau_cur >> win_shift(OP), max(t_prev >> win_shift(OP), WIN_BINS / 2) - WIN_BINS / 2);
 }
 
+constexpr uint32_t FEW = 256;
+
 struct SelShared {
     alignas(16) uint32_t h[4096];      // (the join keeps its tiles in the upper half)
     uint32_t wsum[SEL_WAVES];
     uint32_t rowsum[64];
     int res[6];
     uint32_t kmin;
+    uint32_t few, few_key[FEW], few_res[2];      // the keys that share the prefix of the k-th one, where they are few, and its rank
 };
 
 // Count into an LDS histogram.  With AGG (all 64 lanes must call this together), the
@@ -225,25 +237,81 @@ __device__ __forceinline__ uint32_t hint_extrapolated(uint32_t kmin, uint32_t c,
     return max(tn, 1u);
 }
 
-// Exact selection over `cN` ordered entries of `src`; emits the k winners in
-// order and applies the state fix-up.  If R != 0 and R <= cN, also finds a key
+// The key of rank r2 (from the top) among the `sharing` keys in S.few_key, FEW at most, which differ in their `shift` low bits: those
+// bits, and the rank among the keys equal to it.  One wavefront works it out for all; called behind the barrier that
+// follows the last entry, and ends with one.
+__device__ __forceinline__ void rank_few(SelShared &S, uint32_t sharing, uint32_t r2, uint32_t shift, uint32_t &low, uint32_t &rT)
+{
+    if (uniform(threadIdx.x >> 6) == 0) {
+        const uint32_t lane = lane_id(), mask = (1u << shift) - 1u;
+        const uint32_t mine = (lane < sharing) ? S.few_key[lane] & mask : 0u;
+        uint32_t l = 0, r = 0;
+        {
+            uint32_t more[FEW / 64 - 1];
+#pragma unroll
+            for (uint32_t i = 0; i < FEW / 64 - 1; ++i) more[i] = (64u * (i + 1u) + lane < sharing) ? S.few_key[64u * (i + 1u) + lane] & mask : 0u;
+            auto reach = [&](uint32_t bound) {      // how many are `bound` or more
+                uint32_t m = (uint32_t)__popcll(ballot64(lane < sharing && mine >= bound));
+                if (sharing > 64u) {
+#pragma unroll
+                    for (uint32_t i = 0; i < FEW / 64 - 1; ++i) m += (uint32_t)__popcll(ballot64(64u * (i + 1u) + lane < sharing && more[i] >= bound));
+                }
+                return m;
+            };
+#pragma unroll 1
+            for (uint32_t bit = 1u << (shift - 1u); bit != 0; bit >>= 1)
+                if (reach(l | bit) >= r2) l |= bit;      // (kept while at least r2 keys have it)
+            r = r2 - reach(l + 1u);
+        }
+        if (lane == 0) {
+            S.few_res[0] = l;
+            S.few_res[1] = r;
+        }
+    }
+    __syncthreads();
+    low = S.few_res[0];
+    rT = S.few_res[1];
+}
+
+// The next threshold as a window histogram shows it: its ranks R (bR, rR) and `third` (bE), see select_key.  lo: the first
+// bucket that may hold a result.
+template <int OP>
+__device__ __forceinline__ void window_hint(const uint32_t *h, uint32_t base, int lo, int bR, uint32_t rR, int bE, bool measurable,
+                                            uint32_t R, uint32_t cN, uint32_t qlow, uint32_t kmin, uint32_t *tau_next,
+                                            uint32_t *expect, uint32_t *q_e)
+{
+    constexpr uint32_t SHIFT = win_shift(OP);
+    if (measurable) {
+        const uint32_t edge = (base + (uint32_t)bR) << SHIFT;
+        *tau_next = edge ? edge : 1u;
+        *expect = R - rR + h[bR];
+        if (bE >= lo && bE < (int)WIN_BINS - 1) *q_e = (base + (uint32_t)bE) << SHIFT;
+    } else if (R != 0 && bE >= lo && bE < (int)WIN_BINS - 1) {
+        const uint32_t top = (base + (uint32_t)bE + 1u) << SHIFT;   // the lowest quarter ends below it
+        *tau_next = hint_extrapolated(max(kmin, 1u), cN, R, qlow, top - min(kmin, top - 1u));
+        *expect = R;
+    }
+}
+
+// The k-th key of the `cN` ordered entries of `src` (T), and how many of the entries equal to it are taken
+// (rT).  If R != 0 and R <= cN, also finds a key
 // prefix of the entry of rank R -- 31 - win_shift(OP) bits where the window resolved
 // it, 21 from the passes without one: *tau_next = its lower edge (>= 1) and
 // *expect = how many entries lie at or above that edge; otherwise both 0.
 // Candidate lists come with a window: win_base = first bucket (key >> win_shift(OP)), 0xFFFFFFFF for
 // other sources; win_min = 1 if entries may lie below the base (bucket 0 is then mixed and
 // cannot hold a result), else 0; win_ready: S.h already holds the window histogram of the
-// entries (window_count); kmin = smallest key of the list.
-template <int OP, int ITEMS, class Src>
-__device__ __forceinline__ void select_emit(const Src src, const uint32_t cN, const uint32_t k,
-                                            const uint32_t R, const uint32_t Eq, const uint32_t win_base,
-                                            const uint32_t win_min, const bool win_ready, const uint32_t kmin,
-                                            SelShared &S, const SelectArgs &A, const uint32_t outoff,
-                                            uint32_t *tau_next, uint32_t *expect, uint32_t *q_e,
-                                            uint32_t *t_out)
+// entries (window_count); kmin = smallest key of the list.  With a window, R and Eq need be known to the first three
+// wavefronts only, and what they lead to is thread 0's.  Returns whether it was found (it is, for cN >= k).
+template <int OP, class Src>
+__device__ __forceinline__ bool select_key(const Src src, const uint32_t cN, const uint32_t k,
+                                           uint32_t R, const uint32_t Eq, const uint32_t win_base,
+                                           const uint32_t win_min, const bool win_ready, const uint32_t kmin,
+                                           SelShared &S, const SelectArgs &A, uint32_t *tau_next, uint32_t *expect,
+                                           uint32_t *q_e, uint32_t &T, uint32_t &rT)
 {
     const uint32_t tid = threadIdx.x;
-    const bool measurable = (R != 0) && (cN >= R);
+    bool measurable = (R != 0) && (cN >= R);
     *tau_next = 0;
     *expect = 0;
     *q_e = 0;
@@ -292,16 +360,8 @@ __device__ __forceinline__ void select_emit(const Src src, const uint32_t cN, co
                 pfx = base + (uint32_t)bk;
                 r2 = rk;
                 lowbits = SHIFT;
-                if (measurable) {
-                    const uint32_t edge = (base + (uint32_t)bR) << SHIFT;
-                    *tau_next = edge ? edge : 1u;
-                    *expect = R - rR + S.h[bR];
-                    if (bE >= lo && bE < (int)WIN_BINS - 1) *q_e = (base + (uint32_t)bE) << SHIFT;
-                } else if (R != 0 && bE >= lo && bE < (int)WIN_BINS - 1) {
-                    const uint32_t top = (base + (uint32_t)bE + 1u) << SHIFT;   // the lowest quarter ends below it
-                    *tau_next = hint_extrapolated(max(kmin, 1u), cN, R, qlow, top - min(kmin, top - 1u));
-                    *expect = R;
-                }
+                if (tid == 0)
+                    window_hint<OP>(S.h, base, lo, bR, rR, bE, measurable, R, cN, qlow, kmin, tau_next, expect, q_e);
             }
             __syncthreads();
             if (have_prefix || base == (kmin >> SHIFT)) break;
@@ -312,6 +372,12 @@ __device__ __forceinline__ void select_emit(const Src src, const uint32_t cN, co
     }
 
     if (!have_prefix) {
+        if (Src::AGG && win_base != 0xFFFFFFFFu) {      // (R is known to the wavefronts that search only)
+            if (tid == 0) S.kmin = R;
+            __syncthreads();
+            R = S.kmin;
+            measurable = (R != 0) && (cN >= R);
+        }
         // ---- pass 1: key bits [30:20]
         for (uint32_t b = tid; b < 2048; b += SEL_THREADS) S.h[b] = 0;
         __syncthreads();
@@ -334,7 +400,7 @@ __device__ __forceinline__ void select_emit(const Src src, const uint32_t cN, co
         __syncthreads();
         if (b1 < 0 || c1 < 0) {   // cannot happen for cN >= k
             if (tid == 0) atomicAdd(&A.stats->internal_errors, 1ull);
-            return;
+            return false;
         }
 
         // ---- pass 2: key bits [19:10] inside bucket b1 (and inside c1 for the hint)
@@ -374,7 +440,7 @@ __device__ __forceinline__ void select_emit(const Src src, const uint32_t cN, co
         }
         if (b2 < 0) {
             if (tid == 0) atomicAdd(&A.stats->internal_errors, 1ull);
-            return;
+            return false;
         }
         pfx = ((uint32_t)b1 << 10) | (uint32_t)b2;
         lowbits = 10;
@@ -398,13 +464,28 @@ __device__ __forceinline__ void select_emit(const Src src, const uint32_t cN, co
     }
     find_ranks<(int)LOW_BINS, SEL_WAVES>(S.h, r2, 0u, 0u, S.rowsum, S.res);
     const int b3 = S.res[0];
-    const uint32_t rT = (uint32_t)S.res[1];   // how many entries equal to T are taken (lowest index first)
+    rT = (uint32_t)S.res[1];
     __syncthreads();
     if (b3 < 0) {
         if (tid == 0) atomicAdd(&A.stats->internal_errors, 1ull);
-        return;
+        return false;
     }
-    const uint32_t T = (pfx << lowbits) | (uint32_t)b3;
+    T = (pfx << lowbits) | (uint32_t)b3;
+    return true;
+}
+
+// Exact selection: emits the k winners in order and applies the state fix-up.
+template <int OP, int ITEMS, class Src>
+__device__ __forceinline__ void select_emit(const Src src, const uint32_t cN, const uint32_t k,
+                                            const uint32_t R, const uint32_t Eq, const uint32_t win_base,
+                                            const uint32_t win_min, const bool win_ready, const uint32_t kmin,
+                                            SelShared &S, const SelectArgs &A, const uint32_t outoff,
+                                            uint32_t *tau_next, uint32_t *expect, uint32_t *q_e,
+                                            uint32_t *t_out)
+{
+    const uint32_t tid = threadIdx.x;
+    uint32_t T, rT;      // (ties: lowest index first)
+    if (!select_key<OP>(src, cN, k, R, Eq, win_base, win_min, win_ready, kmin, S, A, tau_next, expect, q_e, T, rT)) return;
     *t_out = T;
 
     // ---- ordered emission
@@ -493,7 +574,8 @@ __device__ __forceinline__ void select_emit(const Src src, const uint32_t cN, co
 // 16.3 / 16.0 / 17.7; pulls on the printed state of the 60 23.3 / - / 21.1; first calls on the 60 27.0 / - / 21.0 (two
 // kernels more).  A miss that left the registers and began again with the generic passes: 26.0, 30.5, 19.0; 29.5; 28.2.
 // Returns whether the window held the k-th key (uniform; tests ask).
-template <int OP>
+// STEP: the worker's accumulate comes first (no streaming pass has), and every element of the state is stored.
+template <int OP, bool STEP = false>
 __device__ __forceinline__ bool small_select(const SelectArgs &A, const TensorDesc &td, const PlanEntry &pe, uint32_t j,
                                              SelShared &S)
 {
@@ -510,6 +592,11 @@ __device__ __forceinline__ bool small_select(const SelectArgs &A, const TensorDe
             const f32x4 s = *(const f32x4_any *)(A.state + td.off + p0 + x);
             f32x4 v = s;
             if (OP == SEL_PULL_V) v = *(const f32x4_any *)(A.model + td.off + p0 + x) - s;
+            if (STEP && OP == SEL_WORKER) {
+                const f32x4 g = *(const f32x4_any *)(A.grad + td.off + p0 + x);
+#pragma unroll
+                for (int y = 0; y < 4; ++y) v[y] = __builtin_fmaf(A.lr, g[y], s[y]);
+            }
 #pragma unroll
             for (int y = 0; y < 4; ++y) {
                 bits[x + y] = __float_as_uint(v[y]);
@@ -519,7 +606,8 @@ __device__ __forceinline__ bool small_select(const SelectArgs &A, const TensorDe
 #pragma unroll
             for (int y = 0; y < 4; ++y) {
                 const bool in = p0 + x + y < td.n;
-                const float s = in ? A.state[td.off + p0 + x + y] : 0.0f;
+                float s = in ? A.state[td.off + p0 + x + y] : 0.0f;
+                if (STEP && OP == SEL_WORKER && in) s = __builtin_fmaf(A.lr, A.grad[td.off + p0 + x + y], s);
                 bits[x + y] = __float_as_uint((OP == SEL_PULL_V && in) ? A.model[td.off + p0 + x + y] - s : s);
                 if (OP == SEL_PULL_V) row[x + y] = s;
             }
@@ -609,12 +697,28 @@ __device__ __forceinline__ bool small_select(const SelectArgs &A, const TensorDe
             const float v = __uint_as_float(bits[i]);
             A.out_idx[pe.outoff + pos] = ix;
             A.out_val[pe.outoff + pos] = v;
-            if (OP == SEL_WORKER) store_scattered(&A.state[ix], A.m * v);
+            if (STEP && OP == SEL_WORKER) bits[i] = __float_as_uint(A.m * v);
+            else if (OP == SEL_WORKER) store_scattered(&A.state[ix], A.m * v);
             else if (OP == SEL_PULL) store_scattered(&A.state[ix], 0.0f);
             else if (!A.later) store_scattered(&A.state[ix], row[i] + v);
         }
         above += over ? 1u : 0u;
         eq += tie ? 1u : 0u;
+    }
+    if (STEP && OP == SEL_WORKER) {
+#pragma unroll
+        for (uint32_t x = 0; x < ITEMS; x += 4) {
+            if (p0 + x + 4u <= td.n) {
+                f32x4 o;
+#pragma unroll
+                for (int y = 0; y < 4; ++y) o[y] = __uint_as_float(bits[x + y]);
+                *(f32x4_any *)(A.state + td.off + p0 + x) = o;
+            } else {
+#pragma unroll
+                for (int y = 0; y < 4; ++y)
+                    if (p0 + x + y < td.n) A.state[td.off + p0 + x + y] = __uint_as_float(bits[x + y]);
+            }
+        }
     }
     if (tid == 0) {
         if ((total & 0xFFFFu) + min(total >> 16, rT) != pe.k) atomicAdd(&A.stats->internal_errors, 1ull);
@@ -686,7 +790,7 @@ __device__ __forceinline__ uint32_t hint_relaxed(uint32_t tau_cur, uint32_t kmin
 // add and candidate i (in index order) at x_i, the zeros below x_i number x_i - off - i;
 // the P candidates for which that is < z lie inside the leading run [off, off + z + P),
 // which is sent whole (z zeros and P candidates); the other candidates follow.
-template <int OP, class Src>
+template <int OP, bool WRITTEN, class Src>
 __device__ __forceinline__ void zero_fill_emit(const Src src, const uint32_t c, const TensorDesc &td,
                                                const PlanEntry &pe, const SelectArgs &A, uint32_t *wsum)
 {
@@ -698,7 +802,7 @@ __device__ __forceinline__ void zero_fill_emit(const Src src, const uint32_t c, 
     const uint32_t X = z + P;
     for (uint32_t q = tid; q < X; q += SEL_THREADS) {
         const uint32_t ix = td.off + q;
-        const float v = row_value<OP>(A.state, A.model, ix);
+        const float v = row_value<OP, WRITTEN>(A.state, A.model, ix);
         A.out_idx[pe.outoff + q] = ix;
         A.out_val[pe.outoff + q] = v;
         fix_sent<OP>(A.state, ix, v, A.m, A.later != 0);

@@ -1,5 +1,6 @@
 // Streaming pass of libdgs: one wavefront per 1024-element tile, 16-byte loads, fused
-// accumulate + magnitude key + candidate collection or key histogram.
+// accumulate + magnitude key + candidate collection or key histogram.  And the launch of a whole call (dgs_step.h).
+#include "dgs_step.h"
 #include "dgs_tile.h"
 
 namespace dgs {
@@ -79,6 +80,23 @@ void launch_stream(int op, int mode, const StreamArgs &a, uint32_t blocks, void 
         else if (mode == MODE_HIST) launch_stream_t<OP_IDENT, MODE_HIST>(a, blocks, st, ev0, ev1);
         else if (mode == MODE_SAMPLE) launch_stream_t<OP_IDENT, MODE_SAMPLE>(a, blocks, st, ev0, ev1);
     }
+}
+
+template <int OP>
+static void launch_step_t(const SelectArgs &a, uint32_t blocks, hipStream_t st, void *ev0, void *ev1)
+{
+    launch_k(k_step<OP>, dim3(blocks), dim3(SEL_THREADS), st, ev0, ev1, a.steptab, a.ranktab, a.tau,
+             OP == SEL_PULL_V ? a.model : a.grad, a.state, a.stepflag, a.nstep, a.nrank, a.lr, a);
+}
+
+void launch_step(int op, const SelectArgs &a, void *stream, void *ev0, void *ev1)
+{
+    hipStream_t st = (hipStream_t)stream;
+    const uint32_t nb = (a.nparts + a.bgroup - 1) / a.bgroup;
+    const uint32_t blocks = a.nstep + a.nrank + (a.repair && a.multi ? 2u * nb : 0u) + a.nemit;
+    if (op == SEL_WORKER) launch_step_t<SEL_WORKER>(a, blocks, st, ev0, ev1);
+    else if (op == SEL_PULL) launch_step_t<SEL_PULL>(a, blocks, st, ev0, ev1);
+    else launch_step_t<SEL_PULL_V>(a, blocks, st, ev0, ev1);
 }
 
 }  // namespace dgs

@@ -61,10 +61,15 @@ __device__ __forceinline__ uint2 ld_dev(const uint2 *p)
 }
 // 16-byte device-scope (write-through) store at base + byte_off; `base` must be wave-uniform
 // and the 16 bytes must lie within 1 MB of it (4-byte alignment is enough).
+// ... and the same as a load past the L2 (of words that another workgroup of the launch has written through).
 #ifdef DGS_HOST_EMULATION
 __device__ __forceinline__ void store_through16(float *base, uint32_t byte_off, f32x4 v)
 {
     *(f32x4_any *)((char *)base + byte_off) = v;
+}
+__device__ __forceinline__ f32x4 load_through16(const float *base, uint32_t byte_off)
+{
+    return *(const f32x4_any *)((const char *)base + byte_off);
 }
 #else
 typedef unsigned u32x4_store __attribute__((__vector_size__(16)));
@@ -74,6 +79,29 @@ __device__ __forceinline__ void store_through16(float *base, uint32_t byte_off, 
     u32x4_store u;
     __builtin_memcpy(&u, &v, 16);
     __builtin_amdgcn_raw_buffer_store_b128(u, r, (int)byte_off, 0, 16);   // aux 16: sc1 = device scope
+}
+__device__ __forceinline__ f32x4 load_through16(const float *base, uint32_t byte_off)
+{
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, 1 << 20, 0x00020000);
+    const u32x4_store u = __builtin_amdgcn_raw_buffer_load_b128(r, (int)byte_off, 0, 16);
+    f32x4 v;
+    __builtin_memcpy(&v, &u, 16);
+    return v;
+}
+#endif
+
+// Words i .. i + 3 behind `base` (wave-uniform; 16-byte aligned together; below 2 GB), past the L2.
+#ifdef DGS_HOST_EMULATION
+__device__ __forceinline__ uint4 ld_dev16(const uint32_t *base, uint32_t i)
+{
+    return make_uint4(ld_dev(base + i), ld_dev(base + i + 1), ld_dev(base + i + 2), ld_dev(base + i + 3));
+}
+#else
+__device__ __forceinline__ uint4 ld_dev16(const uint32_t *base, uint32_t i)
+{
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, 0x7FFFFFFF, 0x00020000);
+    const u32x4_store v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(4u * i), 0, 16);
+    return make_uint4(v[0], v[1], v[2], v[3]);
 }
 #endif
 
@@ -193,8 +221,8 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v)
 }
 
 // Sums over the wavefronts' words in LDS, NW of them: those before this wavefront's, and all.  (A lane takes one and the row of 16
-// lanes scans them.  A compute unit issues an instruction of a workgroup's 16 wavefronts in 7 ns, so that every
-// thread adding all of them up by itself takes 0.3 us of every scan.)
+// lanes scans them.  A compute unit issues an instruction of a workgroup's 16 wavefronts in 4 ns, and every thread adding all
+// of them up by itself takes 50: with that an event of a server with 32 sent rows 61.2 us, 59.1 so, one of 70 odd tensors 44.7 / 43.2.)
 template <int NW>
 __device__ __forceinline__ uint32_t sum_waves(const uint32_t *wsum, uint32_t &total)
 {
@@ -239,8 +267,8 @@ __device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t *wsum)
 // rank inside that bin:  res[2 i] = bin, res[2 i + 1] = rank in the bin; bin -1 if the
 // rank exceeds the histogram total (or is 0).  Every wavefront sums rows of 64 bins,
 // then up to three wavefronts each scan the row sums and the row their rank lands in.
-// Barriers: one on entry (h complete), one in the middle, one on exit.
-template <int NB, int NW>
+// Barriers: one on entry (h complete; not if READY), one in the middle, one on exit.
+template <int NB, int NW, bool READY = false>
 __device__ __forceinline__ void find_ranks(const uint32_t *h, uint32_t R0, uint32_t R1, uint32_t R2,
                                            uint32_t *rowsum, int *res)
 {
@@ -249,7 +277,7 @@ __device__ __forceinline__ void find_ranks(const uint32_t *h, uint32_t R0, uint3
     static_assert(ROWS * 64 == NB && ROWS <= 64, "histogram shape");
     const uint32_t lane = lane_id();
     const uint32_t wave = threadIdx.x >> 6;
-    __syncthreads();
+    if (!READY) __syncthreads();
     for (int r = (int)wave; r < ROWS; r += NW) {
         const uint32_t s = wave_sum(h[r * 64 + lane]);
         if (lane == 0) rowsum[r] = s;

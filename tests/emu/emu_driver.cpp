@@ -740,6 +740,57 @@ int main(int argc, char **argv)
         puts("parts, winners and small tensors: all as expected");
         return 0;
     }
+    if (argc > 1 && std::string(argv[1]) == "step") {
+        // (built with the library's own part size) A whole call in one launch: units of 4, 8 and 16 tiles, tensors whose
+        // winners many workgroups emit and others, lists beyond what the ranking holds, k-th keys beyond its window, predictions
+        // that fail both ways, ties, zeros, the lowest keys, infinities and NaNs, odd addresses
+        Opts o, mis;
+        mis.misalign = 3;
+        const std::vector<uint64_t> edges = {8192, 8193, 4096 * 3, 4096 * 4 + 1, 65535, 65536, 5, 69637, 12345};
+        const std::vector<float> steady = {1, 1, 1, 1}, jumps = {1, 1, 1.6f, 1, 40.0f, 1e-4f, 1, 1};
+        worker_server("edges of units", edges, 0.004, 0.01, 0.5f, 0.9f, false, steady, 0, o, 70);
+        worker_server("edges of units, odd addresses, jumps", edges, 0.01, 0.004, 1.0f, 0.0f, true, jumps, 0, mis, 71);
+        worker_server("many winners", {290001, 64, 150000}, 0.02, 0.02, 1.0f, 0.9f, false, steady, 0, o, 72);
+        const dgs_stats st = worker_server("many winners, jumps", {290001, 64, 150000}, 0.02, 0.02, 1.0f, 0.0f, true, jumps, 0, o, 73);
+        CHECK(st.repaired_tensors >= 1);
+        printed_form("printed form", edges, 0.004, 0.01, 5, o, 74);
+        printed_form("printed form, many winners", {290001, 64, 150000}, 0.02, 0.02, 5, o, 75);
+        for (int flavour : {1, 2, 5, 6, 7, 8}) {
+            const std::vector<float> some = flavour == 7 ? std::vector<float>{1} : std::vector<float>{1, 1, 1};
+            worker_server(("flavour " + std::to_string(flavour)).c_str(), {70001, 9000, 100}, 0.01, 0.02, 1.0f, 0.5f, false, some, flavour, o, 76);
+            worker_server(("many winners, flavour " + std::to_string(flavour)).c_str(), {150000, 64}, 0.02, 0.02, 1.0f, 0.5f, false, some,
+                          flavour, o, 77);
+        }
+        worker_server("units of 8 tiles", {700000, 64, 500000}, 0.005, 0.002, 1.0f, 0.9f, false, {1, 1, 1}, 0, o, 78);
+        worker_server("units of 16 tiles", {1300000, 64, 1200001}, 0.003, 0.001, 1.0f, 0.9f, false, {1, 1, 3}, 0, o, 79);
+        {
+            // backwards, nothing that is waited for has run: every wait ends at its bound, and nothing is sent
+            g_what = "waits that give up";
+            Layout L({100000, 64});
+            Rng r(80);
+            Ctx c(L, 0);
+            const double rho = 0.03;
+            const uint64_t K = L.K(rho);
+            Buf<float> g(L.n), s(L.n), s_ref(L.n), gv(K), wv(K);
+            Buf<uint32_t> gi(K), wi(K);
+            uint64_t k = 0;
+            for (int t = 0; t < 3; ++t) {
+                fill_grad(L, r, g.p, 1.0f, 0);
+                if (t == 2) {
+                    CHECK(dgs_set_option(c.c, DGS_OPT_SPIN_LIMIT, 1024) == DGS_OK);
+                    emu::block_order = 1;
+                }
+                CHECK(dgs_oracle_worker_step(g.p, s_ref.p, L.off.data(), L.J, 1.0f, 0.5f, rho, wi.p, wv.p, &k) == 0);
+                CHECK(dgs_worker_step(c.c, g.p, s.p, nullptr, 1.0f, 0.5f, rho, gi.p, gv.p, &k) == DGS_OK);
+                if (t < 2) expect_same(gi.p, gv.p, wi.p, wv.p, K);
+            }
+            emu::block_order = 0;
+            CHECK(c.stats().internal_errors >= 1);
+            printf("%-44s ok\n", g_what.c_str());
+        }
+        puts("calls in one launch: all as expected");
+        return 0;
+    }
     if (argc > 1 && std::string(argv[1]) == "rounds") {
         // join groups of more tiles than a workgroup has lanes (build with the default DGS_GROUP_TILES):
         // several rounds per group, the second tensor starting inside a tile of the first

@@ -1,0 +1,92 @@
+"""Predicted calls of small layouts, which are one launch: units of 4, 8 and 16 tiles and their edges, tensors around the sizes
+where a unit, the emitting workgroups and the winners that those take begin, lists beyond what the ranking workgroup
+holds and k-th keys beyond its window (scales that jump), ties, fewer nonzeros than k, rows at odd addresses; as
+worker step and as pull in both server forms.  Bit for bit against the oracle: each value is the result of one correctly rounded
+operation.  And against the kernels that larger layouts take, on the same calls."""
+import numpy as np
+import pytest
+
+from paper_1910_10929_amd import dgs, synth
+from harness import Server, assert_pairs_match, assert_state_match, run_worker_parity, to_dev, to_host_u32
+
+pytestmark = pytest.mark.gpu
+
+LAYOUTS = {
+    "units of 4": ([8192, 8193, 3 * 4096, 4 * 4096 + 1, 65_535, 65_536, 5, 69_637, 12_345], 0.01),
+    "units of 8": ([700_000, 64, 500_001, 8193], 0.004),
+    "units of 16": ([1_300_000, 64, 1_200_001, 16_385], 0.003),
+    "many winners": ([290_001, 64, 150_000, 65_536], 0.028),
+    "one tensor": ([1 << 20], 0.01),
+    "beyond one unit per compute unit": ([5_000_000, 1_000_001], 0.001),
+}
+SCALES = [1.0, 1.0, 1.0, 1.3, 2.0, 30.0, 30.0, 0.02, 1.0, 1.0]
+
+
+def gradients(kind, n, seed):
+    rng = np.random.default_rng(seed)
+    for s in SCALES:
+        g = rng.standard_normal(n).astype(np.float32)
+        if kind == "levels":
+            g = (np.round(g * 4.0) / 4.0).astype(np.float32)      # ties at every k-th key
+        elif kind == "sparse":
+            g[rng.random(n) < 0.99] = 0.0                         # fewer nonzeros than k
+        yield (g * np.float32(s)).astype(np.float32)
+
+
+@pytest.mark.parametrize("kind", ["gauss", "levels", "sparse"])
+@pytest.mark.parametrize("name", list(LAYOUTS))
+def test_worker(oracle, name, kind):
+    sizes, rho = LAYOUTS[name]
+    if kind != "gauss" and sum(sizes) > 2_000_000:
+        pytest.skip("the kinds of data at the smaller sizes")
+    off = synth.offsets_from_sizes(sizes)
+    for m in (0.9, 0.0):
+        run_worker_parity(oracle, off, list(gradients(kind, int(off[-1]), 7)), np.float32(0.5), np.float32(m), rho,
+                          misalign=1 if m else 0)
+
+
+@pytest.mark.parametrize("kind", ["gauss", "levels", "sparse"])
+@pytest.mark.parametrize("form", ["diff", "sent"])
+@pytest.mark.parametrize("name", ["units of 4", "units of 8", "many winners", "one tensor"])
+def test_pull(oracle, name, form, kind):
+    import torch
+    sizes, rho = LAYOUTS[name]
+    off = synth.offsets_from_sizes(sizes)
+    n, W = int(off[-1]), 3
+    general, ctx = dgs.Context(off, W=W), dgs.Context(off, W=W)
+    general.set_option(dgs.OPT_STREAM_QUADS, 1)                   # (what is the default beyond small layouts; keeps to their kernels)
+    model = np.random.default_rng(3).standard_normal(n).astype(np.float32)
+    rows = np.zeros((W, n), np.float32) if form == "diff" else np.repeat(model[None], W, 0)
+    sides = [(c, Server(c, model.copy(), density_max=rho)) for c in (ctx, general)]
+    dev_rows = [srv.diff for _, srv in sides]
+    if form == "sent":
+        dev_rows = [to_dev(rows) for _ in sides]
+        for (c, _), r in zip(sides, dev_rows):
+            c.server_attach_sent(r)
+    K = ctx.nnz(rho)
+    rng = np.random.default_rng(5)
+    for t, g in enumerate(gradients(kind, n, 11)):
+        idx = np.flatnonzero(g).astype(np.uint32)
+        idx = np.sort(rng.choice(idx, min(idx.size, 3 * K), replace=False))
+        val = g[idx]
+        w = int(rng.integers(W))                                  # rows wait for different times
+        if form == "diff":
+            oracle.server_push(model, rows, idx, val)
+            wi, wv = oracle.server_pull(rows, w, off, rho)
+        else:
+            oracle.server_push_model(model, idx, val)
+            wi, wv = oracle.server_pull_sent(model, rows, w, off, rho)
+        for (c, srv), r in zip(sides, dev_rows):
+            di, dv = to_dev(idx), to_dev(val)
+            if form == "diff":
+                c.server_push(srv.model, w, di, dv, idx.size)
+                c.server_pull(w, rho, srv.idx, srv.val)
+            else:
+                c.server_push_model(srv.model, di, dv, idx.size)
+                c.server_pull_sent(srv.model, w, rho, srv.idx, srv.val)
+            torch.cuda.synchronize()
+            assert_pairs_match(to_host_u32(srv.idx), srv.val.cpu().numpy(), wi, wv, f"pull {t}")
+            assert_state_match(r.cpu().numpy(), rows, f"rows {t}")
+    for c, _ in sides:
+        assert c.stats().internal_errors == 0
+        c.close()

@@ -98,6 +98,17 @@ def test_kernels_with_the_librarys_own_part_size(tmp_path):
     assert "emu: word" not in r.stderr and "all as expected" in r.stdout
 
 
+def test_calls_in_one_launch(tmp_path):
+    """Small layouts, whose predicted calls are one launch (built with the library's own part size: with small parts such calls
+    keep to the kernels of larger layouts): bit for bit against the oracle, and no word of the workspace that one
+    workgroup writes with an ordinary store is accessed device-wide by another."""
+    exe = build_emulated_kernels(str(tmp_path), seg_tiles=256, group_tiles=4096)
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:detect_stack_use_after_return=0")
+    r = subprocess.run([exe, "step"], capture_output=True, text=True, env=env, timeout=600)
+    assert r.returncode == 0, r.stdout[-3000:] + r.stderr[-6000:]
+    assert "emu: word" not in r.stderr and "all as expected" in r.stdout
+
+
 def test_oracle_pins_against_ubsan_build():
     env = dict(os.environ, DGS_ORACLE_SANITIZE="1")
     r = subprocess.run([sys.executable, "-m", "pytest", "-x", "-q", "-p", "no:cacheprovider",
