@@ -137,7 +137,7 @@ Layout make_layout(const uint64_t *offsets, uint32_t J, uint32_t W, bool one_cal
     L.plans = o;     o = align_up(o + (one_call ? 1 : NPLAN) * L.plan_bytes);
     L.tau = o;       o = align_up(o + (size_t)(W + 1) * J * sizeof(uint32_t));
     L.hint2 = o;     o = align_up(o + (size_t)(W + 1) * J * sizeof(uint32_t));
-    L.tprev = o;     o = align_up(o + (size_t)(W + 1) * J * sizeof(uint32_t));
+    L.tprev = o;     o = align_up(o + (one_call ? 1 : 2) * (size_t)(W + 1) * J * sizeof(uint32_t));   // then dprev
     L.ghist = o;     o = align_up(o + (size_t)J * HBINS * sizeof(uint32_t));
     L.tile_cnt = o;  o = align_up(o + (ntiles + 4) * sizeof(uint32_t));
     L.heads = o;     o = align_up(o + ntiles * HEAD * sizeof(uint2));
@@ -597,9 +597,12 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
         // gives the leading bits of each k-th key; the rest is found by reading the tensors again
         ProfSlot ps(c, prof_stream);
         const uint32_t blocks = stream_blocks(c, MODE_HIST, &sa.quads_per_block);
+        uint32_t *dprev = c->no_alloc ? nullptr : c->tprev + (size_t)(c->W + 1 + hint_set) * c->J;
+        sa.keys = dprev ? (uint32_t *)c->ord : nullptr;
+        sa.tau = dprev ? dprev : tau;
         launch_stream(op_stream, MODE_HIST, sa, blocks, c->stream, ps.ev0, ps.ev1);
         ps.launched();
-        launch_pick_dense(c->tdesc, plan, c->ghist, c->segstate, c->stats, c->J, c->stream);
+        launch_pick_dense(c->tdesc, plan, c->ghist, dprev, c->segstate, c->stats, c->J, c->stream);
     } else if (dense_req) {
         if (op_stream == OP_FMA) {
             ProfSlot ps(c, prof_stream);
@@ -916,7 +919,7 @@ int upload_tables(dgs_ctx *c, const TensorDesc *td, const uint32_t *tau0, const 
     }
     if (rc != DGS_OK) return rc;
     launch_fill_u32(c->hint2, 0u, (size_t)(W + 1) * J, c->stream);
-    launch_fill_u32(c->tprev, 0u, (size_t)(W + 1) * J, c->stream);
+    launch_fill_u32(c->tprev, 0u, (c->no_alloc ? 1 : 2) * (size_t)(W + 1) * J, c->stream);
     launch_fill_u32(c->ghist, 0u, (size_t)J * HBINS, c->stream);
     launch_fill_u32(c->tile_cnt, 0u, (size_t)c->ntiles + 4, c->stream);
     launch_fill_u32((uint32_t *)c->stats, 0u, sizeof(DevStats) / 4, c->stream);

@@ -79,6 +79,10 @@ void launch_chain(int op, const SelectArgs &a, void *stream, void *ev0, void *ev
 // empty workgroups on such a layout, 32 + 28 + 66 us with one workgroup per slab, and 33 + 13 + 57 us since
 // refine 2 goes through the keys that refine 1 has written down (1.6 % of the elements; writing them costs
 // refine 1 what holding two tiles a wavefront instead of four gains it) and the emission has 128 registers.
+// Where the bucket is the one that it was in the last two calls, the accumulate pass has listed its keys (tile_keys) and the refinements
+// read nothing else.  us a pull on Gaussian rows, elements read / keys listed: ResNet-50 shapes at 0.1 137 / 129, 24 tensors of 10M
+// 860 / 718, one of 64M 290 / 254, one of 240M 864 / 717; a round of ResNet-50 shapes, where seven tensors in eight keep their bucket
+// from one call to the next (and have three times as many keys in it), 450 / 439: the refinements 23 + 11 us instead of 33 + 13.
 
 constexpr uint32_t SLAB_WAVES = SLAB_THREADS / 64;
 constexpr uint32_t TPW = 4;                              // consecutive tiles of one wavefront
@@ -87,6 +91,11 @@ constexpr uint32_t TPW = 4;                              // consecutive tiles of
 constexpr uint32_t EMIT_TILES = SLAB_TILES / 2, EMIT_WAVES = EMIT_TILES / TPW, EMIT_THREADS = 64 * EMIT_WAVES;
 constexpr uint32_t REF1_SHIFT = 11, REF1_BINS = 256;     // refine 1: key bits [18:11]
 constexpr uint32_t REF2_BINS = 2048;                     // refine 2: key bits [10:0]
+// Copies of refine 1's counters, and of the count of finished slabs where a tensor has many: adds of the whole device
+// to one word follow each other at 11 ns.  us a pull on one tensor of 64M / 240M at 0.1, one copy / 8: elements read 314 / 290
+// and 938 / 864; the refinements and the emission of 240M from listed keys 681 / 506, of 24 tensors of 10M 533 / 509.
+constexpr uint32_t COPIES = 8;
+static_assert(COPIES * REF1_BINS <= REF2_BINS, "the copies");
 
 struct Slab {
     TensorDesc td;
@@ -124,7 +133,7 @@ __device__ __forceinline__ uint2 *dense_word(const SelectArgs &A, uint32_t tile0
 // each.  The bucket of 1/16 octave around the k-th key of a Gaussian tensor holds 2 % of its elements at
 // density 0.1; there is room for half of a wavefront's elements in slabs of up to 16 tiles (2 CAPT words for
 // the TILE elements of a tile), falling to a quarter in a full slab of 32.
-constexpr uint32_t KEYS_AT = 16;
+constexpr uint32_t KEYS_AT = 16, ROUTE_AT = 4;
 static_assert(KEYS_AT >= 4 + SLAB_WAVES, "two words of the emission and the counts");
 struct SlabKeys {
     uint32_t *count;          // per wavefront
@@ -218,10 +227,33 @@ __global__ __launch_bounds__(SLAB_THREADS, 8) void k_dense_refine(const SelectAr
     uint32_t *g = A.ghist + (size_t)j * HBINS;
     const SlabKeys keys = slab_keys(A, s);
     const uint32_t wave = uniform(tid >> 6);
-    bool from_keys = (LEVEL == 2);
-    if (LEVEL == 2)
+    // What the accumulate pass has listed, if that was the right bucket and no tile of the slab has had more than there is room
+    // for.  (Refinement 1 uses the scratch for its own lists otherwise, and says which it was.)
+    uint32_t *route = (uint32_t *)dense_word(A, s.tile0, j) + ROUTE_AT;
+    bool listed = s.td.big && st->T == 1u;
+    if (LEVEL == 1 && listed) {
+        const uint32_t *cnt = (const uint32_t *)dense_word(A, s.tile0 + lane_id(), j) + TKEYS_COUNT;
+        listed = ballot64(lane_id() < s.ntiles && *cnt > TKEYS_ROOM) == 0;
+    }
+    if (LEVEL == 2 && listed) listed = *route != 0;
+    if (LEVEL == 1) {
+        for (uint32_t b = tid; b < (leading ? HBINS : BINS); b += SLAB_THREADS) h[b] = 0;
+        __syncthreads();
+        if (tid == 0 && s.td.big) *route = listed ? 1u : 0u;
+    }
+    bool from_keys = (LEVEL == 2) && !listed;
+    if (from_keys)
         for (uint32_t w = 0; w < keys.waves; ++w) from_keys &= keys.count[w] <= keys.room;
-    if (from_keys) {
+    if (listed) {
+        // 16 lanes a tile, the wavefront's TPW at once
+        const uint32_t ti = wave * TPW + (lane_id() >> 4);
+        const uint32_t *words = (const uint32_t *)dense_word(A, s.tile0 + min(ti, s.ntiles - 1u), j);
+        const uint32_t c = (ti < s.ntiles) ? words[TKEYS_COUNT] : 0u;
+        for (uint32_t q = lane_id() & 15u; q < c; q += 16) {
+            const uint32_t key = words[TKEYS_AT + q];
+            if (LEVEL == 1 || (key >> SHIFT) == pfx) atomicAdd(&h[(key >> LOW) & (BINS - 1u)], 1u);
+        }
+    } else if (from_keys) {
         // A smooth tensor has a few keys per slab that share the prefix (one in 256 of those written down), but
         // all of them do where keys are tied: quantised ones, or ones that had 16 bits.  So they are counted in LDS
         // and a slab adds at most once to a word: adds of the whole device to one word follow each other at 11 ns
@@ -232,10 +264,6 @@ __global__ __launch_bounds__(SLAB_THREADS, 8) void k_dense_refine(const SelectAr
             if ((key >> SHIFT) == pfx) atomicAdd(&h[key & (BINS - 1u)], 1u);
         }
     } else {
-        if (LEVEL == 1) {
-            for (uint32_t b = tid; b < HBINS; b += SLAB_THREADS) h[b] = 0;
-            __syncthreads();
-        }
         if (leading) {
             each_key<OP>(A, s, [&](uint32_t key, bool in) {
                 if (in) atomicAdd(&h[key >> HSHIFT], 1u);
@@ -267,7 +295,7 @@ __global__ __launch_bounds__(SLAB_THREADS, 8) void k_dense_refine(const SelectAr
     __syncthreads();
     // (16 bytes a thread: with 2048 counters read and cleared one by one this pass takes 15 us instead of 13)
     static_assert(LEVEL == 2 || BINS <= SLAB_THREADS, "a counter each");
-    if (LEVEL == 1 && tid < BINS && h[tid]) atomicAdd(&g[tid], h[tid]);
+    if (LEVEL == 1 && tid < BINS && h[tid]) atomicAdd(&g[(s.idx % COPIES) * BINS + tid], h[tid]);
     for (uint32_t b = 4u * tid; LEVEL == 2 && b < BINS; b += 4u * SLAB_THREADS) {
         const uint4 v = *(const uint4 *)&h[b];
         if (v.x) atomicAdd(&g[b], v.x);
@@ -277,16 +305,25 @@ __global__ __launch_bounds__(SLAB_THREADS, 8) void k_dense_refine(const SelectAr
     }
     // Counted in far from the words that every slab begins with (the status and the prefix): a line that is
     // added to all the time has to be fetched anew by every reader.  On one flat tensor of 64M / 250M / 1e9
-    // parameters refine 1 takes 67 / 212 / 786 us; with the count beside the status 107 / 484 / 2007, and 87 / 298 / 1122
-    // with half as many slabs on a compute unit and no keys written down.
-    static_assert(REF2_BINS + 32u <= HBINS, "a word that neither refinement counts in, on a line of its own");
-    if (!arrive_last(&g[HBINS - 1u], s.count, &bc)) return;
+    // parameters refine 1 (elements read, one copy of everything) takes 67 / 212 / 786 us; with the count beside the status
+    // 107 / 484 / 2007, and 87 / 298 / 1122 with half as many slabs on a compute unit and no keys written down.
+    static_assert(REF2_BINS + (COPIES + 1u) * 32u <= HBINS, "words that neither refinement counts in, on lines of their own");
+    if (s.count > COPIES * 64u &&
+        !arrive_last(&g[HBINS - 1u - (1u + s.idx % COPIES) * 32u], (s.count - s.idx % COPIES + COPIES - 1u) / COPIES, &bc)) return;
+    if (!arrive_last(&g[HBINS - 1u], s.count > COPIES * 64u ? COPIES : s.count, &bc)) return;
 
     // ------------------------------------------------------------------ the tensor's last slab
     for (uint32_t b = tid; b < BINS; b += SLAB_THREADS) {
-        const uint32_t v = ld_dev(&g[b]);
-        h[b] = v;
-        if (v) st_dev(&g[b], 0u);   // clean for the next use
+        constexpr uint32_t N = (LEVEL == 1) ? COPIES : 1u;
+        uint32_t v[N], sum = 0;
+#pragma unroll
+        for (uint32_t x = 0; x < N; ++x) v[x] = ld_dev(&g[x * BINS + b]);
+#pragma unroll
+        for (uint32_t x = 0; x < N; ++x) {
+            sum += v[x];
+            if (v[x]) st_dev(&g[x * BINS + b], 0u);   // clean for the next use
+        }
+        h[b] = sum;
     }
     find_ranks<(int)BINS, (int)SLAB_WAVES>(h, r2, 0u, 0u, rowsum, res);
     const int bin = res[0];

@@ -187,7 +187,7 @@ struct SegState {        // per tensor, rewritten by every selection
     uint32_t status;     // SegStatus
     uint32_t pfx;        // key >> SEG_LOWBITS of the k-th entry (dense request: its leading bits so far)
     uint32_t r2;         // its rank among the entries sharing that prefix (SEG_ZERO: the zeros to add)
-    uint32_t T;          // the k-th key
+    uint32_t T;          // the k-th key (dense request, until it is known: 1 if the accumulate pass has listed the keys with pfx)
     uint32_t rT;         // how many of the entries equal to it are taken (lowest index first)
     // Hand-over between the workgroups of one launch (all zero between launches).  These words share a line with the plain
     // ones above, which the tensor's deciding workgroup stores through its cache: a die's L2 writes back the bytes that were
@@ -229,6 +229,15 @@ enum StoreMode { STORE_PLAIN = 0, STORE_WT = 1, STORE_NT = 2 };
 // SEL_PULL_V state <- state + val (the values themselves are model - state).
 enum SelectOp { SEL_WORKER = 0, SEL_PULL = 1, SEL_PULL_V = 2 };
 
+// Dense requests: a tile's scratch for tensor j (SelectArgs::ord, CAPT * (tile + j)) holds, until the emission, how many of its
+// keys are in the bucket that held the k-th key the call before, and those keys.  Words before and between are the slabs'.
+// (dprev, per stream and tensor: one more than that bucket, 0 = unknown, and DPREV_STABLE if it was the same the call before that:
+// nothing is listed otherwise.  A pull on Gaussian ResNet-50 shapes at 0.1 whose keys are scaled by 1.3 in every second call,
+// nothing listed / listed after every call / so: 134 / 139 / 132 us, the row left as it is 133 / 129 / 129.)
+constexpr uint32_t DPREV_STABLE = 0x80000000u;
+constexpr uint32_t TKEYS_COUNT = 8, TKEYS_AT = 16, TKEYS_ROOM = 2 * CAPT - TKEYS_AT;
+constexpr uint32_t TKEYS_STAGE = 64;                  // of them that a wavefront has in LDS and writes at once
+
 struct StreamArgs {
     const float *grad;            // OP_FMA only
     float *state;                 // OP_FMA: in/out.  OP_IDENT: read only.
@@ -239,6 +248,7 @@ struct StreamArgs {
     uint2 *near;                  // per tile: candidates HEAD .. NEAR-1
     uint2 *far;                   // per tile: candidates NEAR .. CAPT-1
     uint32_t *ghist;              // per tensor HBINS counters
+    uint32_t *keys;               // MODE_HIST for a dense request: the tiles' scratch (SelectArgs::ord); tau is dprev then
     uint32_t n, ntiles, nquads, quads_per_block, J;
     const uint32_t *tile_list;    // MODE_SAMPLE: the tiles to visit, nlist of them, four per "quad"
     uint32_t nlist;               //   (nquads = ceil(nlist / 4))
@@ -308,7 +318,7 @@ void launch_stream(int op, int mode, const StreamArgs &a, uint32_t blocks, void 
 void launch_pick(const TensorDesc *tdesc, const PlanEntry *plan, uint32_t *ghist, uint32_t *tau,
                  uint32_t *tprev, DevStats *stats, uint32_t J, bool sample, void *stream);
 // Dense request: the accumulate pass's histogram -> the leading 12 bits of each k-th key, into segstate.
-void launch_pick_dense(const TensorDesc *tdesc, const PlanEntry *plan, uint32_t *ghist, SegState *segstate,
+void launch_pick_dense(const TensorDesc *tdesc, const PlanEntry *plan, uint32_t *ghist, uint32_t *dprev, SegState *segstate,
                        DevStats *stats, uint32_t J, void *stream);
 // The selection: one launch for every tensor (join, exact k-th key, ordered emission, state
 // fix-up, next hint; failed predictions are collected again inside the same launch).

@@ -81,7 +81,7 @@ void launch_pick(const TensorDesc *tdesc, const PlanEntry *plan, uint32_t *ghist
 // Dense request: the histogram covers every nonzero element of the tensor, so the bucket that
 // holds the k-th key is certain (the zeros, not counted by the pass, complete bucket 0).
 __global__ __launch_bounds__(1024) void k_pick_dense(const TensorDesc *tdesc, const PlanEntry *plan, uint32_t *ghist,
-                                                     SegState *segstate, DevStats *stats)
+                                                     uint32_t *dprev, SegState *segstate, DevStats *stats)
 {
     const uint32_t j = blockIdx.x;
     const TensorDesc td = tdesc[j];
@@ -107,15 +107,18 @@ __global__ __launch_bounds__(1024) void k_pick_dense(const TensorDesc *tdesc, co
         st->status = (k == td.n) ? SEG_ALL : SEG_ACTIVE;
         st->pfx = (uint32_t)res[0];
         st->r2 = (uint32_t)res[1];
+        const uint32_t now = (uint32_t)res[0] + 1u, was = (dprev != nullptr) ? dprev[j] : 0u;
+        st->T = (was == (now | DPREV_STABLE)) ? 1u : 0u;
+        if (dprev != nullptr) dprev[j] = now | ((was & ~DPREV_STABLE) == now ? DPREV_STABLE : 0u);
         atomicAdd(&stats->segmented_tensors, 1ull);
     }
 }
 
-void launch_pick_dense(const TensorDesc *tdesc, const PlanEntry *plan, uint32_t *ghist, SegState *segstate,
+void launch_pick_dense(const TensorDesc *tdesc, const PlanEntry *plan, uint32_t *ghist, uint32_t *dprev, SegState *segstate,
                        DevStats *stats, uint32_t J, void *stream)
 {
-    hipLaunchKernelGGL(k_pick_dense, dim3(J), dim3(SEL_THREADS), 0, (hipStream_t)stream, tdesc, plan, ghist, segstate,
-                       stats);
+    hipLaunchKernelGGL(k_pick_dense, dim3(J), dim3(SEL_THREADS), 0, (hipStream_t)stream, tdesc, plan, ghist, dprev,
+                       segstate, stats);
 }
 
 // ---------------------------------------------------------------------------

@@ -25,9 +25,10 @@ __global__ __launch_bounds__(STREAM_THREADS) void k_stream(const float *grad, fl
     A.lr = lr;
     constexpr bool HISTO = (MODE == MODE_HIST || MODE == MODE_SAMPLE);
     __shared__ uint32_t lhist[HISTO ? HBINS : 1];
-    __shared__ uint2 stage_all[MODE == MODE_COLLECT ? WAVES_PER_BLOCK * STAGE : 1];
+    constexpr uint32_t ROOM = MODE == MODE_COLLECT ? STAGE : (MODE == MODE_HIST ? TKEYS_STAGE / 2 : 0);      // of a wavefront
+    __shared__ uint2 stage_all[ROOM ? WAVES_PER_BLOCK * ROOM : 1];
     const uint32_t wave = uniform(threadIdx.x >> 6);
-    uint2 *stage = stage_all + (MODE == MODE_COLLECT ? wave * STAGE : 0u);
+    uint2 *stage = stage_all + wave * ROOM;
     const uint32_t q0 = blockIdx.x * A.quads_per_block;
     const uint32_t q1 = min(q0 + A.quads_per_block, A.nquads);
     int cur = -1;

@@ -67,6 +67,53 @@ __device__ __forceinline__ uint4 span_desc(const uint32_t *__restrict__ toff, ui
     return d;
 }
 
+// Dense request: the tile's keys (elements [lo, hi) of it: one tensor's) in the bucket that held that tensor's k-th key the call
+// before and the one before that (`prev`: DPREV_STABLE and one more than the bucket), for the refinements, in any order.  Bound by
+// issue: 3 us of a worker's accumulate pass on ResNet-50 shapes at density 0.1 and 4 of a pull's, for 10 and 2 us of the refinements
+// (one ballot an element 6 and 10; 128 staged keys instead of 64 the same).
+__device__ __forceinline__ void tile_keys(const StreamArgs &A, uint32_t prev, uint32_t t, uint32_t j, uint32_t hi, uint32_t lo,
+                                          const float (&a)[4][4], uint2 *stage_)
+{
+    if (prev < DPREV_STABLE) return;
+    const uint32_t lane = lane_id(), base = t * TILE;
+    uint32_t *stage = (uint32_t *)stage_;
+    uint32_t *words = A.keys + (size_t)(t + j) * (2u * CAPT);
+    const bool whole = lo <= base && base + TILE <= hi;
+    const uint32_t first = (prev - DPREV_STABLE - 1u) << HSHIFT;
+    uint32_t inside = 0xFFFFu, mine = 0;
+    if (!whole) {
+        inside = 0;
+#pragma unroll
+        for (uint32_t i = 0; i < 16; ++i) {
+            const uint32_t e = base + (i >> 2) * 256 + lane * 4 + (i & 3u);
+            inside |= (e >= lo && e < hi ? 1u : 0u) << i;
+        }
+    }
+    const auto hit = [&](uint32_t i) {
+        const uint32_t key = __float_as_uint(a[i >> 2][i & 3u]) & 0x7FFFFFFFu;
+        return key - first < (1u << HSHIFT) && (whole || ((inside >> i) & 1u));
+    };
+#pragma unroll
+    for (uint32_t i = 0; i < 16; ++i) mine += hit(i) ? 1u : 0u;
+    uint32_t at = wave_incl_scan(mine);
+    const uint32_t run = (uint32_t)__builtin_amdgcn_readlane((int)at, 63);
+    at -= mine;
+    if (run <= TKEYS_STAGE) {
+#pragma unroll
+        for (uint32_t i = 0; i < 16; ++i)
+            if (hit(i)) stage[at++] = __float_as_uint(a[i >> 2][i & 3u]) & 0x7FFFFFFFu;
+    } else if (run <= TKEYS_ROOM) {
+#pragma unroll
+        for (uint32_t i = 0; i < 16; ++i)
+            if (hit(i)) words[TKEYS_AT + at++] = __float_as_uint(a[i >> 2][i & 3u]) & 0x7FFFFFFFu;
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (run <= TKEYS_STAGE)
+        for (uint32_t q = lane; q < run; q += 64) words[TKEYS_AT + q] = stage[q];      // (TKEYS_STAGE: one turn)
+    if (lane == 0) words[TKEYS_COUNT] = run;
+    __builtin_amdgcn_wave_barrier();
+}
+
 // What follows the accumulate for one tile whose 16 values per lane are in `a`:
 // candidate collection against the per-tensor thresholds, or the key histogram.
 template <int MODE>
@@ -147,6 +194,18 @@ __device__ __forceinline__ void tile_tail(const StreamArgs &A, const uint32_t *_
             A.tile_cnt[t] = (run > CAPT) ? CNT_OVERFLOW : (runA | ((run - runA) << 16));
     } else {  // MODE_HIST, MODE_SAMPLE
         const bool bigA = (d.x >> 31) != 0, bigB = (d.y >> 31) != 0;
+        if (MODE == MODE_HIST && full && !straddle && (int)tA == cur && only < 0) {
+            // (the common tile: nothing to ask of an element)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t key = __float_as_uint(a[r][j]) & 0x7FFFFFFFu;
+                    if (key != 0) atomicAdd(&lhist[key >> HSHIFT], 1u);
+                }
+            if (A.keys != nullptr) tile_keys(A, tau[tA], t, tA, A.n, 0u, a, stage);
+            return;
+        }
         uint32_t zeroA = 0, zeroB = 0;     // MODE_SAMPLE: zero keys of the two tensors, added once per tile
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -175,6 +234,10 @@ __device__ __forceinline__ void tile_tail(const StreamArgs &A, const uint32_t *_
                 if (tt == cur) atomicAdd(&lhist[bin], 1u);
                 else atomicAdd(&A.ghist[(size_t)tt * HBINS + bin], 1u);
             }
+        }
+        if (MODE == MODE_HIST && A.keys != nullptr) {
+            if (bigA) tile_keys(A, tau[tA], t, tA, min(straddle ? endA : 0xFFFFFFFFu, A.n), 0u, a, stage);
+            if (bigB && begB != 0xFFFFFFFFu) tile_keys(A, tau[tB], t, tB, A.n, begB, a, stage);
         }
         if (MODE == MODE_SAMPLE) {
             zeroA = wave_sum(zeroA);

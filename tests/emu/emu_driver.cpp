@@ -463,6 +463,38 @@ static void tied_dense(const char *name, double share, double rho, uint64_t seed
     fflush(stdout);
 }
 
+// Dense requests whose k-th keys stay in their buckets, so that the accumulate pass lists them, and then move: more than a tile
+// has room for in some tiles, tiles of two tensors, a ragged end.
+static void listed_dense(const char *name, uint32_t misalign, uint64_t seed)
+{
+    g_what = name;
+    Layout L({700, 70001, 9000, 8193, 2000, 150003});
+    Rng r(seed);
+    Ctx c(L, 0);
+    const double rho = 0.1;
+    const uint64_t K = L.K(rho);
+    Buf<float> g(L.n + misalign), s_gpu(L.n + misalign), s_ref(L.n);
+    Buf<uint32_t> gi(K), wi(K);
+    Buf<float> gv(K), wv(K);
+    const float lrs[] = {1, 1, 1, 1, 1.5f, 1.5f, 1.5f, 1};
+    for (uint32_t call = 0; call < 8; ++call) {
+        for (uint64_t i = 0; i < L.n; ++i) {
+            const bool crowded = i / 1024 % 9 == 4;
+            const float u = r.uni();
+            g.p[misalign + i] = (crowded ? u < 0.6f : u < 0.05f) ? 1.0f + 0.06f * r.uni() : (!crowded && u < 0.1f ? 4.0f : 0.05f * r.uni());
+            s_gpu.p[misalign + i] = s_ref.p[i] = 0.0f;
+        }
+        uint64_t k1 = 0, k2 = 0;
+        CHECK(dgs_oracle_worker_step(g.p + misalign, s_ref.p, L.off.data(), L.J, lrs[call], 0.9f, rho, wi.p, wv.p, &k1) == 0);
+        CHECK(dgs_worker_step(c.c, g.p + misalign, s_gpu.p + misalign, nullptr, lrs[call], 0.9f, rho, gi.p, gv.p, &k2) == DGS_OK);
+        expect_same(gi.p, gv.p, wi.p, wv.p, K);
+        expect_same_f(s_gpu.p + misalign, s_ref.p, L.n, "state");
+    }
+    CHECK(c.stats().internal_errors == 0);
+    printf("%-44s ok\n", name);
+    fflush(stdout);
+}
+
 // The launch behind a selection on the printed state: the row follows the message, also where the model has moved
 // on since the values were taken; an index outside the row is skipped; and where an internal error has been
 // counted, a pair that the row does not show (one that no selection has written) moves nothing.
@@ -817,6 +849,8 @@ int main(int argc, char **argv)
     gives_up("dense emission gives up", 0.1, 0, 1, 40);
     gives_up("chain emission gives up on the slabs before", 0.01, 1, 2, 41);
     gives_up("chain emission gives up on the ranking", 0.01, 1, 1, 42);
+    listed_dense("dense requests, keys listed by the accumulate pass", 0, 62);
+    listed_dense("the same at odd addresses", 3, 63);
     tied_dense("dense request, 1 in 1000 share the k-th key", 0.001, 0.1, 45);
     tied_dense("dense request, 12 % share the k-th key", 0.12, 0.1, 46);
     tied_dense("dense request, 20 % share the k-th key of 90 %", 0.2, 0.9, 47);
