@@ -69,8 +69,8 @@ __device__ __forceinline__ uint4 span_desc(const uint32_t *__restrict__ toff, ui
 
 // Dense request: the tile's keys (elements [lo, hi) of it: one tensor's) in the bucket that held that tensor's k-th key the call
 // before and the one before that (`prev`: DPREV_STABLE and one more than the bucket), for the refinements, in any order.  Bound by
-// issue: 3 us of a worker's accumulate pass on ResNet-50 shapes at density 0.1 and 4 of a pull's, for 10 and 2 us of the refinements
-// (one ballot an element 6 and 10; 128 staged keys instead of 64 the same).
+// issue: 5 us of a worker's accumulate pass on ResNet-50 shapes at density 0.1 and 4 of a pull's, for 10 and 2 us of the refinements
+// of each (one ballot an element 6 and 10; 128 staged keys instead of 64 the same).
 __device__ __forceinline__ void tile_keys(const StreamArgs &A, uint32_t prev, uint32_t t, uint32_t j, uint32_t hi, uint32_t lo,
                                           const float (&a)[4][4], uint2 *stage_)
 {
