@@ -196,6 +196,8 @@ int dgs_nnz(const dgs_ctx *ctx, double density, uint64_t *K_out /*host*/);
  * schemes) is not part of this method: DGS_ENOTSUP.
  *
  * Buffers must be 4-byte aligned; more alignment is not needed for speed.
+ * idx_out and val_out may lie over grad, which has been read before they are written (such a
+ * call is never one launch, see DGS_PROF_*); neither may overlap the state or the other.
  *
  * Graph capture.  Once a call at `density` has been made eagerly on this context (the
  * launch plan of a density is uploaded on its first use, and the first call of a stream

@@ -531,6 +531,13 @@ const PlanEntry *plan_at(const dgs_ctx *c, uint32_t slot) { return (const PlanEn
 
 bool aligned4(const void *p) { return ((uintptr_t)p & 3u) == 0; }
 
+// Whether n floats at `in` share a byte with a message of K pairs.
+bool under_message(const float *in, uint64_t n, const uint32_t *idx, const float *val, uint64_t K)
+{
+    const uintptr_t at = (uintptr_t)in, i = (uintptr_t)idx, v = (uintptr_t)val;
+    return in && ((at < i + 4 * K && i < at + 4 * n) || (at < v + 4 * K && v < at + 4 * n));
+}
+
 uint32_t stream_blocks(const dgs_ctx *c, int mode, uint32_t *qpb_out)
 {
     uint32_t qpb;
@@ -564,9 +571,11 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
     const int op_again = (op_stream == OP_SUB) ? OP_SUB : OP_IDENT;
     const bool dense_req = density > DENSE_DENSITY;
     const bool exact = !dense_req && (c->force_exact || c->force_sample || c->hint_density[hint_set] != density);
-    // A small layout's predicted call is one launch.  (It rests on waits: not where those are bounded to next to nothing.)
+    // A small layout's predicted call is one launch.  (It rests on waits: not where those are bounded to next to nothing.  And
+    // some of its workgroups emit while others still read: not where the message lies over what is read.)
     const bool step = !dense_req && !exact && c->plan_slot[slot].step && c->repair_round && c->stream_quads == 0 &&
-                      c->spin_limit >= STEP_MIN_SPINS;
+                      c->spin_limit >= STEP_MIN_SPINS && !under_message(grad, c->n, idx_out, val_out, K) &&
+                      !under_message(state, c->n, idx_out, val_out, K);
     uint32_t *tau = c->tau + (size_t)hint_set * c->J;
     const PlanEntry *plan = plan_at(c, slot);
 

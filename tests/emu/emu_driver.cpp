@@ -495,6 +495,32 @@ static void listed_dense(const char *name, uint32_t misalign, uint64_t seed)
     fflush(stdout);
 }
 
+// Messages laid over the gradient, which is not needed after the call: values, or indices, from its element `at` on.
+static void over_gradient(const char *name, const std::vector<uint64_t> &sizes, double rho, bool values, uint64_t at, uint64_t seed)
+{
+    g_what = name;
+    Layout L(sizes);
+    Rng r(seed);
+    Ctx c(L, 0);
+    const uint64_t K = L.K(rho);
+    CHECK(at + K <= L.n);
+    Buf<float> g(L.n), s_gpu(L.n), s_ref(L.n), vals(K), wv(K);
+    Buf<uint32_t> idxs(K), wi(K);
+    for (uint32_t call = 0; call < 4; ++call) {
+        fill_grad(L, r, g.p, 1.0f, 0);
+        uint64_t k1 = 0, k2 = 0;
+        CHECK(dgs_oracle_worker_step(g.p, s_ref.p, L.off.data(), L.J, 0.5f, 0.9f, rho, wi.p, wv.p, &k1) == 0);
+        uint32_t *gi = values ? idxs.p : (uint32_t *)g.p + at;
+        float *gv = values ? g.p + at : vals.p;
+        CHECK(dgs_worker_step(c.c, g.p, s_gpu.p, nullptr, 0.5f, 0.9f, rho, gi, gv, &k2) == DGS_OK);
+        expect_same(gi, gv, wi.p, wv.p, K);
+        expect_same_f(s_gpu.p, s_ref.p, L.n, "state");
+    }
+    CHECK(c.stats().internal_errors == 0);
+    printf("%-44s ok\n", name);
+    fflush(stdout);
+}
+
 // The launch behind a selection on the printed state: the row follows the message, also where the model has moved
 // on since the values were taken; an index outside the row is skipped; and where an internal error has been
 // counted, a pair that the row does not show (one that no selection has written) moves nothing.
@@ -795,6 +821,9 @@ int main(int argc, char **argv)
         }
         worker_server("units of 8 tiles", {700000, 64, 500000}, 0.005, 0.002, 1.0f, 0.9f, false, {1, 1, 1}, 0, o, 78);
         worker_server("units of 16 tiles", {1300000, 64, 1200001}, 0.003, 0.001, 1.0f, 0.9f, false, {1, 1, 3}, 0, o, 79);
+        over_gradient("values over the gradient", {64, 8000, 12000, 100}, 0.01, true, 0, 81);
+        over_gradient("indices over the gradient", {64, 8000, 12000, 100}, 0.01, false, 0, 82);
+        over_gradient("values over the gradient's end", {64, 8000, 12000, 90000}, 0.03, true, 110064 - 3302, 83);
         {
             // backwards, nothing that is waited for has run: every wait ends at its bound, and nothing is sent
             g_what = "waits that give up";

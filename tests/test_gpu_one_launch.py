@@ -90,3 +90,31 @@ def test_pull(oracle, name, form, kind):
     for c, _ in sides:
         assert c.stats().internal_errors == 0
         c.close()
+
+
+@pytest.mark.parametrize("what", ["values", "indices"])
+@pytest.mark.parametrize("sizes", [[64, 8000, 12_000, 100], [64, 90_000, 8000, 200_000]])
+def test_message_over_the_gradient(oracle, sizes, what):
+    """A caller that needs the gradient no more may lay the message over it: that call is not one launch, whose first
+    workgroups emit while others still read."""
+    import torch
+    off = synth.offsets_from_sizes(sizes)
+    n, rho = int(off[-1]), 0.02
+    ctx = dgs.Context(off, W=0)
+    K = ctx.nnz(rho)
+    state = torch.zeros(n, dtype=torch.float32, device=ctx.device)
+    other = torch.zeros(K, dtype=torch.float32, device=ctx.device)
+    s_ref = np.zeros(n, np.float32)
+    rng = np.random.default_rng(9)
+    for call in range(5):
+        g = rng.standard_normal(n).astype(np.float32)
+        wi, wv = oracle.worker_step(g, s_ref, off, np.float32(0.5), np.float32(0.9), rho)
+        grad = to_dev(g, ctx.device)
+        over = grad[:K] if call % 2 else grad[n - K:]
+        idx, val = (over.view(torch.int32), other) if what == "indices" else (other.view(torch.int32), over)
+        ctx.worker_step(grad, state, 0.5, 0.9, rho, idx, val)
+        torch.cuda.synchronize()
+        assert_pairs_match(to_host_u32(idx), val.cpu().numpy(), wi, wv, f"call {call}")
+        assert_state_match(state.cpu().numpy(), s_ref, f"call {call}")
+    assert ctx.stats().internal_errors == 0
+    ctx.close()
