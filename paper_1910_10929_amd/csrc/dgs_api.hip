@@ -141,6 +141,7 @@ Layout make_layout(const uint64_t *offsets, uint32_t J, uint32_t W, bool one_cal
     L.ghist = o;     o = align_up(o + (size_t)J * HBINS * sizeof(uint32_t));
     L.tile_cnt = o;  o = align_up(o + (ntiles + 4) * sizeof(uint32_t));
     L.heads = o;     o = align_up(o + ntiles * HEAD * sizeof(uint2));
+    static_assert(CAPT * sizeof(uint2) % ALIGN == 0, "ord follows the slots, of which one-launch calls use CAPT a tile");
     L.slots = o;     o = align_up(o + ntiles * CAPT * sizeof(uint2));
     L.ord = o;       o = align_up(o + (ntiles + J - 1) * CAPT * sizeof(uint2));   // tensor j from its first tile + j on
     L.stats = o;     o = align_up(o + sizeof(DevStats));

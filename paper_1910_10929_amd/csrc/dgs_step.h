@@ -258,6 +258,82 @@ __device__ __forceinline__ bool step_select(const SelectArgs &A, const TensorDes
     return true;
 }
 
+// What RANK does with lists that step_select has no answer for: too many entries for the registers, too few for the message, or a
+// k-th key that has moved on.  They go into one list, LDS first, from which it is selected as from any other: as it is up to SEL_LIST_HARD
+// entries, cut down beyond, and completed with zeros where every nonzero is in it.  Where many workgroups wait for the k-th key
+// and the list is long, that alone is found.  Returns the tensor's status: SEG_DONE, SEG_ACTIVE (those workgroups go on), or
+// SEG_PENDING (collect again).  us a worker step without momentum whose scale grows by 1.1 each time, in several launches / lists
+// beyond the LDS list cut down where they lie / so: one tensor of 1M elements at 0.1 % 37.3 / 85.3 / 29.5, of 2M 63.5 / 150.7 / 52.6,
+// of 4M at 0.05 % 84.7 / 201.6 / 71.6.
+template <int OP>
+__device__ __forceinline__ uint32_t step_lists(const SelectArgs &A, const TensorDesc &td, const PlanEntry &pe, const SegDesc &rd, uint32_t c,
+                                               bool ovf, uint32_t tau_cur, uint32_t tprev_cur, uint32_t hint2_cur, uint32_t *verdict,
+                                               PartShared &P, uint2 *llist)
+{
+    const uint32_t tid = threadIdx.x, j = rd.j;
+    const bool emits = step_emits(A, td.n);
+    const bool zerofill = !ovf && c < pe.k && tau_cur <= 1u;      // (every nonzero is in the lists)
+    uint32_t status = SEG_PENDING;
+    bool known = false;      // the verdict is out (once: the last of those who wait for it clears it)
+    if (emits && !ovf && c >= pe.k && (c > SEL_LDS_LIST || pe.k > STEP_EMIT_K)) {
+        known = true;
+        status = SEG_ACTIVE;
+        if (verdict && tid == 0) st_dev(verdict, 0x100u | (uint32_t)SEG_DONE);
+        step_rank<OP>(A, td, pe, j, rd.tile0, rd.ntiles, c, tau_cur, hint2_cur, P);
+    } else if (!ovf && (c >= pe.k || zerofill)) {
+        uint2 *glist = step_tail(A, td);
+        uint32_t win = win_base_of<OP>(tau_cur, tprev_cur), km = 0xFFFFFFFFu, tau = tau_cur;
+        const bool whole = c <= SEL_LIST_HARD;
+        if (whole) {
+            known = true;
+            if (verdict && tid == 0) st_dev(verdict, 0x100u | (uint32_t)SEG_DONE);
+        }
+        step_gather<false>(A, rd.tile0, rd.ntiles, P.pbase, [&](uint32_t p, uint32_t ix, uint32_t v) {
+            put_entry(llist, glist, p, make_uint2(ix, v));
+            km = min(km, v & 0x7FFFFFFFu);
+            window_count<OP>(P.S.h, win, v & 0x7FFFFFFFu);      // (the hinted window, on the way)
+        });
+        km = wave_min_to_last(km);
+        if (lane_id() == 63) atomicMin(&P.S.kmin, km);
+        wait_mem();
+        __syncthreads();
+        uint32_t kmin = P.S.kmin;
+        if (zerofill) {
+            zero_fill_emit<OP, written<OP, FORM_STEP>()>(SrcSplit{llist, glist}, c, td, pe, A, P.S.wsum);
+            if (tid == 0) {
+                A.tau[j] = 1u;
+                A.hint2[j] = 0u;
+                A.tprev[j] = 0u;
+                atomicAdd(&A.stats->candidates, (unsigned long long)c);
+            }
+            status = SEG_DONE;
+        } else {
+            if (!whole) {
+                c = trim_list(A, SrcSplit{llist, glist}, c, SEL_LIST_HARD, pe, verdict, P, llist, glist, tau);
+                kmin = tau;      // (a lower bound; the window is counted from the list)
+                win = 0xFFFFFFFFu;
+                if (c != 0) {
+                    known = true;
+                    if (tid == 0) atomicAdd(&A.stats->repaired_tensors, 1ull);
+                }
+            }
+            if (c != 0) {
+                list_select<OP>(A, td, pe, j, c, kmin, tau, hint2_cur, win, whole, !whole, P, llist, glist);
+                if (tid == 0) atomicAdd(&A.stats->candidates, (unsigned long long)c);
+                status = SEG_DONE;
+            }
+        }
+    }
+    if (tid == 0) A.segstate[j].status = status;
+    if (emits && status != SEG_ACTIVE && tid == 0) st_dev(&A.segstate[j].key, make_uint2(STEP_DONE, KEY_READY));
+    if (verdict && !known) {
+        wait_mem();
+        __syncthreads();
+        if (tid == 0) st_dev(verdict, 0x100u | status);
+    }
+    return status;
+}
+
 // RANK of the tensor whose units rd describes.
 template <int OP>
 __device__ __forceinline__ void step_rank_block(const SelectArgs &A, const SegDesc &rd, PartShared &P, uint2 *llist)
@@ -312,7 +388,7 @@ __device__ __forceinline__ void step_rank_block(const SelectArgs &A, const SegDe
         done = emits ? step_select<OP, true>(A, td, pe, rd, c, share, log_lanes, tau_cur, tprev_cur, hint2_cur, verdict, P)
                      : step_select<OP, false>(A, td, pe, rd, c, share, log_lanes, tau_cur, tprev_cur, hint2_cur, verdict, P);
     }
-    if (!done) {
+    if (__builtin_expect(!done, 0)) {
         // too few entries, or too many, or a k-th key that has moved on: as for any other tensor's lists
         __syncthreads();
         for (uint32_t b = tid; b < WIN_BINS; b += SEL_THREADS) P.S.h[b] = 0;
@@ -320,9 +396,7 @@ __device__ __forceinline__ void step_rank_block(const SelectArgs &A, const SegDe
         const uint32_t ex = block_excl_scan<SEL_WAVES>(n, P.S.wsum, c);
         if (tid <= units) P.pbase[tid] = ex;
         __syncthreads();
-        const uint32_t status = tensor_select<OP, FORM_STEP>(A, td, pe, j, 0, true, false, c, bad, 0xFFFFFFFFu, tau_cur, tprev_cur,
-                                                             win_base_of<OP>(tau_cur, tprev_cur), true, verdict, P, llist,
-                                                             StepRun{rd.tile0, units});
+        const uint32_t status = step_lists<OP>(A, td, pe, rd, c, bad, tau_cur, tprev_cur, hint2_cur, verdict, P, llist);
         if (!has_parts && status == SEG_PENDING) recollect_here<OP, FORM_STEP>(A, td, pe, j, P, llist);
     }
     if (tid < units) st_dev(&A.stepflag[rd.tile0 + tid], 0u);       // for the next launch

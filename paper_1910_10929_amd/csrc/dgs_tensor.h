@@ -560,27 +560,15 @@ __device__ __forceinline__ uint2 *step_word(const SelectArgs &A, uint32_t ord0) 
 // Whether a tensor of n elements has emitting workgroups in the launch.
 __device__ __forceinline__ bool step_emits(const SelectArgs &A, uint32_t n) { return A.nemit != 0 && n >= SEG_MIN_N; }
 
-// The candidates of a tensor, addressed by list position (pbase: first position of every unit, in LDS).
-struct SrcStep {
-    static constexpr bool AGG = true;
-    const SelectArgs &A;
-    const uint32_t *pbase;
-    uint32_t first, units;
-    __device__ __forceinline__ uint2 get(uint32_t p) const
-    {
-        uint32_t lo = 0, hi = units;      // last unit whose first position is <= p
-        while (hi - lo > 1) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (pbase[mid] <= p) lo = mid;
-            else hi = mid;
-        }
-        const StepUnit &u = A.steptab[first + lo];
-        const uint32_t *words = (const uint32_t *)A.ord + (p - pbase[lo]);
-        return make_uint2(ld_dev(words + step_idx(u)), ld_dev(words + step_val(u)));
-    }
-    __device__ __forceinline__ uint32_t bits(uint32_t p) const { return get(p).y; }
-    __device__ __forceinline__ uint32_t index(uint32_t p) const { return get(p).x; }
-};
+// Where the ranking workgroup puts what does not fit its LDS list (as SrcSplit's tail: entry SEL_LDS_LIST comes first): the
+// streaming pass's slots, which lie before ord and which nobody uses in such a launch, of the tiles that are wholly the tensor's.
+// There are CAPT a tile, and the units' lists have fewer entries than that for all tiles but the tensor's two outer ones, so
+// that what they hold always fits.
+__device__ __forceinline__ uint2 *step_tail(const SelectArgs &A, const TensorDesc &td)
+{
+    static_assert(SEL_LDS_LIST >= 2u * CAPT, "the outer tiles");
+    return A.ord - (size_t)(A.ntiles - (td.off + TILE - 1u) / TILE) * CAPT - SEL_LDS_LIST;
+}
 
 // put(position, index, value) for every entry of a tensor's lists (KEYS: the index is not read), in any order.  16 lanes take a
 // unit, a lane four entries with one load past the L2: such a load takes a compute unit some 20 ns whatever its width
@@ -766,13 +754,6 @@ __device__ __forceinline__ uint32_t trim_list(const SelectArgs &A, const Src &sr
     return c2;
 }
 
-// The units of a tensor whose call is one launch, as its ranking workgroup has found them: `count` of them in
-// SelectArgs::steptab from `first` on; their list positions are in PartShared::pbase, the counters of the window and
-// the smallest key are clear.
-struct StepRun {
-    uint32_t first, count;
-};
-
 // What the workgroup that completes a tensor's candidate lists does with them (`round` 0: the
 // streaming pass's candidates, 1: re-collected with a fresh threshold).  Returns the tensor's
 // status: SEG_DONE, SEG_ACTIVE / SEG_LISTS / SEG_ZERO (the chain kernels go on), or SEG_PENDING (round 0
@@ -791,28 +772,26 @@ __device__ __forceinline__ uint32_t tensor_select(const SelectArgs &A, const Ten
                                                   uint32_t j, int round, bool multi, bool by_parts, uint32_t c0,
                                                   bool ovf0, uint32_t kmin0, uint32_t tau_cur, uint32_t tprev_cur,
                                                   uint32_t win_join, bool win_counted, uint32_t *verdict,
-                                                  PartShared &P, uint2 *llist, const StepRun run = StepRun{0u, 0u})
+                                                  PartShared &P, uint2 *llist)
 {
     constexpr bool HERE = FORM == FORM_CHAIN;
-    const bool step = FORM == FORM_STEP && round == 0;         // the lists are those of the tensor's units
-    const bool emits = step && step_emits(A, td.n);            // ... and many workgroups wait for its k-th key
     const uint32_t tid = threadIdx.x;
     const uint32_t tlo = td.off / TILE;
     uint2 *glist = A.ord + (size_t)(tlo + j) * CAPT;      // = the first part's list
     const bool exact_mode = A.exact_mode || round != 0;
     const uint32_t hint2_cur = A.write_hint ? A.hint2[j] : 0u;
-    const uint32_t nunits = step ? run.count : by_parts ? td.nseg : td.ngrp;
+    const uint32_t nunits = by_parts ? td.nseg : td.ngrp;
     const SegDesc *units = by_parts ? A.segtab + td.seg_first : A.grptab + td.grp_first;
     const uint32_t *ucnt = by_parts ? A.segcnt + td.seg_first : A.grpcnt + td.grp_first;
     const bool have_pbase = nunits <= SEG_MAX_PER_TENSOR;
     // The longest list this workgroup selects from.  A tensor of several parts is gathered in
     // place: what does not fit the LDS list goes to the first part's global list, which must
     // end before the second part's begins.
-    const uint32_t list_max = step ? SEL_LDS_LIST : multi ? max(SEL_LDS_LIST, min(SEL_LIST_HARD, units[0].ntiles * CAPT))
-                                                         : SEL_LIST_HARD;
+    const uint32_t list_max = multi ? max(SEL_LDS_LIST, min(SEL_LIST_HARD, units[0].ntiles * CAPT))
+                                    : SEL_LIST_HARD;
     uint32_t c = c0, kmin = kmin0;
     bool ovf = ovf0;
-    if (multi && !step) {
+    if (multi) {
         // counts of the units -> list positions
         uint32_t o = 0;
         c = 0;
@@ -835,12 +814,6 @@ __device__ __forceinline__ uint32_t tensor_select(const SelectArgs &A, const Ten
     uint32_t status = 0;
     bool early = false;      // the verdict went out before the work
     if (pe.seg) status = window_step<OP, HERE>(A, td, pe, j, c, ovf, tau_cur, tprev_cur, hint2_cur, exact_mode, round != 0, P);
-    if (emits && !ovf && c >= pe.k && (c > list_max || pe.k > STEP_EMIT_K)) {
-        early = true;
-        status = SEG_ACTIVE;
-        if (verdict && tid == 0) st_dev(verdict, 0x100u | (uint32_t)SEG_DONE);
-        step_rank<OP>(A, td, pe, j, run.first, nunits, c, tau_cur, hint2_cur, P);
-    }
     // every nonzero is in the lists
     const bool zerofill = !ovf && c < pe.k && tau_cur <= 1u && (!multi || have_pbase);
     if (status == 0 && zerofill) {
@@ -857,8 +830,6 @@ __device__ __forceinline__ uint32_t tensor_select(const SelectArgs &A, const Ten
                 st->pfx = 0;
                 atomicAdd(&A.stats->segmented_tensors, 1ull);
             }
-        } else if (step) {
-            zero_fill_emit<OP, written<OP, FORM>()>(SrcStep{A, P.pbase, run.first, nunits}, c, td, pe, A, P.S.wsum);
         } else if (multi) {
             zero_fill_emit<OP, written<OP, FORM>()>(SrcParts{A.ord, P.pbase, P.pofs, nunits}, c, td, pe, A, P.S.wsum);
         } else if (pe.seg) {
@@ -874,28 +845,20 @@ __device__ __forceinline__ uint32_t tensor_select(const SelectArgs &A, const Ten
             A.tprev[j] = 0u;
         }
         if (tid == 0) atomicAdd(&A.stats->candidates, (unsigned long long)c);
-    } else if (status == 0 && !pe.seg && !ovf && c >= pe.k && c <= list_max && (!multi || have_pbase)) {
+    } else if (!pe.seg && !ovf && c >= pe.k && c <= list_max && (!multi || have_pbase)) {
         early = true;
         if (verdict && tid == 0) st_dev(verdict, 0x100u | (uint32_t)SEG_DONE);
         if (multi) {
             // gather the parts' lists into one (positions beyond the LDS list land in the first
             // part's global list: on dead space, or on the very entry that is being moved)
             const bool count_win = (win_join != 0xFFFFFFFFu);   // the hinted window is counted on the way
-            if (!step) {
-                for (uint32_t b = tid; b < WIN_BINS; b += SEL_THREADS) P.S.h[b] = 0;
-                if (tid == 0) P.S.kmin = 0xFFFFFFFFu;
-                __syncthreads();
-            }
+            for (uint32_t b = tid; b < WIN_BINS; b += SEL_THREADS) P.S.h[b] = 0;
+            if (tid == 0) P.S.kmin = 0xFFFFFFFFu;
+            __syncthreads();
             const SrcParts src{A.ord, P.pbase, P.pofs, nunits};
             uint32_t km = 0xFFFFFFFFu;
             constexpr uint32_t GU = 8;      // entries per thread in flight
-            if (step)
-                step_gather<false>(A, run.first, nunits, P.pbase, [&](uint32_t p, uint32_t ix, uint32_t v) {
-                    llist[p] = make_uint2(ix, v);
-                    km = min(km, v & 0x7FFFFFFFu);
-                    window_count<OP>(P.S.h, win_join, v & 0x7FFFFFFFu);
-                });
-            for (uint32_t q0 = 0; !step && q0 < c; q0 += GU * SEL_THREADS) {
+            for (uint32_t q0 = 0; q0 < c; q0 += GU * SEL_THREADS) {
                 uint2 e[GU];
 #pragma unroll
                 for (uint32_t u = 0; u < GU; ++u) {
@@ -927,8 +890,7 @@ __device__ __forceinline__ uint32_t tensor_select(const SelectArgs &A, const Ten
         // Every candidate is in the lists, there are only too many of them for one workgroup
         // (the threshold has fallen behind a scale that grew): trimmed on the spot.
         uint32_t tau_new = tau_cur;
-        const uint32_t c2 = step ? trim_list(A, SrcStep{A, P.pbase, run.first, nunits}, c, list_max, pe, verdict, P, llist, glist, tau_new)
-                          : multi ? trim_list(A, SrcParts{A.ord, P.pbase, P.pofs, nunits}, c, list_max, pe, verdict, P,
+        const uint32_t c2 = multi ? trim_list(A, SrcParts{A.ord, P.pbase, P.pofs, nunits}, c, list_max, pe, verdict, P,
                                               llist, glist, tau_new)
                                   : trim_list(A, SrcSplit{llist, glist}, c, list_max, pe, verdict, P, llist, glist, tau_new);
         if (c2 != 0) {
@@ -955,7 +917,6 @@ __device__ __forceinline__ uint32_t tensor_select(const SelectArgs &A, const Ten
         atomicAdd(&A.stats->repaired_tensors, 1ull);
     }
     if (tid == 0) A.segstate[j].status = status;
-    if (emits && status != SEG_ACTIVE && tid == 0) st_dev(&A.segstate[j].key, make_uint2(STEP_DONE, KEY_READY));
     if (HERE && pe.seg && status != SEG_PENDING && status != SEG_ACTIVE) {      // the slabs of this launch go on
         wait_mem();
         __syncthreads();
@@ -1087,7 +1048,7 @@ __device__ __forceinline__ void standby_block(const SelectArgs &A, uint32_t b, u
     }
     __syncthreads();
     for (uint32_t i = 0; i < A.bgroup; ++i)
-        if ((P.vbuf[i] & 0xFFu) == SEG_PENDING) recollect_part<OP, FORM>(A, role, first + i * nb, P, llist);
+        if (__builtin_expect((P.vbuf[i] & 0xFFu) == SEG_PENDING, 0)) recollect_part<OP, FORM>(A, role, first + i * nb, P, llist);
 }
 
 // A tensor of one part whose prediction failed: its workgroup collects again on the spot.

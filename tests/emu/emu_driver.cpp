@@ -521,6 +521,38 @@ static void over_gradient(const char *name, const std::vector<uint64_t> &sizes, 
     fflush(stdout);
 }
 
+// A scale that grows from step to step (one that `jumps` by a factor, where that is not 0), so that the lists of a tensor without
+// emitting workgroups outgrow what its ranking workgroup holds: selected as they are up to 65,536 entries, cut down beyond,
+// and, where the gradient has few nonzeros, completed with zeros.  `most`: tensors that may be counted as repaired.
+static void growing_lists(const char *name, const std::vector<uint64_t> &sizes, double rho, float growth, int flavour, uint64_t most, uint64_t seed)
+{
+    g_what = name;
+    Layout L(sizes);
+    Rng r(seed);
+    Ctx c(L, 0);
+    const uint64_t K = L.K(rho);
+    Buf<float> g(L.n), s_gpu(L.n), s_ref(L.n), gv(K), wv(K);
+    Buf<uint32_t> gi(K), wi(K);
+    uint64_t before = 0;
+    float lr = 1.0f;
+    for (int call = 0; call < 5; ++call, lr *= growth) {
+        g_what = std::string(name) + " call " + std::to_string(call);
+        fill_grad(L, r, g.p, 1.0f, flavour);
+        uint64_t k = 0;
+        CHECK(dgs_oracle_worker_step(g.p, s_ref.p, L.off.data(), L.J, lr, 0.0f, rho, wi.p, wv.p, &k) == 0);
+        CHECK(dgs_worker_step(c.c, g.p, nullptr, s_gpu.p, lr, 0.0f, rho, gi.p, gv.p, &k) == DGS_OK);
+        expect_same(gi.p, gv.p, wi.p, wv.p, K);
+        expect_same_f(s_gpu.p, s_ref.p, L.n, "state");
+        for (uint64_t i = 0; i < L.n; ++i) s_gpu.p[i] = s_ref.p[i] = 0.0f;      // (the scale alone moves the lists)
+        if (call == 0) before = c.stats().repaired_tensors;
+    }
+    const dgs_stats st = c.stats();
+    CHECK(st.internal_errors == 0);
+    printf("%-44s ok: repaired %llu, fallback %llu\n", name, (unsigned long long)(st.repaired_tensors - before), (unsigned long long)st.fallback_tensors);
+    CHECK(st.repaired_tensors - before <= most && st.fallback_tensors == 0);
+    fflush(stdout);
+}
+
 // The launch behind a selection on the printed state: the row follows the message, also where the model has moved
 // on since the values were taken; an index outside the row is skipped; and where an internal error has been
 // counted, a pair that the row does not show (one that no selection has written) moves nothing.
@@ -821,6 +853,9 @@ int main(int argc, char **argv)
         }
         worker_server("units of 8 tiles", {700000, 64, 500000}, 0.005, 0.002, 1.0f, 0.9f, false, {1, 1, 1}, 0, o, 78);
         worker_server("units of 16 tiles", {1300000, 64, 1200001}, 0.003, 0.001, 1.0f, 0.9f, false, {1, 1, 3}, 0, o, 79);
+        growing_lists("lists beyond the LDS list", {70, 500000, 9000}, 0.004, 1.6f, 0, 0, 84);
+        growing_lists("lists beyond 65,536 entries", {600001, 64}, 0.004, 3.0f, 0, 4, 85);
+        growing_lists("fewer nonzeros than k", {70, 500000, 9000}, 0.004, 1.0f, 5, 0, 86);
         over_gradient("values over the gradient", {64, 8000, 12000, 100}, 0.01, true, 0, 81);
         over_gradient("indices over the gradient", {64, 8000, 12000, 100}, 0.01, false, 0, 82);
         over_gradient("values over the gradient's end", {64, 8000, 12000, 90000}, 0.03, true, 110064 - 3302, 83);

@@ -118,3 +118,16 @@ def test_message_over_the_gradient(oracle, sizes, what):
         assert_state_match(state.cpu().numpy(), s_ref, f"call {call}")
     assert ctx.stats().internal_errors == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("growth, most", [(1.1, 3), (3.0, 12)])
+@pytest.mark.parametrize("sizes, rho", [([1_000_000], 0.001), ([64, 500_000, 9000, 500_000], 0.004)])
+def test_growing_scale(oracle, sizes, rho, growth, most):
+    """Lists beyond what the ranking workgroup holds in LDS are selected as they are up to 65,536 entries (nothing is repaired,
+    but for the calls that follow the first), and cut down beyond: as on larger layouts."""
+    off = synth.offsets_from_sizes(sizes)
+    g = np.random.default_rng(12).standard_normal(int(off[-1])).astype(np.float32)
+    st = run_worker_parity(oracle, off, [(g * np.float32(growth ** i)).astype(np.float32) for i in range(12)], np.float32(1.0),
+                           np.float32(0.0), rho, residual=True)
+    big = sum(s > 8192 for s in sizes)
+    assert st.repaired_tensors <= most * big and st.fallback_tensors == 0
