@@ -252,7 +252,6 @@ __device__ __forceinline__ bool step_select(const SelectArgs &A, const TensorDes
     if (tid == 0) {
         A.segstate[j].status = EMITS ? (uint32_t)SEG_ACTIVE : (uint32_t)SEG_DONE;
         atomicAdd(&A.stats->candidates, (unsigned long long)c);
-        if (EMITS && A.plan[j].seg) atomicAdd(&A.stats->segmented_tensors, 1ull);
     }
     list_hints(A, j, tau_next, expect, q_e, T, tau_cur, kmin);
     return true;

@@ -653,7 +653,6 @@ __device__ __forceinline__ void step_rank(const SelectArgs &A, const TensorDesc 
     if (tid == 0) {
         st_dev(&A.segstate[j].key, make_uint2(rT, KEY_READY | T));
         atomicAdd(&A.stats->candidates, (unsigned long long)c);
-        if (A.plan[j].seg) atomicAdd(&A.stats->segmented_tensors, 1ull);
         if (c > SEL_LIST_HARD) atomicAdd(&A.stats->repaired_tensors, 1ull);
     }
     list_hints(A, j, measurable ? max((edge << HSHIFT) | (bin << LOW), 1u) : 0u, expect, 0u, T, tau_cur, 0xFFFFFFFFu);

@@ -856,6 +856,24 @@ int main(int argc, char **argv)
         growing_lists("lists beyond the LDS list", {70, 500000, 9000}, 0.004, 1.6f, 0, 0, 84);
         growing_lists("lists beyond 65,536 entries", {600001, 64}, 0.004, 3.0f, 0, 4, 85);
         growing_lists("fewer nonzeros than k", {70, 500000, 9000}, 0.004, 1.0f, 5, 0, 86);
+        {
+            // a tensor that its plan has for the chain: the first call takes it, and is counted; those that are one launch are not
+            g_what = "the chain is counted where it runs";
+            Layout L({600001, 64});
+            Rng r(87);
+            Ctx c(L, 0);
+            const uint64_t K = L.K(0.01);
+            Buf<float> g(L.n), s(L.n), gv(K);
+            Buf<uint32_t> gi(K);
+            uint64_t k = 0, first = 0;
+            for (int t = 0; t < 3; ++t) {
+                fill_grad(L, r, g.p, 1.0f, 0);
+                CHECK(dgs_worker_step(c.c, g.p, s.p, nullptr, 1.0f, 0.9f, 0.01, gi.p, gv.p, &k) == DGS_OK);
+                if (t == 0) first = c.stats().segmented_tensors;
+            }
+            CHECK(first == 1 && c.stats().segmented_tensors == first && c.stats().internal_errors == 0);
+            printf("%-44s ok\n", g_what.c_str());
+        }
         over_gradient("values over the gradient", {64, 8000, 12000, 100}, 0.01, true, 0, 81);
         over_gradient("indices over the gradient", {64, 8000, 12000, 100}, 0.01, false, 0, 82);
         over_gradient("values over the gradient's end", {64, 8000, 12000, 90000}, 0.03, true, 110064 - 3302, 83);
