@@ -7,7 +7,7 @@ import pytest
 from paper_1910_10929_amd import dgs, synth
 from harness import assert_pairs_match, assert_state_match, run_worker_parity, to_host_u32
 
-pytestmark = pytest.mark.gpu
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("launches")]
 SIZES = [70_001, 3, 8193, 1023, 20_000, 6]       # odd total; tiles shared by two and more tensors
 
 

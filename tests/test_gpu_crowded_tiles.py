@@ -8,7 +8,7 @@ import pytest
 from paper_1910_10929_amd import dgs, synth
 from harness import Worker, assert_pairs_match, assert_state_match
 
-pytestmark = pytest.mark.gpu
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("launches")]
 
 COUNTS = [9, 24, 25, 40, 8, 41, 10]
 

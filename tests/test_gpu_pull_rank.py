@@ -7,7 +7,7 @@ import pytest
 
 from paper_1910_10929_amd import dgs, synth
 
-pytestmark = pytest.mark.gpu
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("launches")]
 
 
 @pytest.mark.parametrize("sizes,rho,young,old", [

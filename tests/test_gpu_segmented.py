@@ -136,7 +136,7 @@ def test_segmented_server_pull(oracle):
     ctx.close()
 
 
-def test_automatic_mode_mixes_both_selections(oracle):
+def test_automatic_mode_mixes_both_selections(oracle, launches):
     """Default mode: at density 1e-3 both large tensors are selected inside the selection
     launch (their parts joined by several workgroups, the last one selecting); at 0.03 the
     4.2M-element tensor's candidate list is too long for one workgroup and goes through the
@@ -153,7 +153,7 @@ def test_automatic_mode_mixes_both_selections(oracle):
 
 
 @pytest.mark.parametrize("seg_mode", [None, dgs.SEG_NEVER], ids=["auto", "never"])
-def test_single_workgroup_join_over_several_batches(oracle, seg_mode):
+def test_single_workgroup_join_over_several_batches(oracle, seg_mode, launches):
     """Tensors of thousands of tiles whose candidate lists one workgroup can select from: a
     tensor of up to 4096 tiles is joined by one workgroup in rounds of 1024 tiles, the
     7M-element one by two whose lists the last to arrive gathers (with the chain switched off
@@ -170,7 +170,7 @@ def test_single_workgroup_join_over_several_batches(oracle, seg_mode):
     assert st.segmented_tensors == 0 and st.internal_errors == 0
 
 
-def test_recollection_after_a_join_that_outgrew_the_lds_list(oracle):
+def test_recollection_after_a_join_that_outgrew_the_lds_list(oracle, launches):
     """Second step of a momentum run: the hinted threshold lets tens of thousands of candidates
     through, the join of the 3.4M-element tensor (one workgroup, 13 parts) runs past the LDS
     list into the first parts' global lists, the prediction is rejected, and the parts are
@@ -194,7 +194,7 @@ def test_recollection_after_a_join_that_outgrew_the_lds_list(oracle):
     assert st.repaired_tensors >= 2 and st.fallback_tensors == 0 and st.internal_errors == 0
 
 
-def test_collapsed_scale_is_recollected_by_many_workgroups(oracle):
+def test_collapsed_scale_is_recollected_by_many_workgroups(oracle, launches):
     """A 2,359,296-element tensor (9 parts) whose gradient scale collapses by 1e6 and comes back:
     fewer candidates than k pass the hinted threshold, the launch's other workgroups build a
     fresh histogram and collect the parts again, the last of them selects.  No dense
@@ -214,7 +214,7 @@ def test_collapsed_scale_is_recollected_by_many_workgroups(oracle):
     ([6_000_011, 64], 1.5e-3, 2),        # what remains of the gathered lists is longer than the LDS list
     ([4_000_000, 64], 2.5e-3, 2),        # the same for one workgroup's own list
 ], ids=["both-kinds", "gathered-spills", "own-list-spills"])
-def test_overlong_complete_lists_are_trimmed_inside_the_launch(oracle, sizes, rho, trimmed, repair_round):
+def test_overlong_complete_lists_are_trimmed_inside_the_launch(oracle, sizes, rho, trimmed, repair_round, launches):
     """A 6M-element tensor (two join groups) and a 3M- or 4M-element one (joined by one
     workgroup, its list spilling from LDS into global scratch) whose scale triples: the hinted
     threshold lets some 8 % of the elements through -- every candidate is collected, no tile
@@ -235,7 +235,7 @@ def test_overlong_complete_lists_are_trimmed_inside_the_launch(oracle, sizes, rh
         assert st.fallback_tensors == 0
 
 
-def test_a_wait_that_gives_up_is_counted_and_every_kernel_ends(oracle):
+def test_a_wait_that_gives_up_is_counted_and_every_kernel_ends(oracle, launches):
     """The workgroups that stand by to collect a tensor again poll for the verdict of its join
     a bounded number of times.  With the bound set to one poll they give up before the verdict
     is out: the launch still ends, the give-ups are counted as internal errors, and -- in the
@@ -312,7 +312,7 @@ def test_dense_requests_with_tie_classes(oracle, name):
 @pytest.mark.parametrize("option,value", [(dgs.OPT_MARGIN_PCT, 0), (dgs.OPT_MARGIN_PCT, 300),
                                           (dgs.OPT_STREAM_QUADS, 3), (dgs.OPT_REPAIR_ROUND, 0)])
 @pytest.mark.parametrize("seg_mode", [dgs.SEG_AUTO, dgs.SEG_ALWAYS], ids=["auto", "always"])
-def test_tuning_options_do_not_change_results(oracle, option, value, seg_mode):
+def test_tuning_options_do_not_change_results(oracle, option, value, seg_mode, launches):
     """Candidate margin, streaming launch shape and the repair round only steer the code path.
     The gradient scale jumps up and collapses on the way, so thresholds fail and (without the
     repair round) the dense re-selection has to step in."""

@@ -70,7 +70,7 @@ def run_events(oracle, off, W, events, rho_up, rho_down, seed, seg_mode=None, ex
     return st
 
 
-def test_printed_form_random_interleaving(oracle):
+def test_printed_form_random_interleaving(oracle, launches):
     off = synth.offsets_from_sizes([120_000, 64, 9408, 40_000, 7, 8193])
     run_events(oracle, off, W=5, events=30, rho_up=0.004, rho_down=0.002, seed=60,
                extra=[(0, 0.002), (0, 0.002), (0, 0.002), (1, 0.5), (2, 1.0), (2, 0.01)])
@@ -84,7 +84,7 @@ def test_printed_form_segmented(oracle):
 
 
 @pytest.mark.parametrize("k", [1400, 1401, 1536, 1537])
-def test_printed_form_on_both_sides_of_the_row_update(oracle, k):
+def test_printed_form_on_both_sides_of_the_row_update(oracle, k, launches):
     """Up to 1400 entries of a tensor the selection moves the row itself, beyond that a launch behind it does
     (whole workgroups of pairs and one more); messages of a third of the entries, so that the first pulls
     are completed with zeros, and pulls with nothing new."""
@@ -94,7 +94,7 @@ def test_printed_form_on_both_sides_of_the_row_update(oracle, k):
 
 
 @pytest.mark.parametrize("k", [1400, 1401])
-def test_printed_form_with_infinities_and_nans(oracle, k):
+def test_printed_form_with_infinities_and_nans(oracle, k, launches):
     """A few entries of the model become infinite or NaN, on both sides of where the row is updated: they are
     sent, the row follows, and from then on their difference is NaN.  NaN equal to NaN, all else bit for bit."""
     off = synth.offsets_from_sizes([300_001, 5000, 17])
@@ -245,7 +245,7 @@ def test_printed_form_argument_errors():
 
 @pytest.mark.parametrize("repair_round", [1, 0], ids=["roles", "no-roles"])
 @pytest.mark.parametrize("form", ["sent", "diff"])
-def test_pulls_trim_complete_but_overlong_lists(oracle, form, repair_round):
+def test_pulls_trim_complete_but_overlong_lists(oracle, form, repair_round, launches):
     """Dense pushes whose scale grows between pulls, in both server forms: the threshold hinted by
     the previous pull lets several per cent of a 6M-element tensor (two join groups) and of a
     3M-element one (joined by one workgroup) through.  Every candidate is collected, so the

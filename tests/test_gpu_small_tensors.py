@@ -8,7 +8,7 @@ import pytest
 from paper_1910_10929_amd import dgs, synth
 from harness import Server, assert_pairs_match, assert_state_match, run_worker_parity, to_dev, to_host_u32
 
-pytestmark = pytest.mark.gpu
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("launches")]
 
 SIZES = [1, 7, 8, 9, 1023, 1025, 4097, 8191, 8192, 20000, 3]
 SCALES = [1.0, 1.0, 1.1, 30.0, 30.0, 0.02, 1.0, 0.0, 1.0]
