@@ -514,8 +514,8 @@ __device__ __forceinline__ void list_hints(const SelectArgs &A, uint32_t j, uint
 
 // The tensor's candidates are in `llist` (first SEL_LDS_LIST) and `glist` (beyond): exact
 // selection, emission, fix-up and the next hint.  win_*: the window histogram in P.S.h counted
-// while the list was built (single-part tensors), see select_emit.
-template <int OP>
+// while the list was built (single-part tensors), see select_emit.  KEY: the k-th key alone, for the workgroups that await it.
+template <int OP, bool KEY = false>
 __device__ __forceinline__ void list_select(const SelectArgs &A, const TensorDesc &td, const PlanEntry &pe, uint32_t j,
                                             uint32_t c, uint32_t kmin, uint32_t tau_cur, uint32_t hint2_cur,
                                             uint32_t win_join, bool win_counted, bool exact_mode, PartShared &P,
@@ -530,7 +530,12 @@ __device__ __forceinline__ void list_select(const SelectArgs &A, const TensorDes
     uint32_t R = 0, Eq = 0;
     if (A.write_hint && (threadIdx.x < 3u * 64u || win_base == 0xFFFFFFFFu)) R = hint_rank<OP>(td, pe, !exact_mode, c, hint2_cur, A.m, A.young, &Eq);
     uint32_t tau_next = 0, expect = 0, q_e = 0, t_k = 0;
-    if (c <= SEL_LDS_LIST) {
+    if (KEY) {
+        uint32_t rT;
+        if (select_key<OP>(SrcSplit{llist, glist}, c, pe.k, R, Eq, win_base, win_min, win_ready, kmin, P.S, A, &tau_next, &expect, &q_e, t_k, rT) &&
+            threadIdx.x == 0)
+            st_dev(&A.segstate[j].key, make_uint2(rT, KEY_READY | t_k));
+    } else if (c <= SEL_LDS_LIST) {
         // Entries per thread, 2 / 3 / 4 of them: a round on ResNet-50 shapes 111.0 / 109.8 / 111.2 us, an event of a server with
         // 32 sent rows 59.8 / 59.5 / 59.9, with difference rows 83.0 / 82.8 / 83.2; 70 odd tensors, 6 workers 45.4 / 45.1 /
         // 45.6.  (Every instance of the emission costs the kernel scalar registers, which it spills: 194 to 243 of them,
@@ -607,7 +612,7 @@ __device__ __forceinline__ void step_gather(const SelectArgs &A, uint32_t first,
     }
 }
 
-// A tensor with emitting workgroups whose list its ranking workgroup cannot hold, or whose k-th key lies beyond the hinted
+// A pull of a tensor with emitting workgroups whose list its ranking workgroup cannot hold, or whose k-th key lies beyond the hinted
 // window (a row that has waited long): the keys are read three times, for 12 bits, 11 and 8, and the exact
 // one goes on to those workgroups.  21 K keys: 10 us.  (Cut down to what fits, or collected again by the tensor's parts, 100.)
 template <int OP>

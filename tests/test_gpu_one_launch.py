@@ -131,3 +131,33 @@ def test_growing_scale(oracle, sizes, rho, growth, most):
                            np.float32(0.0), rho, residual=True)
     big = sum(s > 8192 for s in sizes)
     assert st.repaired_tensors <= most * big and st.fallback_tensors == 0
+
+
+@pytest.mark.parametrize("momentum", [0.9, 0.0])
+def test_lists_follow_the_drift(momentum):
+    """One tensor whose unsent entries grow for hundreds of steps, with lists of more than the ranking workgroup holds in registers: the
+    threshold follows them as it does in several launches (one that does not lets a third more through), and the messages are the same."""
+    import torch
+    off = synth.layout_flat(5_000_000)
+    n, rho, dev = int(off[-1]), 0.001, "cuda:0"
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(3)
+    grads = [torch.randn(n, device=dev, generator=gen) for _ in range(4)]
+    lists, outs = [], []
+    for quads in (0, 1):
+        ctx = dgs.Context(off, W=0)
+        ctx.set_option(dgs.OPT_STREAM_QUADS, quads)
+        K = ctx.nnz(rho)
+        state = torch.zeros(n, device=dev)
+        idx, val = torch.zeros(K, dtype=torch.int32, device=dev), torch.zeros(K, device=dev)
+        for call in range(60):
+            if call == 40:
+                before = ctx.stats().candidates
+            ctx.worker_step(grads[call % 4], state, 0.1, momentum, rho, idx, val, residual_mode=momentum == 0.0)
+        lists.append((ctx.stats().candidates - before) / 20 / K)
+        assert ctx.stats().internal_errors == 0
+        outs.append((idx, val.view(torch.int32), state.view(torch.int32)))
+        ctx.close()
+    assert abs(lists[0] - lists[1]) < 0.05 * lists[1], lists
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
