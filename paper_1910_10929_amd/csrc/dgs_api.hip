@@ -91,11 +91,12 @@ struct StepCut {
 };
 
 // Units as small as the compute units allow, one each: a unit's loads are what its compute unit takes longest for.
-StepCut step_cut(const uint64_t *offsets, uint32_t J)
+// (Fewer of those, as on a part of a device, only ever make the units larger.)
+StepCut step_cut(const uint64_t *offsets, uint32_t J, uint32_t cus)
 {
     for (uint32_t bt = 4; bt <= 16; bt *= 2) {
         uint64_t units = 0, ranks = 0, emits = 0, most = 0;
-        for (uint32_t j = 0; j < J && units <= STEP_UNITS_FEW; ++j) {
+        for (uint32_t j = 0; j < J && units <= STEP_UNITS_FEW * cus; ++j) {
             const uint64_t n = offsets[j + 1] - offsets[j];
             const uint64_t u = (n > SMALL_N) ? (n + (uint64_t)bt * TILE - 1) / ((uint64_t)bt * TILE) : 1;
             units += u;
@@ -103,7 +104,7 @@ StepCut step_cut(const uint64_t *offsets, uint32_t J)
             ranks += (n > SMALL_N) ? 1 : 0;
             if (n >= SEG_MIN_N) emits += (u + SEL_WAVES - 1) / SEL_WAVES;
         }
-        const bool fits = bt < 16 ? units + ranks + emits <= STEP_BLOCKS : units <= (J <= STEP_FEW ? STEP_UNITS_FEW : STEP_UNITS);
+        const bool fits = bt < 16 ? units + ranks + emits <= cus : units <= (J <= STEP_FEW ? STEP_UNITS_FEW * cus : cus + cus / STEP_UNITS_OVER);
         if (fits && most <= SEG_MAX_PER_TENSOR) return StepCut{bt, (uint32_t)units, (uint32_t)ranks, (uint32_t)emits};
     }
     return StepCut{};
@@ -151,7 +152,7 @@ Layout make_layout(const uint64_t *offsets, uint32_t J, uint32_t W, bool one_cal
     L.grptab = o;    o = align_up(o + (nseg_total + 1) * sizeof(SegDesc));      // groups <= parts
     L.cslabs = o;    o = align_up(o + ncs * sizeof(SegDesc));
     L.dslabs = o;    o = align_up(o + nds * sizeof(uint32_t));
-    const StepCut cut = one_call ? StepCut{} : step_cut(offsets, J);
+    const StepCut cut = one_call ? StepCut{} : step_cut(offsets, J, STEP_CUS);      // (room for any device's)
     L.steptab = o;   o = align_up(o + cut.units * sizeof(StepUnit));
     L.ranktab = o;   o = align_up(o + cut.ranks * sizeof(SegDesc));
     L.emittab = o;   o = align_up(o + cut.emits * sizeof(SegDesc));
@@ -1008,7 +1009,7 @@ int dgs_create(dgs_ctx **out, const uint64_t *offsets, uint32_t J, uint32_t W, v
             *slabs = segs + (L.cslabs - L.segtab) / sizeof(SegDesc);
     uint32_t *dslabs = (uint32_t *)(segs + (L.dslabs - L.segtab) / sizeof(SegDesc));
     c->nseg.assign(J, 0u);
-    c->cut = step_cut(offsets, J);
+    c->cut = step_cut(offsets, J, std::min<uint32_t>((uint32_t)c->cus, STEP_CUS));
     static_assert(sizeof(StepUnit) == 2 * sizeof(SegDesc), "among the other tables");
     if (c->cut.bt)
         fill_step_tables(c, (StepUnit *)(segs + (L.steptab - L.segtab) / sizeof(SegDesc)), segs + (L.ranktab - L.segtab) / sizeof(SegDesc),

@@ -122,14 +122,14 @@ constexpr uint32_t SEG_MAX_PER_TENSOR = 512;       // parts per tensor whose lis
 //   SEG_PENDING   the prediction failed: the parts collect again with a fresh threshold
 //   SEG_FALLBACK  left to the dense single-workgroup selection
 enum SegStatus { SEG_IDLE = 0, SEG_DONE = 1, SEG_FALLBACK = 2, SEG_PENDING = 4, SEG_ALL = 6, SEG_ACTIVE = 8, SEG_LISTS = 10, SEG_ZERO = 12 };
-// A whole call in one launch (k_step): units of 4 or 8 tiles while all workgroups, STEP_BLOCKS, have a compute unit each;
-// then of 16, up to STEP_UNITS of them, or STEP_UNITS_FEW of at most STEP_FEW tensors.  us, streaming pass and selection / one launch: a worker step on
+// A whole call in one launch (k_step): units of 4 or 8 tiles while all workgroups have a compute unit each (of the device's, at most
+// STEP_CUS are counted); then of 16, a 16th more than there are, or STEP_UNITS_FEW times as many of at most STEP_FEW tensors.  us, streaming pass and selection / one launch: a worker step on
 // one tensor of 100 K elements at 0.1 % 14.8 / 11.1, of 1M at 1 % 25.3 / 23.4, of 4M at 0.1 % 31.8 / 24.7, on 64 of 500 K in all at 1 %
 // 13.9 / 12.1, 8 of 4M at 1 % 30.4 / 25.9, 24 of 4M at 1 % (264 units) 23.9 / 24.5; an event of a server with 4 difference rows 16.0 /
 // 13.4, 33.7 / 28.4, 34.3 / 25.2, 15.9 / 13.4, 45.8 / 37.1, 31.5 / 31.6.  Beyond: 8 of 5M at 0.3 % (312) a round 49.3 / 53.3, 8 of 6M at 0.1 % an
 // event 22.3 / 23.0, 200 mixed of 4M a step 21.5 / 22.6; but 3 of 5M at 0.3 % (306) a round 66.7 / 59.5, one of 8M at 0.1 % (489) 102.4 / 91.1.
 // (The CPU test build with small parts keeps to the kernels that larger layouts take.)
-constexpr uint32_t STEP_BLOCKS = SEG_TILES < 128 ? 0 : 256, STEP_UNITS = SEG_TILES < 128 ? 0 : 272, STEP_UNITS_FEW = SEG_TILES < 128 ? 0 : 512;
+constexpr uint32_t STEP_CUS = SEG_TILES < 128 ? 0 : 256, STEP_UNITS_OVER = 16, STEP_UNITS_FEW = 2;
 constexpr uint32_t STEP_FEW = 4;
 // Where a tensor of at least SEG_MIN_N elements has more than STEP_EMIT_K pairs, those tensors have emitting workgroups.
 constexpr uint32_t STEP_EMIT_K = 2500;

@@ -11,6 +11,7 @@ namespace emu {
 
 int block_order = 0;
 int current_device = 0;
+int compute_units = 4;
 hipError_t last_error = hipSuccess;
 bool refuse_stamped = false;
 hipStreamCaptureStatus capture_status = hipStreamCaptureStatusNone;

@@ -553,6 +553,31 @@ static void growing_lists(const char *name, const std::vector<uint64_t> &sizes, 
     fflush(stdout);
 }
 
+// Whether the predicted calls of a layout are one launch on a device of `cus` compute units: nothing is counted as a streaming pass then.
+static bool one_launch(const std::vector<uint64_t> &sizes, double rho, float m, int cus, bool pull = false)
+{
+    Layout L(sizes);
+    Rng r(88);
+    emu::compute_units = cus;
+    Ctx c(L, 1);
+    emu::compute_units = 256;
+    const uint64_t K = L.K(rho);
+    Buf<float> g(L.n), s(L.n), gv(K);
+    Buf<uint32_t> gi(K);
+    CHECK(dgs_server_attach(c.c, s.p) == DGS_OK);
+    uint64_t k = 0, passes = 0;
+    double ms = 0;
+    for (int t = 0; t < 2; ++t) {
+        fill_grad(L, r, pull ? s.p : g.p, 1.0f, 0);
+        CHECK(dgs_set_option(c.c, DGS_OPT_PROFILE, t) == DGS_OK);
+        if (pull) CHECK(dgs_server_pull(c.c, 0, rho, gi.p, gv.p, &k) == DGS_OK);
+        else CHECK(dgs_worker_step(c.c, g.p, s.p, nullptr, 1.0f, m, rho, gi.p, gv.p, &k) == DGS_OK);
+    }
+    CHECK(dgs_profile_read(c.c, pull ? DGS_PROF_PULL_STREAM : DGS_PROF_WORKER_STREAM, &passes, &ms) == DGS_OK);
+    CHECK(c.stats().internal_errors == 0 && passes <= 1);
+    return passes == 0;
+}
+
 // The launch behind a selection on the printed state: the row follows the message, also where the model has moved
 // on since the values were taken; an index outside the row is skipped; and where an internal error has been
 // counted, a pair that the row does not show (one that no selection has written) moves nothing.
@@ -834,6 +859,11 @@ int main(int argc, char **argv)
         // (built with the library's own part size) A whole call in one launch: units of 4, 8 and 16 tiles, tensors whose
         // winners many workgroups emit and others, lists beyond what the ranking holds, k-th keys beyond its window, predictions
         // that fail both ways, ties, zeros, the lowest keys, infinities and NaNs, odd addresses
+        emu::compute_units = 256;
+        g_what = "lines of calls in one launch";
+        const std::vector<uint64_t> three = {70001, 9000, 100};
+        CHECK(one_launch(three, 0.01, 0.9f, 256) && one_launch(three, 0.01, 0.9f, 24) && !one_launch(three, 0.01, 0.9f, 3));
+        printf("%-44s ok\n", g_what.c_str());
         Opts o, mis;
         mis.misalign = 3;
         const std::vector<uint64_t> edges = {8192, 8193, 4096 * 3, 4096 * 4 + 1, 65535, 65536, 5, 69637, 12345};

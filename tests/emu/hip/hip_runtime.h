@@ -64,7 +64,8 @@ static inline hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
 // when it is created, and a launch that stamps an event of the other device fails.
 namespace emu { extern int current_device; }
 static inline hipError_t hipGetDevice(int *d) { *d = emu::current_device; return hipSuccess; }
-static inline hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int) { p->multiProcessorCount = 4; return hipSuccess; }
+namespace emu { extern int compute_units; }
+static inline hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int) { p->multiProcessorCount = emu::compute_units; return hipSuccess; }
 namespace emu { extern hipError_t last_error; extern bool refuse_stamped; }      // launches that stamp an event fail
 static inline hipError_t hipPeekAtLastError() { return emu::last_error; }
 static inline hipError_t hipGetLastError() { const hipError_t e = emu::last_error; emu::last_error = hipSuccess; return e; }
