@@ -90,6 +90,12 @@ struct StepCut {
     uint32_t bt, units, ranks, emits;
 };
 
+// Ranking and emitting workgroups of a launch, which wait for others, at most: on every die a third of what is there besides one compute
+// unit.  Launches of different contexts beside each other end then, four of them at a time (as many as a process has hardware queues by
+// default): the lowest of its workgroups that has not ended waits for nobody, or for a compute unit of a die where the waiting ones of three
+// others leave one.  (Tensors of one part have no other workgroups that wait; stand-by ones are bounded by themselves.)
+uint32_t step_waits(uint32_t cus) { return DIES * ((std::max<uint32_t>(cus / DIES, 1u) - 1u) / 3u); }
+
 // Units as small as the compute units allow, one each: a unit's loads are what its compute unit takes longest for.
 // (Fewer of those, as on a part of a device, only ever make the units larger.)
 StepCut step_cut(const uint64_t *offsets, uint32_t J, uint32_t cus)
@@ -105,7 +111,7 @@ StepCut step_cut(const uint64_t *offsets, uint32_t J, uint32_t cus)
             if (n >= SEG_MIN_N) emits += (u + SEL_WAVES - 1) / SEL_WAVES;
         }
         const bool fits = bt < 16 ? units + ranks + emits <= cus : units <= (J <= STEP_FEW ? STEP_UNITS_FEW * cus : cus + cus / STEP_UNITS_OVER);
-        if (fits && most <= SEG_MAX_PER_TENSOR) return StepCut{bt, (uint32_t)units, (uint32_t)ranks, (uint32_t)emits};
+        if (fits && ranks + emits <= step_waits(cus) && most <= SEG_MAX_PER_TENSOR) return StepCut{bt, (uint32_t)units, (uint32_t)ranks, (uint32_t)emits};
     }
     return StepCut{};
 }

@@ -131,6 +131,7 @@ enum SegStatus { SEG_IDLE = 0, SEG_DONE = 1, SEG_FALLBACK = 2, SEG_PENDING = 4, 
 // (The CPU test build with small parts keeps to the kernels that larger layouts take.)
 constexpr uint32_t STEP_CUS = SEG_TILES < 128 ? 0 : 256, STEP_UNITS_OVER = 16, STEP_UNITS_FEW = 2;
 constexpr uint32_t STEP_FEW = 4;
+constexpr uint32_t DIES = 8;                         // XCDs: a launch's workgroups are dealt out to them in turn
 // Where a tensor of at least SEG_MIN_N elements has more than STEP_EMIT_K pairs, those tensors have emitting workgroups.
 constexpr uint32_t STEP_EMIT_K = 2500;
 constexpr uint32_t STEP_ITEMS = 16, STEP_ITEMS_KEYS = 32;      // entries, or keys, that a thread of the ranking holds in registers

@@ -862,7 +862,9 @@ int main(int argc, char **argv)
         emu::compute_units = 256;
         g_what = "lines of calls in one launch";
         const std::vector<uint64_t> three = {70001, 9000, 100};
-        CHECK(one_launch(three, 0.01, 0.9f, 256) && one_launch(three, 0.01, 0.9f, 24) && !one_launch(three, 0.01, 0.9f, 3));
+        CHECK(one_launch(three, 0.01, 0.9f, 256) && one_launch(three, 0.01, 0.9f, 32) && !one_launch(three, 0.01, 0.9f, 3));
+        // at most 80 workgroups wait (for tensors of one part no other ones do)
+        CHECK(one_launch(std::vector<uint64_t>(80, 8200), 0.001, 0.9f, 256) && !one_launch(std::vector<uint64_t>(81, 8200), 0.001, 0.9f, 256));
         printf("%-44s ok\n", g_what.c_str());
         Opts o, mis;
         mis.misalign = 3;
