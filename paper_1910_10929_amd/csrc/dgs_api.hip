@@ -101,17 +101,24 @@ uint32_t step_waits(uint32_t cus) { return DIES * ((std::max<uint32_t>(cus / DIE
 StepCut step_cut(const uint64_t *offsets, uint32_t J, uint32_t cus)
 {
     for (uint32_t bt = 4; bt <= 16; bt *= 2) {
-        uint64_t units = 0, ranks = 0, emits = 0, most = 0;
-        for (uint32_t j = 0; j < J && units <= STEP_UNITS_FEW * cus; ++j) {
+        uint64_t units = 0, small = 0, ranks = 0, emits = 0, most = 0;      // (units: of the tensors that have several, or large ones)
+        for (uint32_t j = 0; j < J && units + small <= STEP_UNITS_FEW * cus; ++j) {
             const uint64_t n = offsets[j + 1] - offsets[j];
-            const uint64_t u = (n > SMALL_N) ? (n + (uint64_t)bt * TILE - 1) / ((uint64_t)bt * TILE) : 1;
+            if (n <= SMALL_N) {
+                ++small;
+                continue;
+            }
+            const uint64_t u = (n + (uint64_t)bt * TILE - 1) / ((uint64_t)bt * TILE);
             units += u;
             most = std::max(most, u);
-            ranks += (n > SMALL_N) ? 1 : 0;
+            ++ranks;
             if (n >= SEG_MIN_N) emits += (u + SEL_WAVES - 1) / SEL_WAVES;
         }
-        const bool fits = bt < 16 ? units + ranks + emits <= cus : units <= (J <= STEP_FEW ? STEP_UNITS_FEW * cus : cus + cus / STEP_UNITS_OVER);
-        if (fits && ranks + emits <= step_waits(cus) && most <= SEG_MAX_PER_TENSOR) return StepCut{bt, (uint32_t)units, (uint32_t)ranks, (uint32_t)emits};
+        const bool one_each = units <= cus && units + small <= cus + cus / STEP_UNITS_OVER && (bt > 4 || most <= STEP_UNITS_SMALLEST) &&
+                              (bt < 16 || small <= cus / STEP_SMALL);
+        const bool few = bt == 16 && J <= STEP_FEW && units + small <= STEP_UNITS_FEW * cus;
+        if ((one_each || few) && ranks + emits <= step_waits(cus) && most <= SEG_MAX_PER_TENSOR)
+            return StepCut{bt, (uint32_t)(units + small), (uint32_t)ranks, (uint32_t)emits};
     }
     return StepCut{};
 }
@@ -181,7 +188,9 @@ struct PlanSlot {
     uint32_t nwin = 0, nslab = 0;      // entries of the selection launch's tables (0: the chain has launches of its own)
     uint32_t window_max = 0;
     uint32_t kmax = 0;                 // largest k_j
-    bool step = false, emits = false;  // a predicted call may be one launch; it has emitting workgroups then
+    bool step_worker = false, step_residual = false, step_pull = false;      // predicted calls that may be one launch: with momentum,
+                                                                             // without, pulls
+    bool emits = false;                // it has emitting workgroups then
     uint64_t K = 0;
     uint64_t wire_words = 0;           // 32-bit words of the wire form's index area
     uint64_t last_use = 0;
@@ -405,23 +414,36 @@ void fill_plan(const dgs_ctx *c, double density, int margin_pct, PlanEntry *out,
     }
 }
 
-// Whether a predicted call at this plan may be one launch: every list that it expects leaves a fifth of what the ranking workgroup
-// holds free.  (Its threads are dealt out to a power of two of units.  One tensor of 600 K elements at 2 %, 147 units and
-// lists of 18 to 24 K: a worker step 40.6 us in one launch, which reads the lists again, 31.1 in several.)
-bool step_plan(const dgs_ctx *c, const PlanEntry *plan, double density, bool *emits)
+// Which predicted calls at this plan may be one launch, and whether they have emitting workgroups.  The ranking workgroup has to hold what it
+// ranks for those in registers, four standard deviations of a unit's list included: one that reads it again takes 10 to 20 us longer (one tensor
+// of 4M at 0.3 %, in several launches 32.5 us, in one 34.5).
+void step_plan(const dgs_ctx *c, const PlanEntry *plan, double density, PlanSlot *p)
 {
-    *emits = false;
-    if (c->cut.bt == 0 || density > DENSE_DENSITY || c->seg_mode != SEG_MODE_AUTO) return false;
+    p->emits = p->step_worker = p->step_residual = p->step_pull = false;
+    if (c->cut.bt == 0 || density > DENSE_DENSITY || c->seg_mode != SEG_MODE_AUTO) return;
+    bool fits = true, worker = true, residual = true;
+    uint64_t ranked = 0;
     for (uint32_t j = 0; j < c->J; ++j) {
         const uint64_t n = c->offsets[j + 1] - c->offsets[j], units = (n + c->cut.bt * TILE - 1) / (c->cut.bt * TILE);
-        if (n < SEG_MIN_N || plan[j].k <= STEP_EMIT_K) continue;      // (a list that does not fit is selected from LDS)
-        *emits = true;
+        if (n <= SMALL_N) continue;
+        if (n < SEG_MIN_N || plan[j].k <= STEP_EMIT_K) {      // (a list that does not fit the registers is selected from LDS)
+            ranked += plan[j].k;
+            continue;
+        }
+        p->emits = true;
+        // What a unit lists varies by the root of it; the threads of the ranking are dealt out to a power of two of units.
         uint64_t slots = 1;
         while (slots < units) slots *= 2;
-        const uint64_t longest = std::max(plan[j].k2, std::max(plan[j].k2_zero, plan[j].k2_pull));
-        if (longest * 5 * slots > 4ull * STEP_ITEMS_KEYS * SEL_THREADS * units) return false;
+        const double mean = (double)std::max(plan[j].k2, std::max(plan[j].k2_zero, plan[j].k2_pull)) / (double)units;
+        fits &= mean + 4.0 * std::sqrt(mean) <= (double)(STEP_ITEMS_KEYS * SEL_THREADS / slots);
+        if (plan[j].seg) {
+            worker &= plan[j].k2 <= (units <= STEP_CHAIN_UNITS ? STEP_CHAIN_LIST_FEW : STEP_CHAIN_LIST);
+            residual &= plan[j].k2_zero <= STEP_CHAIN_LIST;
+        }
     }
-    return true;
+    p->step_worker = fits && worker;
+    p->step_residual = fits && residual;
+    p->step_pull = fits && ranked <= STEP_PULL_K;
 }
 
 constexpr uint32_t STEP_MIN_SPINS = 1024;
@@ -528,7 +550,7 @@ int get_plan(dgs_ctx *c, double density, uint32_t *slot_out, uint64_t *K_out)
     for (uint32_t j = 0; j < c->J; ++j) p.kmax = std::max(p.kmax, stage[j].k);
     p.K = K;
     p.wire_words = wire_words;
-    p.step = step_plan(c, stage, density, &p.emits);
+    step_plan(c, stage, density, &p);
     p.last_use = c->tick;
     *slot_out = victim;
     *K_out = K;
@@ -581,7 +603,9 @@ int run_selection(dgs_ctx *c, int op_stream, int op_select, const float *grad, f
     const bool exact = !dense_req && (c->force_exact || c->force_sample || c->hint_density[hint_set] != density);
     // A small layout's predicted call is one launch.  (It rests on waits: not where those are bounded to next to nothing.  And
     // some of its workgroups emit while others still read: not where the message lies over what is read.)
-    const bool step = !dense_req && !exact && c->plan_slot[slot].step && c->repair_round && c->stream_quads == 0 &&
+    const PlanSlot &one = c->plan_slot[slot];
+    const bool may = op_select != SEL_WORKER ? one.step_pull : m == 0.0f ? one.step_residual : one.step_worker;
+    const bool step = !dense_req && !exact && may && c->repair_round && c->stream_quads == 0 &&
                       c->spin_limit >= STEP_MIN_SPINS && !under_message(grad, c->n, idx_out, val_out, K) &&
                       !under_message(state, c->n, idx_out, val_out, K);
     uint32_t *tau = c->tau + (size_t)hint_set * c->J;

@@ -122,16 +122,33 @@ constexpr uint32_t SEG_MAX_PER_TENSOR = 512;       // parts per tensor whose lis
 //   SEG_PENDING   the prediction failed: the parts collect again with a fresh threshold
 //   SEG_FALLBACK  left to the dense single-workgroup selection
 enum SegStatus { SEG_IDLE = 0, SEG_DONE = 1, SEG_FALLBACK = 2, SEG_PENDING = 4, SEG_ALL = 6, SEG_ACTIVE = 8, SEG_LISTS = 10, SEG_ZERO = 12 };
-// A whole call in one launch (k_step): units of 4 or 8 tiles while all workgroups have a compute unit each (of the device's, at most
-// STEP_CUS are counted); then of 16, a 16th more than there are, or STEP_UNITS_FEW times as many of at most STEP_FEW tensors.  us, streaming pass and selection / one launch: a worker step on
-// one tensor of 100 K elements at 0.1 % 14.8 / 11.1, of 1M at 1 % 25.3 / 23.4, of 4M at 0.1 % 31.8 / 24.7, on 64 of 500 K in all at 1 %
-// 13.9 / 12.1, 8 of 4M at 1 % 30.4 / 25.9, 24 of 4M at 1 % (264 units) 23.9 / 24.5; an event of a server with 4 difference rows 16.0 /
-// 13.4, 33.7 / 28.4, 34.3 / 25.2, 15.9 / 13.4, 45.8 / 37.1, 31.5 / 31.6.  Beyond: 8 of 5M at 0.3 % (312) a round 49.3 / 53.3, 8 of 6M at 0.1 % an
-// event 22.3 / 23.0, 200 mixed of 4M a step 21.5 / 22.6; but 3 of 5M at 0.3 % (306) a round 66.7 / 59.5, one of 8M at 0.1 % (489) 102.4 / 91.1.
-// (The CPU test build with small parts keeps to the kernels that larger layouts take.)
+// A whole call in one launch (k_step).  Its units have 4, 8 or 16 tiles, as small as the compute units (of the device's at most STEP_CUS
+// are counted) allow one for each unit of the tensors beyond SMALL_N, and a 16th more for small tensors; or 16 tiles and two units to a compute
+// unit, for STEP_FEW tensors.  us in several launches / in one, a worker step with momentum, without, an event of a server with 4 difference
+// rows, with 4 rows of the printed state:
+//   one tensor of 100 K elements at 0.1 %     14.4 / 11.0   14.4 / 11.0   14.8 / 13.1   16.0 / 13.1
+//   of 600 K at 1 %                           26.2 / 23.0   26.5 / 24.2   28.9 / 26.5   31.9 / 25.9
+//   of 4M at 0.1 %                            31.7 / 24.6   31.7 / 25.8   33.9 / 26.0   36.1 / 28.0
+//   of 8M at 0.1 % (489 units of 16)          60.9 / 40.1   58.9 / 40.2   54.8 / 39.1   58.5 / 43.1
+//   64 of 2M in all at 1 % (256 of 8)         17.3 / 15.2   17.6 / 15.5   23.0 / 21.6   21.9 / 20.7
+//   8 of 4M at 1 %                            30.4 / 26.1   30.7 / 25.6   44.8 / 37.9   42.8 / 35.9
+// Beyond: 24 of 4M at 1 % (264) 24.0 / 24.3, 24.1 / 24.3, 31.5 / 32.3, 30.4 / 31.9, at 2 % 27.0 / 30.0, 27.6 / 30.2, 43.5 / 50.3, 39.1 / 45.9;
+// 3 of 5M at 0.5 % (306) 34.2 / 36.7, 34.1 / 38.3, 40.2 / 39.8, 41.5 / 40.2.  Larger units than there is room for smaller ones: 64 of 2M at 1 %
+// in units of 16 17.5, 17.4, 23.1, 22.7.  But a ranking workgroup reads a list per unit, and a tensor does not get more than
+// STEP_UNITS_SMALLEST units of 4: one of 1M at 0.2 % 18.6 / 17.2 / 16.7 and 22.4 / 20.5 / 20.1 in units of 4 / of 8.  Units of 16 beside many small tensors,
+// a 4th of STEP_CUS and more, give nothing: 120 mixed of 2M at 2 % 20.1 / 20.5, 20.5 / 20.2, 30.6 / 32.8, 29.9 / 32.3.
 constexpr uint32_t STEP_CUS = SEG_TILES < 128 ? 0 : 256, STEP_UNITS_OVER = 16, STEP_UNITS_FEW = 2;
-constexpr uint32_t STEP_FEW = 4;
+constexpr uint32_t STEP_FEW = 2, STEP_UNITS_SMALLEST = 192, STEP_SMALL = 4;
+// (The CPU test build with small parts keeps to the kernels that larger layouts take.)
 constexpr uint32_t DIES = 8;                         // XCDs: a launch's workgroups are dealt out to them in turn
+// Where a tensor would take the chain, a worker step is one launch up to planned lists of STEP_CHAIN_LIST entries, or STEP_CHAIN_LIST_FEW with
+// momentum and at most STEP_CHAIN_UNITS units (pulls always, their lists are fetched while others push): on one tensor of 2M at 0.5 %, 10 K pairs, in
+// several launches / in one 26.8 / 28.1, without momentum 26.8 / 29.3, a pull's event 32.9 / 32.4 and 34.1 / 31.3; of 1M at 1 %, 10 K pairs and
+// 123 units, 25.6 / 25.1, 25.8 / 27.1, 32.6 / 30.6, 35.4 / 30.6.
+constexpr uint32_t STEP_CHAIN_LIST = 13312, STEP_CHAIN_LIST_FEW = 16384, STEP_CHAIN_UNITS = 128;
+// A pull whose ranking workgroups emit more pairs than this in all takes several launches: 24 tensors of 2M at 2 %, 40 K pairs, an event
+// 30.0 / 31.3 and 29.1 / 30.3 (a step 20.1 / 19.0), of 3M 36.4 / 37.3 and 34.1 / 35.6 (23.9 / 21.3); at 1 % of 3M 27.5 / 26.5, 29.6 / 25.3.
+constexpr uint32_t STEP_PULL_K = 32768;
 // Where a tensor of at least SEG_MIN_N elements has more than STEP_EMIT_K pairs, those tensors have emitting workgroups.
 constexpr uint32_t STEP_EMIT_K = 2500;
 constexpr uint32_t STEP_ITEMS = 16, STEP_ITEMS_KEYS = 32;      // entries, or keys, that a thread of the ranking holds in registers

@@ -489,6 +489,12 @@ static void listed_dense(const char *name, uint32_t misalign, uint64_t seed)
         CHECK(dgs_worker_step(c.c, g.p + misalign, s_gpu.p + misalign, nullptr, lrs[call], 0.9f, rho, gi.p, gv.p, &k2) == DGS_OK);
         expect_same(gi.p, gv.p, wi.p, wv.p, K);
         expect_same_f(s_gpu.p + misalign, s_ref.p, L.n, "state");
+        // (what the context remembers of the four tensors that have more than a workgroup's elements: the bucket of keys of 1 to 1.06, seen
+        // twice in a row, and so listed by the next call, is known after calls 1 to 3)
+        const uint32_t stable = dgs::DPREV_STABLE | ((0x3F800000u >> dgs::HSHIFT) + 1u), *w = (const uint32_t *)c.ws.p;
+        uint32_t known = 0;
+        for (size_t i = 0; i < c.ws.n / 4; ++i) known += w[i] == stable ? 1u : 0u;
+        CHECK((call >= 1 && call <= 3) ? known >= 4 : known == 0);
     }
     CHECK(c.stats().internal_errors == 0);
     printf("%-44s ok\n", name);
@@ -865,6 +871,11 @@ int main(int argc, char **argv)
         CHECK(one_launch(three, 0.01, 0.9f, 256) && one_launch(three, 0.01, 0.9f, 32) && !one_launch(three, 0.01, 0.9f, 3));
         // at most 80 workgroups wait (for tensors of one part no other ones do)
         CHECK(one_launch(std::vector<uint64_t>(80, 8200), 0.001, 0.9f, 256) && !one_launch(std::vector<uint64_t>(81, 8200), 0.001, 0.9f, 256));
+        // one unit to a compute unit; lists that would take the chain; pulls whose ranking workgroups emit much
+        CHECK(one_launch({163840, 163840, 163840}, 0.001, 0.9f, 32) && !one_launch({180224, 180224, 180224}, 0.001, 0.9f, 32));
+        CHECK(one_launch({900000}, 0.008, 0.9f, 256) && !one_launch({900000}, 0.008, 0.0f, 256) && one_launch({900000}, 0.008, 0.0f, 256, true));
+        CHECK(one_launch(std::vector<uint64_t>(16, 70000), 0.029, 0.0f, 256, true) && !one_launch(std::vector<uint64_t>(16, 70000), 0.03, 0.0f, 256, true) &&
+              one_launch(std::vector<uint64_t>(16, 70000), 0.03, 0.9f, 256));
         printf("%-44s ok\n", g_what.c_str());
         Opts o, mis;
         mis.misalign = 3;

@@ -15,7 +15,7 @@ LAYOUTS = {
     "units of 4": ([8192, 8193, 3 * 4096, 4 * 4096 + 1, 65_535, 65_536, 5, 69_637, 12_345], 0.01),
     "units of 8": ([700_000, 64, 500_001, 8193], 0.004),
     "units of 16": ([1_300_000, 64, 1_200_001, 16_385], 0.003),
-    "many winners": ([290_001, 64, 150_000, 65_536], 0.028),
+    "many winners": ([290_001, 64, 150_000, 65_536], 0.02),
     "one tensor": ([1 << 20], 0.01),
     "beyond one unit per compute unit": ([5_000_000, 1_000_001], 0.001),
 }
@@ -31,6 +31,75 @@ def gradients(kind, n, seed):
         elif kind == "sparse":
             g[rng.random(n) < 0.99] = 0.0                         # fewer nonzeros than k
         yield (g * np.float32(s)).astype(np.float32)
+
+
+def one_launch(oracle, sizes, rho, m=0.9, pull=False, quads=0):
+    """Whether the predicted calls of a layout are one launch (nothing is counted as a streaming pass then); three calls against the
+    oracle on the way, the last one predicted and profiled."""
+    import torch
+    off = synth.offsets_from_sizes(sizes)
+    n = int(off[-1])
+    ctx = dgs.Context(off, W=1)
+    ctx.set_option(dgs.OPT_STREAM_QUADS, quads)
+    rng = np.random.default_rng(31)
+    rows = np.zeros((1, n), np.float32)
+    dev_rows = torch.zeros((1, n), device=ctx.device)
+    ctx.server_attach(dev_rows)
+    K = ctx.nnz(rho)
+    idx, val = torch.zeros(K, dtype=torch.int32, device=ctx.device), torch.zeros(K, device=ctx.device)
+    for call in range(3):
+        g = rng.standard_normal(n).astype(np.float32)
+        ctx.set_option(dgs.OPT_PROFILE, int(call == 2))
+        if pull:
+            rows[0] = g
+            dev_rows.copy_(torch.from_numpy(rows))
+            wi, wv = oracle.server_pull(rows, 0, off, rho)
+            ctx.server_pull(0, rho, idx, val)
+        else:
+            wi, wv = oracle.worker_step(g, rows[0], off, np.float32(1.0), np.float32(m), rho)
+            ctx.worker_step(to_dev(g, ctx.device), dev_rows[0], 1.0, m, rho, idx, val, residual_mode=m == 0.0)
+        torch.cuda.synchronize()
+        assert_pairs_match(to_host_u32(idx), val.cpu().numpy(), wi, wv, f"call {call}")
+        assert_state_match(dev_rows[0].cpu().numpy(), rows[0], f"row {call}")
+    passes = ctx.profile_read(dgs.PROF_PULL_STREAM if pull else dgs.PROF_WORKER_STREAM)[0]
+    selections = ctx.profile_read(dgs.PROF_PULL_SELECT if pull else dgs.PROF_WORKER_SELECT)[0]
+    assert ctx.stats().internal_errors == 0 and passes <= 1 and selections == 1
+    ctx.close()
+    return passes == 0
+
+
+@pytest.mark.parametrize("name", list(LAYOUTS))
+def test_these_layouts_are_one_launch(oracle, name):
+    sizes, rho = LAYOUTS[name]
+    assert one_launch(oracle, sizes, rho) and one_launch(oracle, sizes, rho, pull=True)
+    assert not one_launch(oracle, sizes, rho, quads=1)
+    assert one_launch(oracle, sizes, rho, 0.0) == (name != "one tensor")      # (10.5 K pairs: the chain is quicker)
+
+
+# units of 16 tiles: one to a compute unit (256), or two for at most two tensors; waiting workgroups (80); lists that the ranking
+# holds (128 a unit, so 90 on average); planned lists that would take the chain; pairs that ranking workgroups emit in a pull
+@pytest.mark.parametrize("sizes, rho, m, pull, one", [
+    ([16_384 * 85] * 3, 0.0005, 0.9, False, True),
+    ([16_384 * 86] * 3, 0.0005, 0.9, False, False),
+    ([16_384 * 85] * 3, 0.0005, 0.9, True, True),
+    ([16_384 * 512], 0.0002, 0.9, False, True),
+    ([16_384 * 512 + 1], 0.0002, 0.9, False, False),
+    ([16_384 * 511, 16_385], 0.0002, 0.9, False, False),
+    ([16_384 * 500, 16_384 * 10], 0.0002, 0.0, False, True),
+    ([16_384 * 512], 0.0002, 0.9, True, True),
+    ([8200] * 80, 0.004, 0.9, False, True),
+    ([8200] * 81, 0.004, 0.9, False, False),
+    ([3_000_000], 8080 / 3_000_000, 0.9, False, True),
+    ([3_000_000], 8110 / 3_000_000, 0.9, False, False),
+    ([900_000], 0.008, 0.9, False, True),
+    ([900_000], 0.008, 0.0, False, False),
+    ([900_000], 0.008, 0.0, True, True),
+    ([70_000] * 16, 0.029, 0.0, True, True),
+    ([70_000] * 16, 0.03, 0.0, True, False),
+    ([70_000] * 16, 0.03, 0.9, False, True),
+])
+def test_either_side_of_the_lines(oracle, sizes, rho, m, pull, one):
+    assert one_launch(oracle, sizes, rho, m, pull) == one
 
 
 @pytest.mark.parametrize("kind", ["gauss", "levels", "sparse"])
