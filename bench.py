@@ -270,11 +270,13 @@ def run_worker_server(torch, dgs, name, wl, steps, warmup, dev, *, cpu=True, exa
     us = lambda k: kernel_us.get(k) or 0.0
     worker_us = us("worker_stream") + us("worker_select") + us("worker_segmented")
     pull_us = us("pull_stream") + us("pull_select") + us("pull_segmented")
-    dom_us = kernel_us["worker_stream"]
+    dominant, dom_us = "k_stream<fma,collect> (dgs_worker_step streaming pass)", kernel_us["worker_stream"]
+    if dom_us is None:      # a small layout, whose calls are one launch
+        dominant, dom_us = "k_step<worker> (all of dgs_worker_step)", kernel_us["worker_select"]
     achieved = 12.0 * n / (dom_us * 1e-6) / 1e9 if dom_us else None
     traffic = traffic_entry(name, rho)
     roofline = {
-        "bound": "hbm", "kernel": "k_stream<fma,collect> (dgs_worker_step streaming pass)",
+        "bound": "hbm", "kernel": dominant,
         "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "frac": (achieved / HBM_PEAK_GBS) if achieved else None,
         "traffic": traffic["bytes"] if traffic else None,
@@ -423,6 +425,8 @@ def run_server_stress(torch, dgs, wl, steps, warmup, dev, form, cpu=True):
     kernel_us = read_kernel_us(dgs, ctx)
     us = lambda k: kernel_us.get(k) or 0.0
     dom_us = kernel_us["pull_stream"]
+    if dom_us is None:      # a small layout, whose calls are one launch
+        dominant, dom_us = "k_step<pull> (all of the pull)", kernel_us["pull_select"]
     achieved = dom_bytes / (dom_us * 1e-6) / 1e9 if dom_us else None
     st = ctx.stats()
     assert st.internal_errors == 0
