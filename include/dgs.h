@@ -59,7 +59,9 @@ enum {
     DGS_OPT_PROFILE = 2,     /* 1: attach start/stop HIP events to the kernels of each call */
     DGS_OPT_VALIDATE = 3,    /* 1: dgs_server_push checks idx on the device (synchronises) */
     DGS_OPT_MARGIN_PCT = 4,  /* candidate over-provisioning in percent of k_j (default 50) */
-    DGS_OPT_STREAM_QUADS = 5,/* 4096-element groups per workgroup of the streaming kernel */
+    DGS_OPT_STREAM_QUADS = 5,/* 4096-element groups per workgroup of the streaming kernel; 0 (default): automatic.  A context
+                                for which a value is set always has a streaming kernel: none of its calls is one launch
+                                (see DGS_PROF_*); 1 is what collecting passes take automatically */
     DGS_OPT_SEGMENTED = 6,   /* which tensors are resolved by many workgroups (the "chain") in place of
                                 one: 0 automatic (candidate lists too long for one workgroup,
                                 dense requests), 1 every tensor of at least 65536 elements, 2 never.
@@ -70,7 +72,7 @@ enum {
                                 again, with a fresh threshold, the tensors whose predicted threshold
                                 failed (they wait inside the launch and return at once when their
                                 tensor is fine); 0: such tensors are selected from the state buffer
-                                by one workgroup (slow on large tensors) */
+                                by one workgroup (slow on large tensors), and no call is one launch */
     DGS_OPT_WIRE_VALUE_BITS = 9, /* 32 (default): the wire form carries fp32 values and is lossless; 16: every
                                 value travels as a bfloat16 (the upper half of the fp32, rounded to nearest,
                                 halfway cases to even, NaN kept) -- what dgs_decode returns then differs
@@ -90,8 +92,9 @@ enum {
 };
 
 /*
- * Kernel classes reported by dgs_profile_read().  A call on a layout small enough to be one launch (up to
- * 4 M elements or so, at densities of at most 1/32) is counted under _SELECT alone.
+ * Kernel classes reported by dgs_profile_read().  A call on a small layout that is one launch is counted under
+ * _SELECT alone.  Those are predicted calls of layouts of up to some 256 units of 16,384 elements (4 M elements, or 8 M
+ * in one or two tensors) at densities of at most 1/32, where that is the quicker way.
  */
 enum {
     DGS_PROF_WORKER_STREAM = 0, /* accumulate + candidate pass over grad/state */

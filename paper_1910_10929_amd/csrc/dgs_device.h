@@ -343,10 +343,10 @@ void launch_pick_dense(const TensorDesc *tdesc, const PlanEntry *plan, uint32_t 
 void launch_select(int op, const SelectArgs &a, void *stream, void *ev0, void *ev1);
 // SEL_PULL_V with SelectArgs::later: sent_k += G for the K pairs of the message.
 void launch_add_sent(const SelectArgs &a, uint32_t K, void *stream, void *ev1);
-// Long candidate lists: the parts' window histograms, before the selection kernel, and what
-// remains behind it for tensors left SEG_ACTIVE / SEG_LISTS / SEG_ZERO.
 // A whole worker step or pull.
 void launch_step(int op, const SelectArgs &a, void *stream, void *ev0, void *ev1);
+// Long candidate lists: the parts' window histograms, before the selection kernel, and what
+// remains behind it for tensors left SEG_ACTIVE / SEG_LISTS / SEG_ZERO.
 void launch_window(const SelectArgs &a, void *stream, void *ev0);
 void launch_chain(int op, const SelectArgs &a, void *stream, void *ev0, void *ev1);
 // Dense request: exact k-th keys and emission, reading the tensors themselves.

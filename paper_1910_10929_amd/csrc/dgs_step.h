@@ -479,7 +479,7 @@ __device__ __forceinline__ void step_emit(const SelectArgs &A, const SegDesc &eb
     }
     if (key.x != STEP_DONE) {
         const uint32_t T = uniform(key.y & ~KEY_READY), rT = uniform(key.x);
-        uint32_t mine = 0;                           // entries above T (low half) and equal to it: 16 a lane at most of a unit's 4096
+        uint32_t mine = 0;                           // entries above T (low half) and equal to it: 64 a lane at most of a unit's 4096
         auto count = [&](uint32_t q, const uint32_t (&v)[4]) {
 #pragma unroll
             for (uint32_t i = 0; i < 4; ++i) {
