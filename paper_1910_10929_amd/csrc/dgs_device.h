@@ -142,9 +142,9 @@ constexpr uint32_t STEP_FEW = 2, STEP_UNITS_SMALLEST = 192, STEP_SMALL = 4;
 // (The CPU test build with small parts keeps to the kernels that larger layouts take.)
 constexpr uint32_t DIES = 8;                         // XCDs: a launch's workgroups are dealt out to them in turn
 // Where a tensor would take the chain, a worker step is one launch up to planned lists of STEP_CHAIN_LIST entries, or STEP_CHAIN_LIST_FEW with
-// momentum and at most STEP_CHAIN_UNITS units (pulls always, their lists are fetched while others push): on one tensor of 2M at 0.5 %, 10 K pairs, in
-// several launches / in one 26.8 / 28.1, without momentum 26.8 / 29.3, a pull's event 32.9 / 32.4 and 34.1 / 31.3; of 1M at 1 %, 10 K pairs and
-// 123 units, 25.6 / 25.1, 25.8 / 27.1, 32.6 / 30.6, 35.4 / 30.6.
+// momentum and at most STEP_CHAIN_UNITS units; a pull always, as the chain gains it nothing there.  On one tensor of 2M at 0.5 %, 10 K pairs, in
+// several launches / in one, as above, 26.8 / 28.1, 26.8 / 29.3, 32.9 / 32.4, 34.1 / 31.3; of 1M at 1 %, 10 K pairs and 123 units,
+// 25.6 / 25.1, 25.8 / 27.1, 32.6 / 30.6, 35.4 / 30.6.
 constexpr uint32_t STEP_CHAIN_LIST = 13312, STEP_CHAIN_LIST_FEW = 16384, STEP_CHAIN_UNITS = 128;
 // A pull whose ranking workgroups emit more pairs than this in all takes several launches: 24 tensors of 2M at 2 %, 40 K pairs, an event
 // 30.0 / 31.3 and 29.1 / 30.3 (a step 20.1 / 19.0), of 3M 36.4 / 37.3 and 34.1 / 35.6 (23.9 / 21.3); at 1 % of 3M 27.5 / 26.5, 29.6 / 25.3.
