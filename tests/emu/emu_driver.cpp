@@ -789,6 +789,7 @@ static void missed_windows(const char *name, int flavour, uint64_t seed)
 // predictions fail): `soak <first seed> <count>`.
 static void soak(uint64_t seed)
 {
+    emu::compute_units = seed % 2 ? 256 : 4;      // (with the library's own part size: calls in one launch on the odd ones)
     Rng r(seed * 7919 + 13);
     std::vector<uint64_t> sizes;
     const uint32_t J = 1 + r.u32() % 6;
